@@ -107,8 +107,8 @@ def read_traffic(prefix, schedule):
 def step_kernels(schedule):
     """What one timed step launches for this launch shape."""
     if schedule[0] == lbm.LBM_SCHED_NODE_LIST:
-        return ("k_dens_list + k_step_list (node-list step: densities of the non-solid nodes, "
-                "then fused pull + cohesion/adhesion + BGK); figures per step")
+        return ("k_dens + k_node (two passes over the non-solid nodes: densities, then fused pull + "
+                "cohesion/adhesion + BGK); figures per step")
     return (f"k_step<{schedule[0]},{schedule[1]}> lz {schedule[2]} (fused pull + moments + "
             "cohesion/adhesion + BGK)")
 

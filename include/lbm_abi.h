@@ -136,21 +136,22 @@ typedef struct lbm_throat *lbm_throat_t;
 /* Device-memory budget of the library's allocating calls, for callers that
  * share the GPU: with bytes > 0, lbm_throat_init, lbm_drain_throat,
  * lbm_drain_batch and lbm_place compute the device memory a call needs before allocating
- * anything (per subdomain: two population buffers of 152 bytes per padded
- * node, plus 25 bytes per node of masks, classes, densities and the node
- * list; two more population buffers for the ramp checkpoints of a drain) and
- * refuse a call that needs more than `bytes` with LBM_ENOMEM, having
+ * anything (an upper bound, as if every node were fluid: per subdomain two
+ * population buffers of 152 bytes per padded node, plus 25 bytes per node of
+ * index map, classes, densities and node list; two more population buffers
+ * for the ramp checkpoints of a drain) and refuse a call that needs more than `bytes` with LBM_ENOMEM, having
  * allocated nothing.  0 (the default) sets no budget; calls are then refused
  * only when the device reports less free memory than they need.  Process
  * wide; takes effect for calls that start after it returns. */
 int lbm_set_memory_budget(size_t bytes);
 
 /* Create a subdomain: voxelize the geometry on the device, allocate two FP32
- * population buffers (2 x 152 bytes per node, nx and ny padded to multiples
+ * population buffers (2 x 152 bytes per non-solid node; in a nearly all-fluid
+ * box of 4 million nodes or more, per node with nx and ny padded to multiples
  * of 8 and 4) and set the equilibrium state f = f_eq(rho_init, u = 0)
- * (Eq. 1-3).  Also per node: a 4-byte mask word, a 1-byte class and an
- * 8-byte density slot of the node-list path; per non-solid node an 8-byte
- * list entry.  *out receives the handle.
+ * (Eq. 1-3).  Also per node a 4-byte index-map entry and a 1-byte class, and
+ * per non-solid node a 4-byte list entry and an 8-byte density slot.  *out
+ * receives the handle.
  * Errors: LBM_EINVAL (sizes < 3, tau <= 0.5, non-positive or non-finite
  * densities, bad prism ids, probe outside the fluid), LBM_ENOMEM, LBM_EHIP. */
 int lbm_throat_init(const lbm_params *p, lbm_throat_t *out);
@@ -260,10 +261,10 @@ int lbm_load(lbm_throat_t h, const char *path);
 
 /* Summary of a batched drainage (optional output of lbm_drain_batch). */
 typedef struct {
-  int tx, ty, lz;           /* launch shape chosen by the autotuner          */
-  int n_tiles;              /* live tiles of all subdomains in one launch    */
+  int tx, ty, lz;           /* launch shape: LBM_SCHED_NODE_LIST, 0, 0       */
+  int n_tiles;              /* work items of all subdomains in one launch    */
   long long replays;        /* graph replays (chunks of check_every steps)   */
-  long long lattice_steps;  /* fused-step launches issued                    */
+  long long lattice_steps;  /* lattice steps issued                          */
   long long node_updates;   /* sum over subdomains of active steps x nodes   */
   long long fluid_updates;  /* the same with fluid nodes only                */
   double wall_ms;           /* device time from the first to the last kernel */
@@ -273,13 +274,12 @@ typedef struct {
  * independently): p[t] states subdomain t (each needs a probe node), pc is
  * host [n][n_pc] (each row positive and strictly increasing), out[t] receives the same
  * results as lbm_drain_throat would (bit for bit: the same kernels and the
- * same reduction order).  One fused-step launch covers the live tiles of all
- * running subdomains; the ramp and bisection decisions are taken on the
- * device between chunks of c->check_every steps (even), captured once as a
- * HIP graph and replayed until every subdomain is done.  The launch shape is
- * autotuned over the whole batch.  Device memory: 4 x 152 bytes per node
- * (two buffers and two ramp checkpoints) plus what lbm_throat_init holds per
- * subdomain.  Synchronous.  Returns
+ * same reduction order).  One step covers the non-solid nodes of all running
+ * subdomains in two launches; the ramp and bisection decisions are taken on
+ * the device between chunks of c->check_every steps (even), captured once as a
+ * HIP graph and replayed until every subdomain is done.  Device memory:
+ * 4 x 152 bytes per non-solid node (two buffers and two ramp checkpoints) plus
+ * what lbm_throat_init holds per subdomain.  Synchronous.  Returns
  * LBM_WNOTCONV if a point hit its cap, LBM_WPARTIAL if a subdomain became
  * non-finite: its result has failed = 1, NaN entry pressures and
  * LBM_PT_NONFINITE from the failing point on; the other subdomains are
@@ -304,15 +304,18 @@ int lbm_step_timer(lbm_throat_t h, int enable, double *total_ms, long long *laun
 /* Launch shape of the step: tile (tx, ty) in {(32, 4), (32, 8), (64, 4),
  * (16, 4), (16, 8), (8, 8)} marching a z-segment of lz (>= 1) planes in one
  * fused pass; 0 keeps the current value.  tx = LBM_SCHED_NODE_LIST selects
- * the node-list path instead (two passes over the non-solid nodes only, for
- * mostly solid subdomains; ty and lz are ignored and read back as 0).  All
- * shapes give bit-identical results. */
+ * two passes over the non-solid nodes instead (ty and lz are ignored and read
+ * back as 0).  Only a nearly all-fluid box of 4 million nodes or more is
+ * stored so that it can be stepped in tiles: any other subdomain takes every
+ * shape, reports it and runs the two passes.  All shapes give bit-identical
+ * results. */
 #define LBM_SCHED_NODE_LIST (-1)
 int lbm_set_schedule(lbm_throat_t h, int tx, int ty, int lz);
 
-/* Autotune the launch shape for this subdomain: time `trial_steps` steps
- * for every tile shape in increasing z-segment length (up to the first that
- * is 1.5x slower than the shape's best) and for the node list, time the
+/* Autotune the launch shape for this subdomain.  A subdomain that has only
+ * the two passes (see lbm_set_schedule) gets that shape at once.  Otherwise:
+ * time `trial_steps` steps for every tile shape in increasing z-segment length (up to the first that
+ * is 1.5x slower than the shape's best) and for the two passes, time the
  * candidates within 1.25x of the best once more (each keeps its faster
  * time), keep the fastest and return it (outputs may be NULL).  The trials step the state forward with
  * alternating buffers, as a drain does, from a copy that is restored at the

@@ -34,7 +34,8 @@ void set_err(const char *fmt, ...) {
 }
 
 size_t subdomain_bytes(int nx, int ny, int nz, bool checkpoints) {
-  const size_t pop = sizeof(float) * sc::pop_elems(nx, ny, nz);
+  // an upper bound: solid nodes hold no populations
+  const size_t pop = sizeof(float) * sc::brick_elems(nx, ny, nz);
   const size_t N = (size_t)nx * ny * nz;
   return (checkpoints ? 4 : 2) * pop + 25 * N + ((size_t)1 << 20);
 }
@@ -96,36 +97,48 @@ void fill_phys(lbm_throat *h) {
     }
 }
 
+// launch shape the step runs at: a compact subdomain has the two passes only
+sc::Sched shape_of(const lbm_throat *h) {
+  return h->bricks ? h->sched : sc::Sched{sc::kListTx, 0, 0};
+}
+
 // refresh the device descriptor (buffers, sizes, tile grid, parameters)
 int sync_desc(lbm_throat *h) {
   sc::Throat &T = h->desc;
   T.g[0] = h->g[0];
   T.g[1] = h->g[1];
-  T.mask = h->mask;
-  T.N = (uint32_t)h->N;
+  T.map = h->map_d;
+  T.pos = h->pos_d;
+  T.rho = h->rho_d;
+  T.n_live = (uint32_t)h->n_live;
   T.nx = h->nx;
   T.ny = h->ny;
   T.nz = h->nz;
-  T.per = h->per;
-  const bool tiled = h->sched.tx != sc::kListTx;
-  T.ntx = tiled ? (h->nx + h->sched.tx - 1) / h->sched.tx : 0;
-  T.nty = tiled ? (h->ny + h->sched.ty - 1) / h->sched.ty : 0;
-  T.lz = h->sched.lz;
+  T.res = h->bc[2] == LBM_BC_RESERVOIR;
   T.active = 1;
-  T.list = h->list_d;
-  T.nlist = h->nlist;
-  T.rho = h->rho_d;
   T.P = h->P;
+  T.mask = h->mask_d;
+  T.N = (uint32_t)h->N;
+  T.per = h->per;
+  const sc::Sched s = shape_of(h);
+  const bool tiled = s.tx != sc::kListTx;
+  T.ntx = tiled ? (h->nx + s.tx - 1) / s.tx : 0;
+  T.nty = tiled ? (h->ny + s.ty - 1) / s.ty : 0;
+  T.lz = s.lz;
   HIPCHK(hipMemcpyAsync(h->desc_d, &h->desc, sizeof(sc::Throat), hipMemcpyHostToDevice,
                         h->stream));
   return LBM_OK;
 }
 
-// tiles of the current schedule that hold a non-solid node
+// work items of the current schedule: its tiles that hold a non-solid node,
+// or the items of the two passes
 int rebuild_tiles(lbm_throat *h) {
   std::vector<sc::TileRef> list;
-  sc::list_tiles(h->bricks.data(), h->n_nonsolid, h->nx, h->ny, h->nz, h->sched.tx, h->sched.ty,
-                 h->sched.lz, 0, list);
+  const sc::Sched s = shape_of(h);
+  if (s.tx == sc::kListTx)
+    sc::list_items(h->n_live, 0, list);
+  else
+    sc::list_tiles(h->brick_live.data(), h->nx, h->ny, h->nz, s.tx, s.ty, s.lz, 0, list);
   if (list.size() > h->tiles_cap) {
     if (h->tiles_d) HIPCHK(hipStreamSynchronize(h->stream));
     if (h->tiles_d) (void)hipFree(h->tiles_d);
@@ -156,12 +169,14 @@ sc::Dom dom(const lbm_throat *h, const float *src, float *dst) {
   sc::Dom d;
   d.src = src;
   d.dst = dst;
-  d.mask = h->mask;
+  d.map = h->map_d;
+  d.mask = h->mask_d;
   d.N = h->N;
   d.nx = h->nx;
   d.ny = h->ny;
   d.nz = h->nz;
   d.per = h->per;
+  d.res = h->bc[2] == LBM_BC_RESERVOIR;
   return d;
 }
 
@@ -246,29 +261,27 @@ void release(lbm_throat *h) {
     if (h->ev[i]) (void)hipEventDestroy(h->ev[i]);
     if (h->tev[i]) (void)hipEventDestroy(h->tev[i]);
   }
-  if (h->mask) (void)hipFree(h->mask);
-  if (h->list_d) (void)hipFree(h->list_d);
-  if (h->rho_d) (void)hipFree(h->rho_d);
-  if (h->types_d) (void)hipFree(h->types_d);
-  if (h->rres_d) (void)hipFree(h->rres_d);
-  if (h->partials) (void)hipFree(h->partials);
-  if (h->chunks_d) (void)hipFree(h->chunks_d);
-  if (h->redinfo_d) (void)hipFree(h->redinfo_d);
-  if (h->chunk_first_d) (void)hipFree(h->chunk_first_d);
-  if (h->chunk_count_d) (void)hipFree(h->chunk_count_d);
-  if (h->desc_d) (void)hipFree(h->desc_d);
-  if (h->tiles_d) (void)hipFree(h->tiles_d);
-  if (h->zper_d) (void)hipFree(h->zper_d);
+  for (void *p : {(void *)h->map_d, (void *)h->pos_d, (void *)h->rho_d, (void *)h->mask_d,
+                  (void *)h->types_d, (void *)h->rres_d, (void *)h->partials,
+                  (void *)h->chunks_d, (void *)h->redinfo_d, (void *)h->red_first_d,
+                  (void *)h->red_count_d, (void *)h->desc_d, (void *)h->tiles_d,
+                  (void *)h->zper_d})
+    if (p) (void)hipFree(p);
   if (h->red_d) (void)hipFree(h->red_d);
   if (h->red_h) (void)hipHostFree(h->red_h);
   if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
   delete h;
 }
 
+hipError_t one_step(const lbm_throat *h, int parity) {
+  const sc::Sched s = shape_of(h);
+  return sc::launch_step(h->desc_d, h->tiles_d, h->ntiles, s.tx, s.ty, lbmh::wide(h), parity,
+                         h->stream, h->zper_d, h->n_zper);
+}
+
 int run_steps(lbm_throat *h, long long n) {
   for (long long i = 0; i < n; ++i) {
-    hipError_t e = sc::launch_step(h->desc_d, h->tiles_d, h->ntiles, h->sched.tx, h->sched.ty,
-                                   h->cur, h->stream, h->zper_d, h->n_zper);
+    const hipError_t e = one_step(h, h->cur);
     if (e != hipSuccess) {
       set_err("step launch failed: %s", hipGetErrorString(e));
       return LBM_EHIP;
@@ -280,11 +293,11 @@ int run_steps(lbm_throat *h, long long n) {
 }
 
 // FP64 masses, saturation and probe densities of the current state (the
-// chunked reduction the batched ramp uses too, so both give the same bits)
+// reduction the batched ramp uses too, so both give the same bits)
 int reduce_now(lbm_throat *h, double out[5]) {
   HIPCHK(sc::launch_reduce_chunks(h->desc_d, h->chunks_d, h->nchunks, h->redinfo_d, h->cur,
                                   h->partials, h->red_d + 3, h->stream));
-  HIPCHK(sc::launch_reduce_throats(h->chunk_first_d, h->chunk_count_d, 1, h->partials, h->red_d,
+  HIPCHK(sc::launch_reduce_throats(h->red_first_d, h->red_count_d, 1, h->partials, h->red_d,
                                    h->stream));
   HIPCHK(hipMemcpyAsync(h->red_h, h->red_d, 5 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));
@@ -301,7 +314,7 @@ int set_rho_in(lbm_throat *h, double r) {
 }
 
 int copy_state(lbm_throat *h, float *dst, const float *src) {
-  HIPCHK(hipMemcpyAsync(dst, src, sizeof(float) * sc::pop_elems(h->nx, h->ny, h->nz),
+  HIPCHK(hipMemcpyAsync(dst, src, sizeof(float) * sc::pop_elems(h->n_numbers),
                         hipMemcpyDeviceToDevice, h->stream));
   return LBM_OK;
 }
@@ -310,7 +323,6 @@ int copy_state(lbm_throat *h, float *dst, const float *src) {
 
 namespace lbmh {
 int sync_desc(lbm_throat *h) { return ::sync_desc(h); }
-int rebuild_tiles(lbm_throat *h) { return ::rebuild_tiles(h); }
 int set_rho_in(lbm_throat *h, double r) { return ::set_rho_in(h, r); }
 int copy_state(lbm_throat *h, float *dst, const float *src) { return ::copy_state(h, dst, src); }
 }  // namespace lbmh
@@ -325,7 +337,19 @@ int lbm_set_memory_budget(size_t bytes) {
   return LBM_OK;
 }
 
-int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
+}  // extern "C"
+
+namespace {
+
+// A subdomain is kept in bricks and stepped in tiles from this share of
+// non-solid nodes in the padded box and this many padded nodes on.  Step times
+// in us, two passes / tiles: 512 x 10^3 nodes (80^3) all fluid 45 / 56, 128^3
+// 191 / 193, 192^3 665 / 599, 256^3 1520 / 1324; 256^3 with 10, 20 and 30 %
+// solid 1426 / 1252, 1264 / 1211, 1124 / 1131; 192^3 with 20 % 552 / 559.
+constexpr double kTileFill = 0.85;
+constexpr size_t kTileNodes = (size_t)1 << 22;
+
+int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
   g_err.clear();
   if (!out) {
     set_err("out is NULL");
@@ -356,25 +380,11 @@ int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
   h->rho_out = p->rho_out_w;
   h->phib = (p->rho_major - p->rho_minor) / (p->rho_major + p->rho_minor);
   fill_phys(h);
-  h->sched = default_schedule(h->nx, h->ny, h->nz);
 
   auto fail = [&](int code) {
     release(h);
     return code;
   };
-  // device memory: 2 x 152 B populations + 4 B mask + 1 B class per node
-  size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
-    set_err("hipMemGetInfo failed");
-    return fail(LBM_EHIP);
-  }
-  const size_t pop_bytes = sizeof(float) * sc::pop_elems(h->nx, h->ny, h->nz);
-  const size_t need = 2 * pop_bytes + h->N * (2 * sizeof(uint32_t) + sizeof(float2) + 1) +
-                      (64u << 20);
-  if (need > free_b) {
-    set_err("needs %zu bytes of device memory, %zu free", need, free_b);
-    return fail(LBM_ENOMEM);
-  }
   if (p->stream) {
     h->stream = (hipStream_t)p->stream;
   } else {
@@ -391,20 +401,9 @@ int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
       return fail(LBM_ENOMEM);                                                 \
     }                                                                          \
   } while (0)
-  ALLOC(h->g[0], pop_bytes);
-  ALLOC(h->g[1], pop_bytes);
-  ALLOC(h->mask, sizeof(uint32_t) * h->N);
   ALLOC(h->types_d, h->N);
+  ALLOC(h->map_d, sizeof(uint32_t) * sc::map_elems(h->nx, h->ny, h->nz));
   ALLOC(h->rres_d, 4 * sizeof(double));
-  if (h->per & 4) {
-    const int zero = 0;
-    ALLOC(h->zper_d, sizeof(int));
-    if (hipMemcpy(h->zper_d, &zero, sizeof(int), hipMemcpyHostToDevice) != hipSuccess) {
-      set_err("upload of the ghost-plane list failed");
-      return fail(LBM_EHIP);
-    }
-    h->n_zper = 1;
-  }
   ALLOC(h->redinfo_d, sizeof(sc::RedInfo));
   ALLOC(h->red_d, 5 * sizeof(double));
   ALLOC(h->desc_d, sizeof(sc::Throat));
@@ -441,6 +440,15 @@ int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
     set_err("hipMalloc of the sphere bins failed");
     return fail(LBM_ENOMEM);
   }
+  std::vector<uint32_t> rows((size_t)h->ny * h->nz);
+  uint32_t *rows_d = nullptr;
+  if (hipMalloc((void **)&rows_d, sizeof(uint32_t) * rows.size()) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(sph_d);
+    (void)hipFree(bins_d);
+    set_err("hipMalloc of the row counts failed");
+    return fail(LBM_ENOMEM);
+  }
   int rc = LBM_OK;
   do {
     if (hipMemcpyAsync(sph_d, sph.data(), sizeof(double) * sph.size(), hipMemcpyHostToDevice,
@@ -457,13 +465,15 @@ int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
     const int safe_ids[3] = {p->prism ? ids[0] : 0, p->prism ? ids[1] : 0, p->prism ? ids[2] : 0};
     if (sc::launch_voxelize(sph_d, bins, p->prism ? 1 : 0, safe_ids, h->nx, h->ny, h->nz,
                             p->bc[2] == LBM_BC_RESERVOIR, h->types_d, h->stream) != hipSuccess ||
-        sc::launch_links(h->types_d, h->nx, h->ny, h->nz, h->per, h->mask, h->stream) !=
+        sc::launch_row_counts(h->types_d, h->nx, h->ny, h->nz, rows_d, h->stream) !=
             hipSuccess) {
       rc = LBM_EHIP;
       break;
     }
     h->types.resize(h->N);
-    if (hipMemcpyAsync(h->types.data(), h->types_d, h->N, hipMemcpyDeviceToHost, h->stream) !=
+    if (hipMemcpyAsync(rows.data(), rows_d, sizeof(uint32_t) * rows.size(),
+                       hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
+        hipMemcpyAsync(h->types.data(), h->types_d, h->N, hipMemcpyDeviceToHost, h->stream) !=
             hipSuccess ||
         hipStreamSynchronize(h->stream) != hipSuccess) {
       rc = LBM_EHIP;
@@ -473,14 +483,87 @@ int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
   if (rc == LBM_OK && hipStreamSynchronize(h->stream) != hipSuccess) rc = LBM_EHIP;
   (void)hipFree(sph_d);
   (void)hipFree(bins_d);
+  auto fail_rows = [&](int code) {
+    (void)hipFree(rows_d);
+    return fail(code);
+  };
   if (rc != LBM_OK) {
     set_err("geometry setup failed");
-    return fail(rc);
+    return fail_rows(rc);
   }
-  long long nf = 0;
-  for (size_t n = 0; n < h->N; ++n) nf += h->types[n] == sc::kFluid;
-  h->n_fluid = nf;
-  sc::brick_map(h->types.data(), h->nx, h->ny, h->nz, h->bricks, h->n_nonsolid);
+  // numbering, populations, work items
+  h->n_live = sc::number_rows(rows, h->ny, h->nz);
+  const size_t plane = (size_t)h->nx * h->ny;
+  h->n_fluid = (long long)h->n_live;
+  if (p->bc[2] == LBM_BC_RESERVOIR)
+    for (size_t n = 0; n < plane; ++n)
+      h->n_fluid -= (h->types[n] != sc::kSolid) + (h->types[h->N - plane + n] != sc::kSolid);
+  const size_t slots = (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * h->nz;
+  h->bricks = !compact && slots >= kTileNodes && (double)h->n_live >= kTileFill * (double)slots;
+  h->n_numbers = h->bricks ? slots / h->nz * ((size_t)h->nz + 2) : h->n_live;
+  const size_t pop_bytes = sizeof(float) * sc::pop_elems(h->n_numbers);
+  std::vector<sc::RedChunk> chunks;
+  sc::red_chunks(h->n_live, 0, chunks);
+  h->nchunks = (int)chunks.size();
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+    set_err("hipMemGetInfo failed");
+    return fail_rows(LBM_EHIP);
+  }
+  const size_t need = 2 * pop_bytes + 8 * h->n_numbers + 4 * h->n_live +
+                      (h->bricks ? 4 * h->N : 0) + (64u << 20);
+  if (need > free_b) {
+    set_err("needs %zu bytes of device memory, %zu free", need, free_b);
+    return fail_rows(LBM_ENOMEM);
+  }
+  auto alloc = [&](auto **q, size_t bytes) {
+    if (hipMalloc((void **)q, std::max<size_t>(bytes, 16)) == hipSuccess) return true;
+    *q = nullptr;
+    (void)hipGetLastError();
+    set_err("hipMalloc of %zu bytes failed", bytes);
+    return false;
+  };
+  if (!alloc(&h->g[0], pop_bytes) || !alloc(&h->g[1], pop_bytes) ||
+      !alloc(&h->pos_d, sizeof(uint32_t) * h->n_live) ||
+      !alloc(&h->rho_d, sizeof(float2) * h->n_numbers) ||
+      (h->bricks && !alloc(&h->mask_d, sizeof(uint32_t) * h->N)) ||
+      !alloc(&h->chunks_d, sizeof(sc::RedChunk) * chunks.size()) ||
+      !alloc(&h->partials, sizeof(double) * 3 * chunks.size()) ||
+      !alloc(&h->red_first_d, sizeof(int)) || !alloc(&h->red_count_d, sizeof(int)))
+    return fail_rows(LBM_ENOMEM);
+  {
+    const int zero = 0;
+    bool ok = hipMemcpyAsync(rows_d, rows.data(), sizeof(uint32_t) * rows.size(),
+                             hipMemcpyHostToDevice, h->stream) == hipSuccess &&
+              sc::launch_number(h->types_d, h->nx, h->ny, h->nz, h->per, rows_d, h->bricks,
+                                h->map_d, h->pos_d, h->stream) == hipSuccess;
+    ok = ok && (chunks.empty() ||
+                hipMemcpyAsync(h->chunks_d, chunks.data(), sizeof(sc::RedChunk) * chunks.size(),
+                               hipMemcpyHostToDevice, h->stream) == hipSuccess);
+    ok = ok &&
+         hipMemcpyAsync(h->red_first_d, &zero, sizeof(int), hipMemcpyHostToDevice, h->stream) ==
+             hipSuccess &&
+         hipMemcpyAsync(h->red_count_d, &h->nchunks, sizeof(int), hipMemcpyHostToDevice,
+                        h->stream) == hipSuccess;
+    if (ok && h->bricks) {
+      ok = sc::launch_links(h->types_d, dom(h, nullptr, nullptr), h->mask_d, h->stream) ==
+           hipSuccess;
+      sc::brick_map(h->types.data(), h->nx, h->ny, h->nz, h->brick_live);
+      h->sched = default_schedule(h->nx, h->ny, h->nz);
+      if (ok && (h->per & 4)) {
+        if (!alloc(&h->zper_d, sizeof(int))) return fail_rows(LBM_ENOMEM);
+        ok = hipMemcpyAsync(h->zper_d, &zero, sizeof(int), hipMemcpyHostToDevice, h->stream) ==
+             hipSuccess;
+        h->n_zper = 1;
+      }
+    }
+    if (hipStreamSynchronize(h->stream) != hipSuccess) ok = false;
+    (void)hipFree(rows_d);
+    if (!ok) {
+      set_err("numbering of the nodes failed");
+      return fail(LBM_EHIP);
+    }
+  }
 
   if (p->probe[0] >= 0) {
     if (p->probe[0] >= h->nx || p->probe[1] < 0 || p->probe[1] >= h->ny || p->probe[2] < 0 ||
@@ -488,12 +571,20 @@ int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
       set_err("probe node outside the box");
       return fail(LBM_EINVAL);
     }
-    h->probe = (long long)p->probe[0] +
-               (long long)h->nx * ((long long)p->probe[1] + (long long)h->ny * p->probe[2]);
-    if (h->types[h->probe] != sc::kFluid) {
+    const size_t node = (size_t)p->probe[0] +
+                        (size_t)h->nx * ((size_t)p->probe[1] + (size_t)h->ny * p->probe[2]);
+    if (h->types[node] != sc::kFluid) {
       set_err("probe node is not a fluid node");
       return fail(LBM_EINVAL);
     }
+    uint32_t number = 0;
+    if (hipMemcpy(&number,
+                  h->map_d + sc::map_pos(h->nx, h->ny, p->probe[0], p->probe[1], p->probe[2]),
+                  sizeof number, hipMemcpyDeviceToHost) != hipSuccess) {
+      set_err("reading the probe's number failed");
+      return fail(LBM_EHIP);
+    }
+    h->probe = (long long)number;
   }
   {
     const sc::RedInfo ri{h->probe, h->phib};
@@ -531,66 +622,28 @@ int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
     set_err("initial state failed: %s", hipGetErrorString(e));
     return fail(LBM_EHIP);
   }
-  // node list of the non-solid nodes and the density array of the node-list
-  // path (solid entries stay zero: they are the stencil's solid density)
-  {
-    std::vector<uint32_t> list;
-    list.reserve(h->n_nonsolid);
-    // in storage order (brick by brick), so that the lanes of a wavefront
-    // read and write whole lines of the population buffers
-    const size_t nxy = (size_t)h->nx * h->ny;
-    for (int z = 0; z < h->nz; ++z)
-      for (int by = -sc::kOY; by < h->ny; by += sc::kBY)
-        for (int bx = -sc::kOX; bx < h->nx; bx += sc::kBX)
-          for (int y = std::max(by, 0); y < std::min(by + sc::kBY, h->ny); ++y)
-            for (int x = std::max(bx, 0); x < std::min(bx + sc::kBX, h->nx); ++x) {
-              const size_t n = (size_t)z * nxy + (size_t)y * h->nx + x;
-              if (h->types[n] != sc::kSolid) list.push_back((uint32_t)n);
-            }
-    h->nlist = (uint32_t)list.size();
-    // each entry carries the node's mask word, which saves the list kernels
-    // one dependent load
-    ALLOC(h->list_d, sizeof(uint2) * std::max<size_t>(list.size(), 1));
-    ALLOC(h->rho_d, sizeof(float2) * h->N);
-    uint32_t *ids_d = nullptr;
-    ALLOC(ids_d, sizeof(uint32_t) * std::max<size_t>(list.size(), 1));
-    const bool ok =
-        (list.empty() ||
-         (hipMemcpyAsync(ids_d, list.data(), sizeof(uint32_t) * list.size(),
-                         hipMemcpyHostToDevice, h->stream) == hipSuccess &&
-          sc::launch_list_entries(ids_d, h->mask, h->nlist, h->list_d, h->stream) ==
-              hipSuccess)) &&
-        hipMemsetAsync(h->rho_d, 0, sizeof(float2) * h->N, h->stream) == hipSuccess &&
-        hipStreamSynchronize(h->stream) == hipSuccess;
-    (void)hipFree(ids_d);
-    if (!ok) {
-      set_err("node list upload failed");
-      return fail(LBM_EHIP);
-    }
-  }
-  // reduction chunks over the node list
-  {
-    std::vector<sc::Chunk> ch;
-    sc::list_red_chunks(0, h->nlist, ch);
-    h->nchunks = (int)ch.size();
-    ALLOC(h->chunks_d, sizeof(sc::Chunk) * std::max<size_t>(ch.size(), 1));
-    ALLOC(h->partials, sizeof(double) * 3 * std::max<size_t>(ch.size(), 1));
-    ALLOC(h->chunk_first_d, sizeof(int));
-    ALLOC(h->chunk_count_d, sizeof(int));
-    const int first = 0, cnt = h->nchunks;
-    if ((!ch.empty() && hipMemcpy(h->chunks_d, ch.data(), sizeof(sc::Chunk) * ch.size(),
-                                  hipMemcpyHostToDevice) != hipSuccess) ||
-        hipMemcpy(h->chunk_first_d, &first, sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(h->chunk_count_d, &cnt, sizeof(int), hipMemcpyHostToDevice) != hipSuccess) {
-      set_err("upload of the reduction chunks failed");
-      return fail(LBM_EHIP);
-    }
-  }
   h->cur = 0;
   if (rebuild_tiles(h) != LBM_OK) return fail(LBM_EHIP);
+  if (sc::launch_ghost(h->desc_d, h->zper_d, h->n_zper, 0, h->stream) != hipSuccess ||
+      hipStreamSynchronize(h->stream) != hipSuccess) {
+    set_err("initial ghost planes failed");
+    return fail(LBM_EHIP);
+  }
   *out = h;
   return LBM_OK;
 #undef ALLOC
+}
+
+}  // namespace
+
+namespace lbmh {
+int init_compact(const lbm_params *p, lbm_throat_t *out) { return init_subdomain(p, out, true); }
+}  // namespace lbmh
+
+extern "C" {
+
+int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
+  return init_subdomain(p, out, false);
 }
 
 void lbm_throat_free(lbm_throat_t h) { release(h); }
@@ -785,7 +838,7 @@ int ensure_checkpoints(lbm_throat *h, const char *who) {
     TRY(lbmh::check_budget(lbmh::subdomain_bytes(h->nx, h->ny, h->nz, true), who));
   for (int i = 0; i < 2; ++i)
     if (!h->save[i] &&
-        hipMalloc((void **)&h->save[i], sizeof(float) * sc::pop_elems(h->nx, h->ny, h->nz)) !=
+        hipMalloc((void **)&h->save[i], sizeof(float) * sc::pop_elems(h->n_numbers)) !=
             hipSuccess) {
       set_err("hipMalloc of a ramp checkpoint failed");
       return LBM_ENOMEM;
@@ -1072,7 +1125,7 @@ Header header_of(const lbm_throat *h) {
   H.nz = h->nz;
   H.per = h->per;
   H.N = h->N;
-  H.pop_elems = sc::pop_elems(h->nx, h->ny, h->nz);
+  H.pop_elems = sc::brick_elems(h->nx, h->ny, h->nz);
   H.types = types_hash(h->types);
   H.tau[0] = h->tau[0];
   H.tau[1] = h->tau[1];
@@ -1135,13 +1188,36 @@ bool get_ramp(File &F, HostRamp &R) {
   return ok && (R.phase == HostRamp::kIdle || (n >= 1 && point >= 0 && point <= n));
 }
 
-// one device buffer of pop_elems floats to or from the file, in chunks
-int buffer_out(lbm_throat *h, File &F, const float *dev, size_t n) {
-  std::vector<float> tmp(std::min(n, kIoChunk));
-  for (size_t o = 0; o < n; o += kIoChunk) {
-    const size_t k = std::min(kIoChunk, n - o);
-    HIPCHK(hipMemcpyAsync(tmp.data(), dev + o, sizeof(float) * k, hipMemcpyDeviceToHost,
-                          h->stream));
+// device staging of one chunk of the file layout (compact numbering)
+struct Staging {
+  float *d = nullptr;
+  size_t n = 0;
+  int make(const lbm_throat *h, size_t total) {
+    n = std::min(total, kIoChunk);
+    if (h->bricks) return LBM_OK;
+    if (hipMalloc((void **)&d, sizeof(float) * n) != hipSuccess) {
+      d = nullptr;
+      (void)hipGetLastError();
+      set_err("hipMalloc of the %zu-byte file staging failed", sizeof(float) * n);
+      return LBM_ENOMEM;
+    }
+    return LBM_OK;
+  }
+  ~Staging() {
+    if (d) (void)hipFree(d);
+  }
+};
+
+// one population buffer to or from the file (file_elems floats), in chunks
+int buffer_out(lbm_throat *h, File &F, const Staging &S, const float *dev, size_t n) {
+  std::vector<float> tmp(S.n);
+  const sc::Dom d = dom(h, nullptr, nullptr);
+  for (size_t o = 0; o < n; o += S.n) {
+    const size_t k = std::min(S.n, n - o);
+    // a buffer in bricks is the file layout
+    if (!h->bricks) HIPCHK(sc::launch_to_file(d, dev, o, k, S.d, h->stream));
+    HIPCHK(hipMemcpyAsync(tmp.data(), h->bricks ? dev + o : S.d, sizeof(float) * k,
+                          hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     if (!F.put_n(tmp.data(), k)) {
       set_err("lbm_save: write failed");
@@ -1151,16 +1227,18 @@ int buffer_out(lbm_throat *h, File &F, const float *dev, size_t n) {
   return LBM_OK;
 }
 
-int buffer_in(lbm_throat *h, File &F, float *dev, size_t n) {
-  std::vector<float> tmp(std::min(n, kIoChunk));
-  for (size_t o = 0; o < n; o += kIoChunk) {
-    const size_t k = std::min(kIoChunk, n - o);
+int buffer_in(lbm_throat *h, File &F, const Staging &S, float *dev, size_t n) {
+  std::vector<float> tmp(S.n);
+  const sc::Dom d = dom(h, nullptr, nullptr);
+  for (size_t o = 0; o < n; o += S.n) {
+    const size_t k = std::min(S.n, n - o);
     if (!F.get_n(tmp.data(), k)) {
       set_err("lbm_load: the file ends inside a population buffer");
       return LBM_EIO;
     }
-    HIPCHK(hipMemcpyAsync(dev + o, tmp.data(), sizeof(float) * k, hipMemcpyHostToDevice,
-                          h->stream));
+    HIPCHK(hipMemcpyAsync(h->bricks ? dev + o : S.d, tmp.data(), sizeof(float) * k,
+                          hipMemcpyHostToDevice, h->stream));
+    if (!h->bricks) HIPCHK(sc::launch_from_file(d, S.d, o, k, dev, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
   }
   return LBM_OK;
@@ -1176,6 +1254,9 @@ int lbm_save(lbm_throat_t h, const char *path) {
     return LBM_EINVAL;
   }
   HIPCHK(hipStreamSynchronize(h->stream));
+  const size_t n = sc::brick_elems(h->nx, h->ny, h->nz);
+  Staging stage;
+  TRY(stage.make(h, n));
   File F;
   F.f = fopen(path, "wb");
   if (!F.f) {
@@ -1190,11 +1271,10 @@ int lbm_save(lbm_throat_t h, const char *path) {
     set_err("lbm_save: write to %s failed", path);
     return LBM_EIO;
   }
-  const size_t n = sc::pop_elems(h->nx, h->ny, h->nz);
-  TRY(buffer_out(h, F, h->g[h->cur], n));
+  TRY(buffer_out(h, F, stage, h->g[h->cur], n));
   if (with_ckpt) {
-    TRY(buffer_out(h, F, h->save[0], n));
-    TRY(buffer_out(h, F, h->save[1], n));
+    TRY(buffer_out(h, F, stage, h->save[0], n));
+    TRY(buffer_out(h, F, stage, h->save[1], n));
   }
   if (fflush(F.f) != 0) {
     set_err("lbm_save: write to %s failed", path);
@@ -1246,12 +1326,14 @@ int lbm_load(lbm_throat_t h, const char *path) {
     return LBM_EINVAL;
   }
   if (nbuf == 3) TRY(ensure_checkpoints(h, "lbm_load"));
+  const size_t n = sc::brick_elems(h->nx, h->ny, h->nz);
+  Staging stage;
+  TRY(stage.make(h, n));
   // from here on the handle's state is overwritten
-  const size_t n = sc::pop_elems(h->nx, h->ny, h->nz);
-  TRY(buffer_in(h, F, h->g[h->cur], n));
+  TRY(buffer_in(h, F, stage, h->g[h->cur], n));
   if (nbuf == 3) {
-    TRY(buffer_in(h, F, h->save[0], n));
-    TRY(buffer_in(h, F, h->save[1], n));
+    TRY(buffer_in(h, F, stage, h->save[0], n));
+    TRY(buffer_in(h, F, stage, h->save[1], n));
   }
   TRY(set_rho_in(h, rho_in));
   h->steps_done = steps_done;
@@ -1299,7 +1381,7 @@ int lbm_set_schedule(lbm_throat_t h, int tx, int ty, int lz) {
   if (tx == sc::kListTx) {
     s = sc::Sched{sc::kListTx, 0, 0};
   } else {
-    if (s.tx == sc::kListTx) s = sc::Sched{64, 4, 16};
+    if (s.tx == sc::kListTx) s = sc::Sched{64, 4, 16};  // kept values of a list schedule
     if (tx) s.tx = tx;
     if (ty) s.ty = ty;
     if (lz) s.lz = lz;
@@ -1316,6 +1398,14 @@ int lbm_autotune(lbm_throat_t h, int trial_steps, int *tx, int *ty, int *lz) {
   if (!h || trial_steps < 1) {
     set_err("lbm_autotune: bad handle or trial_steps < 1");
     return LBM_EINVAL;
+  }
+  if (!h->bricks) {  // nothing to choose from
+    h->sched = shape_of(h);
+    TRY(rebuild_tiles(h));
+    if (tx) *tx = h->sched.tx;
+    if (ty) *ty = h->sched.ty;
+    if (lz) *lz = h->sched.lz;
+    return LBM_OK;
   }
   // Trials advance the state with alternating buffers, as the ramp does (a
   // trial that re-reads one unchanged buffer times some shapes faster than
@@ -1335,7 +1425,7 @@ int lbm_autotune(lbm_throat_t h, int trial_steps, int *tx, int *ty, int *lz) {
       (void)hipFree(d);
     }
   } keep{h};
-  keep.bytes = sizeof(float) * sc::pop_elems(h->nx, h->ny, h->nz);
+  keep.bytes = sizeof(float) * sc::pop_elems(h->n_numbers);
   if (hipMalloc((void **)&keep.d, keep.bytes) != hipSuccess) {
     keep.d = nullptr;
     set_err("lbm_autotune: hipMalloc of %zu bytes for the state copy failed", keep.bytes);
@@ -1355,8 +1445,7 @@ int lbm_autotune(lbm_throat_t h, int trial_steps, int *tx, int *ty, int *lz) {
     TRY(rebuild_tiles(h));
     int par = h->cur;
     auto one = [&]() {
-      const hipError_t e = sc::launch_step(h->desc_d, h->tiles_d, h->ntiles, s.tx, s.ty, par,
-                                           h->stream, h->zper_d, h->n_zper);
+      const hipError_t e = one_step(h, par);
       par ^= 1;
       return e;
     };
@@ -1404,8 +1493,10 @@ int lbm_place(lbm_throat_t h, int tries, int trial_steps, double *ms_first, doub
     set_err("lbm_place: bad handle, tries outside 0..8 or trial_steps < 1");
     return LBM_EINVAL;
   }
-  const size_t bytes = sizeof(float) * sc::pop_elems(h->nx, h->ny, h->nz);
-  TRY(lbmh::check_budget(bytes * (1 + 2 * (size_t)tries), "lbm_place"));
+  const size_t bytes = sizeof(float) * sc::pop_elems(h->n_numbers);
+  TRY(lbmh::check_budget(sizeof(float) * sc::brick_elems(h->nx, h->ny, h->nz) *
+                             (1 + 2 * (size_t)tries),
+                         "lbm_place"));
   // The state is kept in a copy; each placement (the current pair, then
   // `tries` new pairs allocated while the earlier ones are still held, so
   // that they land elsewhere) runs 2 + trial_steps steps from that copy with
@@ -1461,8 +1552,7 @@ int lbm_place(lbm_throat_t h, int tries, int trial_steps, double *ms_first, doub
     HIPCHK(hipMemcpyAsync(pr.g[parity], w.keep, bytes, hipMemcpyDeviceToDevice, h->stream));
     int par = parity;
     auto one = [&]() {
-      const hipError_t e = sc::launch_step(h->desc_d, h->tiles_d, h->ntiles, h->sched.tx,
-                                           h->sched.ty, par, h->stream, h->zper_d, h->n_zper);
+      const hipError_t e = one_step(h, par);
       par ^= 1;
       return e;
     };

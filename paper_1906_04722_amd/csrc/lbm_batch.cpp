@@ -1,8 +1,8 @@
 // lbm_batch.cpp -- batched drainage of many pore-throat subdomains
 // (Montella et al., Sec. 2.2.2: the pore throats are solved independently).
 //
-// Every subdomain keeps its own buffers and node classes; one fused-step
-// launch covers the live tiles of all active subdomains, and the ramp /
+// Every subdomain keeps its own buffers and node classes; one step
+// covers the nodes of all active subdomains, and the ramp /
 // bisection decisions of every subdomain are taken on the device between
 // chunks of `check_every` steps.  The chunk [steps, reduction, decisions,
 // state copies] is captured once as a HIP graph and replayed until no
@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdlib>
 #include <vector>
@@ -29,13 +30,12 @@ struct Batch {
   hipStream_t stream = nullptr;
   std::vector<lbm_throat_t> h;
   sc::Throat *th_d = nullptr;
-  sc::TileRef *tiles_d = nullptr;
-  int ntiles = 0;
-  int *zper_d = nullptr;  // z-periodic subdomains (ghost-plane refresh)
-  int n_zper = 0;
-  sc::Chunk *chunks_d = nullptr;   // reduction chunks (node-list ranges)
+  sc::TileRef *items_d = nullptr;   // work items of all subdomains
+  int nitems = 0;
+  bool wide = false;
+  sc::RedChunk *chunks_d = nullptr;  // reduction chunks of all subdomains
   int nchunks = 0;
-  sc::Chunk *cchunks_d = nullptr;  // copy chunks (node ranges) of the checkpoint copies
+  sc::Chunk *cchunks_d = nullptr;  // ranges of the checkpoint copies
   int ncchunks = 0;
   int *first_d = nullptr, *count_d = nullptr;
   sc::RedInfo *info_d = nullptr;
@@ -47,10 +47,7 @@ struct Batch {
   int *status_d = nullptr, *nact_d = nullptr, *nact_h = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  hipEvent_t ev[2] = {nullptr, nullptr};    // autotuner trials
   hipEvent_t wall[2] = {nullptr, nullptr};  // the whole drain, first to last kernel
-  std::vector<sc::Throat> th_h;
-  sc::Sched sched{32, 4, 2};
 
   ~Batch() {
     // an error return can leave replays queued: let them finish before any
@@ -58,15 +55,12 @@ struct Batch {
     if (stream) (void)hipStreamSynchronize(stream);
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
-    for (void *p : {(void *)th_d, (void *)tiles_d, (void *)zper_d, (void *)chunks_d, (void *)cchunks_d,
-                    (void *)first_d,
-                    (void *)count_d, (void *)info_d, (void *)partials, (void *)sums,
+    for (void *p : {(void *)th_d, (void *)items_d, (void *)chunks_d, (void *)cchunks_d, (void *)first_d, (void *)count_d,
+                    (void *)info_d, (void *)partials, (void *)sums,
                     (void *)probe, (void *)rd_d, (void *)ck_d, (void *)pc_d, (void *)S_d,
                     (void *)steps_d, (void *)status_d, (void *)nact_d})
       if (p) (void)hipFree(p);
     if (nact_h) (void)hipHostFree(nact_h);
-    for (auto e : ev)
-      if (e) (void)hipEventDestroy(e);
     for (auto e : wall)
       if (e) (void)hipEventDestroy(e);
     for (auto x : h) lbm_throat_free(x);
@@ -92,98 +86,13 @@ int dalloc(T **p, size_t count) {
   return LBM_OK;
 }
 
-// tile lists of every subdomain for one launch shape
-int build_tiles(Batch &B, const sc::Sched &s) {
-  std::vector<sc::TileRef> tl;
-  for (int t = 0; t < B.n; ++t) {
-    const lbm_throat *x = B.h[t];
-    sc::list_tiles(x->bricks.data(), x->n_nonsolid, x->nx, x->ny, x->nz, s.tx, s.ty, s.lz, t, tl);
-    const bool tiled = s.tx != sc::kListTx;
-    B.th_h[t].ntx = tiled ? (x->nx + s.tx - 1) / s.tx : 0;
-    B.th_h[t].nty = tiled ? (x->ny + s.ty - 1) / s.ty : 0;
-    B.th_h[t].lz = s.lz;
-  }
-  BCHK(hipStreamSynchronize(B.stream));
-  if (B.tiles_d) (void)hipFree(B.tiles_d);
-  B.tiles_d = nullptr;
-  if (dalloc(&B.tiles_d, tl.size())) return LBM_ENOMEM;
-  B.ntiles = (int)tl.size();
-  BCHK(hipMemcpy(B.tiles_d, tl.data(), sizeof(sc::TileRef) * tl.size(), hipMemcpyHostToDevice));
-  BCHK(hipMemcpy(B.th_d, B.th_h.data(), sizeof(sc::Throat) * B.n, hipMemcpyHostToDevice));
-  B.sched = s;
-  return LBM_OK;
-}
-
-// time candidate launch shapes over the whole batch and keep the fastest.
-// Before the ramp every state is in g[0] and the checkpoint buffers are
-// free: the trials advance the states with alternating buffers, as the ramp
-// does, from copies in save[0] that are put back afterwards.  Each candidate
-// runs an even number of steps; the close ones are timed twice.
-int autotune(Batch &B, int trial_steps) {
-  static const int lzs[5] = {1, 2, 4, 8, 16};
-  std::vector<sc::Sched> cand;
-  for (const auto &sh : sc::kShapes)
-    for (int l : lzs) cand.push_back(sc::Sched{sh[0], sh[1], l});
-  cand.push_back(sc::Sched{sc::kListTx, 0, 0});
-  for (lbm_throat *x : B.h)
-    BCHK(hipMemcpyAsync(x->save[0], x->g[0], sizeof(float) * sc::pop_elems(x->nx, x->ny, x->nz),
-                        hipMemcpyDeviceToDevice, B.stream));
-  std::vector<double> t(cand.size(), INFINITY);
-  auto trial = [&](size_t c) -> int {
-    const sc::Sched &s = cand[c];
-    if (int r = build_tiles(B, s)) return r;
-    int par = 0;
-    auto one = [&]() {
-      const hipError_t e = sc::launch_step(B.th_d, B.tiles_d, B.ntiles, s.tx, s.ty, par,
-                                           B.stream, B.zper_d, B.n_zper);
-      par ^= 1;
-      return e;
-    };
-    for (int w = 0; w < 2; ++w) BCHK(one());
-    BCHK(hipEventRecord(B.ev[0], B.stream));
-    for (int i = 0; i < trial_steps; ++i) BCHK(one());
-    BCHK(hipEventRecord(B.ev[1], B.stream));
-    if (trial_steps & 1) BCHK(one());
-    BCHK(hipEventSynchronize(B.ev[1]));
-    float ms = 0.f;
-    BCHK(hipEventElapsedTime(&ms, B.ev[0], B.ev[1]));
-    t[c] = std::min(t[c], (double)ms);
-    return LBM_OK;
-  };
-  // as the single-subdomain autotuner: per shape in increasing lz until a
-  // segment length is 1.5x slower than the shape's best, then the candidates
-  // within 1.25x of the best once more
-  for (size_t c = 0; c < cand.size();) {
-    double shape_best = INFINITY;
-    size_t e = c;
-    while (e < cand.size() && cand[e].tx == cand[c].tx && cand[e].ty == cand[c].ty) ++e;
-    for (size_t k = c; k < e; ++k) {
-      if (int r = trial(k)) return r;
-      if (t[k] > 1.5 * shape_best) break;
-      shape_best = std::min(shape_best, t[k]);
-    }
-    c = e;
-  }
-  const double first = *std::min_element(t.begin(), t.end());
-  for (size_t c = 0; c < cand.size(); ++c)
-    if (t[c] <= 1.25 * first)
-      if (int r = trial(c)) return r;
-  for (lbm_throat *x : B.h)
-    BCHK(hipMemcpyAsync(x->g[0], x->save[0], sizeof(float) * sc::pop_elems(x->nx, x->ny, x->nz),
-                        hipMemcpyDeviceToDevice, B.stream));
-  size_t best = 0;
-  for (size_t c = 1; c < cand.size(); ++c)
-    if (t[c] < t[best]) best = c;
-  return build_tiles(B, cand[best]);
-}
-
 // the kernels of one chunk: check_every fused steps, the reductions, the
 // ramp decisions and the checkpoint copies they request
 hipError_t enqueue_chunk(Batch &B, const sc::RampCfg &cfg) {
   hipError_t e = hipSuccess;
   for (int i = 0; i < cfg.every && e == hipSuccess; ++i)
-    e = sc::launch_step(B.th_d, B.tiles_d, B.ntiles, B.sched.tx, B.sched.ty, i & 1, B.stream,
-                        B.zper_d, B.n_zper);
+    e = sc::launch_step(B.th_d, B.items_d, B.nitems, sc::kListTx, 0, B.wide, i & 1, B.stream,
+                        nullptr, 0);
   if (e == hipSuccess)
     e = sc::launch_reduce_chunks(B.th_d, B.chunks_d, B.nchunks, B.info_d, 0, B.partials, B.probe,
                                  B.stream);
@@ -262,38 +171,40 @@ int lbm_drain_batch(int n, const lbm_params *p, const double *pc, int n_pc, cons
   Batch B;
   B.n = n;
   BCHK(hipStreamCreate(&B.stream));
-  BCHK(hipEventCreate(&B.ev[0]));
-  BCHK(hipEventCreate(&B.ev[1]));
   BCHK(hipEventCreate(&B.wall[0]));
   BCHK(hipEventCreate(&B.wall[1]));
   // subdomains: geometry, initial state, checkpoints
-  std::vector<sc::Chunk> chunks, cchunks;
+  std::vector<sc::Chunk> cchunks;
+  std::vector<sc::Throat> th(n);
   std::vector<int> first(n), count(n);
   std::vector<sc::RedInfo> rinfo(n);
   std::vector<sc::RampDev> rd(n);
   std::vector<sc::Ckpt> ck(n);
-  B.th_h.resize(n);
+  std::vector<sc::TileRef> items;
+  std::vector<sc::RedChunk> chunks;
   for (int t = 0; t < n; ++t) {
     lbm_params q = p[t];
     q.stream = B.stream;
     lbm_throat_t x = nullptr;
-    if (int r = lbm_throat_init(&q, &x)) {
+    if (int r = lbmh::init_compact(&q, &x)) {
       if (r < 0) return r;
     }
     B.h.push_back(x);
     for (int i = 0; i < 2; ++i)
       if (!x->save[i] &&
-          hipMalloc((void **)&x->save[i], sizeof(float) * sc::pop_elems(x->nx, x->ny, x->nz)) !=
+          hipMalloc((void **)&x->save[i], std::max<size_t>(sizeof(float) * sc::pop_elems(x->n_numbers), 16)) !=
               hipSuccess) {
         set_err("lbm_drain_batch: no device memory for the checkpoints of subdomain %d", t);
         return LBM_ENOMEM;
       }
-    B.th_h[t] = x->desc;
+    th[t] = x->desc;
     ck[t] = sc::Ckpt{x->save[0], x->save[1]};
     first[t] = (int)chunks.size();
-    sc::list_red_chunks(t, x->nlist, chunks);
+    sc::red_chunks(x->n_live, t, chunks);
     count[t] = (int)chunks.size() - first[t];
-    sc::list_chunks(t, (uint32_t)x->N, cchunks);
+    sc::list_items(x->n_live, t, items);
+    B.wide = B.wide || lbmh::wide(x);
+    sc::copy_chunks(t, sc::pop_elems(x->n_numbers), cchunks);
     rinfo[t] = sc::RedInfo{x->probe, x->phib};
     sc::RampDev R{};
     R.rho_out = x->rho_out;
@@ -303,9 +214,14 @@ int lbm_drain_batch(int n, const lbm_params *p, const double *pc, int n_pc, cons
     R.phase = sc::kPhaseDone;
     rd[t] = R;
   }
+  if (items.size() > (size_t)INT_MAX) {
+    set_err("lbm_drain_batch: %zu work items exceed one launch", items.size());
+    return LBM_EINVAL;
+  }
+  B.nitems = (int)items.size();
   B.nchunks = (int)chunks.size();
   B.ncchunks = (int)cchunks.size();
-  if (dalloc(&B.th_d, n) || dalloc(&B.chunks_d, chunks.size()) ||
+  if (dalloc(&B.th_d, n) || dalloc(&B.items_d, items.size()) || dalloc(&B.chunks_d, chunks.size()) ||
       dalloc(&B.cchunks_d, cchunks.size()) || dalloc(&B.first_d, n) ||
       dalloc(&B.count_d, n) || dalloc(&B.info_d, n) || dalloc(&B.partials, 3 * chunks.size()) ||
       dalloc(&B.sums, 3 * (size_t)n) || dalloc(&B.probe, 2 * (size_t)n) || dalloc(&B.rd_d, n) ||
@@ -320,9 +236,13 @@ int lbm_drain_batch(int n, const lbm_params *p, const double *pc, int n_pc, cons
   if (!cchunks.empty())
     BCHK(hipMemcpy(B.cchunks_d, cchunks.data(), sizeof(sc::Chunk) * cchunks.size(),
                    hipMemcpyHostToDevice));
-  if (!chunks.empty())
-    BCHK(hipMemcpy(B.chunks_d, chunks.data(), sizeof(sc::Chunk) * chunks.size(),
-                 hipMemcpyHostToDevice));
+  BCHK(hipMemcpy(B.th_d, th.data(), sizeof(sc::Throat) * n, hipMemcpyHostToDevice));
+  if (!items.empty()) {
+    BCHK(hipMemcpy(B.items_d, items.data(), sizeof(sc::TileRef) * items.size(),
+                   hipMemcpyHostToDevice));
+    BCHK(hipMemcpy(B.chunks_d, chunks.data(), sizeof(sc::RedChunk) * chunks.size(),
+                   hipMemcpyHostToDevice));
+  }
   BCHK(hipMemcpy(B.first_d, first.data(), sizeof(int) * n, hipMemcpyHostToDevice));
   BCHK(hipMemcpy(B.count_d, count.data(), sizeof(int) * n, hipMemcpyHostToDevice));
   BCHK(hipMemcpy(B.info_d, rinfo.data(), sizeof(sc::RedInfo) * n, hipMemcpyHostToDevice));
@@ -335,24 +255,9 @@ int lbm_drain_batch(int n, const lbm_params *p, const double *pc, int n_pc, cons
     const std::vector<int> not_run((size_t)n * n_pc, LBM_PT_NOT_RUN);
     BCHK(hipMemcpy(B.status_d, not_run.data(), sizeof(int) * n * n_pc, hipMemcpyHostToDevice));
   }
-  {
-    std::vector<int> zper;
-    for (int t = 0; t < n; ++t)
-      if (B.h[t]->per & 4) zper.push_back(t);
-    if (zper.size() > 65535) {  // the ghost-plane kernel's grid y holds them
-      set_err("lbm_drain_batch: at most 65535 z-periodic subdomains per batch");
-      return LBM_EINVAL;
-    }
-    B.n_zper = (int)zper.size();
-    if (dalloc(&B.zper_d, zper.size())) return LBM_ENOMEM;
-    if (!zper.empty())
-      BCHK(hipMemcpy(B.zper_d, zper.data(), sizeof(int) * zper.size(), hipMemcpyHostToDevice));
-  }
-
   hipEvent_t w0 = B.wall[0], w1 = B.wall[1];
   BCHK(hipEventRecord(w0, B.stream));
-  // shared launch shape, then the initial decisions
-  if (int r = autotune(B, 6)) return r;
+  // the initial decisions
   sc::RampCfg cfg{c->tol, c->bisect_rel, c->max_steps, c->check_every, n_pc};
   BCHK(sc::launch_reduce_chunks(B.th_d, B.chunks_d, B.nchunks, B.info_d, 0, B.partials, B.probe,
                                 B.stream));
@@ -435,15 +340,15 @@ int lbm_drain_batch(int n, const lbm_params *p, const double *pc, int n_pc, cons
     lattice_steps = std::max(lattice_steps, R.total_steps);
   }
   if (info) {
-    info->tx = B.sched.tx;
-    info->ty = B.sched.ty;
-    info->lz = B.sched.lz;
+    info->tx = sc::kListTx;
+    info->ty = 0;
+    info->lz = 0;
     info->replays = replays;
     info->lattice_steps = replays * c->check_every;
     info->node_updates = node_updates;
     info->fluid_updates = fluid_updates;
     info->wall_ms = wall;
-    info->n_tiles = B.ntiles;
+    info->n_tiles = B.nitems;
   }
   if (failed) return LBM_WPARTIAL;
   return warn ? LBM_WNOTCONV : LBM_OK;

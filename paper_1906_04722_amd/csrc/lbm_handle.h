@@ -39,39 +39,41 @@ struct lbm_throat {
   float *g[2] = {nullptr, nullptr};  // A/B population buffers
   int cur = 0;                       // g[cur] holds the current state
   float *save[2] = {nullptr, nullptr};  // checkpoints used by the ramp
-  uint32_t *mask = nullptr;
-  uint2 *list_d = nullptr;           // non-solid nodes, storage order, with mask (node-list path)
-  uint32_t nlist = 0;
-  float2 *rho_d = nullptr;           // densities of the current step (node-list path)
+  bool bricks = false;               // brick numbering (else compact)
+  size_t n_live = 0;                 // non-solid nodes
+  size_t n_numbers = 0;              // numbers: n_live, or with padding and ghost planes
+  uint32_t *map_d = nullptr;         // index map
+  uint32_t *pos_d = nullptr;         // map positions of the non-solid nodes
+  float2 *rho_d = nullptr;           // densities of the current step (two passes)
+  uint32_t *mask_d = nullptr;        // mask words (bricks)
   uint8_t *types_d = nullptr;
   double *rres_d = nullptr;          // [in/out][component]
-  // chunked FP64 reduction: node chunks, per-chunk partials, sums + probe
-  sc::Chunk *chunks_d = nullptr;
+  // FP64 reduction: chunks of the node list, their partials, sums + probe
+  sc::RedChunk *chunks_d = nullptr;
   int nchunks = 0;
   sc::RedInfo *redinfo_d = nullptr;
-  int *chunk_first_d = nullptr;      // [1] = 0
-  int *chunk_count_d = nullptr;      // [1] = nchunks
+  int *red_first_d = nullptr;        // [1] = 0
+  int *red_count_d = nullptr;        // [1] = nchunks
   double *partials = nullptr;        // [nchunks][3]
   double *red_d = nullptr;           // [5]: masses, saturation sum, probe densities
   double *red_h = nullptr;           // pinned [5]
   hipEvent_t ev[2] = {nullptr, nullptr};
   std::vector<uint8_t> types;
-  std::vector<uint8_t> bricks;       // brick liveness map (sc::brick_map)
-  size_t n_nonsolid = 0;
   long long n_fluid = 0;
-  long long probe = -1;
+  long long probe = -1;              // number of the probe node
   double tau[2], G, Gads[2], rho_major, rho_minor, rho_in, rho_out;
   double phib = 1.0;
   sc::Phys P{};
-  sc::Sched sched{64, 4, 16};
+  sc::Sched sched{sc::kListTx, 0, 0};
+  std::vector<uint8_t> brick_live;   // brick liveness map (sc::brick_map)
   long long steps_done = 0;
-  // device descriptor and tile list of the fused step
+  // device descriptor and work items of the step
   sc::Throat desc{};
   sc::Throat *desc_d = nullptr;
   sc::TileRef *tiles_d = nullptr;
   int ntiles = 0;
   size_t tiles_cap = 0;
-  int *zper_d = nullptr;             // {0} on a z-periodic subdomain (ghost planes)
+  int *zper_d = nullptr;             // {0} with ghost planes to refresh
   int n_zper = 0;
   // event-timed step launches inside the drainage ramp
   hipEvent_t tev[2] = {nullptr, nullptr};
@@ -85,11 +87,17 @@ struct lbm_throat {
 namespace lbmh {
 
 void set_err(const char *fmt, ...);
-// refresh the device descriptor / rebuild the tile list of the schedule
+// lbm_throat_init, in the compact numbering whatever the box
+int init_compact(const lbm_params *p, lbm_throat_t *out);
+// refresh the device descriptor
 int sync_desc(lbm_throat *h);
-int rebuild_tiles(lbm_throat *h);
 int set_rho_in(lbm_throat *h, double r);
 int copy_state(lbm_throat *h, float *dst, const float *src);
+// whether the two passes need 64-bit addresses
+inline bool wide(const lbm_throat *h) {
+  return sizeof(float) * sc::pop_elems(h->n_numbers) > sc::kNarrowBytes ||
+         sizeof(uint32_t) * sc::map_elems(h->nx, h->ny, h->nz) > sc::kNarrowBytes;
+}
 // device memory of one subdomain (with or without the two ramp checkpoints)
 // and the refusal of a call whose need exceeds the memory budget
 size_t subdomain_bytes(int nx, int ny, int nz, bool checkpoints);

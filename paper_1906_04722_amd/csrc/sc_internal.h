@@ -10,64 +10,97 @@
 
 namespace sc {
 
-// node classes, stored in bits 24..25 of the per-node mask word; bits 0..18
-// flag the directions k whose pull source x - e_k is solid or beyond a wall
+// node classes
 enum : uint32_t { kFluid = 0, kSolid = 1, kResIn = 2, kResOut = 3 };
-constexpr int kTypeShift = 24;
-// bits 1..18 of a mask word: link k is cut (x - e_k solid or beyond a wall)
-constexpr uint32_t kLinkBits = 0x7FFFEu;
 
 // Population storage of one buffer: shifted FP32 populations g = f - w_k
-// rho_ref, q = 19 c + k for component c and direction k.  Each z-plane is cut
-// into bricks of 8 x 4 nodes (x, y; the plane padded to multiples of 8 and 4)
-// and a brick holds its 38 populations one after another, each a run of 32
-// floats (one 128-byte line) in (y mod 4, x mod 8) order: element (q, x, y, z)
-// is at (z + 1) Pp + ((y / 4) (nxp / 8) + x / 8) 38 * 32 + 32 q + 8 (y mod 4)
-// + x mod 8, Pp = 38 nxp nyp.  A line then holds a compact 8 x 4 patch of one
-// population, so the sparse, irregular fluid of a throat box wastes fewer
-// fetched bytes than with runs along x (1.55 against 2.44 fetched per useful
-// byte on a 96^3 four-sphere throat), and the 38 values of four rows of nodes
-// still share one 608 nxp-byte range.  Planes z = -1 and z = nz are ghost
-// copies of planes nz - 1 and 0 on z-periodic subdomains (unused otherwise),
-// so that the pulls of a node on plane z read planes z - 1 .. z + 1 only: one
-// base address and 32-bit offsets.
+// rho_ref, q = 19 c + k for component c and direction k, of numbered nodes; 32
+// consecutive numbers hold their 38 populations one after another, each a run
+// of 32 floats (one 128-byte line): element (q, i) is at (i / 32) 38 * 32 +
+// 32 q + i % 32.  Two numberings:
+//
+//  - compact: the non-solid nodes only, whole rows along x, in groups of
+//    kGroupY rows that are marched through z.  No solid node takes space or
+//    part of a line, and the 64 lanes of a wavefront pull runs of a few
+//    neighbouring lines.  The step goes over it in two passes.
+//  - bricks: every node of the box padded to whole bricks of 8 x 4 nodes per
+//    z-plane, brick by brick, with a ghost plane at each end (brick_number).
+//    Numbers follow from coordinates, so the tiled step needs no index map; it
+//    reads each population once.  For nearly all-fluid boxes (kTileFill).
 constexpr int kQ = 38;
-constexpr int kBX = 8, kBY = 4, kBN = kBX * kBY;  // brick of one 128-byte line
-#ifndef SC_BRICK_OX
-#define SC_BRICK_OX 0
-#endif
-#ifndef SC_BRICK_OY
-#define SC_BRICK_OY 0
-#endif
-constexpr int kOX = SC_BRICK_OX, kOY = SC_BRICK_OY;
-__host__ __device__ inline int pad_x(int nx) { return (nx + kOX + kBX - 1) / kBX * kBX; }
-__host__ __device__ inline int pad_y(int ny) { return (ny + kOY + kBY - 1) / kBY * kBY; }
-__host__ __device__ inline size_t pop_plane(int nx, int ny) {
+constexpr int kLine = 32;
+__host__ __device__ inline size_t pop_elems(size_t numbers) {
+  return (numbers + kLine - 1) / kLine * (size_t)(kQ * kLine);
+}
+constexpr int kGroupY = 32;
+
+// Index map of one subdomain: the number of the node at (x, y, z), or kNoNode
+// where it is solid or beyond a wall, for -2 <= x < nx + 2 (likewise y, z); on
+// periodic axes the two layers beyond the box repeat the nodes they wrap to.
+// A pull or a density stencil reads its neighbours' numbers here, so no
+// kernel handles walls, wraps or solid neighbours apart from kNoNode.
+constexpr uint32_t kNoNode = 0xFFFFFFFFu;
+constexpr int kPad = 2;
+__host__ __device__ inline size_t map_elems(int nx, int ny, int nz) {
+  return (size_t)(nx + 2 * kPad) * (size_t)(ny + 2 * kPad) * (size_t)(nz + 2 * kPad);
+}
+__host__ __device__ inline size_t map_pos(int nx, int ny, int x, int y, int z) {
+  return ((size_t)(z + kPad) * (size_t)(ny + 2 * kPad) + (size_t)(y + kPad)) *
+             (size_t)(nx + 2 * kPad) +
+         (size_t)(x + kPad);
+}
+
+// Bricks of 8 x 4 nodes (x, y; the plane padded to multiples of 8 and 4):
+// element (q, x, y, z) is at (z + 1) Pp + ((y / 4) (nxp / 8) + x / 8) 38 * 32 +
+// 32 q + 8 (y mod 4) + x mod 8, Pp = 38 nxp nyp.  A line holds a compact 8 x 4
+// patch of one population.  Planes z = -1 and z = nz are ghost copies of
+// planes nz - 1 and 0 on z-periodic subdomains (unused otherwise), so that
+// the pulls of a node on plane z read planes z - 1 .. z + 1 only: one base
+// address and 32-bit offsets.  Checkpoint files hold every subdomain in this
+// layout, solid nodes as zeros, whatever its numbering.
+constexpr int kBX = 8, kBY = 4, kBN = kBX * kBY;
+static_assert(kBN == kLine, "a brick is one line per population");
+__host__ __device__ inline int pad_x(int nx) { return (nx + kBX - 1) / kBX * kBX; }
+__host__ __device__ inline int pad_y(int ny) { return (ny + kBY - 1) / kBY * kBY; }
+__host__ __device__ inline size_t brick_plane(int nx, int ny) {
   return (size_t)kQ * pad_x(nx) * pad_y(ny);
 }
-__host__ __device__ inline size_t pop_elems(int nx, int ny, int nz) {
-  return pop_plane(nx, ny) * (size_t)(nz + 2);
+__host__ __device__ inline size_t brick_elems(int nx, int ny, int nz) {
+  return brick_plane(nx, ny) * (size_t)(nz + 2);
 }
 // offset of population 0 of node (x, y) within its plane (0 <= x < nx,
 // 0 <= y < ny); population q is 32 q further
 __host__ __device__ inline uint32_t brick_x(int x) {
-  return (uint32_t)((x + kOX) / kBX) * (uint32_t)(kQ * kBN) + (uint32_t)((x + kOX) % kBX);
+  return (uint32_t)(x / kBX) * (uint32_t)(kQ * kBN) + (uint32_t)(x % kBX);
 }
 __host__ __device__ inline uint32_t brick_y(int y, int nx) {
-  return (uint32_t)((y + kOY) / kBY) * (uint32_t)(pad_x(nx) / kBX) * (uint32_t)(kQ * kBN) +
-         (uint32_t)((y + kOY) % kBY) * (uint32_t)kBX;
+  return (uint32_t)(y / kBY) * (uint32_t)(pad_x(nx) / kBX) * (uint32_t)(kQ * kBN) +
+         (uint32_t)(y % kBY) * (uint32_t)kBX;
+}
+// number of node (x, y, z) in the brick numbering
+__host__ __device__ inline uint32_t brick_number(int nx, int ny, int x, int y, int z) {
+  const uint32_t bricks = (uint32_t)(pad_x(nx) / kBX) * (uint32_t)(pad_y(ny) / kBY);
+  return ((uint32_t)(z + 1) * bricks + (uint32_t)(y / kBY) * (uint32_t)(pad_x(nx) / kBX) +
+          (uint32_t)(x / kBX)) * (uint32_t)kBN + (uint32_t)(y % kBY) * kBX + (uint32_t)(x % kBX);
 }
 // largest padded nx * ny whose three-plane pull offsets fit 32 bits of bytes
 constexpr long long kMaxPlaneNodes = (1LL << 32) / (3LL * kQ * 4) - 1;
+
+// mask word of a node (tiled step): bits 1..18 flag the directions k whose
+// pull source x - e_k is solid or beyond a wall, bits 24..25 its class
+constexpr int kTypeShift = 24;
+constexpr uint32_t kLinkBits = 0x7FFFEu;
 
 // one subdomain as the per-node kernels see it
 struct Dom {
   const float *src;      // post-collision state of the previous step
   float *dst;            // post-collision state written by this step
-  const uint32_t *mask;  // [N] link bits + node class
-  size_t N;              // nodes = nx * ny * nz
+  const uint32_t *map;   // index map
+  const uint32_t *mask;  // [N] mask words (brick numbering only)
+  size_t N;              // box nodes = nx * ny * nz
   int nx, ny, nz;
   int per;               // bit 0/1/2: x/y/z periodic
+  int res;               // 1: z = 0 and z = nz - 1 are density baths
 };
 
 // physical parameters in the precision the step computes in
@@ -80,42 +113,36 @@ struct Phys {
 };
 
 // launch shape of the step: tiles of tx x ty columns marching lz planes in
-// one fused pass, or (tx = kListTx) the node-list path of two passes over
-// the non-solid nodes only (densities, then the fused pull-collide-store)
+// one fused pass (brick numbering), or (tx = kListTx) two passes over the
+// non-solid nodes
 struct Sched {
   int tx, ty, lz;
 };
 constexpr int kListTx = -1;
 
-// tile shapes (tx, ty) the fused step is built for; lz is free (>= 1).  The
-// narrow shapes fit thin prism subdomains with fewer solid columns per tile.
+// tile shapes (tx, ty) the fused step is built for; lz is free (>= 1)
 constexpr int kNumShapes = 6;
 constexpr int kShapes[kNumShapes][2] = {{32, 4}, {32, 8}, {64, 4}, {16, 4}, {16, 8}, {8, 8}};
 
-// one subdomain as the fused step sees it: both population buffers, the
-// mask, the size, the tile grid of the launch schedule and the parameters
-// (a launch covers the tiles of one or many of these)
+// one subdomain as the step sees it (a launch covers one or many of these)
 struct Throat {
   float *g[2];           // A/B buffers; the state is in g[parity]
-  const uint32_t *mask;
-  uint32_t N;
-  int nx, ny, nz, per;
-  int ntx, nty, lz;      // tile grid: tiles of TX x TY nodes and lz planes
+  const uint32_t *map;
+  const uint32_t *pos;   // map position of each non-solid node, in number order
+  float2 *rho;           // two passes: densities of the current step, by number
+  uint32_t n_live;
+  int nx, ny, nz, res;
   int active;            // 0: the launch skips this subdomain
-  const uint2 *list;     // node-list path: non-solid nodes in storage order (index, mask word)
-  uint32_t nlist;
-  float2 *rho;           // node-list path: densities of the current step [N]
   Phys P;
+  const uint32_t *mask;  // tiled step: mask words, box size, tile grid
+  uint32_t N;
+  int per, ntx, nty, lz;
 };
 
-// node-list path: one workgroup of kListBlock threads per kListNodes
-// consecutive entries of a subdomain's node list (TileRef::tile = chunk), a
-// pair of lanes per node (one per component)
-constexpr int kListBlock = 256;
-constexpr int kListNodes = kListBlock / 2;
-
-// one tile of work: subdomain index and packed tile coordinate
-// tix + ntx * (tiy + nty * tiz)
+// a work item of the two passes: kListNodes consecutive nodes of a subdomain
+constexpr int kListNodes = 128;
+// one item of work: subdomain and its packed tile coordinate
+// tix + ntx * (tiy + nty * tiz), or its index among the subdomain's items
 struct TileRef {
   int throat;
   int tile;
@@ -137,30 +164,48 @@ void bin_spheres(const double *sph, int ns, int nx, int ny, int nz, std::vector<
 hipError_t launch_voxelize(const double *spheres, const VoxBins &bins, int prism,
                            const int *prism_ids, int nx, int ny, int nz, int bc_z_reservoir,
                            uint8_t *types, hipStream_t st);
-hipError_t launch_links(const uint8_t *types, int nx, int ny, int nz, int per, uint32_t *mask,
-                        hipStream_t st);
-// node-list entries: out[i] = (ids[i], mask[ids[i]]) for i < n
-hipError_t launch_list_entries(const uint32_t *ids, const uint32_t *mask, uint32_t n, uint2 *out,
-                               hipStream_t st);
+// non-solid nodes of each row (y, z), counts[z * ny + y]
+hipError_t launch_row_counts(const uint8_t *types, int nx, int ny, int nz, uint32_t *counts,
+                             hipStream_t st);
+// host: first number of each row in the compact numbering, from its count, in
+// place; returns the number of nodes
+size_t number_rows(std::vector<uint32_t> &rows, int ny, int nz);
+// index map and positions: compact from the rows' first numbers, or (rows
+// null) bricks, whose live nodes are listed row by row in the same order
+hipError_t launch_number(const uint8_t *types, int nx, int ny, int nz, int per,
+                         const uint32_t *rows, bool bricks, uint32_t *map, uint32_t *pos,
+                         hipStream_t st);
+hipError_t launch_links(const uint8_t *types, const Dom &d, uint32_t *mask, hipStream_t st);
 hipError_t launch_init(const Dom &d, const Phys &P, const double *rho_init, double rho_major,
                        double rho_minor, int z_front, const double *rres_d, float *g,
                        hipStream_t st);
-// one time step of every active subdomain in `throats` over the listed tiles
-// (device arrays); tx, ty is the tile shape the lists were built for.
-// zper_ids (device, n_zper entries): the z-periodic subdomains, whose ghost
-// planes are refreshed after the step.
+// one time step of every active subdomain in `throats` over the listed items
+// (device arrays) at launch shape tx, ty.  wide: some buffer or index map
+// exceeds kNarrowBytes (two passes).  zper_ids (device, n_zper entries): the
+// z-periodic subdomains in bricks, whose ghost planes are refreshed after the
+// step.
+constexpr size_t kNarrowBytes = ((size_t)1 << 32) - 16384;
 hipError_t launch_step(const Throat *throats, const TileRef *tiles, int ntiles, int tx, int ty,
-                       int parity, hipStream_t st, const int *zper_ids, int n_zper);
+                       bool wide, int parity, hipStream_t st, const int *zper_ids, int n_zper);
+// refresh the ghost planes of buffer g[which] of the listed subdomains
+hipError_t launch_ghost(const Throat *throats, const int *zper_ids, int n_zper, int which,
+                        hipStream_t st);
 // host: per plane, which 8 x 4 bricks hold a non-solid node ([nz][nyp / 4]
-// [nxp / 8] bytes), and the number of non-solid nodes; computed once per
-// subdomain from its node classes
-void brick_map(const uint8_t *types, int nx, int ny, int nz, std::vector<uint8_t> &live,
-               size_t &nonsolid);
+// [nxp / 8] bytes); computed once per subdomain in bricks
+void brick_map(const uint8_t *types, int nx, int ny, int nz, std::vector<uint8_t> &live);
 // host: append the tiles of subdomain `throat` that hold at least one
 // non-solid node (solid-only tiles need no update), from its brick map; every
 // tile shape is a whole number of bricks
-void list_tiles(const uint8_t *live, size_t nonsolid, int nx, int ny, int nz, int tx, int ty,
-                int lz, int throat, std::vector<TileRef> &out);
+void list_tiles(const uint8_t *live, int nx, int ny, int nz, int tx, int ty, int lz, int throat,
+                std::vector<TileRef> &out);
+// host: append the two passes' items of subdomain `throat`
+void list_items(size_t n_live, int throat, std::vector<TileRef> &out);
+// populations of the flat range [first, first + count) of the checkpoint-file
+// layout, gathered from or scattered into a population buffer
+hipError_t launch_to_file(const Dom &d, const float *g, size_t first, size_t count, float *out,
+                          hipStream_t st);
+hipError_t launch_from_file(const Dom &d, const float *in, size_t first, size_t count, float *g,
+                            hipStream_t st);
 hipError_t launch_export(const Dom &d, const Phys &P, const double *rres_d, double *f,
                          hipStream_t st);
 hipError_t launch_density(const Dom &d, const Phys &P, const double *rres_d, double *rho,
@@ -172,31 +217,35 @@ hipError_t launch_density(const Dom &d, const Phys &P, const double *rres_d, dou
 constexpr size_t kScratchNodes = (size_t)1 << 21;
 constexpr size_t kScratchDoubles = 2 * kScratchNodes;
 hipError_t scratch_address(double **out);
-// chunked FP64 reduction over subdomains: each reduction chunk is a range of
-// kRedEntries entries of one subdomain's node list; per chunk the partial
-// sums of rho_w, rho_nw and the saturation term over its fluid nodes, then
-// per subdomain the sum of its chunks in order.  Copy chunks (the batch's
-// checkpoint copies) split each subdomain's buffer by node ranges of
-// kChunkNodes instead, so that a copy gets blocks in proportion to its size.
-struct Chunk {
-  int throat;
-  uint32_t start, count;
-};
+// FP64 reduction over subdomains: the sums of rho_w, rho_nw and the
+// saturation term over the fluid nodes among kRedNodes consecutive non-solid
+// nodes, then per subdomain the sum of these, both in a fixed order.
 struct RedInfo {
-  long long probe;  // probe node or -1
+  long long probe;  // number of the probe node or -1
   double phib;      // bulk order parameter of the saturation map
 };
-constexpr uint32_t kChunkNodes = 4096;
-constexpr uint32_t kRedEntries = 1024;
-void list_chunks(int throat, uint32_t N, std::vector<Chunk> &out);
-void list_red_chunks(int throat, uint32_t nlist, std::vector<Chunk> &out);
+constexpr int kRedNodes = 1024;
+struct RedChunk {
+  int throat;
+  uint32_t first;  // index of its first node
+};
+void red_chunks(size_t n_live, int throat, std::vector<RedChunk> &out);
 // partials[c][3]; probe_out[t][2] = densities at subdomain t's probe node
-hipError_t launch_reduce_chunks(const Throat *th, const Chunk *chunks, int nchunks,
+hipError_t launch_reduce_chunks(const Throat *th, const RedChunk *chunks, int nchunks,
                                 const RedInfo *info, int parity, double *partials,
                                 double *probe_out, hipStream_t st);
-// sums[t][3] = sum over chunks first[t] .. first[t]+count[t]-1, in order
+// sums[t][3] over chunks first[t] .. first[t]+count[t]-1
 hipError_t launch_reduce_throats(const int *first, const int *count, int n, const double *partials,
                                  double *sums, hipStream_t st);
+// a range of a subdomain's population buffer (the batch's checkpoint copies):
+// `count` 16-byte elements from `start`, both in units of 4 floats
+struct Chunk {
+  int throat;
+  uint32_t count;
+  unsigned long long start;
+};
+constexpr uint32_t kCopyChunk = 32768;
+void copy_chunks(int throat, size_t elems, std::vector<Chunk> &out);
 // plain copy of n_floats (a multiple of 4) floats, 16-byte aligned buffers
 hipError_t launch_copy(const float *a, float *b, size_t n_floats, hipStream_t st);
 
@@ -242,7 +291,7 @@ hipError_t launch_ramp_advance(Throat *th, RampDev *rd, const double *pc, const 
                                const double *sums, const double *probe, double *S_out,
                                long long *steps_out, int *status_out, int n, int *n_active_out,
                                hipStream_t st);
-// perform the copy requests of every subdomain (over the reduction chunks)
+// perform the copy requests of every subdomain, over its copy chunks
 hipError_t launch_copy_requests(const Throat *th, const RampDev *rd, const Ckpt *ck,
                                 const Chunk *chunks, int nchunks, int parity, hipStream_t st);
 

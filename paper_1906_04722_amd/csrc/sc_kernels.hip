@@ -1,27 +1,26 @@
 // sc_kernels.hip -- gfx950 kernels of the two-component Shan-Chen D3Q19
 // update (Montella et al., Sec. 2.1, Eq. 1-5) on one pore-throat subdomain.
 //
-// Storage: shifted FP32 populations g = f - w_k rho_ref in bricks of 8 x 4
-// nodes per z-plane, each population of a brick one 128-byte line, so that
-// the 64 lanes of a wavefront read and write two whole lines per population
-// (layout and ghost planes in sc_internal.h).  The update is a
-// pull scheme: buffer `src` holds the post-collision state of step t-1 at
-// each node's own position; pulling g_k from x - e_k gives the pre-collision
-// state f(x, t) of Eq. 1.  One kernel does the whole step: pull + half-way
-// bounce-back, moments (Eq. 2-3), the cohesion force (Eq. 4) from an LDS ring
-// of density planes, the adhesion force from the node's link bits, the
-// velocity shift, BGK relaxation toward the component equilibria (Eq. 1) and
-// the store of the post-collision state.
+// Storage: shifted FP32 populations g = f - w_k rho_ref of numbered nodes, each
+// population of 32 consecutive numbers one 128-byte line (numberings, index
+// map and ghost planes in sc_internal.h).  The update is a pull scheme: buffer
+// `src` holds the post-collision state of step t-1 at each node's own
+// position; pulling g_k from x - e_k gives the pre-collision state f(x, t) of
+// Eq. 1: pull + half-way bounce-back, moments (Eq. 2-3), the cohesion force
+// (Eq. 4) from the 18 neighbours' densities, the adhesion force from the
+// node's cut links, the velocity shift, BGK relaxation toward the component
+// equilibria (Eq. 1) and the store of the post-collision state.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "geom.h"
 #include "sc_internal.h"
 
 // Multiply-adds are fused only where one source expression reads a * b + c,
 // never across statements, so every kernel that shares the arithmetic below
-// (the tiled step, the node-list step, the export) rounds it identically.
+// (both steps, the reduction, the export) rounds it identically.
 #pragma clang fp contract(on)
 
 namespace sc {
@@ -49,92 +48,120 @@ __host__ __device__ constexpr double wd(int k) {
 
 // ---- node addressing ------------------------------------------------------
 
-// Map (X, Y, Z), which may lie one node beyond the box, to a node index:
-// wrapped on periodic axes, -1 beyond a wall.  Coordinates further out (the
-// unused halo slots of a ragged tile) also give -1.
-__device__ __forceinline__ long long node_of(const Dom &d, int X, int Y, int Z) {
-  if (X < -1 || X > d.nx || Y < -1 || Y > d.ny || Z < -1 || Z > d.nz) return -1;
-  if (X < 0 || X >= d.nx) {
-    if (!(d.per & 1)) return -1;
-    X = X < 0 ? X + d.nx : X - d.nx;
-  }
-  if (Y < 0 || Y >= d.ny) {
-    if (!(d.per & 2)) return -1;
-    Y = Y < 0 ? Y + d.ny : Y - d.ny;
-  }
-  if (Z < 0 || Z >= d.nz) {
-    if (!(d.per & 4)) return -1;
-    Z = Z < 0 ? Z + d.nz : Z - d.nz;
-  }
-  return (long long)X + (long long)d.nx * ((long long)Y + (long long)d.ny * Z);
-}
-
-__device__ __forceinline__ int wrap(int c, int n) { return c < 0 ? c + n : (c >= n ? c - n : c); }
-
-// Pull the pre-collision populations f(x,t) - w_k rho_ref of the fluid node
-// at (X, Y, Z) with link bits m: g_k from x - e_k, or the reflected g_opp(k)
-// at x itself when the link to x - e_k is cut by a solid node or a wall
-// (half-way bounce-back).  Addresses are the start of plane Z - 1 (uniform
-// across a tile) plus a 32-bit byte offset per lane.  In the brick storage
-// the offset of a node is the sum of an x part and a y part (brick_x,
-// brick_y); with P the elements of a plane, population q of the node itself
-// is at P + y(Y) + x(X) + 32 q, of the source node at (1 - ez) P + y(Ys) +
-// x(Xs) + 32 q.  The second component's populations follow 19 * 32 later.
-// Xs and Ys are taken modulo nx and ny: across a periodic face that is the
-// wrapped neighbour, across a wall the link is cut and the offset unused.
-// global-memory views of the population buffers: loads and stores then take
-// a uniform 64-bit base and a 32-bit per-lane offset
+// global-memory views of the buffers: loads and stores then take a uniform
+// 64-bit base and a 32-bit per-lane offset
 typedef const __attribute__((address_space(1))) char gcchar;
 typedef __attribute__((address_space(1))) char gchar;
+typedef const __attribute__((address_space(1))) uint32_t gcu32;
+typedef const __attribute__((address_space(1))) float gcfloat;
+typedef __attribute__((address_space(1))) float gfloat;
 
-template <int K>
-__device__ __forceinline__ void pull_dir(gcchar *b0, gcchar *b1, uint32_t m, uint32_t own,
-                                         uint32_t s, float (&v)[2][19]) {
-  constexpr int o = opp(K);
-  const bool cut = (m >> K) & 1u;
-  const uint32_t off = cut ? own + (uint32_t)(o * kBN) : s + (uint32_t)(K * kBN);
-  v[0][K] = *(const __attribute__((address_space(1))) float *)(b0 + (size_t)(off * 4u));
-  v[1][K] = *(const __attribute__((address_space(1))) float *)(b1 + (size_t)(off * 4u));
+// Numbers of a node's D3Q19 neighbours: the nine rows (y + dy, z + dz) of the
+// index map around it, three of x - 1 .. x + 1 where D3Q19 has them all.
+struct Near {
+  uint32_t r[5][3];  // rows (0, 0), (-1, 0), (1, 0), (0, -1), (0, 1) of (dy, dz)
+  uint32_t c[4];     // x itself in rows (-1, -1), (1, -1), (-1, 1), (1, 1)
+};
+// number of the node at x + (DX, DY, DZ)
+template <int DX, int DY, int DZ>
+__device__ __forceinline__ uint32_t near_at(const Near &n) {
+  static_assert(DX * DX + DY * DY + DZ * DZ <= 2, "a D3Q19 neighbour");
+  if constexpr (DY != 0 && DZ != 0)
+    return n.c[(DY > 0 ? 1 : 0) + (DZ > 0 ? 2 : 0)];
+  else
+    return n.r[DZ != 0 ? (DZ < 0 ? 3 : 4) : (DY != 0 ? (DY < 0 ? 1 : 2) : 0)][1 + DX];
 }
 
-// source offset of direction K: planes, then the y and x parts of x - e_k
-// (index 0: coordinate - 1, 1: itself, 2: + 1)
-template <int K>
-__device__ __forceinline__ uint32_t src_index(uint32_t P, const uint32_t (&py)[3],
-                                              const uint32_t (&px)[3]) {
-  return (uint32_t)(1 - ez(K)) * P + py[1 - ey(K)] + px[1 - ex(K)];
+// the map element at map + off is position (x - 1, y - 1, z - 1); px, pp: row
+// and plane strides of the map.  (Written out row by row: an index that is
+// constant only after unrolling can keep a Near in memory.)
+template <class Off, int DY, int DZ>
+__device__ __forceinline__ gcchar *near_row(const uint32_t *map, Off off, uint32_t px, size_t pp) {
+  return (gcchar *)(map + (size_t)(1 + DZ) * pp + (size_t)((uint32_t)(1 + DY) * px)) +
+         (size_t)(Off)(off * (Off)4);
 }
-
-template <int K>
-__device__ __forceinline__ void pull_rec(gcchar *b0, gcchar *b1, uint32_t m, uint32_t own,
-                                         uint32_t P, const uint32_t (&py)[3],
-                                         const uint32_t (&px)[3], float (&v)[2][19]) {
-  pull_dir<K>(b0, b1, m, own, src_index<K>(P, py, px), v);
-  if constexpr (K + 1 < 19) pull_rec<K + 1>(b0, b1, m, own, P, py, px, v);
-}
-
-__device__ __forceinline__ void pull(const Dom &d, uint32_t m, int X, int Y, int Z,
-                                     float (&v)[2][19]) {
-  const uint32_t P = (uint32_t)pop_plane(d.nx, d.ny);
-  gcchar *b0 = (gcchar *)(d.src + (size_t)P * (size_t)Z);
-  gcchar *b1 = b0 + (size_t)(19 * kBN * 4);
-  uint32_t px[3], py[3];
-  px[0] = brick_x(X == 0 ? d.nx - 1 : X - 1);
-  px[1] = brick_x(X);
-  px[2] = brick_x(X == d.nx - 1 ? 0 : X + 1);
-  py[0] = brick_y(Y == 0 ? d.ny - 1 : Y - 1, d.nx);
-  py[1] = brick_y(Y, d.nx);
-  py[2] = brick_y(Y == d.ny - 1 ? 0 : Y + 1, d.nx);
-  // The offsets do not depend on Z (the base does), so a z-marching loop
-  // would otherwise keep all 38 of them live in registers across planes;
-  // these opaque moves make them cheap per-plane arithmetic instead.
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    asm volatile("" : "+v"(px[i]));
-    asm volatile("" : "+v"(py[i]));
+template <class Off>
+__device__ __forceinline__ void load_near(const uint32_t *map, Off off, uint32_t px, size_t pp,
+                                          Near &n) {
+#define NEAR_ROW(i, DY, DZ)                                       \
+  {                                                               \
+    gcchar *row = near_row<Off, DY, DZ>(map, off, px, pp);        \
+    n.r[i][0] = *(gcu32 *)row;                                    \
+    n.r[i][1] = *(gcu32 *)(row + 4);                              \
+    n.r[i][2] = *(gcu32 *)(row + 8);                              \
   }
-  const uint32_t own = P + py[1] + px[1];
-  pull_rec<0>(b0, b1, m, own, P, py, px, v);
+  NEAR_ROW(0, 0, 0)
+  NEAR_ROW(1, -1, 0)
+  NEAR_ROW(2, 1, 0)
+  NEAR_ROW(3, 0, -1)
+  NEAR_ROW(4, 0, 1)
+#undef NEAR_ROW
+  n.c[0] = *(gcu32 *)(near_row<Off, -1, -1>(map, off, px, pp) + 4);
+  n.c[1] = *(gcu32 *)(near_row<Off, 1, -1>(map, off, px, pp) + 4);
+  n.c[2] = *(gcu32 *)(near_row<Off, -1, 1>(map, off, px, pp) + 4);
+  n.c[3] = *(gcu32 *)(near_row<Off, 1, 1>(map, off, px, pp) + 4);
+}
+
+// Element of population 0 of node i within its buffer, and the same in bytes
+// where a buffer is small enough for 32 bits (one full-rate 24-bit
+// multiply-add; i >> 5 < 2^24 there).
+__device__ __forceinline__ size_t node_elem(uint32_t i) {
+  return (size_t)(i >> 5) * (size_t)(kQ * kLine) + (size_t)(i & 31u);
+}
+__device__ __forceinline__ uint32_t node_bytes(uint32_t i) {
+  return __umul24(i >> 5, (uint32_t)(4 * (kQ - 1) * kLine)) + (i << 2);
+}
+
+// Pull the pre-collision populations f(x,t) - w_k rho_ref of the fluid node
+// with number i: g_k from x - e_k, or the reflected g_opp(k) of the node
+// itself when x - e_k is solid or beyond a wall (half-way bounce-back).  m
+// receives the cut links (bits 1..18).  WIDE: 64-bit addresses per lane; else
+// one uniform base and 32-bit byte offsets, kept one line above the start so
+// that the reflected slot of the first node does not go below zero.
+template <bool WIDE, int K>
+__device__ __forceinline__ void pull_rec(const float *src, uint32_t i, const Near &n, uint32_t &m,
+                                         float (&v)[2][19]) {
+  constexpr int o = opp(K);
+  const uint32_t s = near_at<-ex(K), -ey(K), -ez(K)>(n);
+  const bool cut = K != 0 && s == kNoNode;
+  if (K != 0) m |= cut ? 1u << K : 0u;
+  // selects, not branches: the 38 loads issue back to back
+  const uint32_t j = cut ? i : s;
+  const int shift = cut ? (o - K) * 4 * kLine : 0;
+  gcchar *p;
+  if constexpr (WIDE)
+    p = (gcchar *)(src + node_elem(j)) + shift;
+  else
+    p = (gcchar *)src - 4 * kLine + (size_t)(node_bytes(j) + (uint32_t)(4 * kLine + shift));
+  v[0][K] = *(gcfloat *)(p + K * 4 * kLine);
+  v[1][K] = *(gcfloat *)(p + (19 + K) * 4 * kLine);
+  if constexpr (K + 1 < 19) pull_rec<WIDE, K + 1>(src, i, n, m, v);
+}
+
+template <bool WIDE>
+__device__ __forceinline__ void pull(const float *src, const Near &n, uint32_t &m,
+                                     float (&v)[2][19]) {
+  m = 0;
+  pull_rec<WIDE, 0>(src, n.r[0][1], n, m, v);
+}
+
+// the same for the node at (x, y, z) of the box
+__device__ __forceinline__ void pull_at(const Dom &d, int x, int y, int z, float (&v)[2][19]) {
+  Near n;
+  uint32_t m;
+  const uint32_t px = (uint32_t)(d.nx + 2 * kPad);
+  load_near<size_t>(d.map, map_pos(d.nx, d.ny, x - 1, y - 1, z - 1), px,
+                    (size_t)px * (size_t)(d.ny + 2 * kPad), n);
+  pull<true>(d.src, n, m, v);
+}
+
+// class of a box node: solid without a number, a bath on the first and last
+// plane of a subdomain with baths
+__device__ __forceinline__ uint32_t class_at(const Dom &d, int x, int y, int z) {
+  if (d.map[map_pos(d.nx, d.ny, x, y, z)] == kNoNode) return kSolid;
+  if (d.res && z == 0) return kResIn;
+  if (d.res && z == d.nz - 1) return kResOut;
+  return kFluid;
 }
 
 // Type of the density sums.  Populations are stored in FP32 (the HBM
@@ -146,40 +173,6 @@ __device__ __forceinline__ acc_t sum19(const float (&a)[19]) {
 #pragma unroll
   for (int k = 0; k < 19; ++k) s += (acc_t)a[k];
   return s;
-}
-
-// Density seen by the interaction sums at (X, Y, Z): zero on solid nodes and
-// beyond walls, the imposed value on bath nodes, Eq. 2 on fluid nodes.  With
-// KEEP, the pulled populations, the mask word and the two FP64 sums of the
-// shifted populations (zero unless the node is fluid) are returned for the
-// collision of this node.
-template <bool KEEP>
-__device__ __forceinline__ float2 density_at(const Dom &d, const Phys &P, int X, int Y, int Z,
-                                             float (&v)[2][19], uint32_t &mword,
-                                             double (&ds)[2]) {
-  if (KEEP) ds[0] = ds[1] = 0.0;
-  const long long n = node_of(d, X, Y, Z);
-  if (n < 0) {
-    if (KEEP) mword = kSolid << kTypeShift;
-    return make_float2(0.f, 0.f);
-  }
-  const uint32_t m = d.mask[n];
-  if (KEEP) mword = m;
-  const uint32_t t = m >> kTypeShift;
-  if (t == kSolid) return make_float2(0.f, 0.f);
-  if (t == kResIn) return make_float2(P.rres[0][0], P.rres[0][1]);
-  if (t == kResOut) return make_float2(P.rres[1][0], P.rres[1][1]);
-  int X2 = wrap(X, d.nx), Y2 = wrap(Y, d.ny), Z2 = wrap(Z, d.nz);
-  if (KEEP) {
-    pull(d, m, X2, Y2, Z2, v);
-    ds[0] = sum19(v[0]);
-    ds[1] = sum19(v[1]);
-    return make_float2((float)((acc_t)P.rho_ref + ds[0]), (float)((acc_t)P.rho_ref + ds[1]));
-  } else {
-    float t2[2][19];
-    pull(d, m, X2, Y2, Z2, t2);
-    return make_float2((float)((acc_t)P.rho_ref + sum19(t2[0])), (float)((acc_t)P.rho_ref + sum19(t2[1])));
-  }
 }
 
 // BGK collision of one fluid node (Eq. 1 right-hand side) with the cohesion
@@ -196,7 +189,7 @@ __device__ __forceinline__ float2 density_at(const Dom &d, const Phys &P, int X,
 // FP32 rounding of the weights (their FP32 sum is not exactly 1) cannot bias
 // the mass step after step.  Momenta are summed from opposite-pair
 // differences.  drd: the FP64 sums of each component's 19 shifted
-// populations, as density_at() took them when the node was pulled.
+// populations, as taken when the node was pulled; m: the node's cut links (bits 1..18).
 __device__ __forceinline__ void collide(const Phys &P, uint32_t m, const float (&Sw)[3],
                                         const float (&Sn)[3], const double (&drd)[2],
                                         float (&v)[2][19]) {
@@ -236,8 +229,7 @@ __device__ __forceinline__ void collide(const Phys &P, uint32_t m, const float (
   }
   const float it0 = P.itau[0], it1 = P.itau[1];
   const float den = rho[0] * it0 + rho[1] * it1;
-  // quotients as products with three reciprocals (the node-list path below
-  // takes the same ones, so both paths stay bit-identical)
+  // quotients as products with three reciprocals
   const float iden = 1.0f / den;
   float up[3];
 #pragma unroll
@@ -267,11 +259,275 @@ __device__ __forceinline__ void collide(const Phys &P, uint32_t m, const float (
   }
 }
 
+// Store the post-collision populations of node i.
+template <bool WIDE>
+__device__ __forceinline__ void store_node(float *dst, uint32_t i, const float (&v)[2][19]) {
+  gchar *p = WIDE ? (gchar *)(dst + node_elem(i)) : (gchar *)dst + (size_t)node_bytes(i);
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int k = 0; k < 19; ++k)
+      __builtin_nontemporal_store(v[c][k], (gfloat *)(p + (19 * c + k) * 4 * kLine));
+}
+
+// work lists are handed out so that each XCD (workgroups b = xcd mod 8) gets
+// one contiguous range, keeping spatial neighbours in one L2
+__device__ __forceinline__ int xcd_item(int n) {
+  const int b = blockIdx.x, q = n >> 3, r = n & 7, xcd = b & 7, idx = b >> 3;
+  return xcd * q + min(xcd, r) + idx;
+}
+
+// ---- two passes over the non-solid nodes --------------------------------------------
+// k_dens writes each non-solid node's two densities, k_node pulls again, takes
+// the 18-neighbour density stencil from that array, collides and stores.
+//
+// Bound: the rate at which the eight L2s exchange lines with the memory side
+// (6.2 TB/s for a copy).  A step fetches 152 + 152 bytes of populations per
+// node and writes 152, beside 20 of positions, index map and densities; counted
+// on the 256^3 packed sample (6.4 M of 16.8 M nodes): 2.19 GB fetched and
+// 1.02 GB written, against 1.95 and 1.02 without waste.  Before, one fused pass
+// in tiles over all nodes of the box refetched halo lines and moved partly used
+// lines: 3.7 GB and 873-893 us a step on that sample, now 660; 40-sphere
+// sample with membrane 113 -> 64 us, 96^3 throat 18.4 -> 12.9 us, 40^3 throat
+// 11.4 (33 in the default tile shape) -> 7.9 us.
+//
+// Whole rows along x make a wavefront's 64 nodes pull runs of 3-4 lines per
+// population; groups of 32 rows marched through z keep the lines that links to
+// z + 1 and z - 1 share in the L2 until both have read them (raster order over
+// whole planes: 2.86 GB fetched, 676 us; blocks of 8^3: 776 us).  Workgroups of
+// 128: a small subdomain then spreads over twice the CUs of 256 (40^3 9.5 ->
+// 7.9 us, 96^3 14.5 -> 12.9), large ones do not care.  Not faster: one kernel
+// that keeps the densities of a block and its halo in LDS (929-1300 us on the
+// sample: the halo's pulls cost twice the arithmetic), and the second pass
+// trailing the first by a part that fits the 256 MB memory-side cache (690-950
+// us: the second read costs the same L2 misses).
+__device__ __forceinline__ bool list_item(const Throat *__restrict__ throats,
+                                          const TileRef *__restrict__ items, int nitems,
+                                          const Throat *&T, uint32_t &i) {
+  const TileRef it = items[xcd_item(nitems)];
+  T = throats + it.throat;
+  i = (uint32_t)it.tile * kListNodes + threadIdx.x;
+  return T->active && i < T->n_live;
+}
+
+// bath of the node at map position pos: 0 inlet, 1 outlet, -1 none
+__device__ __forceinline__ int bath_of(const Throat &T, uint32_t pos, size_t pp) {
+  if (!T.res) return -1;
+  if ((size_t)pos < (size_t)(1 + kPad) * pp) return 0;
+  return (size_t)pos >= (size_t)(T.nz - 1 + kPad) * pp ? 1 : -1;
+}
+
+template <bool WIDE>
+__device__ __forceinline__ void near_of(const Throat &T, uint32_t pos, uint32_t px, size_t pp,
+                                        Near &n) {
+  typedef typename std::conditional<WIDE, size_t, uint32_t>::type Off;
+  load_near<Off>(T.map - pp - px - 1, (Off)pos, px, pp, n);
+}
+
+template <bool WIDE>
+__global__ __launch_bounds__(kListNodes) void k_dens(const Throat *__restrict__ throats,
+                                                     const TileRef *__restrict__ items,
+                                                     int nitems, int parity) {
+  const Throat *Tp;
+  uint32_t i;
+  if (!list_item(throats, items, nitems, Tp, i)) return;
+  const Throat &T = *Tp;
+  const uint32_t px = (uint32_t)(T.nx + 2 * kPad);
+  const size_t pp = (size_t)px * (size_t)(T.ny + 2 * kPad);
+  const uint32_t pos = *(gcu32 *)((gcchar *)T.pos + (size_t)i * 4);
+  const int bath = bath_of(T, pos, pp);
+  if (bath >= 0) {
+    const bool in = bath == 0;
+    T.rho[T.map[pos]] = make_float2(in ? T.P.rres[0][0] : T.P.rres[1][0],
+                                    in ? T.P.rres[0][1] : T.P.rres[1][1]);
+    return;
+  }
+  Near n;
+  uint32_t m;
+  float v[2][19];
+  near_of<WIDE>(T, pos, px, pp, n);
+  pull<WIDE>(T.g[parity], n, m, v);
+  T.rho[n.r[0][1]] = make_float2((float)((acc_t)T.P.rho_ref + sum19(v[0])),
+                                 (float)((acc_t)T.P.rho_ref + sum19(v[1])));
+}
+
+// densities of the neighbours x + e_k, zero where there is none
+template <bool WIDE, int K>
+__device__ __forceinline__ void stencil_rec(const float2 *rho, const Near &n, float2 (&r)[19]) {
+  typedef typename std::conditional<WIDE, size_t, uint32_t>::type Off;
+  const uint32_t s = near_at<ex(K), ey(K), ez(K)>(n);
+  const bool none = s == kNoNode;
+  gcchar *p = (gcchar *)rho + (size_t)((Off)(none ? n.r[0][1] : s) * (Off)8);
+  r[K] = make_float2(*(gcfloat *)p, *(gcfloat *)(p + 4));
+  if (none) r[K] = make_float2(0.f, 0.f);
+  if constexpr (K + 1 < 19) stencil_rec<WIDE, K + 1>(rho, n, r);
+}
+
+template <bool WIDE>
+__global__ __launch_bounds__(kListNodes) void k_node(const Throat *__restrict__ throats,
+                                                     const TileRef *__restrict__ items,
+                                                     int nitems, int parity) {
+  const Throat *Tp;
+  uint32_t i;
+  if (!list_item(throats, items, nitems, Tp, i)) return;
+  const Throat &T = *Tp;
+  const uint32_t px = (uint32_t)(T.nx + 2 * kPad);
+  const size_t pp = (size_t)px * (size_t)(T.ny + 2 * kPad);
+  const uint32_t pos = *(gcu32 *)((gcchar *)T.pos + (size_t)i * 4);
+  const Phys P = T.P;
+  const int bath = bath_of(T, pos, pp);
+  if (bath >= 0) {
+    const float gw = bath == 0 ? P.gres[0][0] : P.gres[1][0];
+    const float gn = bath == 0 ? P.gres[0][1] : P.gres[1][1];
+    float v[2][19];
+#pragma unroll
+    for (int k = 0; k < 19; ++k) {
+      v[0][k] = wf(k) * gw;
+      v[1][k] = wf(k) * gn;
+    }
+    store_node<WIDE>(T.g[parity ^ 1], T.map[pos], v);
+    return;
+  }
+  Near n;
+  uint32_t m;
+  float v[2][19];
+  float2 r[19];
+  near_of<WIDE>(T, pos, px, pp, n);
+  pull<WIDE>(T.g[parity], n, m, v);
+  stencil_rec<WIDE, 1>(T.rho, n, r);
+  float Sw[3] = {0, 0, 0}, Sn[3] = {0, 0, 0};
+#pragma unroll
+  for (int k = 1; k < 19; ++k) {
+    const float a = wf(k) * r[k].x, bb = wf(k) * r[k].y;
+    if (ex(k)) { Sw[0] += ex(k) > 0 ? a : -a; Sn[0] += ex(k) > 0 ? bb : -bb; }
+    if (ey(k)) { Sw[1] += ey(k) > 0 ? a : -a; Sn[1] += ey(k) > 0 ? bb : -bb; }
+    if (ez(k)) { Sw[2] += ez(k) > 0 ? a : -a; Sn[2] += ez(k) > 0 ? bb : -bb; }
+  }
+  const double ds[2] = {sum19(v[0]), sum19(v[1])};
+  collide(P, m, Sw, Sn, ds, v);
+  store_node<WIDE>(T.g[parity ^ 1], n.r[0][1], v);
+}
+
+// ---- tiled step over the brick numbering ------------------------------------------
+// Map (X, Y, Z), which may lie one node beyond the box, to a node index:
+// wrapped on periodic axes, -1 beyond a wall.  Coordinates further out (the
+// unused halo slots of a ragged tile) also give -1.
+__device__ __forceinline__ long long node_of(const Dom &d, int X, int Y, int Z) {
+  if (X < -1 || X > d.nx || Y < -1 || Y > d.ny || Z < -1 || Z > d.nz) return -1;
+  if (X < 0 || X >= d.nx) {
+    if (!(d.per & 1)) return -1;
+    X = X < 0 ? X + d.nx : X - d.nx;
+  }
+  if (Y < 0 || Y >= d.ny) {
+    if (!(d.per & 2)) return -1;
+    Y = Y < 0 ? Y + d.ny : Y - d.ny;
+  }
+  if (Z < 0 || Z >= d.nz) {
+    if (!(d.per & 4)) return -1;
+    Z = Z < 0 ? Z + d.nz : Z - d.nz;
+  }
+  return (long long)X + (long long)d.nx * ((long long)Y + (long long)d.ny * Z);
+}
+
+__device__ __forceinline__ int wrap(int c, int n) { return c < 0 ? c + n : (c >= n ? c - n : c); }
+
+// Pull from bricks.  Addresses are the start of plane Z - 1 (uniform across a
+// tile) plus a 32-bit byte offset per lane: the offset of a node is the sum of
+// an x part and a y part (brick_x, brick_y); with P the elements of a plane,
+// population q of the node itself is at P + y(Y) + x(X) + 32 q, of the source
+// node at (1 - ez) P + y(Ys) + x(Xs) + 32 q.  The second component's
+// populations follow 19 * 32 later.  Xs and Ys are taken modulo nx and ny:
+// across a periodic face that is the wrapped neighbour, across a wall the link
+// is cut and the offset unused.
+template <int K>
+__device__ __forceinline__ void brick_dir(gcchar *b0, gcchar *b1, uint32_t m, uint32_t own,
+                                         uint32_t s, float (&v)[2][19]) {
+  constexpr int o = opp(K);
+  const bool cut = (m >> K) & 1u;
+  const uint32_t off = cut ? own + (uint32_t)(o * kBN) : s + (uint32_t)(K * kBN);
+  v[0][K] = *(const __attribute__((address_space(1))) float *)(b0 + (size_t)(off * 4u));
+  v[1][K] = *(const __attribute__((address_space(1))) float *)(b1 + (size_t)(off * 4u));
+}
+
+// source offset of direction K: planes, then the y and x parts of x - e_k
+// (index 0: coordinate - 1, 1: itself, 2: + 1)
+template <int K>
+__device__ __forceinline__ uint32_t src_index(uint32_t P, const uint32_t (&py)[3],
+                                              const uint32_t (&px)[3]) {
+  return (uint32_t)(1 - ez(K)) * P + py[1 - ey(K)] + px[1 - ex(K)];
+}
+
+template <int K>
+__device__ __forceinline__ void brick_rec(gcchar *b0, gcchar *b1, uint32_t m, uint32_t own,
+                                         uint32_t P, const uint32_t (&py)[3],
+                                         const uint32_t (&px)[3], float (&v)[2][19]) {
+  brick_dir<K>(b0, b1, m, own, src_index<K>(P, py, px), v);
+  if constexpr (K + 1 < 19) brick_rec<K + 1>(b0, b1, m, own, P, py, px, v);
+}
+
+__device__ __forceinline__ void brick_pull(const Dom &d, uint32_t m, int X, int Y, int Z,
+                                     float (&v)[2][19]) {
+  const uint32_t P = (uint32_t)brick_plane(d.nx, d.ny);
+  gcchar *b0 = (gcchar *)(d.src + (size_t)P * (size_t)Z);
+  gcchar *b1 = b0 + (size_t)(19 * kBN * 4);
+  uint32_t px[3], py[3];
+  px[0] = brick_x(X == 0 ? d.nx - 1 : X - 1);
+  px[1] = brick_x(X);
+  px[2] = brick_x(X == d.nx - 1 ? 0 : X + 1);
+  py[0] = brick_y(Y == 0 ? d.ny - 1 : Y - 1, d.nx);
+  py[1] = brick_y(Y, d.nx);
+  py[2] = brick_y(Y == d.ny - 1 ? 0 : Y + 1, d.nx);
+  // The offsets do not depend on Z (the base does), so a z-marching loop
+  // would otherwise keep all 38 of them live in registers across planes;
+  // these opaque moves make them cheap per-plane arithmetic instead.
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    asm volatile("" : "+v"(px[i]));
+    asm volatile("" : "+v"(py[i]));
+  }
+  const uint32_t own = P + py[1] + px[1];
+  brick_rec<0>(b0, b1, m, own, P, py, px, v);
+}
+
+// Density seen by the interaction sums at (X, Y, Z): zero on solid nodes and
+// beyond walls, the imposed value on bath nodes, Eq. 2 on fluid nodes.  With
+// KEEP, the pulled populations, the mask word and the two FP64 sums of the
+// shifted populations (zero unless the node is fluid) are returned for the
+// collision of this node.
+template <bool KEEP>
+__device__ __forceinline__ float2 density_at(const Dom &d, const Phys &P, int X, int Y, int Z,
+                                             float (&v)[2][19], uint32_t &mword,
+                                             double (&ds)[2]) {
+  if (KEEP) ds[0] = ds[1] = 0.0;
+  const long long n = node_of(d, X, Y, Z);
+  if (n < 0) {
+    if (KEEP) mword = kSolid << kTypeShift;
+    return make_float2(0.f, 0.f);
+  }
+  const uint32_t m = d.mask[n];
+  if (KEEP) mword = m;
+  const uint32_t t = m >> kTypeShift;
+  if (t == kSolid) return make_float2(0.f, 0.f);
+  if (t == kResIn) return make_float2(P.rres[0][0], P.rres[0][1]);
+  if (t == kResOut) return make_float2(P.rres[1][0], P.rres[1][1]);
+  int X2 = wrap(X, d.nx), Y2 = wrap(Y, d.ny), Z2 = wrap(Z, d.nz);
+  if (KEEP) {
+    brick_pull(d, m, X2, Y2, Z2, v);
+    ds[0] = sum19(v[0]);
+    ds[1] = sum19(v[1]);
+    return make_float2((float)((acc_t)P.rho_ref + ds[0]), (float)((acc_t)P.rho_ref + ds[1]));
+  } else {
+    float t2[2][19];
+    brick_pull(d, m, X2, Y2, Z2, t2);
+    return make_float2((float)((acc_t)P.rho_ref + sum19(t2[0])), (float)((acc_t)P.rho_ref + sum19(t2[1])));
+  }
+}
+
 // Store the post-collision populations of the node at (X, Y, Z) (the ghost
 // planes of z-periodic subdomains are refreshed by k_ghost after the step).
-__device__ __forceinline__ void store_node(const Dom &d, int X, int Y, int Z,
+__device__ __forceinline__ void brick_store(const Dom &d, int X, int Y, int Z,
                                            const float (&v)[2][19]) {
-  const size_t P = pop_plane(d.nx, d.ny);
+  const size_t P = brick_plane(d.nx, d.ny);
   uint32_t own = brick_y(Y, d.nx) + brick_x(X);
   asm volatile("" : "+v"(own));  // per-plane offsets, as in pull()
   gchar *b = (gchar *)(d.dst + P * (size_t)(Z + 1));
@@ -284,7 +540,6 @@ __device__ __forceinline__ void store_node(const Dom &d, int X, int Y, int Z,
                        b + (size_t)((own + (uint32_t)((19 * c + k) * kBN)) * 4u)));
 }
 
-// ---- fused step ------------------------------------------------------------
 // A workgroup owns a TX x TY column of nodes and marches it through a
 // z-segment, software-pipelined over three planes.  Entering iteration Z, the
 // thread holds its own node of plane Z in registers, its node of plane Z+1 in
@@ -332,11 +587,7 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(3))) voi
   const int tb = tid / kBN;
   const int tx = (tb % (TX / kBX)) * kBX + tid % kBX;
   const int ty = (tb / (TX / kBX)) * kBY + (tid / kBX) % kBY;
-  // list entries are handed out so that each XCD (blocks b = xcd mod 8) gets
-  // one contiguous range of the tile list, keeping spatial neighbours in one L2
-  const int b = blockIdx.x;
-  const int q = ntiles >> 3, r = ntiles & 7, xcd = b & 7, idx = b >> 3;
-  const TileRef tr = tiles[xcd * q + min(xcd, r) + idx];
+  const TileRef tr = tiles[xcd_item(ntiles)];
   const Throat &T = throats[tr.throat];
   if (!T.active) return;
   Dom d;
@@ -402,14 +653,14 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(3))) voi
           if (ez(k)) { Sw[2] += ez(k) > 0 ? a : -a; Sn[2] += ez(k) > 0 ? bb : -bb; }
         }
         collide(P, mcur, Sw, Sn, dcur, cur);
-        store_node(d, x, y, Z, cur);
+        brick_store(d, x, y, Z, cur);
       } else if (t == kResIn || t == kResOut) {
         const int i = t == kResIn ? 0 : 1;
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
           for (int k = 0; k < 19; ++k) cur[c][k] = wf(k) * P.gres[i][c];
-        store_node(d, x, y, Z, cur);
+        brick_store(d, x, y, Z, cur);
       }
     }
     // 4. publish plane Z+2, rotate Z+1 -> registers, Z+2 -> LDS
@@ -432,239 +683,8 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(3))) voi
   }
 }
 
-// ---- node-list path ---------------------------------------------------------
-// For subdomains where most nodes are solid (thin throat prisms, small
-// throats) the tiles above spend their lanes on solid nodes.  Here every
-// non-solid node of the list (each entry: node index and mask word) gets a
-// pair of adjacent lanes, lane c handling component c: a first pass writes
-// each node's densities (the same FP64 sums rounded to FP32 that the tiles
-// keep in LDS), the second pulls, takes the 18-neighbour stencil of the
-// other component's density from that array (zero where the node's link
-// bits mark a solid neighbour or a wall), collides and stores.  The pair
-// swaps its density and momentum by lane shuffle, so each lane evaluates the
-// collision's shared terms from the same operands in the same order as the
-// one-lane collide(): results are bit-identical to the tiled step.  A pair
-// per node doubles the wavefronts of a small subdomain (a 96^3 throat has
-// about one wavefront of nodes per SIMD) and halves each lane's chain of
-// loads and arithmetic.  Per fluid node the second pass moves the same 304
-// bytes as the fused step plus the stencil reads, the first pass another
-// 152 + 8, and each pass reads the 8-byte list entry.
-__device__ __forceinline__ const TileRef &list_ref(const TileRef *__restrict__ tiles, int ntiles) {
-  const int b = blockIdx.x;
-  const int q = ntiles >> 3, r = ntiles & 7, xcd = b & 7, idx = b >> 3;
-  return tiles[xcd * q + min(xcd, r) + idx];
-}
-
-__device__ __forceinline__ Dom list_dom(const Throat &T, int parity) {
-  Dom d;
-  d.src = T.g[parity];
-  d.dst = T.g[parity ^ 1];
-  d.mask = T.mask;
-  d.N = T.N;
-  d.nx = T.nx;
-  d.ny = T.ny;
-  d.nz = T.nz;
-  d.per = T.per;
-  return d;
-}
-
-// one component's half of pull(): the 19 populations of component c
-template <int K>
-__device__ __forceinline__ void pull1_rec(gcchar *b, uint32_t m, uint32_t own, uint32_t P,
-                                          const uint32_t (&py)[3], const uint32_t (&px)[3],
-                                          float (&v)[19]) {
-  constexpr int o = opp(K);
-  const bool cut = (m >> K) & 1u;
-  const uint32_t off =
-      cut ? own + (uint32_t)(o * kBN) : src_index<K>(P, py, px) + (uint32_t)(K * kBN);
-  v[K] = *(const __attribute__((address_space(1))) float *)(b + (size_t)(off * 4u));
-  if constexpr (K + 1 < 19) pull1_rec<K + 1>(b, m, own, P, py, px, v);
-}
-
-__device__ __forceinline__ void pull1(const Dom &d, uint32_t m, int X, int Y, int Z, int c,
-                                      float (&v)[19]) {
-  const uint32_t P = (uint32_t)pop_plane(d.nx, d.ny);
-  gcchar *b = (gcchar *)(d.src + (size_t)P * (size_t)Z) + (size_t)(c * 19 * kBN * 4);
-  uint32_t px[3], py[3];
-  px[0] = brick_x(X == 0 ? d.nx - 1 : X - 1);
-  px[1] = brick_x(X);
-  px[2] = brick_x(X == d.nx - 1 ? 0 : X + 1);
-  py[0] = brick_y(Y == 0 ? d.ny - 1 : Y - 1, d.nx);
-  py[1] = brick_y(Y, d.nx);
-  py[2] = brick_y(Y == d.ny - 1 ? 0 : Y + 1, d.nx);
-  const uint32_t own = P + py[1] + px[1];
-  pull1_rec<0>(b, m, own, P, py, px, v);
-}
-
-__device__ __forceinline__ void store1(const Dom &d, int X, int Y, int Z, int c,
-                                       const float (&v)[19]) {
-  const size_t P = pop_plane(d.nx, d.ny);
-  const uint32_t own = brick_y(Y, d.nx) + brick_x(X) + (uint32_t)(19 * c * kBN);
-  gchar *b = (gchar *)(d.dst + P * (size_t)(Z + 1));
-#pragma unroll
-  for (int k = 0; k < 19; ++k)
-    __builtin_nontemporal_store(
-        v[k], (__attribute__((address_space(1))) float *)(
-                  b + (size_t)((own + (uint32_t)(k * kBN)) * 4u)));
-}
-
-__device__ __forceinline__ void list_coords(const Dom &d, uint32_t n, int &X, int &Y, int &Z) {
-  const uint32_t nx = (uint32_t)d.nx, nxy = nx * (uint32_t)d.ny;
-  Z = (int)(n / nxy);
-  Y = (int)((n - (uint32_t)Z * nxy) / nx);
-  X = (int)(n - (uint32_t)Z * nxy - (uint32_t)Y * nx);
-}
-
-__global__ void k_list_entries(const uint32_t *ids, const uint32_t *mask, uint32_t n, uint2 *out) {
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    out[i] = make_uint2(ids[i], mask[ids[i]]);
-}
-
-hipError_t launch_list_entries(const uint32_t *ids, const uint32_t *mask, uint32_t n, uint2 *out,
-                               hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  const unsigned blocks = (unsigned)std::min<uint32_t>((n + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_list_entries, dim3(blocks), dim3(256), 0, st, ids, mask, n, out);
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(kListBlock) void k_dens_list(const Throat *__restrict__ throats,
-                                                          const TileRef *__restrict__ tiles,
-                                                          int ntiles, int parity) {
-  const TileRef tr = list_ref(tiles, ntiles);
-  const Throat &T = throats[tr.throat];
-  if (!T.active) return;
-  const uint32_t i = (uint32_t)tr.tile * kListNodes + threadIdx.x / 2;
-  const int c = threadIdx.x & 1;
-  if (i >= T.nlist) return;
-  const Dom d = list_dom(T, parity);
-  const Phys &P = T.P;
-  const uint2 e = T.list[i];
-  const uint32_t n = e.x, m = e.y;
-  const uint32_t t = m >> kTypeShift;
-  float r;
-  if (t == kFluid) {
-    int X, Y, Z;
-    list_coords(d, n, X, Y, Z);
-    float v[19];
-    pull1(d, m, X, Y, Z, c, v);
-    r = (float)((acc_t)P.rho_ref + sum19(v));
-  } else {
-    r = P.rres[t == kResIn ? 0 : 1][c];
-  }
-  reinterpret_cast<float *>(T.rho)[2 * (size_t)n + c] = r;
-}
-
-__global__ __launch_bounds__(kListBlock) void k_step_list(const Throat *__restrict__ throats,
-                                                          const TileRef *__restrict__ tiles,
-                                                          int ntiles, int parity) {
-  const TileRef tr = list_ref(tiles, ntiles);
-  const Throat &T = throats[tr.throat];
-  if (!T.active) return;
-  const uint32_t i = (uint32_t)tr.tile * kListNodes + threadIdx.x / 2;
-  const int c = threadIdx.x & 1;
-  if (i >= T.nlist) return;  // both lanes of a pair leave together
-  const Dom d = list_dom(T, parity);
-  const Phys &P = T.P;
-  const uint2 e = T.list[i];
-  const uint32_t n = e.x, m = e.y;
-  const uint32_t t = m >> kTypeShift;
-  int X, Y, Z;
-  list_coords(d, n, X, Y, Z);
-  float v[19];
-  if (t == kFluid) {
-    pull1(d, m, X, Y, Z, c, v);
-    // stencil of the other component's density (the cohesion of Eq. 4)
-    // Neighbour x + e_k is the pull source of direction opp(k): its link bit
-    // says whether it is solid or beyond a wall (density zero); otherwise it
-    // is in the box or across a periodic face.
-    const float *rho_o = reinterpret_cast<const float *>(T.rho) + (1 - c);
-    const int xm = X == 0 ? d.nx - 1 : X - 1, xp = X == d.nx - 1 ? 0 : X + 1;
-    const int ym = Y == 0 ? d.ny - 1 : Y - 1, yp = Y == d.ny - 1 ? 0 : Y + 1;
-    const int zm = Z == 0 ? d.nz - 1 : Z - 1, zp = Z == d.nz - 1 ? 0 : Z + 1;
-    float So[3] = {0, 0, 0};
-#pragma unroll
-    for (int k = 1; k < 19; ++k) {
-      const int xn = ex(k) > 0 ? xp : (ex(k) < 0 ? xm : X);
-      const int yn = ey(k) > 0 ? yp : (ey(k) < 0 ? ym : Y);
-      const int zn = ez(k) > 0 ? zp : (ez(k) < 0 ? zm : Z);
-      const uint32_t nb = ((uint32_t)zn * (uint32_t)d.ny + (uint32_t)yn) * (uint32_t)d.nx +
-                          (uint32_t)xn;
-      const float a = wf(k) * (((m >> opp(k)) & 1u) ? 0.f : rho_o[2 * (size_t)nb]);
-      if (ex(k)) So[0] += ex(k) > 0 ? a : -a;
-      if (ey(k)) So[1] += ey(k) > 0 ? a : -a;
-      if (ez(k)) So[2] += ez(k) > 0 ? a : -a;
-    }
-    // collide(), one component per lane
-    const double drd = sum19(v);
-    const float dr = (float)drd;
-    const float rho = (float)((double)P.rho_ref + drd);
-    float j[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 1; k < 19; ++k) {
-      if (k > opp(k)) continue;
-      const float dk = v[k] - v[opp(k)];
-      if (ex(k)) j[0] += ex(k) > 0 ? dk : -dk;
-      if (ey(k)) j[1] += ey(k) > 0 ? dk : -dk;
-      if (ez(k)) j[2] += ez(k) > 0 ? dk : -dk;
-    }
-    const float rho_p = __shfl_xor(rho, 1);
-    float jp[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) jp[a] = __shfl_xor(j[a], 1);
-    const float rho0 = c == 0 ? rho : rho_p, rho1 = c == 0 ? rho_p : rho;
-    float A[3] = {0.f, 0.f, 0.f};
-    if ((m & kLinkBits) != 0u)
-#pragma unroll
-    for (int k = 1; k < 19; ++k) {
-      const float s = (float)((m >> opp(k)) & 1u) * wf(k);
-      if (ex(k)) A[0] += ex(k) > 0 ? s : -s;
-      if (ey(k)) A[1] += ey(k) > 0 ? s : -s;
-      if (ez(k)) A[2] += ez(k) > 0 ? s : -s;
-    }
-    const float gads = P.Gads[c];
-    float F[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) F[a] = -P.G * rho * So[a] - gads * rho * A[a];
-    const float it0 = P.itau[0], it1 = P.itau[1];
-    const float den = rho0 * it0 + rho1 * it1;
-    const float iden = 1.0f / den;
-    float up[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const float j0 = c == 0 ? j[a] : jp[a], j1 = c == 0 ? jp[a] : j[a];
-      up[a] = (j0 * it0 + j1 * it1) * iden;
-    }
-    const float tc = P.tau[c], itc = P.itau[c];
-    const float irho = 1.0f / rho;
-    float u[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) u[a] = up[a] + tc * F[a] * irho;
-    const float uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    double rest = drd;
-#pragma unroll
-    for (int k = 1; k < 19; ++k) {
-      float eu = 0.f;
-      if (ex(k)) eu += ex(k) > 0 ? u[0] : -u[0];
-      if (ey(k)) eu += ey(k) > 0 ? u[1] : -u[1];
-      if (ez(k)) eu += ez(k) > 0 ? u[2] : -u[2];
-      const float geq = wf(k) * (dr + rho * (3.f * eu + 4.5f * eu * eu - 1.5f * uu));
-      const float g = v[k];
-      const float gs = g - (g - geq) * itc;
-      v[k] = gs;
-      rest -= (double)gs;
-    }
-    v[0] = (float)rest;
-  } else {
-    const int b = t == kResIn ? 0 : 1;
-#pragma unroll
-    for (int k = 0; k < 19; ++k) v[k] = wf(k) * P.gres[b][c];
-  }
-  store1(d, X, Y, Z, c, v);
-}
-
 bool schedule_valid(const Sched &s) {
-  if (s.tx == kListTx) return true;  // node-list path
+  if (s.tx == kListTx) return true;  // two passes
   // (64, 8) and (32, 16) would need 2 x 78 KB of LDS staging: not offered
   if (s.lz < 1) return false;
   for (int i = 0; i < kNumShapes; ++i)
@@ -681,29 +701,40 @@ static hipError_t step_as(const Throat *th, const TileRef *tiles, int ntiles, in
   return hipGetLastError();
 }
 
-// Ghost planes of z-periodic subdomains after a step: plane 0 of the new
-// state is copied to plane nz, plane nz - 1 to plane -1 (two contiguous runs
-// of one padded plane each).  Grid: x over the run, y over the listed subdomains.
+// Ghost planes of z-periodic subdomains in bricks: plane 0 of buffer g[which]
+// is copied to plane nz, plane nz - 1 to plane -1 (two contiguous runs of one
+// padded plane each).  Grid: x over the run, y over the listed subdomains.
 __global__ __launch_bounds__(256) void k_ghost(const Throat *__restrict__ throats,
-                                               const int *__restrict__ ids, int parity) {
+                                               const int *__restrict__ ids, int which) {
   const Throat &T = throats[ids[blockIdx.y]];
   if (!T.active) return;
-  float *g = T.g[parity ^ 1];
-  const size_t P = pop_plane(T.nx, T.ny);
+  float *g = T.g[which];
+  const size_t P = brick_plane(T.nx, T.ny);
   for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < P; i += (size_t)gridDim.x * 256) {
     g[P * (size_t)(T.nz + 1) + i] = g[P + i];
     g[i] = g[P * (size_t)T.nz + i];
   }
 }
 
+hipError_t launch_ghost(const Throat *th, const int *zper_ids, int n_zper, int which,
+                        hipStream_t st) {
+  if (n_zper <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_ghost, dim3(1024, (unsigned)n_zper), dim3(256), 0, st, th, zper_ids, which);
+  return hipGetLastError();
+}
+
 static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, int tx, int ty,
-                            int parity, hipStream_t st) {
+                            bool wide, int parity, hipStream_t st) {
   if (tx == kListTx) {
     if (ntiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_dens_list, dim3((unsigned)ntiles), dim3(kListBlock), 0, st, th, tiles,
-                       ntiles, parity);
-    hipLaunchKernelGGL(k_step_list, dim3((unsigned)ntiles), dim3(kListBlock), 0, st, th, tiles,
-                       ntiles, parity);
+    const dim3 grid((unsigned)ntiles), block(kListNodes);
+    if (wide) {
+      hipLaunchKernelGGL(k_dens<true>, grid, block, 0, st, th, tiles, ntiles, parity);
+      hipLaunchKernelGGL(k_node<true>, grid, block, 0, st, th, tiles, ntiles, parity);
+    } else {
+      hipLaunchKernelGGL(k_dens<false>, grid, block, 0, st, th, tiles, ntiles, parity);
+      hipLaunchKernelGGL(k_node<false>, grid, block, 0, st, th, tiles, ntiles, parity);
+    }
     return hipGetLastError();
   }
   if (tx == 32) {
@@ -719,39 +750,28 @@ static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, 
 }
 
 hipError_t launch_step(const Throat *th, const TileRef *tiles, int ntiles, int tx, int ty,
-                       int parity, hipStream_t st, const int *zper_ids, int n_zper) {
+                       bool wide, int parity, hipStream_t st, const int *zper_ids, int n_zper) {
   if (!schedule_valid(Sched{tx, ty, 1})) return hipErrorInvalidValue;
-  const hipError_t e = step_body(th, tiles, ntiles, tx, ty, parity, st);
-  if (e != hipSuccess || n_zper <= 0 || ntiles <= 0) return e;
-  hipLaunchKernelGGL(k_ghost, dim3(1024, (unsigned)n_zper), dim3(256), 0, st, th, zper_ids, parity);
-  return hipGetLastError();
+  const hipError_t e = step_body(th, tiles, ntiles, tx, ty, wide, parity, st);
+  // (the two passes pull across a periodic face by number)
+  if (e != hipSuccess || ntiles <= 0 || n_zper <= 0) return e;
+  return launch_ghost(th, zper_ids, n_zper, parity ^ 1, st);
 }
 
-void brick_map(const uint8_t *types, int nx, int ny, int nz, std::vector<uint8_t> &live,
-               size_t &nonsolid) {
-  // 8 x 4 patches of the tile grid (tiles start at multiples of their
-  // sides, which are multiples of 8 and 4), whatever the storage bricks' offset
+void brick_map(const uint8_t *types, int nx, int ny, int nz, std::vector<uint8_t> &live) {
   const int nbx = (nx + kBX - 1) / kBX, nby = (ny + kBY - 1) / kBY;
   live.assign((size_t)nbx * nby * nz, 0);
-  nonsolid = 0;
   for (int z = 0; z < nz; ++z)
     for (int y = 0; y < ny; ++y) {
       const uint8_t *row = types + (size_t)nx * ((size_t)y + (size_t)ny * z);
       uint8_t *b = live.data() + (size_t)nbx * ((size_t)(y / kBY) + (size_t)nby * z);
       for (int x = 0; x < nx; ++x)
-        if (row[x] != kSolid) {
-          b[x / kBX] = 1;
-          ++nonsolid;
-        }
+        if (row[x] != kSolid) b[x / kBX] = 1;
     }
 }
 
-void list_tiles(const uint8_t *live, size_t nonsolid, int nx, int ny, int nz, int tx, int ty,
-                int lz, int throat, std::vector<TileRef> &out) {
-  if (tx == kListTx) {  // node-list path: chunks of kListNodes non-solid nodes
-    for (size_t c = 0; c * kListNodes < nonsolid; ++c) out.push_back(TileRef{throat, (int)c});
-    return;
-  }
+void list_tiles(const uint8_t *live, int nx, int ny, int nz, int tx, int ty, int lz, int throat,
+                std::vector<TileRef> &out) {
   const int nbx = (nx + kBX - 1) / kBX, nby = (ny + kBY - 1) / kBY;
   const int bpx = tx / kBX, bpy = ty / kBY;  // patches per tile side
   const int ntx = (nx + tx - 1) / tx, nty = (ny + ty - 1) / ty, ntz = (nz + lz - 1) / lz;
@@ -772,6 +792,126 @@ void list_tiles(const uint8_t *live, size_t nonsolid, int nx, int ny, int nz, in
           any = cell[(size_t)txi + (size_t)ntx * ((size_t)tyi + (size_t)nty * z)] != 0;
         if (any) out.push_back(TileRef{throat, txi + ntx * (tyi + nty * tz)});
       }
+}
+
+void list_items(size_t n_live, int throat, std::vector<TileRef> &out) {
+  for (size_t c = 0; c * kListNodes < n_live; ++c) out.push_back(TileRef{throat, (int)c});
+}
+
+// ---- numbering ---------------------------------------------------------------------
+// one wavefront per row
+__global__ __launch_bounds__(256) void k_row_counts(const uint8_t *types, int nx, uint32_t rows,
+                                                    uint32_t *counts) {
+  const uint32_t row = blockIdx.x * 4u + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const uint8_t *t = types + (size_t)row * nx;
+  uint32_t n = 0;
+  for (int x0 = 0; x0 < nx; x0 += 64) {
+    const int x = x0 + (int)(threadIdx.x & 63);
+    n += (uint32_t)__popcll(__ballot(x < nx && t[x] != kSolid));
+  }
+  if ((threadIdx.x & 63) == 0) counts[row] = n;
+}
+
+hipError_t launch_row_counts(const uint8_t *types, int nx, int ny, int nz, uint32_t *counts,
+                             hipStream_t st) {
+  const uint32_t rows = (uint32_t)ny * (uint32_t)nz;
+  hipLaunchKernelGGL(k_row_counts, dim3((rows + 3) / 4), dim3(256), 0, st, types, nx, rows, counts);
+  return hipGetLastError();
+}
+
+size_t number_rows(std::vector<uint32_t> &rows, int ny, int nz) {
+  size_t n = 0;
+  for (int Y = 0; Y < ny; Y += kGroupY)
+    for (int z = 0; z < nz; ++z)
+      for (int y = Y; y < std::min(Y + kGroupY, ny); ++y) {
+        uint32_t &r = rows[(size_t)z * ny + y];
+        const uint32_t c = r;
+        r = (uint32_t)n;
+        n += c;
+      }
+  return n;
+}
+
+// one wavefront per row: the row's nodes take consecutive list places from
+// its first one
+__global__ __launch_bounds__(256) void k_number(const uint8_t *types, int nx, int ny, int nz,
+                                                uint32_t nrows, const uint32_t *rows, int bricks,
+                                                uint32_t *map, uint32_t *pos) {
+  const uint32_t row = blockIdx.x * 4u + (threadIdx.x >> 6);
+  if (row >= nrows) return;
+  const uint8_t *t = types + (size_t)row * nx;
+  const int y = (int)(row % (uint32_t)ny), z = (int)(row / (uint32_t)ny);
+  const int lane = (int)(threadIdx.x & 63);
+  uint32_t base = rows[row];
+  for (int x0 = 0; x0 < nx; x0 += 64) {
+    const int x = x0 + lane;
+    const bool live = x < nx && t[x] != kSolid;
+    const unsigned long long bal = __ballot(live);
+    if (live) {
+      const uint32_t i = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+      const size_t p = map_pos(nx, ny, x, y, z);
+      map[p] = bricks ? brick_number(nx, ny, x, y, z) : i;
+      pos[i] = (uint32_t)p;
+    }
+    base += (uint32_t)__popcll(bal);
+  }
+}
+
+// solid nodes, and the two layers beyond the box
+__global__ void k_number_rest(const uint8_t *types, int nx, int ny, int nz, int per,
+                              uint32_t *map) {
+  const size_t M = map_elems(nx, ny, nz);
+  const int n[3] = {nx, ny, nz};
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < M;
+       i += (size_t)gridDim.x * blockDim.x) {
+    int c[3] = {(int)(i % (size_t)(nx + 2 * kPad)) - kPad,
+                (int)((i / (size_t)(nx + 2 * kPad)) % (size_t)(ny + 2 * kPad)) - kPad,
+                (int)(i / ((size_t)(nx + 2 * kPad) * (size_t)(ny + 2 * kPad))) - kPad};
+    bool inside = true, none = false;
+    for (int a = 0; a < 3; ++a)
+      if (c[a] < 0 || c[a] >= n[a]) {
+        inside = false;
+        if (!((per >> a) & 1)) none = true;
+        c[a] += c[a] < 0 ? n[a] : -n[a];
+      }
+    if (!none)
+      none = types[(size_t)c[0] + (size_t)nx * ((size_t)c[1] + (size_t)ny * c[2])] == kSolid;
+    if (none)
+      map[i] = kNoNode;
+    else if (!inside)
+      map[i] = map[map_pos(nx, ny, c[0], c[1], c[2])];
+  }
+}
+
+hipError_t launch_number(const uint8_t *types, int nx, int ny, int nz, int per,
+                         const uint32_t *rows, bool bricks, uint32_t *map, uint32_t *pos,
+                         hipStream_t st) {
+  const uint32_t nrows = (uint32_t)ny * (uint32_t)nz;
+  hipLaunchKernelGGL(k_number, dim3((nrows + 3) / 4), dim3(256), 0, st, types, nx, ny, nz, nrows,
+                     rows, bricks ? 1 : 0, map, pos);
+  const size_t M = map_elems(nx, ny, nz);
+  const unsigned grid = (unsigned)std::min<size_t>((M + 255) / 256, 65536);
+  hipLaunchKernelGGL(k_number_rest, dim3(grid), dim3(256), 0, st, types, nx, ny, nz, per, map);
+  return hipGetLastError();
+}
+
+__global__ void k_links(const uint8_t *types, Dom d, uint32_t *mask) {
+  for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < d.N;
+       n += (size_t)gridDim.x * blockDim.x) {
+    const int x = (int)(n % d.nx), y = (int)((n / d.nx) % d.ny), z = (int)(n / ((size_t)d.nx * d.ny));
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 1; k < 19; ++k)
+      if (d.map[map_pos(d.nx, d.ny, x - ex(k), y - ey(k), z - ez(k))] == kNoNode) m |= 1u << k;
+    mask[n] = m | ((uint32_t)types[n] << kTypeShift);
+  }
+}
+
+hipError_t launch_links(const uint8_t *types, const Dom &d, uint32_t *mask, hipStream_t st) {
+  const unsigned blocks = (unsigned)std::min<size_t>((d.N + 255) / 256, 65536);
+  hipLaunchKernelGGL(k_links, dim3(blocks), dim3(256), 0, st, types, d, mask);
+  return hipGetLastError();
 }
 
 // ---- geometry ----------------------------------------------------------------
@@ -840,82 +980,41 @@ hipError_t launch_voxelize(const double *spheres, const VoxBins &bins, int prism
   return hipGetLastError();
 }
 
-__global__ void k_links(const uint8_t *types, int nx, int ny, int nz, int per, uint32_t *mask) {
-  const size_t N = (size_t)nx * ny * nz;
-  Dom d{};
-  d.nx = nx;
-  d.ny = ny;
-  d.nz = nz;
-  d.per = per;
-  for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < N;
-       n += (size_t)gridDim.x * blockDim.x) {
-    const int x = (int)(n % nx), y = (int)((n / nx) % ny), z = (int)(n / ((size_t)nx * ny));
-    uint32_t m = 0;
-#pragma unroll
-    for (int k = 1; k < 19; ++k) {
-      const long long s = node_of(d, x - ex(k), y - ey(k), z - ez(k));
-      if (s < 0 || types[s] == kSolid) m |= 1u << k;
-    }
-    mask[n] = m | ((uint32_t)types[n] << kTypeShift);
-  }
-}
-
-hipError_t launch_links(const uint8_t *types, int nx, int ny, int nz, int per, uint32_t *mask,
-                        hipStream_t st) {
-  const size_t N = (size_t)nx * ny * nz;
-  const unsigned blocks = (unsigned)std::min<size_t>((N + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_links, dim3(blocks), dim3(256), 0, st, types, nx, ny, nz, per, mask);
-  return hipGetLastError();
-}
-
 // ---- initial state ------------------------------------------------------------
 // Post-collision values of a virtual step -1 chosen so that the first pull
 // yields f(x,0) = f_eq(rho(x,0), u = 0) = w_k rho(x,0) on every fluid node:
 // slot k of node y holds w_k rho(y + e_k), or w_k rho(y) when y + e_k is
 // solid or beyond a wall (that slot is then only read back by y's own
 // bounce-back).
-__device__ __forceinline__ double rho0_of(const uint32_t *mask, const double *rho_init,
-                                          double maj, double mnr, int z_front, const double *rres,
-                                          size_t N, size_t n, int z, int c) {
-  const uint32_t t = mask[n] >> kTypeShift;
-  if (t == kResIn) return rres[0 * 2 + c];
-  if (t == kResOut) return rres[1 * 2 + c];
-  if (rho_init) return rho_init[(size_t)c * N + n];
+__device__ __forceinline__ double rho0_of(const Dom &d, const double *rho_init, double maj,
+                                          double mnr, int z_front, const double *rres, int x,
+                                          int y, int z, int c) {
+  if (d.res && z == 0) return rres[0 * 2 + c];
+  if (d.res && z == d.nz - 1) return rres[1 * 2 + c];
+  if (rho_init)
+    return rho_init[(size_t)c * d.N + (size_t)x + (size_t)d.nx * ((size_t)y + (size_t)d.ny * z)];
   const bool nw = z <= z_front;
   return (c == 1) == nw ? maj : mnr;
 }
 
 __global__ void k_init(Dom d, double rho_ref, const double *rho_init, double maj, double mnr,
                        int z_front, const double *rres, float *g) {
-  const size_t P = pop_plane(d.nx, d.ny);
   for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < d.N;
        n += (size_t)gridDim.x * blockDim.x) {
     const int x = (int)(n % d.nx), y = (int)((n / d.nx) % d.ny), z = (int)(n / ((size_t)d.nx * d.ny));
-    // this node's population 0 in its plane and, on a z-periodic subdomain,
-    // in the ghost plane that mirrors it
-    float *slot = g + P * (size_t)(z + 1) + brick_y(y, d.nx) + brick_x(x);
-    float *ghost = nullptr;
-    if ((d.per & 4) && z == 0) ghost = slot + P * (size_t)d.nz;
-    if ((d.per & 4) && z == d.nz - 1) ghost = slot - P * (size_t)d.nz;
-    const uint32_t t = d.mask[n] >> kTypeShift;
-    if (t == kSolid) {
-      for (int q = 0; q < 38; ++q) {
-        slot[(size_t)q * kBN] = 0.f;
-        if (ghost) ghost[(size_t)q * kBN] = 0.f;
-      }
-      continue;
-    }
+    const uint32_t i = d.map[map_pos(d.nx, d.ny, x, y, z)];
+    if (i == kNoNode) continue;
+    float *slot = g + node_elem(i);
 #pragma unroll
     for (int k = 0; k < 19; ++k) {
-      long long tgt = node_of(d, x + ex(k), y + ey(k), z + ez(k));
-      if (tgt >= 0 && (d.mask[tgt] >> kTypeShift) == kSolid) tgt = -1;
-      const size_t src = tgt < 0 ? n : (size_t)tgt;
-      const int zs = (int)(src / ((size_t)d.nx * d.ny));
+      int X = x + ex(k), Y = y + ey(k), Z = z + ez(k);
+      const bool none = d.map[map_pos(d.nx, d.ny, X, Y, Z)] == kNoNode;
+      X = none ? x : wrap(X, d.nx);
+      Y = none ? y : wrap(Y, d.ny);
+      Z = none ? z : wrap(Z, d.nz);
       for (int c = 0; c < 2; ++c) {
-        const double r = rho0_of(d.mask, rho_init, maj, mnr, z_front, rres, d.N, src, zs, c);
-        const float gv = (float)(wd(k) * (r - rho_ref));
-        slot[(size_t)(c * 19 + k) * kBN] = gv;
-        if (ghost) ghost[(size_t)(c * 19 + k) * kBN] = gv;
+        const double r = rho0_of(d, rho_init, maj, mnr, z_front, rres, X, Y, Z, c);
+        slot[(c * 19 + k) * kLine] = (float)(wd(k) * (r - rho_ref));
       }
     }
   }
@@ -929,15 +1028,67 @@ hipError_t launch_init(const Dom &d, const Phys &P, const double *rho_init, doub
   return hipGetLastError();
 }
 
+// ---- checkpoint-file layout -----------------------------------------------------
+// element `o` of the file layout: population q of box node (x, y, z); false
+// for padding, unused ghost planes and solid nodes
+__device__ __forceinline__ bool file_node(const Dom &d, size_t o, bool ghosts, uint32_t &i,
+                                          int &q) {
+  const size_t P = brick_plane(d.nx, d.ny);
+  int z = (int)(o / P) - 1;
+  const uint32_t r = (uint32_t)(o % P);
+  const uint32_t brick = r / (uint32_t)(kQ * kBX * kBY), w = r % (uint32_t)(kQ * kBX * kBY);
+  const uint32_t nbx = (uint32_t)(pad_x(d.nx) / kBX), l = w % (uint32_t)(kBX * kBY);
+  q = (int)(w / (uint32_t)(kBX * kBY));
+  const int x = (int)((brick % nbx) * kBX + l % kBX), y = (int)((brick / nbx) * kBY + l / kBX);
+  if (x >= d.nx || y >= d.ny) return false;
+  if (z < 0 || z >= d.nz) {
+    if (!ghosts || !(d.per & 4)) return false;
+    z = wrap(z, d.nz);
+  }
+  i = d.map[map_pos(d.nx, d.ny, x, y, z)];
+  return i != kNoNode;
+}
+
+__global__ void k_to_file(Dom d, const float *g, size_t first, size_t count, float *out) {
+  for (size_t o = blockIdx.x * (size_t)blockDim.x + threadIdx.x; o < count;
+       o += (size_t)gridDim.x * blockDim.x) {
+    uint32_t i;
+    int q;
+    out[o] = file_node(d, first + o, true, i, q) ? g[node_elem(i) + (size_t)(q * kLine)] : 0.f;
+  }
+}
+
+__global__ void k_from_file(Dom d, const float *in, size_t first, size_t count, float *g) {
+  for (size_t o = blockIdx.x * (size_t)blockDim.x + threadIdx.x; o < count;
+       o += (size_t)gridDim.x * blockDim.x) {
+    uint32_t i;
+    int q;
+    if (file_node(d, first + o, false, i, q)) g[node_elem(i) + (size_t)(q * kLine)] = in[o];
+  }
+}
+
+hipError_t launch_to_file(const Dom &d, const float *g, size_t first, size_t count, float *out,
+                          hipStream_t st) {
+  const unsigned blocks = (unsigned)std::min<size_t>((count + 255) / 256, 65536);
+  hipLaunchKernelGGL(k_to_file, dim3(blocks), dim3(256), 0, st, d, g, first, count, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_from_file(const Dom &d, const float *in, size_t first, size_t count, float *g,
+                            hipStream_t st) {
+  const unsigned blocks = (unsigned)std::min<size_t>((count + 255) / 256, 65536);
+  hipLaunchKernelGGL(k_from_file, dim3(blocks), dim3(256), 0, st, d, in, first, count, g);
+  return hipGetLastError();
+}
+
 // ---- read-back: pre-collision populations and densities in FP64 ------------
 __global__ void k_export(Dom d, Phys P, const double *rres, double *f) {
   for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < d.N;
        n += (size_t)gridDim.x * blockDim.x) {
     const int x = (int)(n % d.nx), y = (int)((n / d.nx) % d.ny), z = (int)(n / ((size_t)d.nx * d.ny));
-    const uint32_t m = d.mask[n];
-    const uint32_t t = m >> kTypeShift;
+    const uint32_t t = class_at(d, x, y, z);
     float v[2][19];
-    if (t == kFluid) pull(d, m, x, y, z, v);
+    if (t == kFluid) pull_at(d, x, y, z, v);
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
@@ -962,12 +1113,11 @@ __global__ void k_density(Dom d, Phys P, const double *rres, double *rho) {
   for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < d.N;
        n += (size_t)gridDim.x * blockDim.x) {
     const int x = (int)(n % d.nx), y = (int)((n / d.nx) % d.ny), z = (int)(n / ((size_t)d.nx * d.ny));
-    const uint32_t m = d.mask[n];
-    const uint32_t t = m >> kTypeShift;
+    const uint32_t t = class_at(d, x, y, z);
     double r0 = 0.0, r1 = 0.0;
     if (t == kFluid) {
       float v[2][19];
-      pull(d, m, x, y, z, v);
+      pull_at(d, x, y, z, v);
       r0 = (double)(float)((acc_t)P.rho_ref + sum19(v[0]));
       r1 = (double)(float)((acc_t)P.rho_ref + sum19(v[1]));
     } else if (t == kResIn) {
@@ -1017,22 +1167,11 @@ hipError_t scratch_address(double **out) {
 }
 
 // ---- FP64 reductions ------------------------------------------------------
-// Two passes with a fixed summation order (strided per thread inside a node
-// chunk, LDS tree per chunk, then the chunks of a subdomain summed in order
-// by one thread), so results are bitwise reproducible and identical whether
-// a subdomain is reduced alone or inside a batch.
+// Two passes with a fixed summation order (a chunk's nodes strided over one
+// workgroup, then an LDS tree; then a subdomain's chunks likewise), so results are bitwise reproducible and identical whether a
+// subdomain is reduced alone or inside a batch.
 constexpr int kRedThreads = 256;
 constexpr int kRedVals = 3;
-
-void list_chunks(int throat, uint32_t N, std::vector<Chunk> &out) {
-  for (uint32_t s = 0; s < N; s += kChunkNodes)
-    out.push_back(Chunk{throat, s, std::min(kChunkNodes, N - s)});
-}
-
-void list_red_chunks(int throat, uint32_t nlist, std::vector<Chunk> &out) {
-  for (uint32_t s = 0; s < nlist; s += kRedEntries)
-    out.push_back(Chunk{throat, s, std::min(kRedEntries, nlist - s)});
-}
 
 __device__ __forceinline__ void block_sum(double (&v)[kRedVals], double (*sh)[kRedThreads]) {
   const int t = threadIdx.x;
@@ -1050,72 +1189,81 @@ __device__ __forceinline__ void block_sum(double (&v)[kRedVals], double (*sh)[kR
 }
 
 __global__ __launch_bounds__(kRedThreads) void k_reduce_chunks(const Throat *__restrict__ th,
-                                                               const Chunk *__restrict__ chunks,
+                                                               const RedChunk *__restrict__ chunks,
+                                                               int nchunks,
                                                                const RedInfo *__restrict__ info,
                                                                int parity, double *partials,
                                                                double *probe_out) {
   __shared__ double sh[kRedVals][kRedThreads];
-  const Chunk ch = chunks[blockIdx.x];
+  const int item = xcd_item(nchunks);
+  const RedChunk ch = chunks[item];
   const Throat &T = th[ch.throat];
-  Dom d;
-  d.src = T.g[parity];
-  d.dst = nullptr;
-  d.mask = T.mask;
-  d.N = T.N;
-  d.nx = T.nx;
-  d.ny = T.ny;
-  d.nz = T.nz;
-  d.per = T.per;
+  const uint32_t px = (uint32_t)(T.nx + 2 * kPad);
+  const size_t pp = (size_t)px * (size_t)(T.ny + 2 * kPad);
   const float rho_ref = T.P.rho_ref;
   const RedInfo ri = info[ch.throat];
+  const uint32_t end = min(ch.first + (uint32_t)kRedNodes, T.n_live);
   double acc[kRedVals] = {0.0, 0.0, 0.0};
-  for (uint32_t i = threadIdx.x; i < ch.count; i += kRedThreads) {
-    const uint2 e = T.list[ch.start + i];
-    const uint32_t n = e.x, m = e.y;
-    if ((m >> kTypeShift) != kFluid) continue;
-    const int x = (int)(n % (uint32_t)d.nx), y = (int)((n / (uint32_t)d.nx) % (uint32_t)d.ny);
-    const int z = (int)(n / ((uint32_t)d.nx * (uint32_t)d.ny));
+  for (uint32_t i = ch.first + threadIdx.x; i < end; i += kRedThreads) {
+    const uint32_t pos = T.pos[i];
+    if (bath_of(T, pos, pp) >= 0) continue;
+    Near n;
+    uint32_t m;
     float v[2][19];
-    pull(d, m, x, y, z, v);
+    near_of<true>(T, pos, px, pp, n);
+    pull<true>(T.g[parity], n, m, v);
     const double a = (double)(float)((acc_t)rho_ref + sum19(v[0]));
     const double b = (double)(float)((acc_t)rho_ref + sum19(v[1]));
     acc[0] += a;
     acc[1] += b;
     acc[2] += ((a - b) / (a + b) + ri.phib) / (2.0 * ri.phib);
-    if ((long long)n == ri.probe) {
+    if ((long long)n.r[0][1] == ri.probe) {
       probe_out[2 * ch.throat] = a;
       probe_out[2 * ch.throat + 1] = b;
     }
   }
   block_sum(acc, sh);
   if (threadIdx.x == 0)
-    for (int i = 0; i < kRedVals; ++i) partials[(size_t)blockIdx.x * kRedVals + i] = acc[i];
+    for (int i = 0; i < kRedVals; ++i) partials[(size_t)item * kRedVals + i] = acc[i];
 }
 
-__global__ void k_reduce_throats(const int *first, const int *count, int n,
-                                 const double *partials, double *sums) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
+__global__ __launch_bounds__(kRedThreads) void k_reduce_throats(const int *first, const int *count,
+                                                                const double *partials,
+                                                                double *sums) {
+  __shared__ double sh[kRedVals][kRedThreads];
+  const int t = blockIdx.x;
   double acc[kRedVals] = {0.0, 0.0, 0.0};
-  for (int c = first[t]; c < first[t] + count[t]; ++c)
-    for (int i = 0; i < kRedVals; ++i) acc[i] += partials[(size_t)c * kRedVals + i];
-  for (int i = 0; i < kRedVals; ++i) sums[(size_t)t * kRedVals + i] = acc[i];
+  for (int c = threadIdx.x; c < count[t]; c += kRedThreads)
+    for (int i = 0; i < kRedVals; ++i) acc[i] += partials[(size_t)(first[t] + c) * kRedVals + i];
+  block_sum(acc, sh);
+  if (threadIdx.x == 0)
+    for (int i = 0; i < kRedVals; ++i) sums[(size_t)t * kRedVals + i] = acc[i];
 }
 
-hipError_t launch_reduce_chunks(const Throat *th, const Chunk *chunks, int nchunks,
+void red_chunks(size_t n_live, int throat, std::vector<RedChunk> &out) {
+  for (size_t f = 0; f < n_live; f += kRedNodes) out.push_back(RedChunk{throat, (uint32_t)f});
+}
+
+hipError_t launch_reduce_chunks(const Throat *th, const RedChunk *chunks, int nchunks,
                                 const RedInfo *info, int parity, double *partials,
                                 double *probe_out, hipStream_t st) {
   if (nchunks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_reduce_chunks, dim3(nchunks), dim3(kRedThreads), 0, st, th, chunks, info,
-                     parity, partials, probe_out);
+  hipLaunchKernelGGL(k_reduce_chunks, dim3(nchunks), dim3(kRedThreads), 0, st, th, chunks,
+                     nchunks, info, parity, partials, probe_out);
   return hipGetLastError();
 }
 
 hipError_t launch_reduce_throats(const int *first, const int *count, int n, const double *partials,
                                  double *sums, hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_throats, dim3((n + 255) / 256), dim3(256), 0, st, first, count, n,
+  hipLaunchKernelGGL(k_reduce_throats, dim3((unsigned)n), dim3(kRedThreads), 0, st, first, count,
                      partials, sums);
   return hipGetLastError();
+}
+
+void copy_chunks(int throat, size_t elems, std::vector<Chunk> &out) {
+  const size_t n = elems / 4;
+  for (size_t s = 0; s < n; s += kCopyChunk)
+    out.push_back(Chunk{throat, (uint32_t)std::min<size_t>(kCopyChunk, n - s), s});
 }
 
 // ---- device-side drainage ramp (Sec. 2.2.2) ---------------------------------
@@ -1274,6 +1422,8 @@ __global__ __launch_bounds__(256) void k_ramp_advance(Throat *th, RampDev *rd, c
   if (threadIdx.x == 0) n_active_out[0] = cnt[0];
 }
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+
 __global__ __launch_bounds__(256) void k_copy_requests(const Throat *__restrict__ th,
                                                        const RampDev *__restrict__ rd,
                                                        const Ckpt *__restrict__ ck,
@@ -1282,18 +1432,10 @@ __global__ __launch_bounds__(256) void k_copy_requests(const Throat *__restrict_
   const Chunk c = chunks[blockIdx.x];
   const int req = rd[c.throat].req;
   if (!req) return;
-  const Throat &T = th[c.throat];
-  float *g = T.g[parity];
-  float *sa = ck[c.throat].stable, *ma = ck[c.throat].main;
-  // the subdomain's chunks split its whole buffer (ghost planes included)
-  // into equal flat ranges, chunk i taking the i-th
-  const size_t E = pop_elems(T.nx, T.ny, T.nz);
-  const size_t nch = (T.N + kChunkNodes - 1) / kChunkNodes;
-  const size_t len = (E + nch - 1) / nch;
-  const size_t lo = (size_t)(c.start / kChunkNodes) * len;
-  const size_t hi = lo + len < E ? lo + len : E;
-  for (size_t o = lo + threadIdx.x; o < hi; o += blockDim.x) {
-    const float v = g[o];
+  v4f *g = (v4f *)th[c.throat].g[parity] + c.start;
+  v4f *sa = (v4f *)ck[c.throat].stable + c.start, *ma = (v4f *)ck[c.throat].main + c.start;
+  for (uint32_t o = threadIdx.x; o < c.count; o += blockDim.x) {
+    const v4f v = g[o];
     if (req & kSaveStable) sa[o] = v;
     if (req & kSaveMain) ma[o] = v;
     if (req & kRestoreStable) g[o] = sa[o];
@@ -1325,8 +1467,6 @@ hipError_t launch_copy_requests(const Throat *th, const RampDev *rd, const Ckpt 
 }
 
 // ---- stream-copy probe: achievable HBM bandwidth on this device ----------
-typedef float v4f __attribute__((ext_vector_type(4)));
-
 // one 16-byte element per thread, plain loads and stores (the fastest copy
 // form measured on this device)
 __global__ __launch_bounds__(256) void k_copy(const v4f *__restrict__ a, v4f *__restrict__ b,
