@@ -57,6 +57,27 @@ struct Gemm {
 
 hipError_t launch_gemm(const Gemm &g, hipStream_t st);
 
+// BF16 weights packed in the operand order of the 16x16x32 matrix instruction:
+// per member and layer, output tiles of 16 by chunks of 32 inputs, each a
+// fragment of 64 lanes x 8 values, W[16 t + l % 16][32 c + 8 (l / 16) + i] for
+// lane l, zero beyond the layer's widths
+constexpr int kTilesN[kLayers] = {16, 16, 16, 2};
+constexpr int kChunksK[kLayers] = {3, 8, 8, 8};
+constexpr int kFrag = 512;  // values of one fragment
+constexpr int pack_off(int l) {
+  int o = 0;
+  for (int i = 0; i < l; ++i) o += kTilesN[i] * kChunksK[i];
+  return o;
+}
+constexpr long long kPack = (long long)pack_off(kLayers) * kFrag;
+hipError_t launch_pack(const float *w, bf16 *wp, int members, hipStream_t st);
+
+// y[z*ycap + b][17] (f32, standardised outputs) of every member for n rows of
+// X [n][80] (FP64), standardised with mu, sd; bad[0] = 1 when X is not finite
+hipError_t launch_mlp(const double *X, const double *mu, const double *sd, int n, int members,
+                      const bf16 *wp, const float *w, float *y, long long ycap, int *bad,
+                      hipStream_t st);
+
 // per-column mean and population std (FP64) of X [n][cols], std < 1e-12 -> 1
 hipError_t launch_col_stats(const double *X, int n, int cols, double *mu, double *sd,
                             hipStream_t st);

@@ -161,6 +161,162 @@ hipError_t launch_gemm(const Gemm &g, hipStream_t st) {
   return hipGetLastError();
 }
 
+// ---- ensemble forward in one kernel --------------------------------------------
+__global__ void k_pack(const float *w, bf16 *wp, int members) {
+  const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (i >= members * kPack) return;
+  const int z = (int)(i / kPack), r = (int)(i % kPack);
+  int f = r / kFrag, l = 0;
+  while (l + 1 < kLayers && f >= pack_off(l + 1)) ++l;
+  f -= pack_off(l);
+  const int lane = (r % kFrag) / 8, j = r % 8;
+  const int n = 16 * (f / kChunksK[l]) + lane % 16;
+  const int k = 32 * (f % kChunksK[l]) + 8 * (lane / 16) + j;
+  const bool in = n < kWidth[l + 1] && k < kWidth[l];
+  wp[i] = in ? to_bf16(w[(long long)z * kParams + w_off(l) + (long long)n * kWidth[l] + k])
+             : (bf16)0;
+}
+
+hipError_t launch_pack(const float *w, bf16 *wp, int members, hipStream_t st) {
+  const long long total = members * kPack;
+  hipLaunchKernelGGL(k_pack, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, w, wp,
+                     members);
+  return hipGetLastError();
+}
+
+// Rows of activations in LDS, k-contiguous; 264 (104) values apart, so that
+// the 16 rows of an operand start in different banks.
+constexpr int LDA = kHidden + 8, LDX = 32 * kChunksK[0] + 8;
+
+// acc[t][j] = W tiles (rows) times activation tiles (columns): TPW output
+// tiles from `tile0`, MT tiles of 16 rows of the batch in `in`
+template <int L, int MT, int TPW, int LD>
+__device__ __forceinline__ void layer_acc(const bf16 *wp, const bf16 *in, int tile0, int lane,
+                                          v4f (&acc)[TPW][MT]) {
+#pragma unroll
+  for (int t = 0; t < TPW; ++t)
+#pragma unroll
+    for (int j = 0; j < MT; ++j) acc[t][j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < kChunksK[L]; ++c) {
+    v8bf a[TPW], b[MT];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+      a[t] = *(const v8bf *)(wp + ((long long)(pack_off(L) + (tile0 + t) * kChunksK[L] + c) * 64 +
+                                   lane) * 8);
+#pragma unroll
+    for (int j = 0; j < MT; ++j)
+      b[j] = *(const v8bf *)(in + (16 * j + (lane & 15)) * LD + 32 * c + 8 * (lane >> 4));
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int j = 0; j < MT; ++j)
+        acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b[j], acc[t][j], 0, 0, 0);
+  }
+}
+
+// a hidden layer's bias and SiLU; the result goes to act once every wavefront
+// has read the layer's input
+template <int L, int MT, int TPW>
+__device__ __forceinline__ void layer_silu(const float *w, int tile0, int lane,
+                                           const v4f (&acc)[TPW][MT], bf16 *act) {
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int n = 16 * (tile0 + t) + 4 * (lane >> 4);
+    float bias[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bias[i] = w[b_off(L) + n + i];
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+      uint2 q;
+      bf16 *e = (bf16 *)&q;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float zz = acc[t][j][i] + bias[i];
+        e[i] = to_bf16(silu(zz));
+      }
+      *(uint2 *)(act + (16 * j + (lane & 15)) * LDA + n) = q;
+    }
+  }
+  __syncthreads();
+}
+
+// One workgroup carries 16 MT rows through all four layers of `per` members:
+// the activations stay in LDS, the weights come as whole packed fragments
+// straight into the operand registers.  Each wavefront owns 16 / NW output
+// tiles of a hidden layer.
+//
+// Bound: a workgroup reads a member's 320 KB of weights from the L2 for every
+// 16 MT rows; at MT = 4 that is as many bytes per clock as a CU can take while
+// its matrix cores run at full rate.  One row tile per workgroup (MT = 1) and
+// one member per workgroup spread a small call over the chip.
+template <int MT, int NW>
+__global__ __launch_bounds__(64 * NW) void k_mlp(const double *X, const double *mu,
+                                                 const double *sd, int n, int per,
+                                                 const bf16 *wp, const float *w, float *y,
+                                                 long long ycap, int *bad) {
+  constexpr int TPW = 16 / NW;
+  __shared__ __attribute__((aligned(16))) bf16 x0[16 * MT * LDX];
+  __shared__ __attribute__((aligned(16))) bf16 act[16 * MT * LDA];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int row0 = blockIdx.x * 16 * MT;
+  bool finite = true;
+  for (int e = tid; e < 16 * MT * 32 * kChunksK[0]; e += 64 * NW) {
+    const int r = e / (32 * kChunksK[0]), c = e % (32 * kChunksK[0]);
+    bf16 v = 0;
+    if (c < kFeat && row0 + r < n) {
+      const double x = X[(long long)(row0 + r) * kFeat + c];
+      finite = finite && isfinite(x);
+      v = to_bf16((float)((x - mu[c]) / sd[c]));
+    }
+    x0[r * LDX + c] = v;
+  }
+  if (!finite) *bad = 1;
+  __syncthreads();
+  for (int z = blockIdx.y * per; z < (int)(blockIdx.y + 1) * per; ++z) {
+    const bf16 *wz = wp + z * kPack;
+    const float *pz = w + z * kParams;
+    v4f acc[TPW][MT];
+    layer_acc<0, MT, TPW, LDX>(wz, x0, wv * TPW, lane, acc);
+    layer_silu<0, MT, TPW>(pz, wv * TPW, lane, acc, act);
+    layer_acc<1, MT, TPW, LDA>(wz, act, wv * TPW, lane, acc);
+    layer_silu<1, MT, TPW>(pz, wv * TPW, lane, acc, act);
+    layer_acc<2, MT, TPW, LDA>(wz, act, wv * TPW, lane, acc);
+    layer_silu<2, MT, TPW>(pz, wv * TPW, lane, acc, act);
+    if (wv < kTilesN[3]) {
+      v4f out[1][MT];
+      layer_acc<3, MT, 1, LDA>(wz, act, wv, lane, out);
+#pragma unroll
+      for (int j = 0; j < MT; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int o = 16 * wv + 4 * (lane >> 4) + i, row = row0 + 16 * j + (lane & 15);
+          if (o < kOut && row < n)
+            y[(z * ycap + row) * kOut + o] = out[0][j][i] + pz[b_off(3) + o];
+        }
+    }
+  }
+}
+
+hipError_t launch_mlp(const double *X, const double *mu, const double *sd, int n, int members,
+                      const bf16 *wp, const float *w, float *y, long long ycap, int *bad,
+                      hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  // 64 rows a workgroup once that gives every CU two of them
+  const int big = (n + 63) / 64;
+  if (big >= 512)
+    hipLaunchKernelGGL((k_mlp<4, 4>), dim3((unsigned)big, 1), dim3(256), 0, st, X, mu, sd, n,
+                       members, wp, w, y, ycap, bad);
+  else if (big * members >= 512)
+    hipLaunchKernelGGL((k_mlp<4, 4>), dim3((unsigned)big, (unsigned)members), dim3(256), 0, st, X,
+                       mu, sd, n, 1, wp, w, y, ycap, bad);
+  else
+    hipLaunchKernelGGL((k_mlp<1, 8>), dim3((unsigned)((n + 15) / 16), (unsigned)members),
+                       dim3(512), 0, st, X, mu, sd, n, 1, wp, w, y, ycap, bad);
+  return hipGetLastError();
+}
+
 // ---- fixed-order block reduction (FP64) -------------------------------------
 template <int NT>
 __device__ __forceinline__ double block_sum(double v, double *sh) {

@@ -38,6 +38,9 @@ namespace {
 
 constexpr long long P = sg::kParams;
 constexpr int H = sg::kHidden;
+constexpr int kPinRows = 512;     // rows of a call that go through host-visible buffers
+constexpr int kChunkRows = 32768; // rows of one forward launch
+constexpr int kKeepRows = 131072; // rows whose statistics buffer a handle keeps
 
 uint64_t splitmix64(uint64_t seed, uint64_t i) {
   // i-th output (i >= 0) of SplitMix64 seeded with seed, counter style
@@ -76,6 +79,7 @@ struct lbm_surrogate {
   bool own_stream = false;
   float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;  // [members][P]
   sg::bf16 *wb = nullptr;
+  sg::bf16 *wp = nullptr;  // packed weights of the one-kernel forward [members][kPack]
   long long adam_t = 0;
   bool has_stats = false;
   double *stats_d = nullptr;  // xmu[80] xsd[80] tmu[17] tsd[17]
@@ -89,6 +93,15 @@ struct lbm_surrogate {
   float *y = nullptr, *t = nullptr, *dy = nullptr;  // [members][cap][17]
   sg::bf16 *dyb = nullptr;
   hipEvent_t ev[2] = {};
+  // inference: no standardisation (80 zeros, 80 ones), rows on the device, the
+  // members' outputs, ensemble statistics, the non-finite flag; host-visible
+  // rows and results of a small call
+  double *id_d = nullptr;
+  double *feat_d = nullptr, *stat_d = nullptr;
+  float *yi_d = nullptr;
+  int feat_cap = 0, stat_cap = 0;
+  double *pin_in = nullptr, *pin_out = nullptr;  // pinned, kPinRows rows
+  int *bad = nullptr;                            // pinned
 
   double *xmu() { return stats_d; }
   double *xsd() { return stats_d + 80; }
@@ -130,9 +143,37 @@ struct lbm_surrogate {
     return LBM_OK;
   }
 
+  // inference buffers for chunks of `rows` rows, and statistics of `n` rows
+  // (kept for later calls up to kKeepRows)
+  int ensure_infer(int rows, int n) {
+    if (rows > feat_cap) {
+      dfree(feat_d);
+      dfree(yi_d);
+      feat_cap = 0;
+      SGTRY(dalloc(&feat_d, (size_t)rows * sg::kFeat));
+      SGTRY(dalloc(&yi_d, (size_t)members * rows * sg::kOut));
+      feat_cap = rows;
+    }
+    if (n > stat_cap) {
+      dfree(stat_d);
+      stat_cap = 0;
+      SGTRY(dalloc(&stat_d, (size_t)n * 2 * sg::kOut));
+      stat_cap = n;
+    }
+    return LBM_OK;
+  }
+
   ~lbm_surrogate() {
     if (stream) (void)hipStreamSynchronize(stream);
     free_work();
+    dfree(wp);
+    dfree(id_d);
+    dfree(feat_d);
+    dfree(stat_d);
+    dfree(yi_d);
+    if (pin_in) (void)hipHostFree(pin_in);
+    if (pin_out) (void)hipHostFree(pin_out);
+    if (bad) (void)hipHostFree(bad);
     dfree(w);
     dfree(m);
     dfree(v);
@@ -292,22 +333,6 @@ struct Identity {
     dfree(one);
   }
 };
-
-// forward of n standardised rows (device f32 [n][80]) in chunks; calls
-// sink(start, count) after each chunk with the outputs in s->y
-template <class F>
-int forward_chunks(lbm_surrogate_t s, const float *xs_d, int n, F sink) {
-  const int chunk = std::min(n, LBM_SG_MAX_BATCH);
-  SGTRY(s->ensure(chunk));
-  for (int start = 0; start < n; start += chunk) {
-    const int cnt = std::min(chunk, n - start);
-    SGCHK(sg::launch_gather(xs_d + (size_t)start * sg::kFeat, nullptr, nullptr, 0, 1, cnt, s->cap,
-                            s->act[0], nullptr, s->stream));
-    SGTRY(s->forward(cnt, 0));
-    SGTRY(sink(start, cnt));
-  }
-  return LBM_OK;
-}
 
 // Mayer-Stowe-Princen entry radius of the throat's cross-section (Sec. 1 of
 // the paper names the method): the triangle of the three throat-sphere
@@ -506,6 +531,17 @@ int lbm_surrogate_create(int members, unsigned long long seed, void *stream,
   if (int r = dalloc(&s->v, count)) return fail(r);
   if (int r = dalloc(&s->g, count)) return fail(r);
   if (int r = dalloc(&s->wb, count)) return fail(r);
+  if (int r = dalloc(&s->wp, (size_t)members * sg::kPack)) return fail(r);
+  if (int r = dalloc(&s->id_d, 2 * sg::kFeat)) return fail(r);
+  if (hipHostMalloc((void **)&s->pin_in, sizeof(double) * kPinRows * sg::kFeat,
+                    hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void **)&s->pin_out, sizeof(double) * kPinRows * 2 * sg::kOut,
+                    hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void **)&s->bad, sizeof(int), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    set_err("hipHostMalloc of the inference buffers failed");
+    return fail(LBM_ENOMEM);
+  }
   if (int r = dalloc(&s->stats_d, 194)) return fail(r);
   if (int r = dalloc(&s->loss_d, (size_t)members)) return fail(r);
   for (auto &e : s->ev)
@@ -530,7 +566,12 @@ int lbm_surrogate_create(int members, unsigned long long seed, void *stream,
       return fail(LBM_EHIP);
     }
   }
-  if (hipMemset(s->m, 0, sizeof(float) * count) != hipSuccess ||
+  std::vector<double> ident(2 * sg::kFeat, 0.0);
+  std::fill(ident.begin() + sg::kFeat, ident.end(), 1.0);
+  if (hipMemcpy(s->id_d, ident.data(), sizeof(double) * ident.size(), hipMemcpyHostToDevice) !=
+          hipSuccess ||
+      sg::launch_pack(s->w, s->wp, members, s->stream) != hipSuccess ||
+      hipMemset(s->m, 0, sizeof(float) * count) != hipSuccess ||
       hipMemset(s->v, 0, sizeof(float) * count) != hipSuccess ||
       sg::launch_to_bf16(s->w, s->wb, (long long)count, s->stream) != hipSuccess ||
       hipStreamSynchronize(s->stream) != hipSuccess) {
@@ -561,6 +602,7 @@ int lbm_surrogate_set_params(lbm_surrogate_t s, int member, const float *w) {
   SGCHK(hipMemsetAsync(s->m + (size_t)member * P, 0, sizeof(float) * P, s->stream));
   SGCHK(hipMemsetAsync(s->v + (size_t)member * P, 0, sizeof(float) * P, s->stream));
   SGCHK(sg::launch_to_bf16(dst, s->wb + (size_t)member * P, P, s->stream));
+  SGCHK(sg::launch_pack(dst, s->wp + (size_t)member * sg::kPack, 1, s->stream));
   SGCHK(hipStreamSynchronize(s->stream));
   return LBM_OK;
 }
@@ -673,20 +715,21 @@ int lbm_surrogate_forward(lbm_surrogate_t s, int n, const double *xs, float *y) 
     set_err("lbm_surrogate_forward: inputs must be finite");
     return LBM_ENONFINITE;
   }
-  Identity id;
-  SGTRY(id.make(s->stream));
-  float *xs_d = nullptr;
-  SGTRY(upload_std(s, xs, n, sg::kFeat, id.zero, id.one, &xs_d));
-  int rc = forward_chunks(s, xs_d, n, [&](int start, int cnt) -> int {
+  const int chunk = std::min(n, kChunkRows);
+  SGTRY(s->ensure_infer(chunk, 0));
+  for (int start = 0; start < n; start += chunk) {
+    const int cnt = std::min(chunk, n - start);
+    SGCHK(hipMemcpyAsync(s->feat_d, xs + (size_t)start * sg::kFeat,
+                         sizeof(double) * cnt * sg::kFeat, hipMemcpyHostToDevice, s->stream));
+    SGCHK(sg::launch_mlp(s->feat_d, s->id_d, s->id_d + sg::kFeat, cnt, s->members, s->wp, s->w,
+                         s->yi_d, cnt, s->bad, s->stream));
     for (int z = 0; z < s->members; ++z)
       SGCHK(hipMemcpyAsync(y + ((size_t)z * n + start) * sg::kOut,
-                           s->y + (size_t)z * s->cap * sg::kOut, sizeof(float) * cnt * sg::kOut,
+                           s->yi_d + (size_t)z * cnt * sg::kOut, sizeof(float) * cnt * sg::kOut,
                            hipMemcpyDeviceToHost, s->stream));
     SGCHK(hipStreamSynchronize(s->stream));
-    return LBM_OK;
-  });
-  dfree(xs_d);
-  return rc;
+  }
+  return LBM_OK;
 }
 
 int lbm_surrogate_grad(lbm_surrogate_t s, int n, const double *xs, const double *ts, float *grad,
@@ -854,6 +897,10 @@ int lbm_surrogate_train(lbm_surrogate_t s, int n, const double *feat, const doub
       loss_hist[e] = a / Mb;
     }
   }
+  if (sg::launch_pack(s->w, s->wp, Mb, s->stream) != hipSuccess && rc == LBM_OK) {
+    set_err("packing the weights failed");
+    rc = LBM_EHIP;
+  }
   if (rc == LBM_OK && hipStreamSynchronize(s->stream) != hipSuccess) {
     set_err("training did not complete");
     rc = LBM_EHIP;
@@ -866,28 +913,27 @@ int lbm_surrogate_train(lbm_surrogate_t s, int n, const double *feat, const doub
 
 namespace {
 
+// ensemble mean and std of cnt raw descriptor rows (device or host-visible
+// memory; so may mean and std be)
+int predict_rows(lbm_surrogate_t s, const double *feat, int cnt, double *mean, double *std) {
+  SGCHK(sg::launch_mlp(feat, s->xmu(), s->xsd(), cnt, s->members, s->wp, s->w, s->yi_d, cnt,
+                       s->bad, s->stream));
+  SGCHK(sg::launch_ensemble(s->yi_d, s->members, cnt, cnt, s->tmu(), s->tsd(), mean, std,
+                            s->stream));
+  return LBM_OK;
+}
+
 // predictions for n raw descriptor rows already on the device
 int predict_device(lbm_surrogate_t s, const double *feat_d, int n, double *mean_d, double *std_d) {
-  float *xs_d = nullptr;
-  SGTRY(dalloc(&xs_d, (size_t)n * sg::kFeat));
-  hipError_t e = sg::launch_standardise(feat_d, n, sg::kFeat, s->xmu(), s->xsd(), xs_d, s->stream);
-  if (e != hipSuccess) {
-    dfree(xs_d);
-    set_err("standardise failed: %s", hipGetErrorString(e));
+  SGTRY(s->ensure_infer(std::min(n, kChunkRows), 0));
+  for (int start = 0; start < n; start += kChunkRows)
+    SGTRY(predict_rows(s, feat_d + (size_t)start * sg::kFeat, std::min(kChunkRows, n - start),
+                       mean_d + (size_t)start * sg::kOut, std_d + (size_t)start * sg::kOut));
+  if (hipStreamSynchronize(s->stream) != hipSuccess) {
+    set_err("prediction did not complete");
     return LBM_EHIP;
   }
-  int rc = forward_chunks(s, xs_d, n, [&](int start, int cnt) -> int {
-    SGCHK(sg::launch_ensemble(s->y, s->members, cnt, s->cap, s->tmu(), s->tsd(),
-                              mean_d + (size_t)start * sg::kOut, std_d + (size_t)start * sg::kOut,
-                              s->stream));
-    return LBM_OK;
-  });
-  if (rc == LBM_OK && hipStreamSynchronize(s->stream) != hipSuccess) {
-    set_err("prediction did not complete");
-    rc = LBM_EHIP;
-  }
-  dfree(xs_d);
-  return rc;
+  return LBM_OK;
 }
 
 }  // namespace
@@ -904,36 +950,45 @@ int lbm_surrogate_predict(lbm_surrogate_t s, int n, const double *feat, double *
     return LBM_ESTATE;
   }
   if (n == 0) return LBM_OK;
-  if (!all_finite(feat, (size_t)n * sg::kFeat)) {
+  // the rows are checked where they are read, by the forward kernel; nothing
+  // is written to the caller's arrays before its flag is known
+  const int chunk = std::min(n, kChunkRows);
+  const bool small = n <= kPinRows;
+  SGTRY(s->ensure_infer(chunk, small ? 0 : n));
+  double *mean_d = small ? s->pin_out : s->stat_d;
+  double *std_d = mean_d + (size_t)n * sg::kOut;
+  *s->bad = 0;
+  if (small) {
+    std::memcpy(s->pin_in, feat, sizeof(double) * n * sg::kFeat);
+    SGTRY(predict_rows(s, s->pin_in, n, mean_d, std_d));
+  } else {
+    for (int start = 0; start < n; start += chunk) {
+      const int cnt = std::min(chunk, n - start);
+      SGCHK(hipMemcpyAsync(s->feat_d, feat + (size_t)start * sg::kFeat,
+                           sizeof(double) * cnt * sg::kFeat, hipMemcpyHostToDevice, s->stream));
+      SGTRY(predict_rows(s, s->feat_d, cnt, mean_d + (size_t)start * sg::kOut,
+                         std_d + (size_t)start * sg::kOut));
+    }
+  }
+  SGCHK(hipStreamSynchronize(s->stream));
+  if (*s->bad) {
     set_err("lbm_surrogate_predict: features must be finite");
     return LBM_ENONFINITE;
   }
-  double *f_d = nullptr, *mean_d = nullptr, *std_d = nullptr;
-  SGTRY(dalloc(&f_d, (size_t)n * sg::kFeat));
-  int rc = dalloc(&mean_d, (size_t)n * sg::kOut);
-  if (rc == LBM_OK) rc = dalloc(&std_d, (size_t)n * sg::kOut);
-  if (rc == LBM_OK && hipMemcpyAsync(f_d, feat, sizeof(double) * n * sg::kFeat,
-                                     hipMemcpyHostToDevice, s->stream) != hipSuccess) {
-    set_err("feature upload failed");
-    rc = LBM_EHIP;
+  const size_t bytes = sizeof(double) * n * sg::kOut;
+  if (small) {
+    std::memcpy(mean, mean_d, bytes);
+    std::memcpy(std, std_d, bytes);
+    return LBM_OK;
   }
-  if (rc == LBM_OK) rc = predict_device(s, f_d, n, mean_d, std_d);
-  if (rc == LBM_OK) {
-    hipError_t e = hipMemcpyAsync(mean, mean_d, sizeof(double) * n * sg::kOut,
-                                  hipMemcpyDeviceToHost, s->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(std, std_d, sizeof(double) * n * sg::kOut, hipMemcpyDeviceToHost,
-                         s->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-    if (e != hipSuccess) {
-      set_err("prediction download failed: %s", hipGetErrorString(e));
-      rc = LBM_EHIP;
-    }
+  SGCHK(hipMemcpyAsync(mean, mean_d, bytes, hipMemcpyDeviceToHost, s->stream));
+  SGCHK(hipMemcpyAsync(std, std_d, bytes, hipMemcpyDeviceToHost, s->stream));
+  SGCHK(hipStreamSynchronize(s->stream));
+  if (s->stat_cap > kKeepRows) {
+    dfree(s->stat_d);
+    s->stat_cap = 0;
   }
-  dfree(f_d);
-  dfree(mean_d);
-  dfree(std_d);
-  return rc;
+  return LBM_OK;
 }
 
 int lbm_surrogate_pce(lbm_surrogate_t s, int n, const lbm_params *p, const double *pc, int n_pc,
