@@ -28,35 +28,6 @@ static_assert(kParams == 156689, "parameter count");
 constexpr int kOcc = 32;   // occupancy samples per axis
 constexpr int kPool = 8;   // samples per pooled cell and axis
 
-// epilogues of the contraction C[m][n] = sum_k A(m,k) B(k,n)
-enum Epi : int {
-  kEpiF32 = 0,       // C = acc
-  kEpiBiasF32 = 1,   // C = acc + bias[n]
-  kEpiBiasSilu = 2,  // C = z = acc + bias[n], Cb = bf16(silu(z))
-  kEpiDsilu = 3,     // C = d = acc * silu'(Zin[m][n]), Cb = bf16(d)
-};
-
-// A(m,k) = A[z*saz + m*sam + k*sak]; B(k,n) = B[z*sbz + k*sbk + n*sbn];
-// outputs are row-major [M][N] per member z (member stride scz / sbzc)
-struct Gemm {
-  const bf16 *A;
-  long long sam, sak, saz;
-  const bf16 *B;
-  long long sbk, sbn, sbz;
-  int M, N, K, members;
-  int epi;
-  const float *bias;  // [z*bstride + n]
-  long long bstride;
-  float *C;           // f32 out
-  long long scz;
-  bf16 *Cb;           // bf16 out (epilogues 2, 3)
-  long long sbzc;
-  const float *Zin;   // pre-activation (epilogue 3), same layout as C
-  long long szz;
-};
-
-hipError_t launch_gemm(const Gemm &g, hipStream_t st);
-
 // BF16 weights packed in the operand order of the 16x16x32 matrix instruction:
 // per member and layer, output tiles of 16 by chunks of 32 inputs, each a
 // fragment of 64 lanes x 8 values, W[16 t + l % 16][32 c + 8 (l / 16) + i] for
@@ -69,7 +40,16 @@ constexpr int pack_off(int l) {
   for (int i = 0; i < l; ++i) o += kTilesN[i] * kChunksK[i];
   return o;
 }
-constexpr long long kPack = (long long)pack_off(kLayers) * kFrag;
+constexpr long long kPackF = (long long)pack_off(kLayers) * kFrag;
+// then, for layers 1..3, the transposed weights of the backward products:
+// tiles of 16 inputs by chunks of 32 outputs, W[32 c + 8 (l / 16) + i][16 t + l % 16]
+constexpr int kChunksN[kLayers] = {8, 8, 8, 1};
+constexpr int packt_off(int l) {
+  int o = pack_off(kLayers);
+  for (int i = 1; i < l; ++i) o += 16 * kChunksN[i];
+  return o;
+}
+constexpr long long kPack = (long long)packt_off(kLayers) * kFrag;
 hipError_t launch_pack(const float *w, bf16 *wp, int members, hipStream_t st);
 
 // y[z*ycap + b][17] (f32, standardised outputs) of every member for n rows of
@@ -84,23 +64,40 @@ hipError_t launch_col_stats(const double *X, int n, int cols, double *mu, double
 // Y[i][j] = (float)((X[i][j] - mu[j]) / sd[j])
 hipError_t launch_standardise(const double *X, int n, int cols, const double *mu,
                               const double *sd, float *Y, hipStream_t st);
-// Per-member work buffers are [member][cap][width] with cap the batch
-// capacity.  A0[z][b][k] = bf16(X[idx[z*idx_stride + b]][k]) (k < 80),
-// T0[z][b][j] = T[idx[...]][j] (T may be null); idx null means row b
-hipError_t launch_gather(const float *X, const float *T, const int *idx, long long idx_stride,
-                         int members, int bsz, long long cap, bf16 *A0, float *T0,
-                         hipStream_t st);
-// dY = 2 (Y - T) / (bsz * 17) in f32 and bf16; loss[z] = mean (Y - T)^2 (FP64)
-hipError_t launch_loss_grad(const float *Y, const float *T, int members, int bsz, long long cap,
-                            float *dY, bf16 *dYb, double *loss, hipStream_t st);
-// db[z*pstride + n] = sum_b D[z][b][n]
-hipError_t launch_bias_grad(const float *D, int members, int bsz, int N, long long cap, float *db,
-                            long long pstride, hipStream_t st);
-// Adam on all members' flat parameters, then the bf16 copy
-hipError_t launch_adam(float *w, const float *g, float *m, float *v, bf16 *wb, long long count,
-                       float lr, float b1, float b2, float eps, float bc1, float bc2,
-                       hipStream_t st);
-hipError_t launch_to_bf16(const float *w, bf16 *wb, long long count, hipStream_t st);
+// ---- one training batch: forward, loss gradient and backward in one kernel,
+// the weight gradients and Adam in a second ------------------------------------
+// Operands of the weight gradients, per member and layer in fragments over
+// chunks of 32 batch rows: inputs act[b][k] as tiles of 16 k, gradients D[b][n]
+// as tiles of 16 n, lane l holding row 32 c + 8 (l / 16) + i of column
+// 16 t + l % 16; rows beyond the batch are zero.  cb = chunks of the batch.
+constexpr int kTilesK[kLayers] = {5, 16, 16, 16};
+constexpr int kActTiles = 5 + 3 * 16, kGradTiles = 3 * 16 + 2;
+constexpr int act_tile(int l) { return l == 0 ? 0 : 5 + 16 * (l - 1); }
+constexpr int grad_tile(int l) { return 16 * l; }
+// FP32 gradients of the biases' sums: D[b][n] of all layers, 785 columns
+constexpr int kGradCols = 3 * kHidden + kOut;
+constexpr int grad_col(int l) { return l * kHidden; }
+inline int batch_chunks(int bsz) { return (bsz + 31) / 32; }
+
+struct Batch {
+  const float *X, *T;      // standardised rows [n][80], targets [n][17]
+  const int *idx;          // row of batch entry b of member z: idx[z idx_stride + b]
+  long long idx_stride;    //   (null: row b)
+  int bsz, members;
+  const bf16 *wp;
+  bf16 *actp;              // [members][kActTiles][cb][512]
+  bf16 *gradp;             // [members][kGradTiles][cb][512]
+  float *gradf;            // [members][bsz][kGradCols]
+  double *lossp;           // [members][2 cb] squared errors of 16 rows
+};
+struct AdamStep {
+  float lr, b1, b2, eps, bc1, bc2;
+};
+hipError_t launch_fb(const Batch &q, const float *w, hipStream_t st);
+// gradients into g (adam null), or Adam on w, m, v and the packed weights
+// wp; loss[z] = mean squared error of the batch (FP64)
+hipError_t launch_update(const Batch &q, float *g, float *w, float *m, float *v, bf16 *wp,
+                         const AdamStep *adam, double *loss, hipStream_t st);
 // ensemble mean / population std of the de-standardised outputs
 hipError_t launch_ensemble(const float *Y, int members, int n, long long cap, const double *mu,
                            const double *sd, double *mean, double *std, hipStream_t st);

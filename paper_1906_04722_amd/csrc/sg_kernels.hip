@@ -1,8 +1,8 @@
 // sg_kernels.hip -- kernels of the learned entry-pressure surrogate on gfx950:
-// a BF16 matrix-core contraction with fused bias / SiLU / SiLU-derivative
-// epilogues (FP32 accumulation), the loss gradient, bias gradients, Adam on
-// FP32 master weights, standardisation, ensemble statistics and the
-// geometry + occupancy descriptor of a throat.
+// the ensemble's forward in one kernel, a training batch in two (forward, loss
+// gradient and backward; weight gradients and Adam on FP32 master weights), all
+// on BF16 matrix-core products with FP32 accumulation, standardisation,
+// ensemble statistics and the geometry + occupancy descriptor of a throat.
 #include <hip/hip_runtime.h>
 
 #include "geom.h"
@@ -26,152 +26,30 @@ __device__ __forceinline__ float dsilu(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// ---- contraction ----------------------------------------------------------
-// Block tile 64 x 64 of C, four waves of 32 x 32, K staged through LDS 64 at a
-// time.  Each wave issues 2 x 2 v_mfma_f32_16x16x32_bf16 (gfx950) per 32 of
-// K.  Operand layout of that instruction (64 lanes, 8 values each): lane l
-// holds A[l % 16][8 (l / 16) + i] and B[8 (l / 16) + i][l % 16]; the result
-// C[4 (l / 16) + i][l % 16].  Both tiles sit in LDS k-contiguous ([row][k],
-// rows padded to 72 bf16 = 144 bytes), so every operand is one 16-byte LDS
-// read.  Staging moves 16 bytes (8 bf16) per load where the operand allows:
-// along k when it is k-contiguous (X W^T, D W), along the rows when it is
-// row-contiguous (the weight gradients D^T A), scattering the 8 values into
-// their k-contiguous LDS rows; other shapes fall back to one value per load.
-constexpr int BM = 64, BN = 64, BK = 64, LDK = BK + 8;
+// Products are v_mfma_f32_16x16x32_bf16 (gfx950).  Operand layout of that
+// instruction (64 lanes, 8 values each): lane l holds A[l % 16][8 (l / 16) + i]
+// and B[8 (l / 16) + i][l % 16]; the result C[4 (l / 16) + i][l % 16].
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-
-// stage rows r0 .. r0+63 and k0 .. k0+63 of X(row, k) = X[row*srow + k*sk]
-// (nrow rows, K columns) into S[row - r0][k - k0], zero outside
-__device__ __forceinline__ void stage(bf16 (&S)[64][LDK], const bf16 *X, long long srow,
-                                      long long sk, int nrow, int K, int r0, int k0, int tid) {
-  const bool aligned = ((uintptr_t)X & 15u) == 0;
-  if (sk == 1 && aligned && (srow & 7) == 0 && (K & 7) == 0) {
-    // k-contiguous: 8 consecutive k of one row per load (K % 8 == 0: a group
-    // of 8 lies wholly inside or outside the matrix)
-#pragma unroll
-    for (int t = 0; t < (64 * BK / 8) / 256; ++t) {
-      const int v = tid + 256 * t, r = v / (BK / 8), c = (v % (BK / 8)) * 8;
-      const int row = r0 + r, k = k0 + c;
-      uint4 q = make_uint4(0u, 0u, 0u, 0u);
-      if (row < nrow && k < K) q = *(const uint4 *)(X + (long long)row * srow + k);
-      *(uint4 *)&S[r][c] = q;
-    }
-  } else if (srow == 1 && aligned && (sk & 7) == 0 && (nrow & 7) == 0) {
-    // row-contiguous: 8 consecutive rows of one k per load, scattered into
-    // the k-contiguous tile (nrow % 8 == 0: a group lies wholly inside or out)
-#pragma unroll
-    for (int t = 0; t < (64 * BK / 8) / 256; ++t) {
-      const int v = tid + 256 * t, c = v / (64 / 8), r = (v % (64 / 8)) * 8;
-      const int row = r0 + r, k = k0 + c;
-      uint4 q = make_uint4(0u, 0u, 0u, 0u);
-      if (row < nrow && k < K) q = *(const uint4 *)(X + (long long)k * sk + row);
-      const bf16 *e = (const bf16 *)&q;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) S[r + i][c] = e[i];
-    }
-  } else {
-    // one value per load; consecutive threads walk the contiguous index
-    const bool kc = sk == 1;
-#pragma unroll 4
-    for (int t = 0; t < (64 * BK) / 256; ++t) {
-      const int idx = tid + 256 * t;
-      const int r = kc ? idx / BK : idx % 64;
-      const int c = kc ? idx % BK : idx / 64;
-      const int row = r0 + r, k = k0 + c;
-      S[r][c] = (row < nrow && k < K) ? X[(long long)row * srow + (long long)k * sk] : (bf16)0;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void k_gemm(Gemm g) {
-  __shared__ __attribute__((aligned(16))) bf16 As[BM][LDK];
-  __shared__ __attribute__((aligned(16))) bf16 Bs[BN][LDK];
-  const int z = blockIdx.z;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
-  const bf16 *A = g.A + (long long)z * g.saz;
-  const bf16 *B = g.B + (long long)z * g.sbz;
-  v4f acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-  for (int k0 = 0; k0 < g.K; k0 += BK) {
-    // A(m, k) rows m; B(k, n) staged as rows n
-    stage(As, A, g.sam, g.sak, g.M, g.K, m0, k0, tid);
-    stage(Bs, B, g.sbn, g.sbk, g.N, g.K, n0, k0, tid);
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 32) {
-      v8bf a[2], b[2];
-      const int q = kk + 8 * (lane >> 4);
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = *(const v8bf *)&As[wm + 16 * i + (lane & 15)][q];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = *(const v8bf *)&Bs[wn + 16 * j + (lane & 15)][q];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-        const int n = n0 + wn + 16 * j + (lane & 15);
-        if (m >= g.M || n >= g.N) continue;
-        const long long o = (long long)m * g.N + n;
-        float s = acc[i][j][r];
-        switch (g.epi) {
-          case kEpiF32:
-            g.C[(long long)z * g.scz + o] = s;
-            break;
-          case kEpiBiasF32:
-            g.C[(long long)z * g.scz + o] = s + g.bias[(long long)z * g.bstride + n];
-            break;
-          case kEpiBiasSilu: {
-            const float zz = s + g.bias[(long long)z * g.bstride + n];
-            g.C[(long long)z * g.scz + o] = zz;
-            g.Cb[(long long)z * g.sbzc + o] = to_bf16(silu(zz));
-            break;
-          }
-          default: {  // kEpiDsilu
-            const float d = s * dsilu(g.Zin[(long long)z * g.szz + o]);
-            g.C[(long long)z * g.scz + o] = d;
-            g.Cb[(long long)z * g.sbzc + o] = to_bf16(d);
-            break;
-          }
-        }
-      }
-}
-
-hipError_t launch_gemm(const Gemm &g, hipStream_t st) {
-  if (g.M <= 0 || g.N <= 0 || g.members <= 0) return hipSuccess;
-  dim3 grid((unsigned)((g.N + BN - 1) / BN), (unsigned)((g.M + BM - 1) / BM), (unsigned)g.members);
-  hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, st, g);
-  return hipGetLastError();
-}
 
 // ---- ensemble forward in one kernel --------------------------------------------
 __global__ void k_pack(const float *w, bf16 *wp, int members) {
   const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (i >= members * kPack) return;
   const int z = (int)(i / kPack), r = (int)(i % kPack);
-  int f = r / kFrag, l = 0;
-  while (l + 1 < kLayers && f >= pack_off(l + 1)) ++l;
-  f -= pack_off(l);
+  int f = r / kFrag, l = 0, n, k;
   const int lane = (r % kFrag) / 8, j = r % 8;
-  const int n = 16 * (f / kChunksK[l]) + lane % 16;
-  const int k = 32 * (f % kChunksK[l]) + 8 * (lane / 16) + j;
+  if (f < pack_off(kLayers)) {
+    while (l + 1 < kLayers && f >= pack_off(l + 1)) ++l;
+    f -= pack_off(l);
+    n = 16 * (f / kChunksK[l]) + lane % 16;
+    k = 32 * (f % kChunksK[l]) + 8 * (lane / 16) + j;
+  } else {
+    l = 1;
+    while (l + 1 < kLayers && f >= packt_off(l + 1)) ++l;
+    f -= packt_off(l);
+    k = 16 * (f / kChunksN[l]) + lane % 16;
+    n = 32 * (f % kChunksN[l]) + 8 * (lane / 16) + j;
+  }
   const bool in = n < kWidth[l + 1] && k < kWidth[l];
   wp[i] = in ? to_bf16(w[(long long)z * kParams + w_off(l) + (long long)n * kWidth[l] + k])
              : (bf16)0;
@@ -212,6 +90,31 @@ __device__ __forceinline__ void layer_acc(const bf16 *wp, const bf16 *in, int ti
 #pragma unroll
       for (int j = 0; j < MT; ++j)
         acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b[j], acc[t][j], 0, 0, 0);
+  }
+}
+
+// The same in two halves for workgroups of one row tile: the weights of a
+// layer go to registers while the layer before it is still in its barriers,
+// which hides their trip from the L2.
+template <int OFF, int TPW, int C>
+__device__ __forceinline__ void frag_load(const bf16 *wp, int tile0, int lane, v8bf (&a)[TPW][C]) {
+#pragma unroll
+  for (int t = 0; t < TPW; ++t)
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      a[t][c] = *(const v8bf *)(wp + ((long long)(OFF + (tile0 + t) * C + c) * 64 + lane) * 8);
+}
+template <int TPW, int C, int LD>
+__device__ __forceinline__ void frag_mul(const v8bf (&a)[TPW][C], const bf16 *in, int lane,
+                                         v4f (&acc)[TPW][1]) {
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) acc[t][0] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const v8bf b = *(const v8bf *)(in + (lane & 15) * LD + 32 * c + 8 * (lane >> 4));
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+      acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][c], b, acc[t][0], 0, 0, 0);
   }
 }
 
@@ -277,16 +180,30 @@ __global__ __launch_bounds__(64 * NW) void k_mlp(const double *X, const double *
   for (int z = blockIdx.y * per; z < (int)(blockIdx.y + 1) * per; ++z) {
     const bf16 *wz = wp + z * kPack;
     const float *pz = w + z * kParams;
-    v4f acc[TPW][MT];
-    layer_acc<0, MT, TPW, LDX>(wz, x0, wv * TPW, lane, acc);
-    layer_silu<0, MT, TPW>(pz, wv * TPW, lane, acc, act);
-    layer_acc<1, MT, TPW, LDA>(wz, act, wv * TPW, lane, acc);
-    layer_silu<1, MT, TPW>(pz, wv * TPW, lane, acc, act);
-    layer_acc<2, MT, TPW, LDA>(wz, act, wv * TPW, lane, acc);
-    layer_silu<2, MT, TPW>(pz, wv * TPW, lane, acc, act);
+    v4f acc[TPW][MT], out[1][MT];
+    if constexpr (MT == 1) {
+      v8bf a0[TPW][kChunksK[0]], a1[TPW][kChunksK[1]], a2[TPW][kChunksK[2]], a3[1][kChunksK[3]];
+      frag_load<pack_off(0)>(wz, wv * TPW, lane, a0);
+      frag_load<pack_off(1)>(wz, wv * TPW, lane, a1);
+      frag_mul<TPW, kChunksK[0], LDX>(a0, x0, lane, acc);
+      layer_silu<0, MT, TPW>(pz, wv * TPW, lane, acc, act);
+      frag_load<pack_off(2)>(wz, wv * TPW, lane, a2);
+      frag_mul<TPW, kChunksK[1], LDA>(a1, act, lane, acc);
+      layer_silu<1, MT, TPW>(pz, wv * TPW, lane, acc, act);
+      if (wv < kTilesN[3]) frag_load<pack_off(3)>(wz, wv, lane, a3);
+      frag_mul<TPW, kChunksK[2], LDA>(a2, act, lane, acc);
+      layer_silu<2, MT, TPW>(pz, wv * TPW, lane, acc, act);
+      if (wv < kTilesN[3]) frag_mul<1, kChunksK[3], LDA>(a3, act, lane, out);
+    } else {
+      layer_acc<0, MT, TPW, LDX>(wz, x0, wv * TPW, lane, acc);
+      layer_silu<0, MT, TPW>(pz, wv * TPW, lane, acc, act);
+      layer_acc<1, MT, TPW, LDA>(wz, act, wv * TPW, lane, acc);
+      layer_silu<1, MT, TPW>(pz, wv * TPW, lane, acc, act);
+      layer_acc<2, MT, TPW, LDA>(wz, act, wv * TPW, lane, acc);
+      layer_silu<2, MT, TPW>(pz, wv * TPW, lane, acc, act);
+      if (wv < kTilesN[3]) layer_acc<3, MT, 1, LDA>(wz, act, wv, lane, out);
+    }
     if (wv < kTilesN[3]) {
-      v4f out[1][MT];
-      layer_acc<3, MT, 1, LDA>(wz, act, wv, lane, out);
 #pragma unroll
       for (int j = 0; j < MT; ++j)
 #pragma unroll
@@ -375,106 +292,341 @@ hipError_t launch_standardise(const double *X, int n, int cols, const double *mu
   return hipGetLastError();
 }
 
-__global__ void k_gather(const float *X, const float *T, const int *idx, long long idx_stride,
-                         int members, int bsz, long long cap, bf16 *A0, float *T0) {
-  const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  const long long per = (long long)bsz * (kFeat + kOut);
-  if (i >= per * members) return;
-  const int z = (int)(i / per);
-  const long long r = i % per;
-  const int b = (int)(r / (kFeat + kOut)), c = (int)(r % (kFeat + kOut));
-  const long long src = idx ? idx[z * idx_stride + b] : b;
-  if (c < kFeat)
-    A0[(long long)z * cap * kFeat + (long long)b * kFeat + c] = to_bf16(X[src * kFeat + c]);
-  else if (T)
-    T0[(long long)z * cap * kOut + (long long)b * kOut + (c - kFeat)] = T[src * kOut + (c - kFeat)];
+// ---- training -----------------------------------------------------------------
+// Forward, loss gradient and backward of 16 batch rows of one member: nothing
+// crosses rows, so a workgroup carries its rows down and up the four layers
+// without leaving the CU.  The pre-activations stay in registers (the backward
+// products leave d act in the lanes that hold the same z), activations and
+// gradients in LDS; what the weight gradients need goes out in their operand
+// layout.  The chain of seven dependent products bounds it, not their rate (5
+// members x 64 rows are 20 workgroups): eight wavefronts of two tiles each share
+// a product, and the weights of a later product and the biases are loaded
+// before the one that is being computed.  5 members, batches of 64 rows on an
+// MI355X: 18.8 us a batch (23 without the early loads) where a kernel per
+// product, activation and bias gradient took eighteen launches and, with the
+// download of the loss, 286 us (now 52 for both kernels and the host's share).
+constexpr int kFbWaves = 8, kFbTiles = 16 / kFbWaves;
+
+// four values of column tile `tile` (columns 16 tile + 4 (lane / 16) + i) of
+// batch row b into their fragments
+__device__ __forceinline__ void put_frag(bf16 *frags, int tile, int cb, int b, int lane,
+                                         const bf16 (&e)[4]) {
+  bf16 *f = frags + ((long long)tile * cb + b / 32) * kFrag + (16 * ((b % 32) / 8)) * 8 + b % 8;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) f[(4 * (lane >> 4) + i) * 8] = e[i];
 }
 
-hipError_t launch_gather(const float *X, const float *T, const int *idx, long long idx_stride,
-                         int members, int bsz, long long cap, bf16 *A0, float *T0,
-                         hipStream_t st) {
-  const long long total = (long long)members * bsz * (kFeat + kOut);
-  if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, X, T, idx,
-                     idx_stride, members, bsz, cap, A0, T0);
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_loss_grad(const float *Y, const float *T, int bsz,
-                                                   long long cap, float *dY, bf16 *dYb,
-                                                   double *loss) {
-  __shared__ double sh[256];
-  const int z = blockIdx.x;
-  const long long base = (long long)z * cap * kOut;
-  const int cnt = bsz * kOut;
-  const float sc = 2.0f / (float)cnt;
-  double s = 0;
-  for (int i = threadIdx.x; i < cnt; i += 256) {
-    const float d = Y[base + i] - T[base + i];
-    const float gd = sc * d;
-    dY[base + i] = gd;
-    dYb[base + i] = to_bf16(gd);
-    s += (double)d * (double)d;
+template <int L>
+__device__ __forceinline__ void fb_forward(const v4f (&acc)[kFbTiles][1],
+                                           const float (&bias)[kFbTiles][4], bf16 *out,
+                                           bf16 *actp, int cb, int row, bool live, int wv,
+                                           int lane, float (&z)[kFbTiles][4]) {
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kFbTiles; ++t) {
+    const int tile = wv * kFbTiles + t, n = 16 * tile + 4 * (lane >> 4);
+    bf16 e[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float zz = acc[t][0][i] + bias[t][i];
+      z[t][i] = zz;
+      e[i] = live ? to_bf16(silu(zz)) : (bf16)0;
+    }
+    uint2 w2;
+    w2.x = (uint32_t)e[0] | (uint32_t)e[1] << 16;
+    w2.y = (uint32_t)e[2] | (uint32_t)e[3] << 16;
+    *(uint2 *)(out + (lane & 15) * LDA + n) = w2;
+    put_frag(actp, act_tile(L + 1) + tile, cb, row, lane, e);
   }
-  const double tot = block_sum<256>(s, sh);
-  if (threadIdx.x == 0) loss[z] = tot / cnt;
+  __syncthreads();
 }
 
-hipError_t launch_loss_grad(const float *Y, const float *T, int members, int bsz, long long cap,
-                            float *dY, bf16 *dYb, double *loss, hipStream_t st) {
-  hipLaunchKernelGGL(k_loss_grad, dim3((unsigned)members), dim3(256), 0, st, Y, T, bsz, cap, dY,
-                     dYb, loss);
+// gradients of layer L - 1's pre-activations: d act of layer L's input (acc, in
+// the lanes that hold the same z) times silu' of z
+template <int L>
+__device__ __forceinline__ void fb_backward(const v4f (&acc)[kFbTiles][1], bf16 *out, bf16 *gradp,
+                                            float *gradf, int cb, int row, bool live, int wv,
+                                            int lane, const float (&z)[kFbTiles][4]) {
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kFbTiles; ++t) {
+    const int tile = wv * kFbTiles + t, n = 16 * tile + 4 * (lane >> 4);
+    bf16 e[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float d = acc[t][0][i] * dsilu(z[t][i]);
+      e[i] = live ? to_bf16(d) : (bf16)0;
+      if (live) gradf[(long long)row * kGradCols + grad_col(L - 1) + n + i] = d;
+    }
+    if (L > 1) {
+      uint2 w2;
+      w2.x = (uint32_t)e[0] | (uint32_t)e[1] << 16;
+      w2.y = (uint32_t)e[2] | (uint32_t)e[3] << 16;
+      *(uint2 *)(out + (lane & 15) * LDA + n) = w2;
+    }
+    put_frag(gradp, grad_tile(L - 1) + tile, cb, row, lane, e);
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(64 * kFbWaves) void k_fb(Batch q, const float *w) {
+  __shared__ __attribute__((aligned(16))) bf16 x0[16 * LDX];
+  __shared__ __attribute__((aligned(16))) bf16 act[16 * LDA];
+  __shared__ __attribute__((aligned(16))) bf16 dy[16 * (32 + 8)];
+  __shared__ double sq[32];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int zm = blockIdx.y, cb = gridDim.x / 2;
+  const int row = blockIdx.x * 16 + (lane & 15);  // of this lane's results
+  const bool live = row < q.bsz;
+  const bf16 *wz = q.wp + zm * kPack;
+  const float *pz = w + zm * kParams;
+  bf16 *actp = q.actp + (long long)zm * kActTiles * cb * kFrag;
+  bf16 *gradp = q.gradp + (long long)zm * kGradTiles * cb * kFrag;
+  float *gradf = q.gradf + (long long)zm * q.bsz * kGradCols;
+  const int t0 = wv * kFbTiles;
+  v8bf a0[kFbTiles][kChunksK[0]], a1[kFbTiles][kChunksK[1]], a2[kFbTiles][kChunksK[2]];
+  v8bf a3[1][kChunksK[3]], r3[kFbTiles][kChunksN[3]], r2[kFbTiles][kChunksN[2]],
+      r1[kFbTiles][kChunksN[1]];
+  v4f acc[kFbTiles][1];
+  frag_load<pack_off(0)>(wz, t0, lane, a0);
+  frag_load<pack_off(1)>(wz, t0, lane, a1);
+  float bias[3][kFbTiles][4];
+#pragma unroll
+  for (int l = 0; l < 3; ++l)
+#pragma unroll
+    for (int t = 0; t < kFbTiles; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        bias[l][t][i] = pz[b_off(l) + 16 * (t0 + t) + 4 * (lane >> 4) + i];
+  for (int e = tid; e < 16 * 32 * kChunksK[0]; e += 64 * kFbWaves) {
+    const int r = e / (32 * kChunksK[0]), c = e % (32 * kChunksK[0]), b = blockIdx.x * 16 + r;
+    bf16 v = 0;
+    if (c < kFeat && b < q.bsz) {
+      const long long src = q.idx ? q.idx[zm * q.idx_stride + b] : b;
+      v = to_bf16(q.X[src * kFeat + c]);
+    }
+    x0[r * LDX + c] = v;
+    if (c < kFeat)
+      actp[((long long)(c / 16) * cb + b / 32) * kFrag + (c % 16 + 16 * ((b % 32) / 8)) * 8 +
+           b % 8] = v;
+  }
+  for (int e = tid; e < 16 * (32 + 8); e += 64 * kFbWaves) dy[e] = 0;
+  __syncthreads();
+  float z0[kFbTiles][4], z1[kFbTiles][4], z2[kFbTiles][4];
+  frag_mul<kFbTiles, kChunksK[0], LDX>(a0, x0, lane, acc);
+  fb_forward<0>(acc, bias[0], act, actp, cb, row, live, wv, lane, z0);
+  frag_load<pack_off(2)>(wz, t0, lane, a2);
+  frag_mul<kFbTiles, kChunksK[1], LDA>(a1, act, lane, acc);
+  fb_forward<1>(acc, bias[1], act, actp, cb, row, live, wv, lane, z1);
+  if (wv < kTilesN[3]) frag_load<pack_off(3)>(wz, wv, lane, a3);
+  frag_load<packt_off(3)>(wz, t0, lane, r3);
+  frag_mul<kFbTiles, kChunksK[2], LDA>(a2, act, lane, acc);
+  fb_forward<2>(acc, bias[2], act, actp, cb, row, live, wv, lane, z2);
+  frag_load<packt_off(2)>(wz, t0, lane, r2);
+  if (wv < kTilesN[3]) {
+    v4f out[1][1];
+    frag_mul<1, kChunksK[3], LDA>(a3, act, lane, out);
+    const float sc = 2.0f / (float)(q.bsz * kOut);
+    const long long src = live ? (q.idx ? q.idx[zm * q.idx_stride + row] : row) : 0;
+    double s = 0;
+    bf16 e[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int o = 16 * wv + 4 * (lane >> 4) + i;
+      e[i] = 0;
+      if (o < kOut && live) {
+        const float y = out[0][0][i] + pz[b_off(3) + o];
+        const float d = y - q.T[src * kOut + o];
+        const float gd = sc * d;
+        gradf[(long long)row * kGradCols + grad_col(3) + o] = gd;
+        e[i] = to_bf16(gd);
+        dy[(lane & 15) * (32 + 8) + o] = e[i];
+        s += (double)d * (double)d;
+      }
+    }
+    put_frag(gradp, grad_tile(3) + wv, cb, row, lane, e);
+    // squared errors in a fixed order: lanes 16 apart hold the same row
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0) sq[wv] = s;
+  }
+  __syncthreads();
+  if (tid == 0) q.lossp[zm * gridDim.x + blockIdx.x] = sq[0] + sq[1];
+  frag_mul<kFbTiles, kChunksN[3], 32 + 8>(r3, dy, lane, acc);
+  fb_backward<3>(acc, act, gradp, gradf, cb, row, live, wv, lane, z2);
+  frag_load<packt_off(1)>(wz, t0, lane, r1);
+  frag_mul<kFbTiles, kChunksN[2], LDA>(r2, act, lane, acc);
+  fb_backward<2>(acc, act, gradp, gradf, cb, row, live, wv, lane, z1);
+  frag_mul<kFbTiles, kChunksN[1], LDA>(r1, act, lane, acc);
+  fb_backward<1>(acc, act, gradp, gradf, cb, row, live, wv, lane, z0);
+}
+
+hipError_t launch_fb(const Batch &q, const float *w, hipStream_t st) {
+  const unsigned tiles = 2u * (unsigned)batch_chunks(q.bsz);
+  hipLaunchKernelGGL(k_fb, dim3(tiles, (unsigned)q.members), dim3(64 * kFbWaves), 0, st, q, w);
   return hipGetLastError();
 }
 
-__global__ void k_bias_grad(const float *D, int bsz, int N, long long cap, float *db,
-                            long long pstride) {
-  const int z = blockIdx.y;
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  const float *d = D + (long long)z * cap * N + n;
+// One wavefront computes 32 inputs x 32 outputs of a layer's dW = D^T act over
+// the whole batch and, while they are in its registers, takes the Adam step on
+// those weights and refreshes their packed copies: gradients never go to
+// memory.  The last workgroups sum the bias gradients (in batch order, so one
+// chain per output) and the loss.  Bound by latency at a batch of 64: 5
+// members' weights and moments are 9 MB read and written in 16.7 us (21.8 with
+// their loads behind the products).
+constexpr int wave_tiles(int l) { return ((kTilesK[l] + 1) / 2) * ((kTilesN[l] + 1) / 2); }
+constexpr int kUpdWaves = wave_tiles(0) + wave_tiles(1) + wave_tiles(2) + wave_tiles(3);
+static_assert(kUpdWaves % 4 == 0, "whole workgroups of four wavefronts");
+constexpr int kBiasBlocks = 4;
+
+// Adam on one weight: gradient g, first and second moments m, v
+__device__ __forceinline__ float adam_step(const AdamStep &a, float g, float w, float &m,
+                                           float &v) {
+  // the two moments with one rounding of their last product and sum each,
+  // written out so that every caller rounds alike
+  m = fmaf(1.0f - a.b1, g, a.b1 * m);
+  v = fmaf(g, (1.0f - a.b2) * g, a.b2 * v);
+  return w - a.lr * (m / a.bc1) / (sqrtf(v / a.bc2) + a.eps);
+}
+
+template <int L, bool ADAM>
+__device__ __forceinline__ void update_tile(const Batch &q, int cb, int zm, int tile, int lane,
+                                            float *g, float *w, float *m, float *v, bf16 *wp,
+                                            const AdamStep &adam) {
+  constexpr int KT = kTilesK[L], NT = kTilesN[L], K = kWidth[L], N = kWidth[L + 1];
+  const int kt = 2 * (tile / ((NT + 1) / 2)), nt = 2 * (tile % ((NT + 1) / 2));
+  const bf16 *A = q.actp + ((long long)zm * kActTiles + act_tile(L) + kt) * cb * kFrag + lane * 8;
+  const bf16 *B = q.gradp + ((long long)zm * kGradTiles + grad_tile(L) + nt) * cb * kFrag +
+                  lane * 8;
+  // (an odd last tile of inputs computes its partner on itself, unused)
+  const long long ka = kt + 1 < KT ? (long long)cb * kFrag : 0;
+  const long long kb = (long long)cb * kFrag;
+  // weights and moments of this wavefront's 2 x 2 tiles, all in flight before
+  // the products: four inputs of one output per lane and tile
+  float w4[2][2][4], m4[2][2][4], v4[2][2][4];
+  long long o[2][2];
+  bool in[2][2];
+#pragma unroll
+  for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj) {
+      const int k = 16 * (kt + ti) + 4 * (lane >> 4), n = 16 * (nt + tj) + (lane & 15);
+      in[ti][tj] = kt + ti < KT && n < N;
+      o[ti][tj] = (long long)zm * kParams + w_off(L) + (in[ti][tj] ? (long long)n * K + k : 0);
+      if constexpr (ADAM)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          w4[ti][tj][i] = w[o[ti][tj] + i];
+          m4[ti][tj][i] = m[o[ti][tj] + i];
+          v4[ti][tj][i] = v[o[ti][tj] + i];
+        }
+    }
+  v4f acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < cb; ++c) {
+    const v8bf a0 = *(const v8bf *)(A + (long long)c * kFrag);
+    const v8bf a1 = *(const v8bf *)(A + ka + (long long)c * kFrag);
+    const v8bf b0 = *(const v8bf *)(B + (long long)c * kFrag);
+    const v8bf b1 = *(const v8bf *)(B + kb + (long long)c * kFrag);
+    acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b0, acc[0][0], 0, 0, 0);
+    acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b1, acc[0][1], 0, 0, 0);
+    acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b0, acc[1][0], 0, 0, 0);
+    acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, acc[1][1], 0, 0, 0);
+  }
+#pragma unroll
+  for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj) {
+      if (!in[ti][tj]) continue;
+      const int k = 16 * (kt + ti) + 4 * (lane >> 4), n = 16 * (nt + tj) + (lane & 15);
+      const long long at = o[ti][tj];
+      if constexpr (!ADAM) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g[at + i] = acc[ti][tj][i];
+      } else {
+        bf16 e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float x = adam_step(adam, acc[ti][tj][i], w4[ti][tj][i], m4[ti][tj][i],
+                                    v4[ti][tj][i]);
+          w[at + i] = x;
+          m[at + i] = m4[ti][tj][i];
+          v[at + i] = v4[ti][tj][i];
+          e[i] = to_bf16(x);
+        }
+        // four inputs in a row: one 8-byte store in the forward fragments, four
+        // places in the transposed ones
+        bf16 *p = wp + zm * kPack;
+        uint2 w2;
+        w2.x = (uint32_t)e[0] | (uint32_t)e[1] << 16;
+        w2.y = (uint32_t)e[2] | (uint32_t)e[3] << 16;
+        *(uint2 *)(p + (long long)(pack_off(L) + (n / 16) * kChunksK[L] + k / 32) * kFrag +
+                   (n % 16 + 16 * ((k % 32) / 8)) * 8 + k % 8) = w2;
+        if constexpr (L > 0) {
+          bf16 *pt = p + (long long)(packt_off(L) + (k / 16) * kChunksN[L] + n / 32) * kFrag +
+                     (k % 16 + 16 * ((n % 32) / 8)) * 8 + n % 8;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pt[8 * i] = e[i];
+        }
+      }
+    }
+}
+
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_update(Batch q, int cb, float *g, float *w, float *m,
+                                                float *v, bf16 *wp, AdamStep adam, double *loss) {
+  const int zm = blockIdx.y, lane = threadIdx.x & 63;
+  int t = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+  if (t < kUpdWaves) {
+    if (t < wave_tiles(0)) return update_tile<0, ADAM>(q, cb, zm, t, lane, g, w, m, v, wp, adam);
+    t -= wave_tiles(0);
+    if (t < wave_tiles(1)) return update_tile<1, ADAM>(q, cb, zm, t, lane, g, w, m, v, wp, adam);
+    t -= wave_tiles(1);
+    if (t < wave_tiles(2)) return update_tile<2, ADAM>(q, cb, zm, t, lane, g, w, m, v, wp, adam);
+    t -= wave_tiles(2);
+    return update_tile<3, ADAM>(q, cb, zm, t, lane, g, w, m, v, wp, adam);
+  }
+  // biases: one layer per workgroup, one output per thread
+  const int l = (int)blockIdx.x - kUpdWaves / 4, n = threadIdx.x;
+  if (l == 3 && n == 255) {
+    double s = 0;
+    for (int i = 0; i < 2 * cb; ++i) s += q.lossp[zm * 2 * cb + i];
+    loss[zm] = s / (q.bsz * kOut);
+  }
+  if (n >= kWidth[l + 1]) return;
+  const float *d = q.gradf + (long long)zm * q.bsz * kGradCols + grad_col(l) + n;
   float s = 0.f;
-  for (int b = 0; b < bsz; ++b) s += d[(long long)b * N];
-  db[(long long)z * pstride + n] = s;
+  int b = 0;
+  for (; b + 16 <= q.bsz; b += 16) {  // loads in flight together, added in order
+    float e[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) e[i] = d[(long long)(b + i) * kGradCols];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += e[i];
+  }
+  for (; b < q.bsz; ++b) s += d[(long long)b * kGradCols];
+  const long long o = (long long)zm * kParams + b_off(l) + n;
+  if constexpr (ADAM) {
+    float mi = m[o], vi = v[o];
+    w[o] = adam_step(adam, s, w[o], mi, vi);
+    m[o] = mi;
+    v[o] = vi;
+  } else {
+    g[o] = s;
+  }
 }
 
-hipError_t launch_bias_grad(const float *D, int members, int bsz, int N, long long cap, float *db,
-                            long long pstride, hipStream_t st) {
-  hipLaunchKernelGGL(k_bias_grad, dim3((unsigned)((N + 255) / 256), (unsigned)members), dim3(256),
-                     0, st, D, bsz, N, cap, db, pstride);
-  return hipGetLastError();
-}
-
-__global__ void k_adam(float *w, const float *g, float *m, float *v, bf16 *wb, long long count,
-                       float lr, float b1, float b2, float eps, float bc1, float bc2) {
-  const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float wi = w[i] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
-  w[i] = wi;
-  wb[i] = to_bf16(wi);
-}
-
-hipError_t launch_adam(float *w, const float *g, float *m, float *v, bf16 *wb, long long count,
-                       float lr, float b1, float b2, float eps, float bc1, float bc2,
-                       hipStream_t st) {
-  hipLaunchKernelGGL(k_adam, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, w, g, m, v,
-                     wb, count, lr, b1, b2, eps, bc1, bc2);
-  return hipGetLastError();
-}
-
-__global__ void k_to_bf16(const float *w, bf16 *wb, long long count) {
-  const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (i < count) wb[i] = to_bf16(w[i]);
-}
-
-hipError_t launch_to_bf16(const float *w, bf16 *wb, long long count, hipStream_t st) {
-  hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, w, wb,
-                     count);
+hipError_t launch_update(const Batch &q, float *g, float *w, float *m, float *v, bf16 *wp,
+                         const AdamStep *adam, double *loss, hipStream_t st) {
+  const dim3 grid(kUpdWaves / 4 + kBiasBlocks, (unsigned)q.members);
+  const int cb = batch_chunks(q.bsz);
+  if (adam)
+    hipLaunchKernelGGL(k_update<true>, grid, dim3(256), 0, st, q, cb, g, w, m, v, wp, *adam, loss);
+  else
+    hipLaunchKernelGGL(k_update<false>, grid, dim3(256), 0, st, q, cb, g, w, m, v, wp, AdamStep{},
+                       loss);
   return hipGetLastError();
 }
 

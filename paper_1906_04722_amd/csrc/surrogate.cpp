@@ -37,7 +37,6 @@ static_assert(sg::kFeat == LBM_SG_NFEAT && sg::kOut == LBM_SG_NOUT, "widths");
 namespace {
 
 constexpr long long P = sg::kParams;
-constexpr int H = sg::kHidden;
 constexpr int kPinRows = 512;     // rows of a call that go through host-visible buffers
 constexpr int kChunkRows = 32768; // rows of one forward launch
 constexpr int kKeepRows = 131072; // rows whose statistics buffer a handle keeps
@@ -77,21 +76,16 @@ struct lbm_surrogate {
   int members = 0;
   hipStream_t stream = nullptr;
   bool own_stream = false;
-  float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;  // [members][P]
-  sg::bf16 *wb = nullptr;
-  sg::bf16 *wp = nullptr;  // packed weights of the one-kernel forward [members][kPack]
+  float *w = nullptr, *m = nullptr, *v = nullptr;  // [members][P]
+  sg::bf16 *wp = nullptr;  // packed BF16 weights [members][kPack]
   long long adam_t = 0;
   bool has_stats = false;
   double *stats_d = nullptr;  // xmu[80] xsd[80] tmu[17] tsd[17]
-  double *loss_d = nullptr;   // [members]
-  // work buffers of batch capacity cap
+  // work buffers of a training batch of up to cap rows
   int cap = 0;
-  sg::bf16 *act[4] = {};  // bf16 layer inputs [members][cap][width]
-  float *zpre[3] = {};    // hidden pre-activations [members][cap][256]
-  float *dz[3] = {};      // their gradients, f32 and bf16
-  sg::bf16 *dzb[3] = {};
-  float *y = nullptr, *t = nullptr, *dy = nullptr;  // [members][cap][17]
-  sg::bf16 *dyb = nullptr;
+  sg::bf16 *actp = nullptr, *gradp = nullptr;
+  float *gradf = nullptr;
+  double *lossp = nullptr;
   hipEvent_t ev[2] = {};
   // inference: no standardisation (80 zeros, 80 ones), rows on the device, the
   // members' outputs, ensemble statistics, the non-finite flag; host-visible
@@ -109,14 +103,10 @@ struct lbm_surrogate {
   double *tsd() { return stats_d + 177; }
 
   void free_work() {
-    for (auto &p : act) dfree(p);
-    for (auto &p : zpre) dfree(p);
-    for (auto &p : dz) dfree(p);
-    for (auto &p : dzb) dfree(p);
-    dfree(y);
-    dfree(t);
-    dfree(dy);
-    dfree(dyb);
+    dfree(actp);
+    dfree(gradp);
+    dfree(gradf);
+    dfree(lossp);
     cap = 0;
   }
 
@@ -127,20 +117,18 @@ struct lbm_surrogate {
       return LBM_EHIP;
     }
     free_work();
-    const size_t M = (size_t)members, c = (size_t)need;
-    SGTRY(dalloc(&act[0], M * c * sg::kFeat));
-    for (int l = 1; l < 4; ++l) SGTRY(dalloc(&act[l], M * c * H));
-    for (int l = 0; l < 3; ++l) {
-      SGTRY(dalloc(&zpre[l], M * c * H));
-      SGTRY(dalloc(&dz[l], M * c * H));
-      SGTRY(dalloc(&dzb[l], M * c * H));
-    }
-    SGTRY(dalloc(&y, M * c * sg::kOut));
-    SGTRY(dalloc(&t, M * c * sg::kOut));
-    SGTRY(dalloc(&dy, M * c * sg::kOut));
-    SGTRY(dalloc(&dyb, M * c * sg::kOut));
+    const size_t M = (size_t)members, cb = (size_t)sg::batch_chunks(need);
+    SGTRY(dalloc(&actp, M * sg::kActTiles * cb * sg::kFrag));
+    SGTRY(dalloc(&gradp, M * sg::kGradTiles * cb * sg::kFrag));
+    SGTRY(dalloc(&gradf, M * (size_t)need * sg::kGradCols));
+    SGTRY(dalloc(&lossp, M * 2 * cb));
     cap = need;
     return LBM_OK;
+  }
+
+  // one batch on the device: forward, loss and backward into the buffers
+  sg::Batch batch(const float *X, const float *T, const int *idx, long long stride, int bsz) const {
+    return sg::Batch{X, T, idx, stride, bsz, members, wp, actp, gradp, gradf, lossp};
   }
 
   // inference buffers for chunks of `rows` rows, and statistics of `n` rows
@@ -177,104 +165,10 @@ struct lbm_surrogate {
     dfree(w);
     dfree(m);
     dfree(v);
-    dfree(g);
-    dfree(wb);
     dfree(stats_d);
-    dfree(loss_d);
     for (auto &e : ev)
       if (e) (void)hipEventDestroy(e);
     if (own_stream && stream) (void)hipStreamDestroy(stream);
-  }
-
-  // forward of a batch already in act[0]; saz0 = 0 shares one input among
-  // the members
-  int forward(int bsz, long long saz0) {
-    const long long c = cap;
-    for (int l = 0; l < 4; ++l) {
-      const int K = sg::kWidth[l], N = sg::kWidth[l + 1];
-      sg::Gemm q{};
-      q.A = act[l];
-      q.sam = K;
-      q.sak = 1;
-      q.saz = l == 0 ? saz0 : c * K;
-      q.B = wb + sg::w_off(l);  // B(k, n) = W[n][k]
-      q.sbk = 1;
-      q.sbn = K;
-      q.sbz = P;
-      q.M = bsz;
-      q.N = N;
-      q.K = K;
-      q.members = members;
-      q.bias = w + sg::b_off(l);
-      q.bstride = P;
-      if (l < 3) {
-        q.epi = sg::kEpiBiasSilu;
-        q.C = zpre[l];
-        q.scz = c * N;
-        q.Cb = act[l + 1];
-        q.sbzc = c * N;
-      } else {
-        q.epi = sg::kEpiBiasF32;
-        q.C = y;
-        q.scz = c * N;
-      }
-      SGCHK(sg::launch_gemm(q, stream));
-    }
-    return LBM_OK;
-  }
-
-  // gradients of the loss into g after forward(); targets in t
-  int backward(int bsz) {
-    const long long c = cap;
-    SGCHK(sg::launch_loss_grad(y, t, members, bsz, c, dy, dyb, loss_d, stream));
-    for (int l = 3; l >= 0; --l) {
-      const int K = sg::kWidth[l], N = sg::kWidth[l + 1];
-      const sg::bf16 *Db = l == 3 ? dyb : dzb[l];
-      const float *Df = l == 3 ? dy : dz[l];
-      // dW[n][k] = sum_b D[b][n] act[b][k]
-      sg::Gemm q{};
-      q.A = Db;
-      q.sam = 1;
-      q.sak = N;
-      q.saz = c * N;
-      q.B = act[l];
-      q.sbk = K;
-      q.sbn = 1;
-      q.sbz = c * K;
-      q.M = N;
-      q.N = K;
-      q.K = bsz;
-      q.members = members;
-      q.epi = sg::kEpiF32;
-      q.C = g + sg::w_off(l);
-      q.scz = P;
-      SGCHK(sg::launch_gemm(q, stream));
-      SGCHK(sg::launch_bias_grad(Df, members, bsz, N, c, g + sg::b_off(l), P, stream));
-      if (l == 0) break;
-      // d act[b][k] = sum_n D[b][n] W[n][k], times silu'(z) of the layer below
-      sg::Gemm r{};
-      r.A = Db;
-      r.sam = N;
-      r.sak = 1;
-      r.saz = c * N;
-      r.B = wb + sg::w_off(l);
-      r.sbk = K;
-      r.sbn = 1;
-      r.sbz = P;
-      r.M = bsz;
-      r.N = K;
-      r.K = N;
-      r.members = members;
-      r.epi = sg::kEpiDsilu;
-      r.Zin = zpre[l - 1];
-      r.szz = c * K;
-      r.C = dz[l - 1];
-      r.scz = c * K;
-      r.Cb = dzb[l - 1];
-      r.sbzc = c * K;
-      SGCHK(sg::launch_gemm(r, stream));
-    }
-    return LBM_OK;
   }
 };
 
@@ -316,23 +210,6 @@ int upload_std(lbm_surrogate_t s, const double *host, int n, int cols, const dou
   }
   return LBM_OK;
 }
-
-// device arrays of zeros / ones for "no standardisation"
-struct Identity {
-  double *zero = nullptr, *one = nullptr;
-  int make(hipStream_t st) {
-    std::vector<double> z(sg::kFeat, 0.0), o(sg::kFeat, 1.0);
-    SGTRY(dalloc(&zero, z.size()));
-    SGTRY(dalloc(&one, o.size()));
-    SGCHK(hipMemcpyAsync(zero, z.data(), sizeof(double) * z.size(), hipMemcpyHostToDevice, st));
-    SGCHK(hipMemcpyAsync(one, o.data(), sizeof(double) * o.size(), hipMemcpyHostToDevice, st));
-    return LBM_OK;
-  }
-  ~Identity() {
-    dfree(zero);
-    dfree(one);
-  }
-};
 
 // Mayer-Stowe-Princen entry radius of the throat's cross-section (Sec. 1 of
 // the paper names the method): the triangle of the three throat-sphere
@@ -529,8 +406,6 @@ int lbm_surrogate_create(int members, unsigned long long seed, void *stream,
   if (int r = dalloc(&s->w, count)) return fail(r);
   if (int r = dalloc(&s->m, count)) return fail(r);
   if (int r = dalloc(&s->v, count)) return fail(r);
-  if (int r = dalloc(&s->g, count)) return fail(r);
-  if (int r = dalloc(&s->wb, count)) return fail(r);
   if (int r = dalloc(&s->wp, (size_t)members * sg::kPack)) return fail(r);
   if (int r = dalloc(&s->id_d, 2 * sg::kFeat)) return fail(r);
   if (hipHostMalloc((void **)&s->pin_in, sizeof(double) * kPinRows * sg::kFeat,
@@ -543,7 +418,6 @@ int lbm_surrogate_create(int members, unsigned long long seed, void *stream,
     return fail(LBM_ENOMEM);
   }
   if (int r = dalloc(&s->stats_d, 194)) return fail(r);
-  if (int r = dalloc(&s->loss_d, (size_t)members)) return fail(r);
   for (auto &e : s->ev)
     if (hipEventCreate(&e) != hipSuccess) {
       set_err("hipEventCreate failed");
@@ -573,7 +447,6 @@ int lbm_surrogate_create(int members, unsigned long long seed, void *stream,
       sg::launch_pack(s->w, s->wp, members, s->stream) != hipSuccess ||
       hipMemset(s->m, 0, sizeof(float) * count) != hipSuccess ||
       hipMemset(s->v, 0, sizeof(float) * count) != hipSuccess ||
-      sg::launch_to_bf16(s->w, s->wb, (long long)count, s->stream) != hipSuccess ||
       hipStreamSynchronize(s->stream) != hipSuccess) {
     set_err("model initialisation failed");
     return fail(LBM_EHIP);
@@ -601,7 +474,6 @@ int lbm_surrogate_set_params(lbm_surrogate_t s, int member, const float *w) {
   SGCHK(hipMemcpyAsync(dst, w, sizeof(float) * P, hipMemcpyHostToDevice, s->stream));
   SGCHK(hipMemsetAsync(s->m + (size_t)member * P, 0, sizeof(float) * P, s->stream));
   SGCHK(hipMemsetAsync(s->v + (size_t)member * P, 0, sizeof(float) * P, s->stream));
-  SGCHK(sg::launch_to_bf16(dst, s->wb + (size_t)member * P, P, s->stream));
   SGCHK(sg::launch_pack(dst, s->wp + (size_t)member * sg::kPack, 1, s->stream));
   SGCHK(hipStreamSynchronize(s->stream));
   return LBM_OK;
@@ -743,30 +615,23 @@ int lbm_surrogate_grad(lbm_surrogate_t s, int n, const double *xs, const double 
     set_err("lbm_surrogate_grad: inputs must be finite");
     return LBM_ENONFINITE;
   }
-  Identity id;
-  SGTRY(id.make(s->stream));
-  float *xs_d = nullptr, *ts_d = nullptr;
-  SGTRY(upload_std(s, xs, n, sg::kFeat, id.zero, id.one, &xs_d));
-  if (int r = upload_std(s, ts, n, sg::kOut, id.zero, id.one, &ts_d)) {
-    dfree(xs_d);
-    return r;
-  }
-  int rc = s->ensure(n);
+  float *xs_d = nullptr, *ts_d = nullptr, *g_d = nullptr;
+  double *loss_d = nullptr;
+  int rc = upload_std(s, xs, n, sg::kFeat, s->id_d, s->id_d + sg::kFeat, &xs_d);
+  if (rc == LBM_OK) rc = upload_std(s, ts, n, sg::kOut, s->id_d, s->id_d + sg::kFeat, &ts_d);
+  if (rc == LBM_OK) rc = dalloc(&g_d, (size_t)s->members * P);
+  if (rc == LBM_OK) rc = dalloc(&loss_d, (size_t)s->members);
+  if (rc == LBM_OK) rc = s->ensure(n);
   if (rc == LBM_OK) {
-    hipError_t e = sg::launch_gather(xs_d, ts_d, nullptr, 0, s->members, n, s->cap, s->act[0],
-                                     s->t, s->stream);
-    if (e != hipSuccess) {
-      set_err("gather failed: %s", hipGetErrorString(e));
-      rc = LBM_EHIP;
-    }
-  }
-  if (rc == LBM_OK) rc = s->forward(n, (long long)s->cap * sg::kFeat);
-  if (rc == LBM_OK) rc = s->backward(n);
-  if (rc == LBM_OK) {
-    hipError_t e = hipMemcpyAsync(grad, s->g, sizeof(float) * s->members * P,
-                                  hipMemcpyDeviceToHost, s->stream);
+    const sg::Batch q = s->batch(xs_d, ts_d, nullptr, 0, n);
+    hipError_t e = sg::launch_fb(q, s->w, s->stream);
+    if (e == hipSuccess)
+      e = sg::launch_update(q, g_d, nullptr, nullptr, nullptr, nullptr, nullptr, loss_d, s->stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(grad, g_d, sizeof(float) * s->members * P, hipMemcpyDeviceToHost,
+                         s->stream);
     if (e == hipSuccess && loss)
-      e = hipMemcpyAsync(loss, s->loss_d, sizeof(double) * s->members, hipMemcpyDeviceToHost,
+      e = hipMemcpyAsync(loss, loss_d, sizeof(double) * s->members, hipMemcpyDeviceToHost,
                          s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) {
@@ -776,6 +641,8 @@ int lbm_surrogate_grad(lbm_surrogate_t s, int n, const double *xs, const double 
   }
   dfree(xs_d);
   dfree(ts_d);
+  dfree(g_d);
+  dfree(loss_d);
   return rc;
 }
 
@@ -838,7 +705,10 @@ int lbm_surrogate_train(lbm_surrogate_t s, int n, const double *feat, const doub
                            : j;
   const int per_epoch = (n + cfg->batch - 1) / cfg->batch;
   const long long total = (long long)cfg->epochs * per_epoch;
-  std::vector<double> lsum(Mb), lstep(Mb);
+  // the losses of an epoch's batches stay on the device until its end
+  double *loss_d = nullptr;
+  if (rc == LBM_OK) rc = dalloc(&loss_d, (size_t)per_epoch * Mb);
+  std::vector<double> lsum(Mb), lstep((size_t)per_epoch * Mb);
   for (int e = 0; e < cfg->epochs && rc == LBM_OK; ++e) {
     if (order) {
       std::memcpy(ord.data(), order + (size_t)e * Mb * n, sizeof(int) * Mb * n);
@@ -857,49 +727,43 @@ int lbm_surrogate_train(lbm_surrogate_t s, int n, const double *feat, const doub
       rc = LBM_EHIP;
       break;
     }
-    std::fill(lsum.begin(), lsum.end(), 0.0);
     for (int st = 0; st < per_epoch && rc == LBM_OK; ++st) {
       const int start = st * cfg->batch, cnt = std::min(cfg->batch, n - start);
-      he = sg::launch_gather(xs_d, ts_d, idx_d + start, n, Mb, cnt, s->cap, s->act[0], s->t,
-                             s->stream);
-      if (he != hipSuccess) {
-        set_err("gather failed: %s", hipGetErrorString(he));
-        rc = LBM_EHIP;
-        break;
-      }
-      rc = s->forward(cnt, (long long)s->cap * sg::kFeat);
-      if (rc == LBM_OK) rc = s->backward(cnt);
-      if (rc != LBM_OK) break;
       const long long step = (long long)e * per_epoch + st;
       const double cosw = 0.5 * (1.0 + std::cos(M_PI * (double)step / (double)std::max(total, 1LL)));
       const double lr = cfg->lr * (cfg->lr_min_frac + (1.0 - cfg->lr_min_frac) * cosw);
       s->adam_t += 1;
       const double bc1 = 1.0 - std::pow(cfg->beta1, (double)s->adam_t);
       const double bc2 = 1.0 - std::pow(cfg->beta2, (double)s->adam_t);
-      he = sg::launch_adam(s->w, s->g, s->m, s->v, s->wb, (long long)Mb * P, (float)lr,
-                           (float)cfg->beta1, (float)cfg->beta2, (float)cfg->eps, (float)bc1,
-                           (float)bc2, s->stream);
-      if (he == hipSuccess && loss_hist)
-        he = hipMemcpyAsync(lstep.data(), s->loss_d, sizeof(double) * Mb, hipMemcpyDeviceToHost,
-                            s->stream);
-      if (he == hipSuccess && loss_hist) he = hipStreamSynchronize(s->stream);
+      const sg::AdamStep adam{(float)lr, (float)cfg->beta1, (float)cfg->beta2, (float)cfg->eps,
+                              (float)bc1, (float)bc2};
+      const sg::Batch q = s->batch(xs_d, ts_d, idx_d + start, n, cnt);
+      he = sg::launch_fb(q, s->w, s->stream);
+      if (he == hipSuccess)
+        he = sg::launch_update(q, nullptr, s->w, s->m, s->v, s->wp, &adam,
+                               loss_d + (size_t)st * Mb, s->stream);
       if (he != hipSuccess) {
         set_err("training step failed: %s", hipGetErrorString(he));
         rc = LBM_EHIP;
         break;
       }
-      if (loss_hist)
-        for (int z = 0; z < Mb; ++z) lsum[z] += lstep[z];
     }
     if (rc == LBM_OK && loss_hist) {
+      he = hipMemcpyAsync(lstep.data(), loss_d, sizeof(double) * lstep.size(),
+                          hipMemcpyDeviceToHost, s->stream);
+      if (he == hipSuccess) he = hipStreamSynchronize(s->stream);
+      if (he != hipSuccess) {
+        set_err("training step failed: %s", hipGetErrorString(he));
+        rc = LBM_EHIP;
+        break;
+      }
+      std::fill(lsum.begin(), lsum.end(), 0.0);
+      for (int st = 0; st < per_epoch; ++st)
+        for (int z = 0; z < Mb; ++z) lsum[z] += lstep[(size_t)st * Mb + z];
       double a = 0;
       for (int z = 0; z < Mb; ++z) a += lsum[z] / per_epoch;
       loss_hist[e] = a / Mb;
     }
-  }
-  if (sg::launch_pack(s->w, s->wp, Mb, s->stream) != hipSuccess && rc == LBM_OK) {
-    set_err("packing the weights failed");
-    rc = LBM_EHIP;
   }
   if (rc == LBM_OK && hipStreamSynchronize(s->stream) != hipSuccess) {
     set_err("training did not complete");
@@ -908,6 +772,7 @@ int lbm_surrogate_train(lbm_surrogate_t s, int n, const double *feat, const doub
   dfree(xs_d);
   dfree(ts_d);
   dfree(idx_d);
+  dfree(loss_d);
   return rc;
 }
 
