@@ -259,15 +259,21 @@ __device__ __forceinline__ void collide(const Phys &P, uint32_t m, const float (
   }
 }
 
-// Store the post-collision populations of node i.
-template <bool WIDE>
+// Store the post-collision populations of node i.  KEEP: through the caches as
+// any store; else non-temporal.
+template <bool WIDE, bool KEEP>
 __device__ __forceinline__ void store_node(float *dst, uint32_t i, const float (&v)[2][19]) {
   gchar *p = WIDE ? (gchar *)(dst + node_elem(i)) : (gchar *)dst + (size_t)node_bytes(i);
 #pragma unroll
   for (int c = 0; c < 2; ++c)
 #pragma unroll
-    for (int k = 0; k < 19; ++k)
-      __builtin_nontemporal_store(v[c][k], (gfloat *)(p + (19 * c + k) * 4 * kLine));
+    for (int k = 0; k < 19; ++k) {
+      gfloat *q = (gfloat *)(p + (19 * c + k) * 4 * kLine);
+      if constexpr (KEEP)
+        *q = v[c][k];
+      else
+        __builtin_nontemporal_store(v[c][k], q);
+    }
 }
 
 // work lists are handed out so that each XCD (workgroups b = xcd mod 8) gets
@@ -363,7 +369,7 @@ __device__ __forceinline__ void stencil_rec(const float2 *rho, const Near &n, fl
   if constexpr (K + 1 < 19) stencil_rec<WIDE, K + 1>(rho, n, r);
 }
 
-template <bool WIDE>
+template <bool WIDE, bool KEEP>
 __global__ __launch_bounds__(kListNodes) void k_node(const Throat *__restrict__ throats,
                                                      const TileRef *__restrict__ items,
                                                      int nitems, int parity) {
@@ -385,7 +391,7 @@ __global__ __launch_bounds__(kListNodes) void k_node(const Throat *__restrict__ 
       v[0][k] = wf(k) * gw;
       v[1][k] = wf(k) * gn;
     }
-    store_node<WIDE>(T.g[parity ^ 1], T.map[pos], v);
+    store_node<WIDE, KEEP>(T.g[parity ^ 1], T.map[pos], v);
     return;
   }
   Near n;
@@ -405,7 +411,7 @@ __global__ __launch_bounds__(kListNodes) void k_node(const Throat *__restrict__ 
   }
   const double ds[2] = {sum19(v[0]), sum19(v[1])};
   collide(P, m, Sw, Sn, ds, v);
-  store_node<WIDE>(T.g[parity ^ 1], n.r[0][1], v);
+  store_node<WIDE, KEEP>(T.g[parity ^ 1], n.r[0][1], v);
 }
 
 // ---- tiled step over the brick numbering ------------------------------------------
@@ -723,6 +729,18 @@ hipError_t launch_ghost(const Throat *th, const int *zper_ids, int n_zper, int w
   return hipGetLastError();
 }
 
+// Both buffers of the populations, in bytes of listed nodes, for which k_node
+// stores through the caches: between what the L2s hold (8 x 4 MB) and the
+// 256 MB memory-side cache, where the lines just stored are the next step's
+// reads.  Step time, cached against non-temporal: up to 10 MB 0.97-0.98, 17-34
+// MB 1.01-1.06, 69-80 MB 0.95-0.97, 102 MB 0.95, 133-156 MB 0.92, 212 MB 0.89,
+// 242 MB 0.93-0.97, 269 MB 0.91-0.95, from 335 MB on 1.01-1.13.
+constexpr long long kKeepLo = 48ll << 20, kKeepHi = 288ll << 20;
+static bool keep_stores(long long items) {
+  const long long bytes = items * kListNodes * 2 * 38 * 4;
+  return bytes >= kKeepLo && bytes <= kKeepHi;
+}
+
 static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, int tx, int ty,
                             bool wide, int parity, hipStream_t st) {
   if (tx == kListTx) {
@@ -730,10 +748,13 @@ static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, 
     const dim3 grid((unsigned)ntiles), block(kListNodes);
     if (wide) {
       hipLaunchKernelGGL(k_dens<true>, grid, block, 0, st, th, tiles, ntiles, parity);
-      hipLaunchKernelGGL(k_node<true>, grid, block, 0, st, th, tiles, ntiles, parity);
+      hipLaunchKernelGGL((k_node<true, false>), grid, block, 0, st, th, tiles, ntiles, parity);
     } else {
       hipLaunchKernelGGL(k_dens<false>, grid, block, 0, st, th, tiles, ntiles, parity);
-      hipLaunchKernelGGL(k_node<false>, grid, block, 0, st, th, tiles, ntiles, parity);
+      if (keep_stores(ntiles))
+        hipLaunchKernelGGL((k_node<false, true>), grid, block, 0, st, th, tiles, ntiles, parity);
+      else
+        hipLaunchKernelGGL((k_node<false, false>), grid, block, 0, st, th, tiles, ntiles, parity);
     }
     return hipGetLastError();
   }
