@@ -102,8 +102,8 @@ sc::Sched shape_of(const lbm_throat *h) {
   return h->bricks ? h->sched : sc::Sched{sc::kListTx, 0, 0};
 }
 
-// refresh the device descriptor (buffers, sizes, tile grid, parameters)
-int sync_desc(lbm_throat *h) {
+// the descriptor: buffers, sizes, tile grid, parameters
+void fill_desc(lbm_throat *h) {
   sc::Throat &T = h->desc;
   T.g[0] = h->g[0];
   T.g[1] = h->g[1];
@@ -125,6 +125,11 @@ int sync_desc(lbm_throat *h) {
   T.ntx = tiled ? (h->nx + s.tx - 1) / s.tx : 0;
   T.nty = tiled ? (h->ny + s.ty - 1) / s.ty : 0;
   T.lz = s.lz;
+}
+
+// refresh the device descriptor
+int sync_desc(lbm_throat *h) {
+  fill_desc(h);
   HIPCHK(hipMemcpyAsync(h->desc_d, &h->desc, sizeof(sc::Throat), hipMemcpyHostToDevice,
                         h->stream));
   return LBM_OK;
@@ -189,6 +194,27 @@ sc::Sched default_schedule(int nx, int ny, int nz) {
   long long lz = (ntx * nty * nz + 1023) / 1024;
   s.lz = (int)std::max(4LL, std::min<long long>(64, lz));
   return s;
+}
+
+void fill_handle(const lbm_params *p, lbm_throat *h) {
+  h->nx = p->nx;
+  h->ny = p->ny;
+  h->nz = p->nz;
+  h->N = (size_t)p->nx * p->ny * p->nz;
+  for (int a = 0; a < 3; ++a) h->bc[a] = p->bc[a];
+  h->per = (p->bc[0] == LBM_BC_PERIODIC ? 1 : 0) | (p->bc[1] == LBM_BC_PERIODIC ? 2 : 0) |
+           (p->bc[2] == LBM_BC_PERIODIC ? 4 : 0);
+  for (int c = 0; c < 2; ++c) {
+    h->tau[c] = p->tau[c];
+    h->Gads[c] = p->G_ads[c];
+  }
+  h->G = p->G;
+  h->rho_major = p->rho_major;
+  h->rho_minor = p->rho_minor;
+  h->rho_in = p->rho_in_nw;
+  h->rho_out = p->rho_out_w;
+  h->phib = (p->rho_major - p->rho_minor) / (p->rho_major + p->rho_minor);
+  fill_phys(h);
 }
 
 int validate(const lbm_params *p) {
@@ -322,9 +348,38 @@ int copy_state(lbm_throat *h, float *dst, const float *src) {
 }  // namespace
 
 namespace lbmh {
-int sync_desc(lbm_throat *h) { return ::sync_desc(h); }
-int set_rho_in(lbm_throat *h, double r) { return ::set_rho_in(h, r); }
-int copy_state(lbm_throat *h, float *dst, const float *src) { return ::copy_state(h, dst, src); }
+int describe(const lbm_params *p, lbm_throat *h) {
+  TRY(validate(p));
+  fill_handle(p, h);
+  return LBM_OK;
+}
+
+Geometry::Geometry(const lbm_params &p) : sph(4 * (size_t)std::max(p.n_spheres, 1)) {
+  for (int i = 0; i < p.n_spheres; ++i) {
+    for (int a = 0; a < 3; ++a) sph[4 * i + a] = p.spheres[i].c[a];
+    sph[4 * i + 3] = p.spheres[i].r;
+  }
+  sc::bin_spheres(sph.data(), p.n_spheres, p.nx, p.ny, p.nz, bin_start, bin_ids, ncx, ncy, ncz);
+  if (bin_ids.empty()) bin_ids.push_back(0);
+}
+
+hipError_t Geometry::voxelize(const lbm_params &p, const double *sph_d, const int *start_d,
+                              const int *ids_d, uint8_t *types_d, hipStream_t st) const {
+  const sc::VoxBins bins{start_d, ids_d, ncx, ncy, ncz};
+  int prism[3] = {0, 0, 0};
+  for (int a = 0; a < 3 && p.prism; ++a) prism[a] = p.prism_ids[a];
+  return sc::launch_voxelize(sph_d, bins, p.prism ? 1 : 0, prism, p.nx, p.ny, p.nz,
+                             p.bc[2] == LBM_BC_RESERVOIR, types_d, st);
+}
+
+int check_rho_init(const lbm_throat *h, unsigned long long bad) {
+  if (bad >= 2 * (unsigned long long)h->N) return LBM_OK;
+  set_err("rho_init is not finite and positive on fluid node %zu", (size_t)(bad % h->N));
+  return LBM_EINVAL;
+}
+
+void fill_desc(lbm_throat *h) { ::fill_desc(h); }
+sc::Dom dom(const lbm_throat *h) { return ::dom(h, nullptr, nullptr); }
 }  // namespace lbmh
 
 
@@ -349,7 +404,7 @@ namespace {
 constexpr double kTileFill = 0.85;
 constexpr size_t kTileNodes = (size_t)1 << 22;
 
-int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
+int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
   g_err.clear();
   if (!out) {
     set_err("out is NULL");
@@ -362,24 +417,7 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
     set_err("host allocation failed");
     return LBM_ENOMEM;
   }
-  h->nx = p->nx;
-  h->ny = p->ny;
-  h->nz = p->nz;
-  h->N = (size_t)p->nx * p->ny * p->nz;
-  for (int a = 0; a < 3; ++a) h->bc[a] = p->bc[a];
-  h->per = (p->bc[0] == LBM_BC_PERIODIC ? 1 : 0) | (p->bc[1] == LBM_BC_PERIODIC ? 2 : 0) |
-           (p->bc[2] == LBM_BC_PERIODIC ? 4 : 0);
-  for (int c = 0; c < 2; ++c) {
-    h->tau[c] = p->tau[c];
-    h->Gads[c] = p->G_ads[c];
-  }
-  h->G = p->G;
-  h->rho_major = p->rho_major;
-  h->rho_minor = p->rho_minor;
-  h->rho_in = p->rho_in_nw;
-  h->rho_out = p->rho_out_w;
-  h->phib = (p->rho_major - p->rho_minor) / (p->rho_major + p->rho_minor);
-  fill_phys(h);
+  fill_handle(p, h);
 
   auto fail = [&](int code) {
     release(h);
@@ -419,18 +457,9 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
 
   // geometry on the device
   double *sph_d = nullptr, *rho_d = nullptr;
-  const int ns = p->n_spheres;
-  std::vector<double> sph(4 * (size_t)std::max(ns, 1));
-  for (int i = 0; i < ns; ++i) {
-    sph[4 * i + 0] = p->spheres[i].c[0];
-    sph[4 * i + 1] = p->spheres[i].c[1];
-    sph[4 * i + 2] = p->spheres[i].c[2];
-    sph[4 * i + 3] = p->spheres[i].r;
-  }
-  std::vector<int> bin_start, bin_ids;
-  int ncx = 0, ncy = 0, ncz = 0;
-  sc::bin_spheres(sph.data(), ns, h->nx, h->ny, h->nz, bin_start, bin_ids, ncx, ncy, ncz);
-  if (bin_ids.empty()) bin_ids.push_back(0);
+  const lbmh::Geometry geo(*p);
+  const std::vector<double> &sph = geo.sph;
+  const std::vector<int> &bin_start = geo.bin_start, &bin_ids = geo.bin_ids;
   int *bins_d = nullptr;
   ALLOC(sph_d, sizeof(double) * sph.size());
   if (hipMalloc((void **)&bins_d, sizeof(int) * (bin_start.size() + bin_ids.size())) !=
@@ -460,11 +489,8 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
       rc = LBM_EHIP;
       break;
     }
-    const sc::VoxBins bins{bins_d, bins_d + bin_start.size(), ncx, ncy, ncz};
-    const int ids[3] = {p->prism_ids[0], p->prism_ids[1], p->prism_ids[2]};
-    const int safe_ids[3] = {p->prism ? ids[0] : 0, p->prism ? ids[1] : 0, p->prism ? ids[2] : 0};
-    if (sc::launch_voxelize(sph_d, bins, p->prism ? 1 : 0, safe_ids, h->nx, h->ny, h->nz,
-                            p->bc[2] == LBM_BC_RESERVOIR, h->types_d, h->stream) != hipSuccess ||
+    if (geo.voxelize(*p, sph_d, bins_d, bins_d + bin_start.size(), h->types_d, h->stream) !=
+            hipSuccess ||
         sc::launch_row_counts(h->types_d, h->nx, h->ny, h->nz, rows_d, h->stream) !=
             hipSuccess) {
       rc = LBM_EHIP;
@@ -492,14 +518,14 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
     return fail_rows(rc);
   }
   // numbering, populations, work items
-  h->n_live = sc::number_rows(rows, h->ny, h->nz);
+  h->n_live = sc::number_rows(rows.data(), h->ny, h->nz);
   const size_t plane = (size_t)h->nx * h->ny;
   h->n_fluid = (long long)h->n_live;
   if (p->bc[2] == LBM_BC_RESERVOIR)
     for (size_t n = 0; n < plane; ++n)
       h->n_fluid -= (h->types[n] != sc::kSolid) + (h->types[h->N - plane + n] != sc::kSolid);
   const size_t slots = (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * h->nz;
-  h->bricks = !compact && slots >= kTileNodes && (double)h->n_live >= kTileFill * (double)slots;
+  h->bricks = slots >= kTileNodes && (double)h->n_live >= kTileFill * (double)slots;
   h->n_numbers = h->bricks ? slots / h->nz * ((size_t)h->nz + 2) : h->n_live;
   const size_t pop_bytes = sizeof(float) * sc::pop_elems(h->n_numbers);
   std::vector<sc::RedChunk> chunks;
@@ -593,15 +619,12 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
       return fail(LBM_EHIP);
     }
   }
+  unsigned long long bad = ~0ull, *bad_d = nullptr;
   if (p->rho_init) {
-    for (int c = 0; c < 2; ++c)
-      for (size_t n = 0; n < h->N; ++n)
-        if (h->types[n] == sc::kFluid && !finite_pos(p->rho_init[c * h->N + n])) {
-          set_err("rho_init is not finite and positive on fluid node %zu", n);
-          return fail(LBM_EINVAL);
-        }
-    ALLOC(rho_d, sizeof(double) * 2 * h->N);
-    if (hipMemcpyAsync(rho_d, p->rho_init, sizeof(double) * 2 * h->N, hipMemcpyHostToDevice,
+    ALLOC(rho_d, sizeof(double) * (2 * h->N + 1));
+    bad_d = (unsigned long long *)(rho_d + 2 * h->N);
+    if (hipMemsetAsync(bad_d, 0xff, sizeof bad, h->stream) != hipSuccess ||
+        hipMemcpyAsync(rho_d, p->rho_init, sizeof(double) * 2 * h->N, hipMemcpyHostToDevice,
                        h->stream) != hipSuccess) {
       (void)hipFree(rho_d);
       set_err("rho_init upload failed");
@@ -614,7 +637,9 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
   }
   const sc::Dom d = dom(h, nullptr, nullptr);
   hipError_t e = sc::launch_init(d, h->P, rho_d, h->rho_major, h->rho_minor, p->z_front, h->rres_d,
-                                 h->g[0], h->stream);
+                                 h->g[0], bad_d, h->stream);
+  if (e == hipSuccess && bad_d)
+    e = hipMemcpyAsync(&bad, bad_d, sizeof bad, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipMemsetAsync(h->g[1], 0, pop_bytes, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (rho_d) (void)hipFree(rho_d);
@@ -622,6 +647,7 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
     set_err("initial state failed: %s", hipGetErrorString(e));
     return fail(LBM_EHIP);
   }
+  if (const int r = lbmh::check_rho_init(h, bad)) return fail(r);
   h->cur = 0;
   if (rebuild_tiles(h) != LBM_OK) return fail(LBM_EHIP);
   if (sc::launch_ghost(h->desc_d, h->zper_d, h->n_zper, 0, h->stream) != hipSuccess ||
@@ -636,14 +662,10 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out, bool compact) {
 
 }  // namespace
 
-namespace lbmh {
-int init_compact(const lbm_params *p, lbm_throat_t *out) { return init_subdomain(p, out, true); }
-}  // namespace lbmh
-
 extern "C" {
 
 int lbm_throat_init(const lbm_params *p, lbm_throat_t *out) {
-  return init_subdomain(p, out, false);
+  return init_subdomain(p, out);
 }
 
 void lbm_throat_free(lbm_throat_t h) { release(h); }

@@ -13,6 +13,9 @@
 #include <climits>
 #include <cmath>
 #include <cstdlib>
+#include <cstring>
+#include <memory>
+#include <new>
 #include <vector>
 
 #include "lbm_abi.h"
@@ -28,7 +31,10 @@ constexpr double kCs2 = 1.0 / 3.0;
 struct Batch {
   int n = 0;
   hipStream_t stream = nullptr;
-  std::vector<lbm_throat_t> h;
+  std::vector<std::unique_ptr<lbm_throat>> h;  // their buffers lie in geo_d and mem_d
+  char *geo_d = nullptr, *mem_d = nullptr;     // all device memory of the batch,
+  char *rho_d = nullptr;                       // besides given initial states
+  char *geo_h = nullptr, *mem_h = nullptr;     // pinned images of their exchanged parts
   sc::Throat *th_d = nullptr;
   sc::TileRef *items_d = nullptr;   // work items of all subdomains
   int nitems = 0;
@@ -40,11 +46,15 @@ struct Batch {
   int *first_d = nullptr, *count_d = nullptr;
   sc::RedInfo *info_d = nullptr;
   double *partials = nullptr, *sums = nullptr, *probe = nullptr;
-  sc::RampDev *rd_d = nullptr;
   sc::Ckpt *ck_d = nullptr;
-  double *pc_d = nullptr, *S_d = nullptr;
-  long long *steps_d = nullptr;
-  int *status_d = nullptr, *nact_d = nullptr, *nact_h = nullptr;
+  double *pc_d = nullptr;
+  // results, contiguous on the device and in the pinned image
+  size_t res_lo = 0, res_hi = 0;
+  sc::RampDev *rd_d = nullptr, *rd = nullptr;
+  double *S_d = nullptr, *S = nullptr;
+  long long *steps_d = nullptr, *steps = nullptr;
+  int *status_d = nullptr, *status = nullptr;
+  int *nact_d = nullptr, *nact_h = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hipEvent_t wall[2] = {nullptr, nullptr};  // the whole drain, first to last kernel
@@ -55,16 +65,23 @@ struct Batch {
     if (stream) (void)hipStreamSynchronize(stream);
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
-    for (void *p : {(void *)th_d, (void *)items_d, (void *)chunks_d, (void *)cchunks_d, (void *)first_d, (void *)count_d,
-                    (void *)info_d, (void *)partials, (void *)sums,
-                    (void *)probe, (void *)rd_d, (void *)ck_d, (void *)pc_d, (void *)S_d,
-                    (void *)steps_d, (void *)status_d, (void *)nact_d})
+    for (char *p : {geo_d, mem_d, rho_d})
       if (p) (void)hipFree(p);
-    if (nact_h) (void)hipHostFree(nact_h);
+    for (char *p : {geo_h, mem_h})
+      if (p) (void)hipHostFree(p);
     for (auto e : wall)
       if (e) (void)hipEventDestroy(e);
-    for (auto x : h) lbm_throat_free(x);
     if (stream) (void)hipStreamDestroy(stream);
+  }
+};
+
+// places of arrays in one block of memory
+struct Layout {
+  size_t size = 0;
+  size_t add(size_t bytes, size_t align = 256) {
+    const size_t at = (size + align - 1) / align * align;
+    size = at + bytes;
+    return at;
   }
 };
 
@@ -77,11 +94,251 @@ struct Batch {
     }                                                                          \
   } while (0)
 
-template <class T>
-int dalloc(T **p, size_t count) {
-  if (hipMalloc((void **)p, sizeof(T) * std::max<size_t>(count, 1)) != hipSuccess) {
-    set_err("hipMalloc of %zu bytes failed", sizeof(T) * count);
+int block(char **d, size_t bytes) {
+  if (hipMalloc((void **)d, bytes) == hipSuccess) return LBM_OK;
+  *d = nullptr;
+  (void)hipGetLastError();
+  set_err("lbm_drain_batch: hipMalloc of %zu bytes failed", bytes);
+  return LBM_ENOMEM;
+}
+
+int pinned(char **h, size_t bytes) {
+  if (hipHostMalloc((void **)h, bytes, hipHostMallocDefault) == hipSuccess) return LBM_OK;
+  *h = nullptr;
+  (void)hipGetLastError();
+  set_err("lbm_drain_batch: hipHostMalloc of %zu bytes failed", bytes);
+  return LBM_ENOMEM;
+}
+
+// Geometry, numbering, initial state and ramp tables of all subdomains, in two
+// rounds of one upload, the kernels and one wait each: the second block can be
+// laid out only when the nodes are counted.  Set up one by one, with an
+// allocation and a release per array and a wait per copy, 16 throats of 24 to
+// 36 nodes a side took 34 ms for a batch of which 17 are kernels, 8 throats of
+// 48 to 128 took 114 ms (77); now 19.8 and 78 ms.
+int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
+  const int n = B.n;
+  struct At {
+    size_t sph, start, ids, rows, types, map;
+  };
+  std::vector<At> at(n);
+  std::vector<lbmh::Geometry> geo;
+  geo.reserve(n);
+  B.h.resize(n);
+  Layout G;
+  for (int t = 0; t < n; ++t) {
+    B.h[t].reset(new (std::nothrow) lbm_throat());
+    if (!B.h[t]) {
+      set_err("host allocation failed");
+      return LBM_ENOMEM;
+    }
+    if (const int r = lbmh::describe(&p[t], B.h[t].get())) return r;
+    B.h[t]->stream = B.stream;
+    if (p[t].probe[0] >= p[t].nx || p[t].probe[1] < 0 || p[t].probe[1] >= p[t].ny ||
+        p[t].probe[2] < 0 || p[t].probe[2] >= p[t].nz) {
+      set_err("probe node outside the box");
+      return LBM_EINVAL;
+    }
+    geo.emplace_back(p[t]);
+    at[t].sph = G.add(sizeof(double) * geo[t].sph.size(), 16);
+    at[t].start = G.add(sizeof(int) * geo[t].bin_start.size(), 16);
+    at[t].ids = G.add(sizeof(int) * geo[t].bin_ids.size(), 16);
+  }
+  const size_t up = G.size, rows_lo = G.add(0);
+  for (int t = 0; t < n; ++t)
+    at[t].rows = G.add(sizeof(uint32_t) * (size_t)p[t].ny * p[t].nz, 16);
+  const size_t rows_hi = G.size;
+  for (int t = 0; t < n; ++t) {
+    at[t].types = G.add(B.h[t]->N);
+    at[t].map = G.add(sizeof(uint32_t) * sc::map_elems(p[t].nx, p[t].ny, p[t].nz));
+  }
+  if (const int r = block(&B.geo_d, G.size)) return r;
+  if (const int r = pinned(&B.geo_h, rows_hi)) return r;
+  for (int t = 0; t < n; ++t) {
+    auto put = [&](size_t o, const auto &v) {
+      std::memcpy(B.geo_h + o, v.data(), sizeof(v[0]) * v.size());
+    };
+    put(at[t].sph, geo[t].sph);
+    put(at[t].start, geo[t].bin_start);
+    put(at[t].ids, geo[t].bin_ids);
+  }
+  BCHK(hipMemcpyAsync(B.geo_d, B.geo_h, up, hipMemcpyHostToDevice, B.stream));
+  for (int t = 0; t < n; ++t) {
+    lbm_throat &h = *B.h[t];
+    h.types_d = (uint8_t *)(B.geo_d + at[t].types);
+    h.map_d = (uint32_t *)(B.geo_d + at[t].map);
+    BCHK(geo[t].voxelize(p[t], (double *)(B.geo_d + at[t].sph), (int *)(B.geo_d + at[t].start),
+                         (int *)(B.geo_d + at[t].ids), h.types_d, B.stream));
+    BCHK(sc::launch_row_counts(h.types_d, h.nx, h.ny, h.nz, (uint32_t *)(B.geo_d + at[t].rows),
+                               B.stream));
+  }
+  BCHK(hipMemcpyAsync(B.geo_h + rows_lo, B.geo_d + rows_lo, rows_hi - rows_lo,
+                      hipMemcpyDeviceToHost, B.stream));
+  BCHK(hipStreamSynchronize(B.stream));
+
+  // numbers and work items
+  std::vector<int> first(n), count(n);
+  std::vector<sc::TileRef> items;
+  std::vector<sc::RedChunk> chunks;
+  std::vector<sc::Chunk> cchunks;
+  for (int t = 0; t < n; ++t) {
+    lbm_throat &h = *B.h[t];
+    uint32_t *rows = (uint32_t *)(B.geo_h + at[t].rows);
+    long long baths = 0;
+    if (h.bc[2] == LBM_BC_RESERVOIR)
+      for (int y = 0; y < h.ny; ++y)
+        baths += (long long)rows[y] + rows[(size_t)(h.nz - 1) * h.ny + y];
+    h.n_live = h.n_numbers = sc::number_rows(rows, h.ny, h.nz);
+    h.n_fluid = (long long)h.n_live - baths;
+    first[t] = (int)chunks.size();
+    sc::red_chunks(h.n_live, t, chunks);
+    count[t] = (int)chunks.size() - first[t];
+    sc::list_items(h.n_live, t, items);
+    sc::copy_chunks(t, sc::pop_elems(h.n_numbers), cchunks);
+    B.wide = B.wide || lbmh::wide(&h);
+  }
+  if (items.size() > (size_t)INT_MAX) {
+    set_err("lbm_drain_batch: %zu work items exceed one launch", items.size());
+    return LBM_EINVAL;
+  }
+  B.nitems = (int)items.size();
+  B.nchunks = (int)chunks.size();
+  B.ncchunks = (int)cchunks.size();
+  const size_t points = (size_t)n * n_pc;
+  Layout M;
+  const size_t o_th = M.add(sizeof(sc::Throat) * n),
+               o_items = M.add(sizeof(sc::TileRef) * items.size()),
+               o_chunks = M.add(sizeof(sc::RedChunk) * chunks.size()),
+               o_cchunks = M.add(sizeof(sc::Chunk) * cchunks.size()),
+               o_first = M.add(sizeof(int) * n), o_count = M.add(sizeof(int) * n),
+               o_info = M.add(sizeof(sc::RedInfo) * n), o_ck = M.add(sizeof(sc::Ckpt) * n),
+               o_pc = M.add(sizeof(double) * points), o_rres = M.add(sizeof(double) * 4 * n),
+               o_rd = M.add(sizeof(sc::RampDev) * n), o_S = M.add(sizeof(double) * points),
+               o_steps = M.add(sizeof(long long) * points), o_status = M.add(sizeof(int) * points);
+  B.res_lo = o_rd;
+  B.res_hi = M.size;
+  const size_t o_nact = M.add(sizeof(int)), o_bad = M.add(sizeof(unsigned long long) * n),
+               image = M.size;
+  const size_t o_partials = M.add(sizeof(double) * 3 * std::max<size_t>(chunks.size(), 1)),
+               o_sums = M.add(sizeof(double) * 3 * n), o_probe = M.add(sizeof(double) * 2 * n);
+  std::vector<size_t> o_pos(n), o_rho(n), o_pop[4];
+  for (int t = 0; t < n; ++t) {
+    o_pos[t] = M.add(sizeof(uint32_t) * B.h[t]->n_live);
+    o_rho[t] = M.add(sizeof(float2) * B.h[t]->n_numbers);
+  }
+  size_t lo[4];  // first buffers, second buffers, the two sets of checkpoints
+  for (int i = 0; i < 4; ++i) {
+    lo[i] = M.add(0, 4096);
+    for (int t = 0; t < n; ++t)
+      o_pop[i].push_back(M.add(sizeof(float) * sc::pop_elems(B.h[t]->n_numbers), 4096));
+  }
+  size_t free_b = 0, total_b = 0;
+  BCHK(hipMemGetInfo(&free_b, &total_b));
+  if (M.size + (64u << 20) > free_b) {
+    set_err("needs %zu bytes of device memory, %zu free", M.size + (64u << 20), free_b);
     return LBM_ENOMEM;
+  }
+  if (const int r = block(&B.mem_d, M.size)) return r;
+  if (const int r = pinned(&B.mem_h, image)) return r;
+  std::memset(B.mem_h, 0, image);
+  auto put = [&](size_t o, const auto &v) {
+    if (!v.empty()) std::memcpy(B.mem_h + o, v.data(), sizeof(v[0]) * v.size());
+  };
+  put(o_items, items);
+  put(o_chunks, chunks);
+  put(o_cchunks, cchunks);
+  put(o_first, first);
+  put(o_count, count);
+  std::memcpy(B.mem_h + o_pc, pc, sizeof(double) * points);
+  sc::RedInfo *info = (sc::RedInfo *)(B.mem_h + o_info);
+  B.rd = (sc::RampDev *)(B.mem_h + o_rd);
+  B.S = (double *)(B.mem_h + o_S);
+  B.steps = (long long *)(B.mem_h + o_steps);
+  B.status = (int *)(B.mem_h + o_status);
+  B.nact_h = (int *)(B.mem_h + o_nact);
+  unsigned long long *bad = (unsigned long long *)(B.mem_h + o_bad);
+  std::fill(bad, bad + n, ~0ull);
+  for (size_t i = 0; i < points; ++i) B.status[i] = LBM_PT_NOT_RUN;
+  for (int t = 0; t < n; ++t) {
+    lbm_throat &h = *B.h[t];
+    for (int i = 0; i < 2; ++i) {
+      h.g[i] = (float *)(B.mem_d + o_pop[i][t]);
+      h.save[i] = (float *)(B.mem_d + o_pop[2 + i][t]);
+    }
+    h.pos_d = (uint32_t *)(B.mem_d + o_pos[t]);
+    h.rho_d = (float2 *)(B.mem_d + o_rho[t]);
+    h.rres_d = (double *)(B.mem_d + o_rres) + 4 * t;
+    lbmh::fill_desc(&h);
+    ((sc::Throat *)(B.mem_h + o_th))[t] = h.desc;
+    ((sc::Ckpt *)(B.mem_h + o_ck))[t] = sc::Ckpt{h.save[0], h.save[1]};
+    info[t] = sc::RedInfo{(long long)sc::map_pos(h.nx, h.ny, p[t].probe[0], p[t].probe[1],
+                                                 p[t].probe[2]),
+                          h.phib};
+    const double rr[4] = {h.rho_minor, h.rho_in, h.rho_out, h.rho_minor};
+    std::memcpy(B.mem_h + o_rres + 4 * t * sizeof(double), rr, sizeof rr);
+    sc::RampDev R{};
+    R.rho_out = h.rho_out;
+    R.dpc_drho = kCs2 * (1.0 + h.G * h.rho_minor);
+    R.rho_ref = h.rho_minor;
+    R.n_fluid = (unsigned)h.n_fluid;
+    R.phase = sc::kPhaseDone;
+    B.rd[t] = R;
+  }
+  B.th_d = (sc::Throat *)(B.mem_d + o_th);
+  B.items_d = (sc::TileRef *)(B.mem_d + o_items);
+  B.chunks_d = (sc::RedChunk *)(B.mem_d + o_chunks);
+  B.cchunks_d = (sc::Chunk *)(B.mem_d + o_cchunks);
+  B.first_d = (int *)(B.mem_d + o_first);
+  B.count_d = (int *)(B.mem_d + o_count);
+  B.info_d = (sc::RedInfo *)(B.mem_d + o_info);
+  B.ck_d = (sc::Ckpt *)(B.mem_d + o_ck);
+  B.pc_d = (double *)(B.mem_d + o_pc);
+  B.rd_d = (sc::RampDev *)(B.mem_d + o_rd);
+  B.S_d = (double *)(B.mem_d + o_S);
+  B.steps_d = (long long *)(B.mem_d + o_steps);
+  B.status_d = (int *)(B.mem_d + o_status);
+  B.nact_d = (int *)(B.mem_d + o_nact);
+  B.partials = (double *)(B.mem_d + o_partials);
+  B.sums = (double *)(B.mem_d + o_sums);
+  B.probe = (double *)(B.mem_d + o_probe);
+  BCHK(hipMemcpyAsync(B.geo_d + rows_lo, B.geo_h + rows_lo, rows_hi - rows_lo,
+                      hipMemcpyHostToDevice, B.stream));
+  BCHK(hipMemcpyAsync(B.mem_d, B.mem_h, image, hipMemcpyHostToDevice, B.stream));
+  for (int t = 0; t < n; ++t) {
+    const lbm_throat &h = *B.h[t];
+    BCHK(sc::launch_number(h.types_d, h.nx, h.ny, h.nz, h.per, (uint32_t *)(B.geo_d + at[t].rows),
+                           false, h.map_d, h.pos_d, B.stream));
+  }
+  BCHK(sc::launch_probe_numbers(B.th_d, n, B.info_d, B.stream));
+  BCHK(hipMemcpyAsync(info, B.info_d, sizeof(sc::RedInfo) * n, hipMemcpyDeviceToHost, B.stream));
+  BCHK(hipMemsetAsync(B.mem_d + lo[1], 0, lo[2] - lo[1], B.stream));
+  // given initial states pass through one buffer, in stream order
+  size_t given = 0;
+  for (int t = 0; t < n; ++t)
+    if (p[t].rho_init) given = std::max(given, sizeof(double) * 2 * B.h[t]->N);
+  if (given)
+    if (const int r = block(&B.rho_d, given)) return r;
+  for (int t = 0; t < n; ++t) {
+    const lbm_throat &h = *B.h[t];
+    if (p[t].rho_init)
+      BCHK(hipMemcpyAsync(B.rho_d, p[t].rho_init, sizeof(double) * 2 * h.N, hipMemcpyHostToDevice,
+                          B.stream));
+    BCHK(sc::launch_init(lbmh::dom(&h), h.P, p[t].rho_init ? (const double *)B.rho_d : nullptr,
+                         h.rho_major, h.rho_minor, p[t].z_front, h.rres_d, h.g[0],
+                         (unsigned long long *)(B.mem_d + o_bad) + t, B.stream));
+  }
+  BCHK(hipMemcpyAsync(bad, B.mem_d + o_bad, sizeof(unsigned long long) * n, hipMemcpyDeviceToHost,
+                      B.stream));
+  BCHK(hipStreamSynchronize(B.stream));
+  for (int t = 0; t < n; ++t) {
+    const lbm_throat &h = *B.h[t];
+    const int z = p[t].probe[2];
+    if ((uint32_t)info[t].probe == sc::kNoNode ||
+        (h.bc[2] == LBM_BC_RESERVOIR && (z == 0 || z == h.nz - 1))) {
+      set_err("probe node is not a fluid node");
+      return LBM_EINVAL;
+    }
+    if (const int r = lbmh::check_rho_init(&h, bad[t])) return r;
   }
   return LBM_OK;
 }
@@ -173,88 +430,7 @@ int lbm_drain_batch(int n, const lbm_params *p, const double *pc, int n_pc, cons
   BCHK(hipStreamCreate(&B.stream));
   BCHK(hipEventCreate(&B.wall[0]));
   BCHK(hipEventCreate(&B.wall[1]));
-  // subdomains: geometry, initial state, checkpoints
-  std::vector<sc::Chunk> cchunks;
-  std::vector<sc::Throat> th(n);
-  std::vector<int> first(n), count(n);
-  std::vector<sc::RedInfo> rinfo(n);
-  std::vector<sc::RampDev> rd(n);
-  std::vector<sc::Ckpt> ck(n);
-  std::vector<sc::TileRef> items;
-  std::vector<sc::RedChunk> chunks;
-  for (int t = 0; t < n; ++t) {
-    lbm_params q = p[t];
-    q.stream = B.stream;
-    lbm_throat_t x = nullptr;
-    if (int r = lbmh::init_compact(&q, &x)) {
-      if (r < 0) return r;
-    }
-    B.h.push_back(x);
-    for (int i = 0; i < 2; ++i)
-      if (!x->save[i] &&
-          hipMalloc((void **)&x->save[i], std::max<size_t>(sizeof(float) * sc::pop_elems(x->n_numbers), 16)) !=
-              hipSuccess) {
-        set_err("lbm_drain_batch: no device memory for the checkpoints of subdomain %d", t);
-        return LBM_ENOMEM;
-      }
-    th[t] = x->desc;
-    ck[t] = sc::Ckpt{x->save[0], x->save[1]};
-    first[t] = (int)chunks.size();
-    sc::red_chunks(x->n_live, t, chunks);
-    count[t] = (int)chunks.size() - first[t];
-    sc::list_items(x->n_live, t, items);
-    B.wide = B.wide || lbmh::wide(x);
-    sc::copy_chunks(t, sc::pop_elems(x->n_numbers), cchunks);
-    rinfo[t] = sc::RedInfo{x->probe, x->phib};
-    sc::RampDev R{};
-    R.rho_out = x->rho_out;
-    R.dpc_drho = kCs2 * (1.0 + x->G * x->rho_minor);
-    R.rho_ref = x->rho_minor;
-    R.n_fluid = (unsigned)x->n_fluid;
-    R.phase = sc::kPhaseDone;
-    rd[t] = R;
-  }
-  if (items.size() > (size_t)INT_MAX) {
-    set_err("lbm_drain_batch: %zu work items exceed one launch", items.size());
-    return LBM_EINVAL;
-  }
-  B.nitems = (int)items.size();
-  B.nchunks = (int)chunks.size();
-  B.ncchunks = (int)cchunks.size();
-  if (dalloc(&B.th_d, n) || dalloc(&B.items_d, items.size()) || dalloc(&B.chunks_d, chunks.size()) ||
-      dalloc(&B.cchunks_d, cchunks.size()) || dalloc(&B.first_d, n) ||
-      dalloc(&B.count_d, n) || dalloc(&B.info_d, n) || dalloc(&B.partials, 3 * chunks.size()) ||
-      dalloc(&B.sums, 3 * (size_t)n) || dalloc(&B.probe, 2 * (size_t)n) || dalloc(&B.rd_d, n) ||
-      dalloc(&B.ck_d, n) || dalloc(&B.pc_d, (size_t)n * n_pc) || dalloc(&B.S_d, (size_t)n * n_pc) ||
-      dalloc(&B.steps_d, (size_t)n * n_pc) || dalloc(&B.status_d, (size_t)n * n_pc) ||
-      dalloc(&B.nact_d, 1))
-    return LBM_ENOMEM;
-  if (hipHostMalloc((void **)&B.nact_h, sizeof(int), hipHostMallocDefault) != hipSuccess) {
-    set_err("hipHostMalloc failed");
-    return LBM_ENOMEM;
-  }
-  if (!cchunks.empty())
-    BCHK(hipMemcpy(B.cchunks_d, cchunks.data(), sizeof(sc::Chunk) * cchunks.size(),
-                   hipMemcpyHostToDevice));
-  BCHK(hipMemcpy(B.th_d, th.data(), sizeof(sc::Throat) * n, hipMemcpyHostToDevice));
-  if (!items.empty()) {
-    BCHK(hipMemcpy(B.items_d, items.data(), sizeof(sc::TileRef) * items.size(),
-                   hipMemcpyHostToDevice));
-    BCHK(hipMemcpy(B.chunks_d, chunks.data(), sizeof(sc::RedChunk) * chunks.size(),
-                   hipMemcpyHostToDevice));
-  }
-  BCHK(hipMemcpy(B.first_d, first.data(), sizeof(int) * n, hipMemcpyHostToDevice));
-  BCHK(hipMemcpy(B.count_d, count.data(), sizeof(int) * n, hipMemcpyHostToDevice));
-  BCHK(hipMemcpy(B.info_d, rinfo.data(), sizeof(sc::RedInfo) * n, hipMemcpyHostToDevice));
-  BCHK(hipMemcpy(B.rd_d, rd.data(), sizeof(sc::RampDev) * n, hipMemcpyHostToDevice));
-  BCHK(hipMemcpy(B.ck_d, ck.data(), sizeof(sc::Ckpt) * n, hipMemcpyHostToDevice));
-  BCHK(hipMemcpy(B.pc_d, pc, sizeof(double) * n * n_pc, hipMemcpyHostToDevice));
-  BCHK(hipMemset(B.S_d, 0, sizeof(double) * n * n_pc));
-  BCHK(hipMemset(B.steps_d, 0, sizeof(long long) * n * n_pc));
-  {
-    const std::vector<int> not_run((size_t)n * n_pc, LBM_PT_NOT_RUN);
-    BCHK(hipMemcpy(B.status_d, not_run.data(), sizeof(int) * n * n_pc, hipMemcpyHostToDevice));
-  }
+  if (const int r = setup(B, p, pc, n_pc)) return r;
   hipEvent_t w0 = B.wall[0], w1 = B.wall[1];
   BCHK(hipEventRecord(w0, B.stream));
   // the initial decisions
@@ -300,21 +476,17 @@ int lbm_drain_batch(int n, const lbm_params *p, const double *pc, int n_pc, cons
   float wall = 0.f;
   BCHK(hipEventElapsedTime(&wall, w0, w1));
   // results
-  std::vector<double> S((size_t)n * n_pc);
-  std::vector<long long> steps((size_t)n * n_pc);
-  std::vector<int> status((size_t)n * n_pc);
-  BCHK(hipMemcpy(rd.data(), B.rd_d, sizeof(sc::RampDev) * n, hipMemcpyDeviceToHost));
-  BCHK(hipMemcpy(S.data(), B.S_d, sizeof(double) * n * n_pc, hipMemcpyDeviceToHost));
-  BCHK(hipMemcpy(steps.data(), B.steps_d, sizeof(long long) * n * n_pc, hipMemcpyDeviceToHost));
-  BCHK(hipMemcpy(status.data(), B.status_d, sizeof(int) * n * n_pc, hipMemcpyDeviceToHost));
+  BCHK(hipMemcpyAsync(B.mem_h + B.res_lo, B.mem_d + B.res_lo, B.res_hi - B.res_lo,
+                      hipMemcpyDeviceToHost, B.stream));
+  BCHK(hipStreamSynchronize(B.stream));
   bool warn = false, failed = false;
   long long node_updates = 0, fluid_updates = 0, lattice_steps = 0;
   for (int t = 0; t < n; ++t) {
-    const sc::RampDev &R = rd[t];
+    const sc::RampDev &R = B.rd[t];
     for (int i = 0; i < n_pc; ++i) {
-      out[t].S[i] = S[(size_t)t * n_pc + i];
-      out[t].steps[i] = steps[(size_t)t * n_pc + i];
-      out[t].status[i] = status[(size_t)t * n_pc + i];
+      out[t].S[i] = B.S[(size_t)t * n_pc + i];
+      out[t].steps[i] = B.steps[(size_t)t * n_pc + i];
+      out[t].status[i] = B.status[(size_t)t * n_pc + i];
     }
     out[t].invaded_at = R.invaded_at;
     out[t].n_bisect = R.n_bisect;

@@ -87,12 +87,22 @@ struct lbm_throat {
 namespace lbmh {
 
 void set_err(const char *fmt, ...);
-// lbm_throat_init, in the compact numbering whatever the box
-int init_compact(const lbm_params *p, lbm_throat_t *out);
-// refresh the device descriptor
-int sync_desc(lbm_throat *h);
-int set_rho_in(lbm_throat *h, double r);
-int copy_state(lbm_throat *h, float *dst, const float *src);
+// check the parameters and take them into a fresh handle (no device call)
+int describe(const lbm_params *p, lbm_throat *h);
+// the descriptor h->desc from the handle's buffers and parameters
+void fill_desc(lbm_throat *h);
+sc::Dom dom(const lbm_throat *h);
+// spheres of a subdomain and their bins, as the voxelisation reads them
+struct Geometry {
+  std::vector<double> sph;  // (cx, cy, cz, r); at least one
+  std::vector<int> bin_start, bin_ids;
+  int ncx = 0, ncy = 0, ncz = 0;
+  explicit Geometry(const lbm_params &p);
+  hipError_t voxelize(const lbm_params &p, const double *sph_d, const int *start_d,
+                      const int *ids_d, uint8_t *types_d, hipStream_t st) const;
+};
+// refuse a given initial state that is not finite and positive at c N + n = bad
+int check_rho_init(const lbm_throat *h, unsigned long long bad);
 // whether the two passes need 64-bit addresses
 inline bool wide(const lbm_throat *h) {
   return sizeof(float) * sc::pop_elems(h->n_numbers) > sc::kNarrowBytes ||

@@ -169,16 +169,18 @@ hipError_t launch_row_counts(const uint8_t *types, int nx, int ny, int nz, uint3
                              hipStream_t st);
 // host: first number of each row in the compact numbering, from its count, in
 // place; returns the number of nodes
-size_t number_rows(std::vector<uint32_t> &rows, int ny, int nz);
+size_t number_rows(uint32_t *rows, int ny, int nz);
 // index map and positions: compact from the rows' first numbers, or (rows
 // null) bricks, whose live nodes are listed row by row in the same order
 hipError_t launch_number(const uint8_t *types, int nx, int ny, int nz, int per,
                          const uint32_t *rows, bool bricks, uint32_t *map, uint32_t *pos,
                          hipStream_t st);
 hipError_t launch_links(const uint8_t *types, const Dom &d, uint32_t *mask, hipStream_t st);
+// initial state; with a given one (rho_init [2][N]), *bad falls to the first
+// c N + n at which it is not finite and positive on a fluid node
 hipError_t launch_init(const Dom &d, const Phys &P, const double *rho_init, double rho_major,
                        double rho_minor, int z_front, const double *rres_d, float *g,
-                       hipStream_t st);
+                       unsigned long long *bad, hipStream_t st);
 // one time step of every active subdomain in `throats` over the listed items
 // (device arrays) at launch shape tx, ty.  wide: some buffer or index map
 // exceeds kNarrowBytes (two passes).  zper_ids (device, n_zper entries): the
@@ -224,6 +226,8 @@ struct RedInfo {
   long long probe;  // number of the probe node or -1
   double phib;      // bulk order parameter of the saturation map
 };
+// replace the map position that info[t].probe holds by the number found there
+hipError_t launch_probe_numbers(const Throat *throats, int n, RedInfo *info, hipStream_t st);
 constexpr int kRedNodes = 1024;
 struct RedChunk {
   int throat;

@@ -841,7 +841,7 @@ hipError_t launch_row_counts(const uint8_t *types, int nx, int ny, int nz, uint3
   return hipGetLastError();
 }
 
-size_t number_rows(std::vector<uint32_t> &rows, int ny, int nz) {
+size_t number_rows(uint32_t *rows, int ny, int nz) {
   size_t n = 0;
   for (int Y = 0; Y < ny; Y += kGroupY)
     for (int z = 0; z < nz; ++z)
@@ -914,6 +914,18 @@ hipError_t launch_number(const uint8_t *types, int nx, int ny, int nz, int per,
   const size_t M = map_elems(nx, ny, nz);
   const unsigned grid = (unsigned)std::min<size_t>((M + 255) / 256, 65536);
   hipLaunchKernelGGL(k_number_rest, dim3(grid), dim3(256), 0, st, types, nx, ny, nz, per, map);
+  return hipGetLastError();
+}
+
+// number of every subdomain's probe node, whose map position info[t].probe holds
+__global__ void k_probe_numbers(const Throat *throats, int n, RedInfo *info) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < n) info[t].probe = throats[t].map[info[t].probe];
+}
+
+hipError_t launch_probe_numbers(const Throat *throats, int n, RedInfo *info, hipStream_t st) {
+  hipLaunchKernelGGL(k_probe_numbers, dim3((unsigned)(n + 255) / 256), dim3(256), 0, st, throats,
+                     n, info);
   return hipGetLastError();
 }
 
@@ -1019,12 +1031,17 @@ __device__ __forceinline__ double rho0_of(const Dom &d, const double *rho_init, 
 }
 
 __global__ void k_init(Dom d, double rho_ref, const double *rho_init, double maj, double mnr,
-                       int z_front, const double *rres, float *g) {
+                       int z_front, const double *rres, float *g, unsigned long long *bad) {
   for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < d.N;
        n += (size_t)gridDim.x * blockDim.x) {
     const int x = (int)(n % d.nx), y = (int)((n / d.nx) % d.ny), z = (int)(n / ((size_t)d.nx * d.ny));
     const uint32_t i = d.map[map_pos(d.nx, d.ny, x, y, z)];
     if (i == kNoNode) continue;
+    if (rho_init && class_at(d, x, y, z) == kFluid)
+      for (int c = 0; c < 2; ++c) {
+        const double r = rho_init[c * d.N + n];
+        if (!(isfinite(r) && r > 0)) atomicMin(bad, (unsigned long long)(c * d.N + n));
+      }
     float *slot = g + node_elem(i);
 #pragma unroll
     for (int k = 0; k < 19; ++k) {
@@ -1042,10 +1059,11 @@ __global__ void k_init(Dom d, double rho_ref, const double *rho_init, double maj
 }
 
 hipError_t launch_init(const Dom &d, const Phys &P, const double *rho_init, double maj, double mnr,
-                       int z_front, const double *rres_d, float *g, hipStream_t st) {
+                       int z_front, const double *rres_d, float *g, unsigned long long *bad,
+                       hipStream_t st) {
   const unsigned blocks = (unsigned)std::min<size_t>((d.N + 255) / 256, 65536);
   hipLaunchKernelGGL(k_init, dim3(blocks), dim3(256), 0, st, d, (double)P.rho_ref, rho_init, maj,
-                     mnr, z_front, rres_d, g);
+                     mnr, z_front, rres_d, g, bad);
   return hipGetLastError();
 }
 
