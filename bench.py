@@ -109,7 +109,7 @@ def step_kernels(schedule):
     if schedule[0] == lbm.LBM_SCHED_NODE_LIST:
         return ("k_dens + k_node (two passes over the non-solid nodes: densities, then fused pull + "
                 "cohesion/adhesion + BGK); figures per step")
-    return (f"k_step<{schedule[0]},{schedule[1]}> lz {schedule[2]} (fused pull + moments + "
+    return (f"k_step<{schedule[0]},{2 * schedule[1]}> lz {schedule[2]} (fused pull + moments + "
             "cohesion/adhesion + BGK)")
 
 

@@ -303,22 +303,24 @@ int lbm_step_timer(lbm_throat_t h, int enable, double *total_ms, long long *laun
 
 /* Launch shape of the step: tile (tx, ty) in {(32, 4), (32, 8), (64, 4),
  * (16, 4), (16, 8), (8, 8)} marching a z-segment of lz (>= 1) planes in one
- * fused pass; 0 keeps the current value.  tx = LBM_SCHED_NODE_LIST selects
- * two passes over the non-solid nodes instead (ty and lz are ignored and read
- * back as 0).  Only a nearly all-fluid box of 4 million nodes or more is
- * stored so that it can be stepped in tiles: any other subdomain takes every
- * shape, reports it and runs the two passes.  All shapes give bit-identical
- * results. */
+ * fused pass, a workgroup taking two such tiles on top of each other in y; 0
+ * keeps the current value.  tx = LBM_SCHED_NODE_LIST selects two passes over
+ * the non-solid nodes instead (ty and lz are ignored and read back as 0).  A
+ * box of 2 million nodes or more, three quarters of them not solid, is stored
+ * so that it is stepped in tiles, any other so that it is stepped in two
+ * passes: every subdomain takes every shape and reports it, but one that is
+ * not its own leaves the step as it is (two passes, or the default tiles).
+ * All shapes give bit-identical results. */
 #define LBM_SCHED_NODE_LIST (-1)
 int lbm_set_schedule(lbm_throat_t h, int tx, int ty, int lz);
 
 /* Autotune the launch shape for this subdomain.  A subdomain that has only
  * the two passes (see lbm_set_schedule) gets that shape at once.  Otherwise:
- * time `trial_steps` steps for every tile shape in increasing z-segment length (up to the first that
- * is 1.5x slower than the shape's best) and for the two passes, time the
- * candidates within 1.25x of the best once more (each keeps its faster
- * time), keep the fastest and return it (outputs may be NULL).  The trials step the state forward with
- * alternating buffers, as a drain does, from a copy that is restored at the
+ * time `trial_steps` steps for every tile shape in increasing z-segment length
+ * (up to the first that is 1.5x slower than the shape's best) and for the
+ * default shape, time the candidates within 1.25x of the best once more (each
+ * keeps its faster time), keep the fastest and return it (outputs may be
+ * NULL).  The trials step the state forward with alternating buffers, as a drain does, from a copy that is restored at the
  * end, so the state is unchanged; the copy takes one more population buffer
  * of device memory while tuning (LBM_ENOMEM if it cannot be had).
  * Synchronous. */

@@ -97,9 +97,35 @@ void fill_phys(lbm_throat *h) {
     }
 }
 
-// launch shape the step runs at: a compact subdomain has the two passes only
+// Tiles of 32 x 16 nodes (64 x 8 measured 1 % behind) in the number of
+// z-segments that leaves the fewest planes to march: a CU holds one workgroup,
+// so a launch is ceil(workgroups / 256) rounds of a segment and about eight
+// planes' time to fill the pipeline.  us a step: 256^3 segments of 16, 32, 64,
+// 128 planes 1274, 1216, 1185, 1150; 192^3 of 16, 32, 64, 128 617, 589, 567,
+// 931 (144 workgroups, one of two segments short).
+sc::Sched default_schedule(int nx, int ny, int nz) {
+  sc::Sched s{32, 8, nz};
+  const int rows = sc::tile_rows(s.ty);
+  const long long columns = (long long)((nx + s.tx - 1) / s.tx) * ((ny + rows - 1) / rows);
+  long long best = LLONG_MAX;
+  for (int n = 1; n <= std::max(1, nz / 16); ++n) {
+    const int lz = (nz + n - 1) / n;
+    const long long segments = (nz + lz - 1) / lz;
+    const long long t = (columns * segments + 255) / 256 * (lz + 8);
+    if (t < best) {
+      best = t;
+      s.lz = lz;
+    }
+  }
+  return s;
+}
+
+// launch shape the step runs at: a compact subdomain has the two passes only,
+// one in bricks the tiles only (the two passes over bricks touch four lines
+// where tiles touch one: 4200 us a step at 256^3 against 1154)
 sc::Sched shape_of(const lbm_throat *h) {
-  return h->bricks ? h->sched : sc::Sched{sc::kListTx, 0, 0};
+  if (!h->bricks) return sc::Sched{sc::kListTx, 0, 0};
+  return h->sched.tx == sc::kListTx ? default_schedule(h->nx, h->ny, h->nz) : h->sched;
 }
 
 // the descriptor: buffers, sizes, tile grid, parameters
@@ -123,7 +149,8 @@ void fill_desc(lbm_throat *h) {
   const sc::Sched s = shape_of(h);
   const bool tiled = s.tx != sc::kListTx;
   T.ntx = tiled ? (h->nx + s.tx - 1) / s.tx : 0;
-  T.nty = tiled ? (h->ny + s.ty - 1) / s.ty : 0;
+  const int rows = sc::tile_rows(s.ty);
+  T.nty = tiled ? (h->ny + rows - 1) / rows : 0;
   T.lz = s.lz;
 }
 
@@ -143,7 +170,8 @@ int rebuild_tiles(lbm_throat *h) {
   if (s.tx == sc::kListTx)
     sc::list_items(h->n_live, 0, list);
   else
-    sc::list_tiles(h->brick_live.data(), h->nx, h->ny, h->nz, s.tx, s.ty, s.lz, 0, list);
+    sc::list_tiles(h->brick_live.data(), h->nx, h->ny, h->nz, s.tx, sc::tile_rows(s.ty), s.lz, 0,
+                   list);
   if (list.size() > h->tiles_cap) {
     if (h->tiles_d) HIPCHK(hipStreamSynchronize(h->stream));
     if (h->tiles_d) (void)hipFree(h->tiles_d);
@@ -183,17 +211,6 @@ sc::Dom dom(const lbm_throat *h, const float *src, float *dst) {
   d.per = h->per;
   d.res = h->bc[2] == LBM_BC_RESERVOIR;
   return d;
-}
-
-sc::Sched default_schedule(int nx, int ny, int nz) {
-  sc::Sched s;
-  const int w64 = (nx + 63) / 64 * 64, w32 = (nx + 31) / 32 * 32;
-  s.tx = w32 < w64 ? 32 : 64;
-  s.ty = s.tx == 64 ? 4 : 8;
-  const long long ntx = (nx + s.tx - 1) / s.tx, nty = (ny + s.ty - 1) / s.ty;
-  long long lz = (ntx * nty * nz + 1023) / 1024;
-  s.lz = (int)std::max(4LL, std::min<long long>(64, lz));
-  return s;
 }
 
 void fill_handle(const lbm_params *p, lbm_throat *h) {
@@ -398,11 +415,13 @@ namespace {
 
 // A subdomain is kept in bricks and stepped in tiles from this share of
 // non-solid nodes in the padded box and this many padded nodes on.  Step times
-// in us, two passes / tiles: 512 x 10^3 nodes (80^3) all fluid 45 / 56, 128^3
-// 191 / 193, 192^3 665 / 599, 256^3 1520 / 1324; 256^3 with 10, 20 and 30 %
-// solid 1426 / 1252, 1264 / 1211, 1124 / 1131; 192^3 with 20 % 552 / 559.
-constexpr double kTileFill = 0.85;
-constexpr size_t kTileNodes = (size_t)1 << 22;
+// in us, two passes / tiles, all fluid: 96^3 71 / 88, 112^3 123 / 145, 128^3
+// 192 / 168, 160^3 377 / 307, 192^3 667 / 569, 256^3 1523 / 1154; with 10, 20,
+// 30 and 40 % solid 128^3 184 / 159, 165 / 151, 135 / 149, 128 / 144; 192^3
+// 605 / 543, 553 / 522, 486 / 498, 424 / 480; 256^3 1414 / 1133, 1268 / 1099,
+// 1130 / 1047, 975 / 982.
+constexpr double kTileFill = 0.75;
+constexpr size_t kTileNodes = (size_t)1 << 21;
 
 int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
   g_err.clear();
@@ -536,8 +555,8 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
     set_err("hipMemGetInfo failed");
     return fail_rows(LBM_EHIP);
   }
-  const size_t need = 2 * pop_bytes + 8 * h->n_numbers + 4 * h->n_live +
-                      (h->bricks ? 4 * h->N : 0) + (64u << 20);
+  const size_t need = 2 * pop_bytes + 4 * h->n_live +
+                      (h->bricks ? 4 * h->N : 8 * h->n_numbers) + (64u << 20);
   if (need > free_b) {
     set_err("needs %zu bytes of device memory, %zu free", need, free_b);
     return fail_rows(LBM_ENOMEM);
@@ -551,7 +570,7 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
   };
   if (!alloc(&h->g[0], pop_bytes) || !alloc(&h->g[1], pop_bytes) ||
       !alloc(&h->pos_d, sizeof(uint32_t) * h->n_live) ||
-      !alloc(&h->rho_d, sizeof(float2) * h->n_numbers) ||
+      (!h->bricks && !alloc(&h->rho_d, sizeof(float2) * h->n_numbers)) ||
       (h->bricks && !alloc(&h->mask_d, sizeof(uint32_t) * h->N)) ||
       !alloc(&h->chunks_d, sizeof(sc::RedChunk) * chunks.size()) ||
       !alloc(&h->partials, sizeof(double) * 3 * chunks.size()) ||
@@ -1454,12 +1473,12 @@ int lbm_autotune(lbm_throat_t h, int trial_steps, int *tx, int *ty, int *lz) {
     return LBM_ENOMEM;
   }
   HIPCHK(hipMemcpyAsync(keep.d, h->g[h->cur], keep.bytes, hipMemcpyDeviceToDevice, h->stream));
-  static const int lzs[7] = {1, 2, 4, 8, 16, 32, 64};
+  static const int lzs[8] = {1, 2, 4, 8, 16, 32, 64, 128};
   std::vector<sc::Sched> cand;
   for (const auto &sh : sc::kShapes)
     for (int l : lzs)
       if (l <= h->nz) cand.push_back(sc::Sched{sh[0], sh[1], l});
-  cand.push_back(sc::Sched{sc::kListTx, 0, 0});
+  cand.push_back(default_schedule(h->nx, h->ny, h->nz));
   std::vector<double> t(cand.size(), INFINITY);
   auto trial = [&](size_t c) -> int {
     const sc::Sched &s = cand[c];

@@ -123,6 +123,8 @@ constexpr int kListTx = -1;
 // tile shapes (tx, ty) the fused step is built for; lz is free (>= 1)
 constexpr int kNumShapes = 6;
 constexpr int kShapes[kNumShapes][2] = {{32, 4}, {32, 8}, {64, 4}, {16, 4}, {16, 8}, {8, 8}};
+// rows of a workgroup's tile: two of the schedule's tiles in y
+constexpr int tile_rows(int ty) { return 2 * ty; }
 
 // one subdomain as the step sees it (a launch covers one or many of these)
 struct Throat {

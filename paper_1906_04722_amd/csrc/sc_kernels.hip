@@ -495,38 +495,32 @@ __device__ __forceinline__ void brick_pull(const Dom &d, uint32_t m, int X, int 
   brick_rec<0>(b0, b1, m, own, P, py, px, v);
 }
 
-// Density seen by the interaction sums at (X, Y, Z): zero on solid nodes and
-// beyond walls, the imposed value on bath nodes, Eq. 2 on fluid nodes.  With
-// KEEP, the pulled populations, the mask word and the two FP64 sums of the
-// shifted populations (zero unless the node is fluid) are returned for the
-// collision of this node.
-template <bool KEEP>
-__device__ __forceinline__ float2 density_at(const Dom &d, const Phys &P, int X, int Y, int Z,
-                                             float (&v)[2][19], uint32_t &mword,
-                                             double (&ds)[2]) {
-  if (KEEP) ds[0] = ds[1] = 0.0;
+// mask word of a node as the march sees it: solid beyond a wall
+__device__ __forceinline__ uint32_t mask_at(const Dom &d, int X, int Y, int Z) {
   const long long n = node_of(d, X, Y, Z);
-  if (n < 0) {
-    if (KEEP) mword = kSolid << kTypeShift;
-    return make_float2(0.f, 0.f);
-  }
-  const uint32_t m = d.mask[n];
-  if (KEEP) mword = m;
+  return n < 0 ? kSolid << kTypeShift : d.mask[n];
+}
+
+// the pulls of a fluid node (others keep v undefined)
+__device__ __forceinline__ void pull_fluid(const Dom &d, uint32_t m, int X, int Y, int Z,
+                                           float (&v)[2][19]) {
+  if (m >> kTypeShift == kFluid) brick_pull(d, m, X, Y, wrap(Z, d.nz), v);
+}
+
+// Density seen by the interaction sums: zero on solid nodes and beyond walls,
+// the imposed value on bath nodes, Eq. 2 on fluid nodes, whose pulled
+// populations are v.  ds: the two FP64 sums of a fluid node's shifted
+// populations (zero otherwise), for its collision.
+__device__ __forceinline__ float2 density_of(const Phys &P, uint32_t m, const float (&v)[2][19],
+                                             double (&ds)[2]) {
+  ds[0] = ds[1] = 0.0;
   const uint32_t t = m >> kTypeShift;
   if (t == kSolid) return make_float2(0.f, 0.f);
   if (t == kResIn) return make_float2(P.rres[0][0], P.rres[0][1]);
   if (t == kResOut) return make_float2(P.rres[1][0], P.rres[1][1]);
-  int X2 = wrap(X, d.nx), Y2 = wrap(Y, d.ny), Z2 = wrap(Z, d.nz);
-  if (KEEP) {
-    brick_pull(d, m, X2, Y2, Z2, v);
-    ds[0] = sum19(v[0]);
-    ds[1] = sum19(v[1]);
-    return make_float2((float)((acc_t)P.rho_ref + ds[0]), (float)((acc_t)P.rho_ref + ds[1]));
-  } else {
-    float t2[2][19];
-    brick_pull(d, m, X2, Y2, Z2, t2);
-    return make_float2((float)((acc_t)P.rho_ref + sum19(t2[0])), (float)((acc_t)P.rho_ref + sum19(t2[1])));
-  }
+  ds[0] = sum19(v[0]);
+  ds[1] = sum19(v[1]);
+  return make_float2((float)((acc_t)P.rho_ref + ds[0]), (float)((acc_t)P.rho_ref + ds[1]));
 }
 
 // Store the post-collision populations of the node at (X, Y, Z) (the ghost
@@ -548,17 +542,25 @@ __device__ __forceinline__ void brick_store(const Dom &d, int X, int Y, int Z,
 
 // A workgroup owns a TX x TY column of nodes and marches it through a
 // z-segment, software-pipelined over three planes.  Entering iteration Z, the
-// thread holds its own node of plane Z in registers, its node of plane Z+1 in
-// a private LDS slot, and the LDS density ring holds planes Z-1..Z+1.  It
-//   1. issues the pulls of plane Z+2 for its halo node and its own node,
-//   2. sums the halo pull into the ring (plane Z+2),
-//   3. collides plane Z with the 18-neighbour density stencil while the own
-//      pull is still in flight, and stores it,
-//   4. sums the own pull into the ring, rotates plane Z+1 from LDS into
-//      registers and parks plane Z+2 in LDS,
-//   5. synchronises the workgroup.
+// thread holds its own nodes of planes Z and Z+1 in registers, the mask words
+// of plane Z+2, and the LDS density ring holds planes Z-1..Z+1.  It
+//   1. issues the pulls of plane Z+2 for its halo node and its own node, and
+//      the loads of plane Z+3's mask words,
+//   2. collides plane Z with the 18-neighbour density stencil while those are
+//      in flight, and stores it,
+//   3. sums the pulls into the ring (plane Z+2) and moves the planes down,
+//   4. synchronises the workgroup.
 // Every population is read from memory once per step (halo pulls re-read
 // neighbour tiles' lines, which are normally still in L2).
+//
+// Bound: the lines exchanged between L2 and memory, and how much of a plane
+// the L2s can hold until the neighbouring tiles have read it.  So the tile is
+// as large as the registers allow, 512 threads of up to 256 registers (a CU's
+// two wavefronts per SIMD), and no population waits in LDS.  All fluid, us a
+// step, against tiles of 256 threads with the middle plane in LDS and three
+// workgroups a CU (three times the lines through L1, 1.57 times the population
+// reads through L2): 256^3 1150 / 1325 (304 B a node: 4.4 TB/s), 192^3 567 /
+// 672.  Halo and own pulls one after the other: 1238 and 610.
 template <int TX, int TY>
 __device__ __forceinline__ void halo_slot(int h, int &hx, int &hy) {
   constexpr int HR = 2 * (TX + 2);
@@ -572,20 +574,14 @@ __device__ __forceinline__ void halo_slot(int h, int &hx, int &hy) {
   }
 }
 
-// At most 168 VGPRs per lane: three waves per SIMD, which the z-march needs
-// to keep enough pulls in flight.
 template <int TX, int TY>
-__global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(3))) void k_step(
-    const Throat *__restrict__ throats,
-                                                 const TileRef *__restrict__ tiles, int ntiles,
-                                                 int parity) {
+__global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step(
+    const Throat *__restrict__ throats, const TileRef *__restrict__ tiles, int ntiles,
+    int parity) {
   constexpr int NT = TX * TY;
   constexpr int H = 2 * (TX + 2) + 2 * TY;  // halo ring of one plane
   static_assert(NT >= H, "tile too small for its halo");
   __shared__ float2 ring[4][TY + 2][TX + 2];
-  __shared__ float stage[38][NT];
-  __shared__ uint32_t stage_m[NT];
-
   // lanes follow the storage bricks: 32 consecutive lanes own one 8 x 4
   // brick, so each population load or store of a wavefront is whole lines
   static_assert(TX % kBX == 0 && TY % kBY == 0, "tiles are whole bricks");
@@ -617,35 +613,45 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(3))) voi
   const bool halo = tid < H;
   int hx = 0, hy = 0;
   if (halo) halo_slot<TX, TY>(tid, hx, hy);
+  const int X = wrap(x, d.nx), Y = wrap(y, d.ny);
+  const int XH = wrap(x0 + hx, d.nx), YH = wrap(y0 + hy, d.ny);
 
-  float cur[2][19], nxt[2][19], hv[2][19];
-  uint32_t mcur = 0, mnxt = 0, mh;
+  float cur[2][19], mid[2][19], nxt[2][19], hv[2][19];
+  uint32_t mcur, mmid, mnxt, mh = kSolid << kTypeShift;
   // FP64 population sums of the own node at planes Z, Z+1, Z+2 (for collide)
   double dcur[2], dmid[2], dnxt[2], dh[2];
 
   // prologue: densities of planes z0-1 .. z0+1, populations of z0 and z0+1
-  ring[(z0 - 1) & 3][ty + 1][tx + 1] = density_at<false>(d, P, x, y, z0 - 1, hv, mh, dh);
-  if (halo) ring[(z0 - 1) & 3][hy + 1][hx + 1] = density_at<false>(d, P, x0 + hx, y0 + hy, z0 - 1, hv, mh, dh);
-  ring[z0 & 3][ty + 1][tx + 1] = density_at<true>(d, P, x, y, z0, cur, mcur, dcur);
-  if (halo) ring[z0 & 3][hy + 1][hx + 1] = density_at<false>(d, P, x0 + hx, y0 + hy, z0, hv, mh, dh);
-  ring[(z0 + 1) & 3][ty + 1][tx + 1] = density_at<true>(d, P, x, y, z0 + 1, nxt, mnxt, dmid);
-  if (halo) ring[(z0 + 1) & 3][hy + 1][hx + 1] = density_at<false>(d, P, x0 + hx, y0 + hy, z0 + 1, hv, mh, dh);
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int k = 0; k < 19; ++k) stage[c * 19 + k][tid] = nxt[c][k];
-  stage_m[tid] = mnxt;
+  auto own_plane = [&](int Z, uint32_t &m, float (&v)[2][19], double (&ds)[2]) {
+    m = mask_at(d, x, y, Z);
+    pull_fluid(d, m, X, Y, Z, v);
+    ring[Z & 3][ty + 1][tx + 1] = density_of(P, m, v, ds);
+  };
+  auto halo_plane = [&](int Z) {
+    if (!halo) return;
+    mh = mask_at(d, x0 + hx, y0 + hy, Z);
+    pull_fluid(d, mh, XH, YH, Z, hv);
+    ring[Z & 3][hy + 1][hx + 1] = density_of(P, mh, hv, dh);
+  };
+  own_plane(z0 - 1, mcur, cur, dcur);
+  halo_plane(z0 - 1);
+  own_plane(z0, mcur, cur, dcur);
+  halo_plane(z0);
+  own_plane(z0 + 1, mmid, mid, dmid);
+  halo_plane(z0 + 1);
+  mnxt = mask_at(d, x, y, min(z0 + 2, z1));
+  if (halo) mh = mask_at(d, x0 + hx, y0 + hy, min(z0 + 2, z1));
   __syncthreads();
 
   for (int Z = z0; Z < z1; ++Z) {
     const bool ahead = Z + 2 <= z1;  // plane Z+2 is needed (density halo or next own)
-    // 1-2. halo node of plane Z+2, then own node of plane Z+2 (left in flight)
-    if (ahead && halo)
-      ring[(Z + 2) & 3][hy + 1][hx + 1] = density_at<false>(d, P, x0 + hx, y0 + hy, Z + 2, hv, mh, dh);
-    float2 rho_ahead = make_float2(0.f, 0.f);
-    dnxt[0] = dnxt[1] = 0.0;
-    if (ahead) rho_ahead = density_at<true>(d, P, x, y, Z + 2, nxt, mnxt, dnxt);
-    // 3. collide plane Z
+    if (ahead) {
+      pull_fluid(d, mh, XH, YH, Z + 2, hv);
+      pull_fluid(d, mnxt, X, Y, Z + 2, nxt);
+    }
+    const int Z3 = min(Z + 3, z1);
+    const uint32_t mnxt3 = mask_at(d, x, y, Z3);
+    const uint32_t mh3 = halo ? mask_at(d, x0 + hx, y0 + hy, Z3) : mh;
     if (own) {
       const uint32_t t = mcur >> kTypeShift;
       if (t == kFluid) {
@@ -669,29 +675,30 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(3))) voi
         brick_store(d, x, y, Z, cur);
       }
     }
-    // 4. publish plane Z+2, rotate Z+1 -> registers, Z+2 -> LDS
-    if (ahead) ring[(Z + 2) & 3][ty + 1][tx + 1] = rho_ahead;
+    if (ahead) {
+      if (halo) ring[(Z + 2) & 3][hy + 1][hx + 1] = density_of(P, mh, hv, dh);
+      ring[(Z + 2) & 3][ty + 1][tx + 1] = density_of(P, mnxt, nxt, dnxt);
+    }
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < 2; ++c) {
 #pragma unroll
       for (int k = 0; k < 19; ++k) {
-        cur[c][k] = stage[c * 19 + k][tid];
-        stage[c * 19 + k][tid] = nxt[c][k];
+        cur[c][k] = mid[c][k];
+        mid[c][k] = nxt[c][k];
       }
-    mcur = stage_m[tid];
-    stage_m[tid] = mnxt;
-    dcur[0] = dmid[0];
-    dcur[1] = dmid[1];
-    dmid[0] = dnxt[0];
-    dmid[1] = dnxt[1];
-    // 5.
+      dcur[c] = dmid[c];
+      dmid[c] = dnxt[c];
+    }
+    mcur = mmid;
+    mmid = mnxt;
+    mnxt = mnxt3;
+    mh = mh3;
     __syncthreads();
   }
 }
 
 bool schedule_valid(const Sched &s) {
   if (s.tx == kListTx) return true;  // two passes
-  // (64, 8) and (32, 16) would need 2 x 78 KB of LDS staging: not offered
   if (s.lz < 1) return false;
   for (int i = 0; i < kNumShapes; ++i)
     if (s.tx == kShapes[i][0] && s.ty == kShapes[i][1]) return true;
@@ -759,15 +766,15 @@ static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, 
     return hipGetLastError();
   }
   if (tx == 32) {
-    if (ty == 4) return step_as<32, 4>(th, tiles, ntiles, parity, st);
-    return step_as<32, 8>(th, tiles, ntiles, parity, st);
+    if (ty == 4) return step_as<32, tile_rows(4)>(th, tiles, ntiles, parity, st);
+    return step_as<32, tile_rows(8)>(th, tiles, ntiles, parity, st);
   }
   if (tx == 16) {
-    if (ty == 4) return step_as<16, 4>(th, tiles, ntiles, parity, st);
-    return step_as<16, 8>(th, tiles, ntiles, parity, st);
+    if (ty == 4) return step_as<16, tile_rows(4)>(th, tiles, ntiles, parity, st);
+    return step_as<16, tile_rows(8)>(th, tiles, ntiles, parity, st);
   }
-  if (tx == 8) return step_as<8, 8>(th, tiles, ntiles, parity, st);
-  return step_as<64, 4>(th, tiles, ntiles, parity, st);
+  if (tx == 8) return step_as<8, tile_rows(8)>(th, tiles, ntiles, parity, st);
+  return step_as<64, tile_rows(4)>(th, tiles, ntiles, parity, st);
 }
 
 hipError_t launch_step(const Throat *th, const TileRef *tiles, int ntiles, int tx, int ty,
