@@ -162,16 +162,17 @@ int sync_desc(lbm_throat *h) {
   return LBM_OK;
 }
 
-// work items of the current schedule: its tiles that hold a non-solid node,
-// or the items of the two passes
+// work items of the current schedule: its tiles that hold a non-solid node, or
+// the number of items of the two passes (one subdomain's need no list)
 int rebuild_tiles(lbm_throat *h) {
   std::vector<sc::TileRef> list;
   const sc::Sched s = shape_of(h);
-  if (s.tx == sc::kListTx)
-    sc::list_items(h->n_live, 0, list);
-  else
-    sc::list_tiles(h->brick_live.data(), h->nx, h->ny, h->nz, s.tx, sc::tile_rows(s.ty), s.lz, 0,
-                   list);
+  if (s.tx == sc::kListTx) {
+    h->ntiles = (int)sc::list_count(h->n_live);
+    return sync_desc(h);
+  }
+  sc::list_tiles(h->brick_live.data(), h->nx, h->ny, h->nz, s.tx, sc::tile_rows(s.ty), s.lz, 0,
+                 list);
   if (list.size() > h->tiles_cap) {
     if (h->tiles_d) HIPCHK(hipStreamSynchronize(h->stream));
     if (h->tiles_d) (void)hipFree(h->tiles_d);

@@ -142,7 +142,8 @@ struct Throat {
 };
 
 // a work item of the two passes: kListNodes consecutive nodes of a subdomain
-constexpr int kListNodes = 128;
+constexpr int kListNodes = 64;
+inline size_t list_count(size_t n_live) { return (n_live + kListNodes - 1) / kListNodes; }
 // one item of work: subdomain and its packed tile coordinate
 // tix + ntx * (tiy + nty * tiz), or its index among the subdomain's items
 struct TileRef {

@@ -190,30 +190,33 @@ __device__ __forceinline__ acc_t sum19(const float (&a)[19]) {
 // the mass step after step.  Momenta are summed from opposite-pair
 // differences.  drd: the FP64 sums of each component's 19 shifted
 // populations, as taken when the node was pulled; m: the node's cut links (bits 1..18).
-__device__ __forceinline__ void collide(const Phys &P, uint32_t m, const float (&Sw)[3],
-                                        const float (&Sn)[3], const double (&drd)[2],
-                                        float (&v)[2][19]) {
-  float dr[2], rho[2], j[2][3];
+//
+// It comes in parts, so that one lane can take both components of a node or
+// one lane each.
+
+// density shift, density and momentum of one component
+__device__ __forceinline__ void moments(const Phys &P, double drd, const float (&v)[19], float &dr,
+                                        float &rho, float (&j)[3]) {
+  dr = (float)drd;
+  rho = (float)((double)P.rho_ref + drd);
+  float jx = 0.f, jy = 0.f, jz = 0.f;
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    dr[c] = (float)drd[c];
-    rho[c] = (float)((double)P.rho_ref + drd[c]);
-    float jx = 0.f, jy = 0.f, jz = 0.f;
-#pragma unroll
-    for (int k = 1; k < 19; ++k) {
-      if (k > opp(k)) continue;
-      const float dk = v[c][k] - v[c][opp(k)];
-      if (ex(k)) jx += ex(k) > 0 ? dk : -dk;
-      if (ey(k)) jy += ey(k) > 0 ? dk : -dk;
-      if (ez(k)) jz += ez(k) > 0 ? dk : -dk;
-    }
-    j[c][0] = jx;
-    j[c][1] = jy;
-    j[c][2] = jz;
+  for (int k = 1; k < 19; ++k) {
+    if (k > opp(k)) continue;
+    const float dk = v[k] - v[opp(k)];
+    if (ex(k)) jx += ex(k) > 0 ? dk : -dk;
+    if (ey(k)) jy += ey(k) > 0 ? dk : -dk;
+    if (ez(k)) jz += ez(k) > 0 ? dk : -dk;
   }
-  // adhesion direction: zero (the same +0 the sum gives) when no link is cut
-  float A[3] = {0.f, 0.f, 0.f};
-  if ((m & kLinkBits) != 0u)
+  j[0] = jx;
+  j[1] = jy;
+  j[2] = jz;
+}
+
+// adhesion direction: zero (the same +0 the sum gives) when no link is cut
+__device__ __forceinline__ void adhesion(uint32_t m, float (&A)[3]) {
+  A[0] = A[1] = A[2] = 0.f;
+  if ((m & kLinkBits) == 0u) return;
 #pragma unroll
   for (int k = 1; k < 19; ++k) {
     const float s = (float)((m >> opp(k)) & 1u) * wf(k);
@@ -221,42 +224,63 @@ __device__ __forceinline__ void collide(const Phys &P, uint32_t m, const float (
     if (ey(k)) A[1] += ey(k) > 0 ? s : -s;
     if (ez(k)) A[2] += ez(k) > 0 ? s : -s;
   }
-  float F[2][3];
+}
+
+// force on a component: S from the other component's densities
+__device__ __forceinline__ void force(const Phys &P, float Gads, float rho, const float (&S)[3],
+                                      const float (&A)[3], float (&F)[3]) {
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    F[0][a] = -P.G * rho[0] * Sn[a] - P.Gads[0] * rho[0] * A[a];
-    F[1][a] = -P.G * rho[1] * Sw[a] - P.Gads[1] * rho[1] * A[a];
-  }
+  for (int a = 0; a < 3; ++a) F[a] = -P.G * rho * S[a] - Gads * rho * A[a];
+}
+
+// common velocity (quotients as products with three reciprocals)
+__device__ __forceinline__ void velocity(const Phys &P, float rho0, float rho1,
+                                         const float (&j0)[3], const float (&j1)[3],
+                                         float (&up)[3]) {
   const float it0 = P.itau[0], it1 = P.itau[1];
-  const float den = rho[0] * it0 + rho[1] * it1;
-  // quotients as products with three reciprocals
+  const float den = rho0 * it0 + rho1 * it1;
   const float iden = 1.0f / den;
-  float up[3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) up[a] = (j[0][a] * it0 + j[1][a] * it1) * iden;
+  for (int a = 0; a < 3; ++a) up[a] = (j0[a] * it0 + j1[a] * it1) * iden;
+}
+
+// relaxation of one component
+__device__ __forceinline__ void relax(float tc, float itc, const float (&up)[3],
+                                      const float (&F)[3], double drd, float dr, float rho,
+                                      float (&v)[19]) {
+  float u[3];
+  const float irho = 1.0f / rho;
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    float u[3];
-    const float tc = P.tau[c], itc = P.itau[c];
-    const float irho = 1.0f / rho[c];
+  for (int a = 0; a < 3; ++a) u[a] = up[a] + tc * F[a] * irho;
+  const float uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+  double rest = drd;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) u[a] = up[a] + tc * F[c][a] * irho;
-    const float uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    double rest = drd[c];
-#pragma unroll
-    for (int k = 1; k < 19; ++k) {
-      float eu = 0.f;
-      if (ex(k)) eu += ex(k) > 0 ? u[0] : -u[0];
-      if (ey(k)) eu += ey(k) > 0 ? u[1] : -u[1];
-      if (ez(k)) eu += ez(k) > 0 ? u[2] : -u[2];
-      const float geq = wf(k) * (dr[c] + rho[c] * (3.f * eu + 4.5f * eu * eu - 1.5f * uu));
-      const float g = v[c][k];
-      const float gs = g - (g - geq) * itc;
-      v[c][k] = gs;
-      rest -= (double)gs;
-    }
-    v[c][0] = (float)rest;
+  for (int k = 1; k < 19; ++k) {
+    float eu = 0.f;
+    if (ex(k)) eu += ex(k) > 0 ? u[0] : -u[0];
+    if (ey(k)) eu += ey(k) > 0 ? u[1] : -u[1];
+    if (ez(k)) eu += ez(k) > 0 ? u[2] : -u[2];
+    const float geq = wf(k) * (dr + rho * (3.f * eu + 4.5f * eu * eu - 1.5f * uu));
+    const float g = v[k];
+    const float gs = g - (g - geq) * itc;
+    v[k] = gs;
+    rest -= (double)gs;
   }
+  v[0] = (float)rest;
+}
+
+__device__ __forceinline__ void collide(const Phys &P, uint32_t m, const float (&Sw)[3],
+                                        const float (&Sn)[3], const double (&drd)[2],
+                                        float (&v)[2][19]) {
+  float dr[2], rho[2], j[2][3], A[3], F[2][3], up[3];
+  moments(P, drd[0], v[0], dr[0], rho[0], j[0]);
+  moments(P, drd[1], v[1], dr[1], rho[1], j[1]);
+  adhesion(m, A);
+  force(P, P.Gads[0], rho[0], Sn, A, F[0]);
+  force(P, P.Gads[1], rho[1], Sw, A, F[1]);
+  velocity(P, rho[0], rho[1], j[0], j[1], up);
+  relax(P.tau[0], P.itau[0], up, F[0], drd[0], dr[0], rho[0], v[0]);
+  relax(P.tau[1], P.itau[1], up, F[1], drd[1], dr[1], rho[1], v[1]);
 }
 
 // Store the post-collision populations of node i.  KEEP: through the caches as
@@ -294,23 +318,26 @@ __device__ __forceinline__ int xcd_item(int n) {
 // 1.02 GB written, against 1.95 and 1.02 without waste.  Before, one fused pass
 // in tiles over all nodes of the box refetched halo lines and moved partly used
 // lines: 3.7 GB and 873-893 us a step on that sample, now 660; 40-sphere
-// sample with membrane 113 -> 64 us, 96^3 throat 18.4 -> 12.9 us, 40^3 throat
-// 11.4 (33 in the default tile shape) -> 7.9 us.
+// sample with membrane 113 -> 64 us (57 with kept stores), 96^3 throat 18.4 ->
+// 12.9 us, 40^3 throat 11.4 (33 in the default tile shape) -> 6.5 us.
 //
 // Whole rows along x make a wavefront's 64 nodes pull runs of 3-4 lines per
 // population; groups of 32 rows marched through z keep the lines that links to
 // z + 1 and z - 1 share in the L2 until both have read them (raster order over
 // whole planes: 2.86 GB fetched, 676 us; blocks of 8^3: 776 us).  Workgroups of
-// 128: a small subdomain then spreads over twice the CUs of 256 (40^3 9.5 ->
-// 7.9 us, 96^3 14.5 -> 12.9), large ones do not care.  Not faster: one kernel
-// that keeps the densities of a block and its halo in LDS (929-1300 us on the
-// sample: the halo's pulls cost twice the arithmetic), and the second pass
-// trailing the first by a part that fits the 256 MB memory-side cache (690-950
-// us: the second read costs the same L2 misses).
+// one wavefront: those of two or four put a CU's wavefronts on the same SIMDs
+// or leave CUs idle where the chip is not full (us a step with workgroups of
+// 64 / 128 / 256: 1 k nodes 7.2 / 7.5 / 8.3, 41 k 8.4 / 10.1 / 8.9, 55 k 10.1
+// / 11.5, 131 k 13.2 / 13.4 / 13.3), large ones do not care.
+// Not faster: one kernel that keeps the densities of a block and its halo in
+// LDS (929-1300 us on the sample: the halo's pulls cost twice the arithmetic),
+// and the second pass trailing the first by a part that fits the 256 MB
+// memory-side cache (690-950 us: the second read costs the same L2 misses).
 __device__ __forceinline__ bool list_item(const Throat *__restrict__ throats,
                                           const TileRef *__restrict__ items, int nitems,
                                           const Throat *&T, uint32_t &i) {
-  const TileRef it = items[xcd_item(nitems)];
+  const int k = xcd_item(nitems);
+  const TileRef it = items ? items[k] : TileRef{0, k};
   T = throats + it.throat;
   i = (uint32_t)it.tile * kListNodes + threadIdx.x;
   return T->active && i < T->n_live;
@@ -412,6 +439,140 @@ __global__ __launch_bounds__(kListNodes) void k_node(const Throat *__restrict__ 
   const double ds[2] = {sum19(v[0]), sum19(v[1])};
   collide(P, m, Sw, Sn, ds, v);
   store_node<WIDE, KEEP>(T.g[parity ^ 1], n.r[0][1], v);
+}
+
+// ---- the two passes with a lane per component ---------------------------------------
+// For subdomains that leave the chip with a wavefront or less per SIMD, where a
+// step is the time of one wavefront through both kernels: lanes l and l + 32
+// share a node and take one component each, half the loads, sums and
+// relaxation per wavefront and twice the wavefronts.  They exchange density
+// and momentum for the common velocity, and each reads the other component's
+// densities for its force.  Same arithmetic, same bits.
+
+// the 32-bit value of lanes l and l + 32, in both
+__device__ __forceinline__ void both(float x, float &x0, float &x1) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false,
+                                                  false);
+  x0 = __uint_as_float(r[0]);
+  x1 = __uint_as_float(r[1]);
+}
+
+template <int K>
+__device__ __forceinline__ void pull_one(const float *src, uint32_t cofs, uint32_t i,
+                                         const Near &n, uint32_t &m, float (&v)[19]) {
+  constexpr int o = opp(K);
+  const uint32_t s = near_at<-ex(K), -ey(K), -ez(K)>(n);
+  const bool cut = K != 0 && s == kNoNode;
+  if (K != 0) m |= cut ? 1u << K : 0u;
+  const uint32_t j = cut ? i : s;
+  const uint32_t shift = cofs + (uint32_t)(cut ? (o - K) * 4 * kLine : 0);
+  v[K] = *(gcfloat *)((gcchar *)src - 4 * kLine + (size_t)(node_bytes(j) + shift) + K * 4 * kLine);
+  if constexpr (K + 1 < 19) pull_one<K + 1>(src, cofs, i, n, m, v);
+}
+
+template <int K>
+__device__ __forceinline__ void stencil_one(const float2 *rho, uint32_t cofs, const Near &n,
+                                            float (&r)[19]) {
+  const uint32_t s = near_at<ex(K), ey(K), ez(K)>(n);
+  const bool none = s == kNoNode;
+  r[K] = *(gcfloat *)((gcchar *)rho + (size_t)((none ? n.r[0][1] : s) * 8u + cofs));
+  if (none) r[K] = 0.f;
+  if constexpr (K + 1 < 19) stencil_one<K + 1>(rho, cofs, n, r);
+}
+
+// a workgroup takes half an item; c: this lane's component
+__device__ __forceinline__ bool split_item(const Throat *__restrict__ throats,
+                                           const TileRef *__restrict__ items, int nitems,
+                                           const Throat *&T, uint32_t &i, int &c) {
+  const int half = xcd_item(2 * nitems);
+  const TileRef it = items ? items[half >> 1] : TileRef{0, half >> 1};
+  T = throats + it.throat;
+  i = (uint32_t)it.tile * kListNodes + (uint32_t)(half & 1) * 32u + (threadIdx.x & 31u);
+  c = (int)(threadIdx.x >> 5);
+  return T->active && i < T->n_live;
+}
+
+__global__ __launch_bounds__(kListNodes) void k_dens_split(const Throat *__restrict__ throats,
+                                                           const TileRef *__restrict__ items,
+                                                           int nitems, int parity) {
+  const Throat *Tp;
+  uint32_t i;
+  int c;
+  if (!split_item(throats, items, nitems, Tp, i, c)) return;
+  const Throat &T = *Tp;
+  const uint32_t px = (uint32_t)(T.nx + 2 * kPad);
+  const size_t pp = (size_t)px * (size_t)(T.ny + 2 * kPad);
+  const uint32_t pos = *(gcu32 *)((gcchar *)T.pos + (size_t)i * 4);
+  const int bath = bath_of(T, pos, pp);
+  float *rho = (float *)T.rho;
+  if (bath >= 0) {
+    const float w = bath == 0 ? T.P.rres[0][0] : T.P.rres[1][0];
+    const float nw = bath == 0 ? T.P.rres[0][1] : T.P.rres[1][1];
+    rho[2 * T.map[pos] + c] = c ? nw : w;
+    return;
+  }
+  Near n;
+  uint32_t m = 0;
+  float v[19];
+  near_of<false>(T, pos, px, pp, n);
+  pull_one<0>(T.g[parity], (uint32_t)(4 * kLine) + (uint32_t)c * (19 * 4 * kLine), n.r[0][1], n, m,
+              v);
+  rho[2 * n.r[0][1] + c] = (float)((acc_t)T.P.rho_ref + sum19(v));
+}
+
+__global__ __launch_bounds__(kListNodes) void k_node_split(const Throat *__restrict__ throats,
+                                                           const TileRef *__restrict__ items,
+                                                           int nitems, int parity) {
+  const Throat *Tp;
+  uint32_t i;
+  int c;
+  if (!split_item(throats, items, nitems, Tp, i, c)) return;
+  const Throat &T = *Tp;
+  const uint32_t px = (uint32_t)(T.nx + 2 * kPad);
+  const size_t pp = (size_t)px * (size_t)(T.ny + 2 * kPad);
+  const uint32_t pos = *(gcu32 *)((gcchar *)T.pos + (size_t)i * 4);
+  const Phys P = T.P;
+  const int bath = bath_of(T, pos, pp);
+  const uint32_t cofs = (uint32_t)c * (19 * 4 * kLine);
+  uint32_t own;
+  float v[19];
+  if (bath >= 0) {
+    const float gw = bath == 0 ? P.gres[0][0] : P.gres[1][0];
+    const float gn = bath == 0 ? P.gres[0][1] : P.gres[1][1];
+    const float g = c ? gn : gw;
+#pragma unroll
+    for (int k = 0; k < 19; ++k) v[k] = wf(k) * g;
+    own = T.map[pos];
+  } else {
+    Near n;
+    uint32_t m = 0;
+    float r[19];
+    near_of<false>(T, pos, px, pp, n);
+    own = n.r[0][1];
+    pull_one<0>(T.g[parity], (uint32_t)(4 * kLine) + cofs, own, n, m, v);
+    stencil_one<1>(T.rho, (uint32_t)(1 - c) * 4u, n, r);
+    float S[3] = {0, 0, 0};
+#pragma unroll
+    for (int k = 1; k < 19; ++k) {
+      const float a = wf(k) * r[k];
+      if (ex(k)) S[0] += ex(k) > 0 ? a : -a;
+      if (ey(k)) S[1] += ey(k) > 0 ? a : -a;
+      if (ez(k)) S[2] += ez(k) > 0 ? a : -a;
+    }
+    const double drd = sum19(v);
+    float dr, rho, rho0, rho1, j[3], j0[3], j1[3], A[3], F[3], up[3];
+    moments(P, drd, v, dr, rho, j);
+    both(rho, rho0, rho1);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) both(j[a], j0[a], j1[a]);
+    adhesion(m, A);
+    force(P, c ? P.Gads[1] : P.Gads[0], rho, S, A, F);
+    velocity(P, rho0, rho1, j0, j1, up);
+    relax(c ? P.tau[1] : P.tau[0], c ? P.itau[1] : P.itau[0], up, F, drd, dr, rho, v);
+  }
+  gchar *p = (gchar *)T.g[parity ^ 1] + (size_t)(node_bytes(own) + cofs);
+#pragma unroll
+  for (int k = 0; k < 19; ++k) __builtin_nontemporal_store(v[k], (gfloat *)(p + k * 4 * kLine));
 }
 
 // ---- tiled step over the brick numbering ------------------------------------------
@@ -748,6 +909,13 @@ static bool keep_stores(long long items) {
   return bytes >= kKeepLo && bytes <= kKeepHi;
 }
 
+// Up to this many items (32768 nodes: two wavefronts a CU) the two passes take
+// a lane per component.  us a step, one lane a node / a lane per component:
+// 1 k nodes 7.15 / 6.33, 8 k 7.31 / 6.50, 16 k 7.39 / 6.84, 24 k 7.87 / 7.27,
+// 32 k 8.07 / 7.75, 41 k 8.36 / 8.39, 66 k 8.98 / 9.06, 74 k 10.6 / 9.9, 98 k
+// 11.0 / 11.1, 131 k 13.3 / 13.8, 440 k 39.8 / 47.5.
+constexpr int kSplitItems = 512;
+
 static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, int tx, int ty,
                             bool wide, int parity, hipStream_t st) {
   if (tx == kListTx) {
@@ -756,6 +924,10 @@ static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, 
     if (wide) {
       hipLaunchKernelGGL(k_dens<true>, grid, block, 0, st, th, tiles, ntiles, parity);
       hipLaunchKernelGGL((k_node<true, false>), grid, block, 0, st, th, tiles, ntiles, parity);
+    } else if (ntiles <= kSplitItems) {
+      const dim3 halves(2 * (unsigned)ntiles);
+      hipLaunchKernelGGL(k_dens_split, halves, block, 0, st, th, tiles, ntiles, parity);
+      hipLaunchKernelGGL(k_node_split, halves, block, 0, st, th, tiles, ntiles, parity);
     } else {
       hipLaunchKernelGGL(k_dens<false>, grid, block, 0, st, th, tiles, ntiles, parity);
       if (keep_stores(ntiles))
