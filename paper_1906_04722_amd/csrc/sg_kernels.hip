@@ -299,13 +299,21 @@ hipError_t launch_standardise(const double *X, int n, int cols, const double *mu
 // products leave d act in the lanes that hold the same z), activations and
 // gradients in LDS; what the weight gradients need goes out in their operand
 // layout.  The chain of seven dependent products bounds it, not their rate (5
-// members x 64 rows are 20 workgroups): eight wavefronts of two tiles each share
+// members x 64 rows are 20 workgroups): sixteen wavefronts of a tile each share
 // a product, and the weights of a later product and the biases are loaded
-// before the one that is being computed.  5 members, batches of 64 rows on an
-// MI355X: 18.8 us a batch (23 without the early loads) where a kernel per
-// product, activation and bias gradient took eighteen launches and, with the
-// download of the loss, 286 us (now 52 for both kernels and the host's share).
-constexpr int kFbWaves = 8, kFbTiles = 16 / kFbWaves;
+// before the one that is being computed (each workgroup reads all weights, 0.6
+// MB at 64 bytes a cycle 4 us).  5 members, batches of 64 rows on an MI355X:
+// 17.1 us a batch (18.1 with eight wavefronts, 18.8 with two-byte stores of the
+// operands too, 23 without the early loads) where a kernel per product,
+// activation and bias gradient took eighteen launches and, with the download of
+// the loss, 286 us (now 43 for both kernels and the host's share).
+constexpr int kFbWaves = 16, kFbTiles = 16 / kFbWaves;
+
+// four floats in a row, at any float's address
+__device__ __forceinline__ void store4(float *p, const float (&x)[4]) {
+  typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+  *(f4 *)p = f4{x[0], x[1], x[2], x[3]};
+}
 
 // four values of column tile `tile` (columns 16 tile + 4 (lane / 16) + i) of
 // batch row b into their fragments
@@ -316,11 +324,27 @@ __device__ __forceinline__ void put_frag(bf16 *frags, int tile, int cb, int b, i
   for (int i = 0; i < 4; ++i) f[(4 * (lane >> 4) + i) * 8] = e[i];
 }
 
+// the 16 rows x 256 columns of `act` (LDS), rows b0 + r of the batch, into
+// their fragments: eight rows of a column are one 16-byte store
+__device__ __forceinline__ void put_frags(const bf16 *act, bf16 *frags, int tile0, int cb, int b0,
+                                          int tid) {
+#pragma unroll
+  for (int e = tid; e < 16 * 32; e += 64 * kFbWaves) {
+    const int l = e % 32, n = 16 * (e / 32) + l % 16;
+    v8bf x;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      x[i] = __builtin_bit_cast(__bf16, act[(8 * (l / 16) + i) * LDA + n]);
+    *(v8bf *)(frags + ((long long)(tile0 + e / 32) * cb + b0 / 32) * kFrag +
+              (16 * ((b0 % 32) / 8 + l / 16) + l % 16) * 8) = x;
+  }
+}
+
 template <int L>
 __device__ __forceinline__ void fb_forward(const v4f (&acc)[kFbTiles][1],
                                            const float (&bias)[kFbTiles][4], bf16 *out,
-                                           bf16 *actp, int cb, int row, bool live, int wv,
-                                           int lane, float (&z)[kFbTiles][4]) {
+                                           bf16 *actp, int cb, bool live, int wv, int lane,
+                                           float (&z)[kFbTiles][4]) {
   __syncthreads();
 #pragma unroll
   for (int t = 0; t < kFbTiles; ++t) {
@@ -336,9 +360,9 @@ __device__ __forceinline__ void fb_forward(const v4f (&acc)[kFbTiles][1],
     w2.x = (uint32_t)e[0] | (uint32_t)e[1] << 16;
     w2.y = (uint32_t)e[2] | (uint32_t)e[3] << 16;
     *(uint2 *)(out + (lane & 15) * LDA + n) = w2;
-    put_frag(actp, act_tile(L + 1) + tile, cb, row, lane, e);
   }
   __syncthreads();
+  put_frags(out, actp, act_tile(L + 1), cb, blockIdx.x * 16, 64 * wv + lane);
 }
 
 // gradients of layer L - 1's pre-activations: d act of layer L's input (acc, in
@@ -352,21 +376,20 @@ __device__ __forceinline__ void fb_backward(const v4f (&acc)[kFbTiles][1], bf16 
   for (int t = 0; t < kFbTiles; ++t) {
     const int tile = wv * kFbTiles + t, n = 16 * tile + 4 * (lane >> 4);
     bf16 e[4];
+    float d[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float d = acc[t][0][i] * dsilu(z[t][i]);
-      e[i] = live ? to_bf16(d) : (bf16)0;
-      if (live) gradf[(long long)row * kGradCols + grad_col(L - 1) + n + i] = d;
+      d[i] = acc[t][0][i] * dsilu(z[t][i]);
+      e[i] = live ? to_bf16(d[i]) : (bf16)0;
     }
-    if (L > 1) {
-      uint2 w2;
-      w2.x = (uint32_t)e[0] | (uint32_t)e[1] << 16;
-      w2.y = (uint32_t)e[2] | (uint32_t)e[3] << 16;
-      *(uint2 *)(out + (lane & 15) * LDA + n) = w2;
-    }
-    put_frag(gradp, grad_tile(L - 1) + tile, cb, row, lane, e);
+    if (live) store4(gradf + (long long)row * kGradCols + grad_col(L - 1) + n, d);
+    uint2 w2;
+    w2.x = (uint32_t)e[0] | (uint32_t)e[1] << 16;
+    w2.y = (uint32_t)e[2] | (uint32_t)e[3] << 16;
+    *(uint2 *)(out + (lane & 15) * LDA + n) = w2;
   }
   __syncthreads();
+  put_frags(out, gradp, grad_tile(L - 1), cb, blockIdx.x * 16, 64 * wv + lane);
 }
 
 __global__ __launch_bounds__(64 * kFbWaves) void k_fb(Batch q, const float *w) {
@@ -414,14 +437,14 @@ __global__ __launch_bounds__(64 * kFbWaves) void k_fb(Batch q, const float *w) {
   __syncthreads();
   float z0[kFbTiles][4], z1[kFbTiles][4], z2[kFbTiles][4];
   frag_mul<kFbTiles, kChunksK[0], LDX>(a0, x0, lane, acc);
-  fb_forward<0>(acc, bias[0], act, actp, cb, row, live, wv, lane, z0);
+  fb_forward<0>(acc, bias[0], act, actp, cb, live, wv, lane, z0);
   frag_load<pack_off(2)>(wz, t0, lane, a2);
   frag_mul<kFbTiles, kChunksK[1], LDA>(a1, act, lane, acc);
-  fb_forward<1>(acc, bias[1], act, actp, cb, row, live, wv, lane, z1);
+  fb_forward<1>(acc, bias[1], act, actp, cb, live, wv, lane, z1);
   if (wv < kTilesN[3]) frag_load<pack_off(3)>(wz, wv, lane, a3);
   frag_load<packt_off(3)>(wz, t0, lane, r3);
   frag_mul<kFbTiles, kChunksK[2], LDA>(a2, act, lane, acc);
-  fb_forward<2>(acc, bias[2], act, actp, cb, row, live, wv, lane, z2);
+  fb_forward<2>(acc, bias[2], act, actp, cb, live, wv, lane, z2);
   frag_load<packt_off(2)>(wz, t0, lane, r2);
   if (wv < kTilesN[3]) {
     v4f out[1][1];
@@ -470,9 +493,11 @@ hipError_t launch_fb(const Batch &q, const float *w, hipStream_t st) {
 // the whole batch and, while they are in its registers, takes the Adam step on
 // those weights and refreshes their packed copies: gradients never go to
 // memory.  The last workgroups sum the bias gradients (in batch order, so one
-// chain per output) and the loss.  Bound by latency at a batch of 64: 5
-// members' weights and moments are 9 MB read and written in 16.7 us (21.8 with
-// their loads behind the products).
+// chain per output) and the loss.  Bound by latency and by the accesses to the
+// weights' rows: at a batch of 64, 9 MB of 5 members' weights and moments are
+// read and written in 10.1 us; 13.9 with a store per float, 16.5 with a
+// workgroup's wavefronts along the outputs, each line then written by two
+// workgroups, 21.8 with the loads behind the products.
 constexpr int wave_tiles(int l) { return ((kTilesK[l] + 1) / 2) * ((kTilesN[l] + 1) / 2); }
 constexpr int kUpdWaves = wave_tiles(0) + wave_tiles(1) + wave_tiles(2) + wave_tiles(3);
 static_assert(kUpdWaves % 4 == 0, "whole workgroups of four wavefronts");
@@ -492,8 +517,9 @@ template <int L, bool ADAM>
 __device__ __forceinline__ void update_tile(const Batch &q, int cb, int zm, int tile, int lane,
                                             float *g, float *w, float *m, float *v, bf16 *wp,
                                             const AdamStep &adam) {
-  constexpr int KT = kTilesK[L], NT = kTilesN[L], K = kWidth[L], N = kWidth[L + 1];
-  const int kt = 2 * (tile / ((NT + 1) / 2)), nt = 2 * (tile % ((NT + 1) / 2));
+  constexpr int KT = kTilesK[L], K = kWidth[L], N = kWidth[L + 1];
+  // neighbouring wavefronts along the rows of W, which are contiguous
+  const int kt = 2 * (tile % ((KT + 1) / 2)), nt = 2 * (tile / ((KT + 1) / 2));
   const bf16 *A = q.actp + ((long long)zm * kActTiles + act_tile(L) + kt) * cb * kFrag + lane * 8;
   const bf16 *B = q.gradp + ((long long)zm * kGradTiles + grad_tile(L) + nt) * cb * kFrag +
                   lane * 8;
@@ -543,19 +569,19 @@ __device__ __forceinline__ void update_tile(const Batch &q, int cb, int zm, int 
       const int k = 16 * (kt + ti) + 4 * (lane >> 4), n = 16 * (nt + tj) + (lane & 15);
       const long long at = o[ti][tj];
       if constexpr (!ADAM) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) g[at + i] = acc[ti][tj][i];
+        const float d[4] = {acc[ti][tj][0], acc[ti][tj][1], acc[ti][tj][2], acc[ti][tj][3]};
+        store4(g + at, d);
       } else {
         bf16 e[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float x = adam_step(adam, acc[ti][tj][i], w4[ti][tj][i], m4[ti][tj][i],
+          w4[ti][tj][i] = adam_step(adam, acc[ti][tj][i], w4[ti][tj][i], m4[ti][tj][i],
                                     v4[ti][tj][i]);
-          w[at + i] = x;
-          m[at + i] = m4[ti][tj][i];
-          v[at + i] = v4[ti][tj][i];
-          e[i] = to_bf16(x);
+          e[i] = to_bf16(w4[ti][tj][i]);
         }
+        store4(w + at, w4[ti][tj]);
+        store4(m + at, m4[ti][tj]);
+        store4(v + at, v4[ti][tj]);
         // four inputs in a row: one 8-byte store in the forward fragments, four
         // places in the transposed ones
         bf16 *p = wp + zm * kPack;
