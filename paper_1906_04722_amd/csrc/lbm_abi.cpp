@@ -311,7 +311,6 @@ void release(lbm_throat *h) {
                   (void *)h->red_count_d, (void *)h->desc_d, (void *)h->tiles_d,
                   (void *)h->zper_d})
     if (p) (void)hipFree(p);
-  if (h->red_d) (void)hipFree(h->red_d);
   if (h->red_h) (void)hipHostFree(h->red_h);
   if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
   delete h;
@@ -340,10 +339,9 @@ int run_steps(lbm_throat *h, long long n) {
 // reduction the batched ramp uses too, so both give the same bits)
 int reduce_now(lbm_throat *h, double out[5]) {
   HIPCHK(sc::launch_reduce_chunks(h->desc_d, h->chunks_d, h->nchunks, h->redinfo_d, h->cur,
-                                  h->partials, h->red_d + 3, h->stream));
-  HIPCHK(sc::launch_reduce_throats(h->red_first_d, h->red_count_d, 1, h->partials, h->red_d,
+                                  h->partials, h->red_h + 3, h->stream));
+  HIPCHK(sc::launch_reduce_throats(h->red_first_d, h->red_count_d, 1, h->partials, h->red_h,
                                    h->stream));
-  HIPCHK(hipMemcpyAsync(h->red_h, h->red_d, 5 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));
   for (int i = 0; i < 5; ++i) out[i] = h->red_h[i];
   out[2] = h->n_fluid ? out[2] / (double)h->n_fluid : 0.0;
@@ -463,7 +461,6 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
   ALLOC(h->map_d, sizeof(uint32_t) * sc::map_elems(h->nx, h->ny, h->nz));
   ALLOC(h->rres_d, 4 * sizeof(double));
   ALLOC(h->redinfo_d, sizeof(sc::RedInfo));
-  ALLOC(h->red_d, 5 * sizeof(double));
   ALLOC(h->desc_d, sizeof(sc::Throat));
   if (hipHostMalloc((void **)&h->red_h, 5 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
     set_err("hipHostMalloc failed");

@@ -55,8 +55,8 @@ struct lbm_throat {
   int *red_first_d = nullptr;        // [1] = 0
   int *red_count_d = nullptr;        // [1] = nchunks
   double *partials = nullptr;        // [nchunks][3]
-  double *red_d = nullptr;           // [5]: masses, saturation sum, probe densities
-  double *red_h = nullptr;           // pinned [5]
+  // [5]: masses, saturation sum, probe densities; pinned, the kernels write it
+  double *red_h = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
   std::vector<uint8_t> types;
   long long n_fluid = 0;

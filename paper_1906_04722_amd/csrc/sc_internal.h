@@ -223,7 +223,7 @@ constexpr size_t kScratchNodes = (size_t)1 << 21;
 constexpr size_t kScratchDoubles = 2 * kScratchNodes;
 hipError_t scratch_address(double **out);
 // FP64 reduction over subdomains: the sums of rho_w, rho_nw and the
-// saturation term over the fluid nodes among kRedNodes consecutive non-solid
+// saturation term over the fluid nodes among a chunk of consecutive non-solid
 // nodes, then per subdomain the sum of these, both in a fixed order.
 struct RedInfo {
   long long probe;  // number of the probe node or -1
@@ -231,10 +231,9 @@ struct RedInfo {
 };
 // replace the map position that info[t].probe holds by the number found there
 hipError_t launch_probe_numbers(const Throat *throats, int n, RedInfo *info, hipStream_t st);
-constexpr int kRedNodes = 1024;
 struct RedChunk {
   int throat;
-  uint32_t first;  // index of its first node
+  uint32_t first, end;  // indices of its nodes
 };
 void red_chunks(size_t n_live, int throat, std::vector<RedChunk> &out);
 // partials[c][3]; probe_out[t][2] = densities at subdomain t's probe node

@@ -719,9 +719,9 @@ __device__ __forceinline__ void brick_store(const Dom &d, int X, int Y, int Z,
 // as large as the registers allow, 512 threads of up to 256 registers (a CU's
 // two wavefronts per SIMD), and no population waits in LDS.  All fluid, us a
 // step, against tiles of 256 threads with the middle plane in LDS and three
-// workgroups a CU (three times the lines through L1, 1.57 times the population
-// reads through L2): 256^3 1150 / 1325 (304 B a node: 4.4 TB/s), 192^3 567 /
-// 672.  Halo and own pulls one after the other: 1238 and 610.
+// workgroups a CU (1.58 times the populations fetched into the L2s, 1.14 now):
+// 256^3 1150 / 1325 (304 B a node: 4.4 TB/s), 192^3 567 / 672.  Halo and own
+// pulls one after the other: 1238 and 610.
 template <int TX, int TY>
 __device__ __forceinline__ void halo_slot(int h, int &hx, int &hy) {
   constexpr int HR = 2 * (TX + 2);
@@ -1386,8 +1386,9 @@ hipError_t scratch_address(double **out) {
 
 // ---- FP64 reductions ------------------------------------------------------
 // Two passes with a fixed summation order (a chunk's nodes strided over one
-// workgroup, then an LDS tree; then a subdomain's chunks likewise), so results are bitwise reproducible and identical whether a
-// subdomain is reduced alone or inside a batch.
+// workgroup, then an LDS tree; then a subdomain's chunks likewise), so results
+// are bitwise reproducible and identical whether a subdomain is reduced alone or
+// inside a batch.
 constexpr int kRedThreads = 256;
 constexpr int kRedVals = 3;
 
@@ -1420,9 +1421,8 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_chunks(const Throat *__r
   const size_t pp = (size_t)px * (size_t)(T.ny + 2 * kPad);
   const float rho_ref = T.P.rho_ref;
   const RedInfo ri = info[ch.throat];
-  const uint32_t end = min(ch.first + (uint32_t)kRedNodes, T.n_live);
   double acc[kRedVals] = {0.0, 0.0, 0.0};
-  for (uint32_t i = ch.first + threadIdx.x; i < end; i += kRedThreads) {
+  for (uint32_t i = ch.first + threadIdx.x; i < ch.end; i += kRedThreads) {
     const uint32_t pos = T.pos[i];
     if (bath_of(T, pos, pp) >= 0) continue;
     Near n;
@@ -1458,8 +1458,14 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_throats(const int *first
     for (int i = 0; i < kRedVals; ++i) sums[(size_t)t * kRedVals + i] = acc[i];
 }
 
+// A node per thread up to 2^18 nodes, where a chunk's time is its chain of
+// loads (a check of 1 k to 94 k nodes takes 22-24 us, with four nodes a thread
+// and a copy of the sums to the host 29), four beyond, where there are chunks
+// enough to fill the chip and their partial sums are one workgroup's work.
 void red_chunks(size_t n_live, int throat, std::vector<RedChunk> &out) {
-  for (size_t f = 0; f < n_live; f += kRedNodes) out.push_back(RedChunk{throat, (uint32_t)f});
+  const size_t step = n_live <= ((size_t)1 << 18) ? kRedThreads : 4 * kRedThreads;
+  for (size_t f = 0; f < n_live; f += step)
+    out.push_back(RedChunk{throat, (uint32_t)f, (uint32_t)std::min(f + step, n_live)});
 }
 
 hipError_t launch_reduce_chunks(const Throat *th, const RedChunk *chunks, int nchunks,
