@@ -17,8 +17,8 @@ writer for the counter output.
   python3 -m paper_1906_04722_amd.profile_run summarize --stats S.csv
       --fetch F.csv --write W.csv --out profiles/NAME.txt --command "..."
       writes the per-step averages of the step kernels (the fused k_step, or
-      with --kernels k_dens_list,k_step_list the two passes of the node-list
-      step, summed), the copy-kernel calibration factors and the calibrated
+      with --kernels k_dens,k_node the two passes over the non-solid nodes,
+      summed), the copy-kernel calibration factors and the calibrated
       HBM traffic per step.
 """
 import argparse
