@@ -247,7 +247,7 @@ def cpu_baseline(p, budget_s=10.0):
 def batch_leg(n_throats=BATCH_THROATS):
     """Batched drainage of n_throats packing throats in one lbm_drain_batch
     call: throats per second (all, and those with an entry pressure
-    bracketed to 1 %) over the call's wall time (subdomain setup, autotuning
+    bracketed to 1 %) over the call's wall time (subdomain setup
     and the whole graph-replayed ramp; the packing and throat geometry are
     generated on the host before it)."""
     t0 = time.perf_counter()

@@ -147,7 +147,7 @@ int lbm_set_memory_budget(size_t bytes);
 
 /* Create a subdomain: voxelize the geometry on the device, allocate two FP32
  * population buffers (2 x 152 bytes per non-solid node; in a nearly all-fluid
- * box of 4 million nodes or more, per node with nx and ny padded to multiples
+ * box of 2 million nodes or more, per node with nx and ny padded to multiples
  * of 8 and 4) and set the equilibrium state f = f_eq(rho_init, u = 0)
  * (Eq. 1-3).  Also per node a 4-byte index-map entry and a 1-byte class, and
  * per non-solid node a 4-byte list entry and an 8-byte density slot.  *out
