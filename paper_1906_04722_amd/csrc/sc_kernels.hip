@@ -659,7 +659,7 @@ __device__ __forceinline__ void brick_pull(const Dom &d, uint32_t m, int X, int 
 // mask word of a node as the march sees it: solid beyond a wall
 __device__ __forceinline__ uint32_t mask_at(const Dom &d, int X, int Y, int Z) {
   const long long n = node_of(d, X, Y, Z);
-  return n < 0 ? kSolid << kTypeShift : d.mask[n];
+  return n < 0 ? kSolid << kTypeShift : ((gcu32 *)d.mask)[n];
 }
 
 // the pulls of a fluid node (others keep v undefined)
@@ -705,11 +705,12 @@ __device__ __forceinline__ void brick_store(const Dom &d, int X, int Y, int Z,
 // z-segment, software-pipelined over three planes.  Entering iteration Z, the
 // thread holds its own nodes of planes Z and Z+1 in registers, the mask words
 // of plane Z+2, and the LDS density ring holds planes Z-1..Z+1.  It
-//   1. issues the pulls of plane Z+2 for its halo node and its own node, and
-//      the loads of plane Z+3's mask words,
+//   1. issues the loads of plane Z+3's mask words and the pulls of plane Z+2
+//      for its halo node and its own node,
 //   2. collides plane Z with the 18-neighbour density stencil while those are
-//      in flight, and stores it,
-//   3. sums the pulls into the ring (plane Z+2) and moves the planes down,
+//      in flight,
+//   3. sums the pulls into the ring (plane Z+2), stores plane Z and moves the
+//      planes down,
 //   4. synchronises the workgroup.
 // Every population is read from memory once per step (halo pulls re-read
 // neighbour tiles' lines, which are normally still in L2).
@@ -720,8 +721,9 @@ __device__ __forceinline__ void brick_store(const Dom &d, int X, int Y, int Z,
 // two wavefronts per SIMD), and no population waits in LDS.  All fluid, us a
 // step, against tiles of 256 threads with the middle plane in LDS and three
 // workgroups a CU (1.58 times the populations fetched into the L2s, 1.14 now):
-// 256^3 1150 / 1325 (304 B a node: 4.4 TB/s), 192^3 567 / 672.  Halo and own
-// pulls one after the other: 1238 and 610.
+// 256^3 1137 / 1325 (304 B a node: 4.5 TB/s), 192^3 554 / 672.  Halo and own
+// pulls one after the other: 1238 and 610; stores ahead of the sums, whose wait
+// for the pulls then waits for them as well: 1152 and 570.
 template <int TX, int TY>
 __device__ __forceinline__ void halo_slot(int h, int &hx, int &hy) {
   constexpr int HR = 2 * (TX + 2);
@@ -806,13 +808,13 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
   for (int Z = z0; Z < z1; ++Z) {
     const bool ahead = Z + 2 <= z1;  // plane Z+2 is needed (density halo or next own)
+    const int Z3 = min(Z + 3, z1);
+    uint32_t mnxt3 = mask_at(d, x, y, Z3);
+    uint32_t mh3 = halo ? mask_at(d, x0 + hx, y0 + hy, Z3) : mh;
     if (ahead) {
       pull_fluid(d, mh, XH, YH, Z + 2, hv);
       pull_fluid(d, mnxt, X, Y, Z + 2, nxt);
     }
-    const int Z3 = min(Z + 3, z1);
-    const uint32_t mnxt3 = mask_at(d, x, y, Z3);
-    const uint32_t mh3 = halo ? mask_at(d, x0 + hx, y0 + hy, Z3) : mh;
     if (own) {
       const uint32_t t = mcur >> kTypeShift;
       if (t == kFluid) {
@@ -826,20 +828,21 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2, 2))) 
           if (ez(k)) { Sw[2] += ez(k) > 0 ? a : -a; Sn[2] += ez(k) > 0 ? bb : -bb; }
         }
         collide(P, mcur, Sw, Sn, dcur, cur);
-        brick_store(d, x, y, Z, cur);
       } else if (t == kResIn || t == kResOut) {
         const int i = t == kResIn ? 0 : 1;
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
           for (int k = 0; k < 19; ++k) cur[c][k] = wf(k) * P.gres[i][c];
-        brick_store(d, x, y, Z, cur);
       }
     }
     if (ahead) {
       if (halo) ring[(Z + 2) & 3][hy + 1][hx + 1] = density_of(P, mh, hv, dh);
       ring[(Z + 2) & 3][ty + 1][tx + 1] = density_of(P, mnxt, nxt, dnxt);
     }
+    // (the opaque moves put the wait for the mask words ahead of the stores)
+    asm volatile("" : "+v"(mnxt3), "+v"(mh3));
+    if (own && mcur >> kTypeShift != kSolid) brick_store(d, x, y, Z, cur);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
 #pragma unroll
