@@ -912,12 +912,14 @@ static bool keep_stores(long long items) {
   return bytes >= kKeepLo && bytes <= kKeepHi;
 }
 
-// Up to this many items (32768 nodes: two wavefronts a CU) the two passes take
-// a lane per component.  us a step, one lane a node / a lane per component:
-// 1 k nodes 7.15 / 6.33, 8 k 7.31 / 6.50, 16 k 7.39 / 6.84, 24 k 7.87 / 7.27,
-// 32 k 8.07 / 7.75, 41 k 8.36 / 8.39, 66 k 8.98 / 9.06, 74 k 10.6 / 9.9, 98 k
-// 11.0 / 11.1, 131 k 13.3 / 13.8, 440 k 39.8 / 47.5.
-constexpr int kSplitItems = 512;
+// Where the two passes take a lane per component: up to 512 items (32768 nodes,
+// two wavefronts a CU), and again just above one item per SIMD (1024), where
+// whole items put two wavefronts on some SIMDs and half ones three halves.  us
+// a step, one lane a node / a lane per component: 1 k nodes 7.15 / 6.33, 8 k
+// 7.31 / 6.50, 16 k 7.39 / 6.84, 24 k 7.87 / 7.27, 32 k 8.07 / 7.75, 41 k 8.36 /
+// 8.39, 66 k 8.97 / 9.06, 67 k 10.4 / 9.6, 74 k 10.4 / 9.7, 78 k 10.4 / 10.2, 82
+// k 10.3 / 10.3, 98 k 11.0 / 11.1, 131 k 13.3 / 13.8, 440 k 39.8 / 47.5.
+static bool split_lanes(int items) { return items <= 512 || (items > 1024 && items <= 1216); }
 
 static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, int tx, int ty,
                             bool wide, int parity, hipStream_t st) {
@@ -927,7 +929,7 @@ static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, 
     if (wide) {
       hipLaunchKernelGGL(k_dens<true>, grid, block, 0, st, th, tiles, ntiles, parity);
       hipLaunchKernelGGL((k_node<true, false>), grid, block, 0, st, th, tiles, ntiles, parity);
-    } else if (ntiles <= kSplitItems) {
+    } else if (split_lanes(ntiles)) {
       const dim3 halves(2 * (unsigned)ntiles);
       hipLaunchKernelGGL(k_dens_split, halves, block, 0, st, th, tiles, ntiles, parity);
       hipLaunchKernelGGL(k_node_split, halves, block, 0, st, th, tiles, ntiles, parity);
