@@ -709,8 +709,8 @@ __device__ __forceinline__ void brick_store(const Dom &d, int X, int Y, int Z,
 //      for its halo node and its own node,
 //   2. collides plane Z with the 18-neighbour density stencil while those are
 //      in flight,
-//   3. sums the pulls into the ring (plane Z+2), stores plane Z and moves the
-//      planes down,
+//   3. sums the pulls into the ring (plane Z+2), stores plane Z (see kLateNodes)
+//      and moves the planes down,
 //   4. synchronises the workgroup.
 // Every population is read from memory once per step (halo pulls re-read
 // neighbour tiles' lines, which are normally still in L2).
@@ -722,8 +722,8 @@ __device__ __forceinline__ void brick_store(const Dom &d, int X, int Y, int Z,
 // step, against tiles of 256 threads with the middle plane in LDS and three
 // workgroups a CU (1.58 times the populations fetched into the L2s, 1.14 now):
 // 256^3 1137 / 1325 (304 B a node: 4.5 TB/s), 192^3 554 / 672.  Halo and own
-// pulls one after the other: 1238 and 610; stores ahead of the sums, whose wait
-// for the pulls then waits for them as well: 1152 and 570.
+// pulls one after the other: 1238 and 610; mask words through generic addresses
+// behind the pulls: 1152 and 570.
 template <int TX, int TY>
 __device__ __forceinline__ void halo_slot(int h, int &hx, int &hy) {
   constexpr int HR = 2 * (TX + 2);
@@ -737,6 +737,12 @@ __device__ __forceinline__ void halo_slot(int h, int &hx, int &hy) {
   }
 }
 
+// Up to this many nodes of the box plane Z is stored behind the sums of plane
+// Z+2, whose wait for the pulls would wait for the stores as well; beyond, ahead
+// of them: there the step is bound by lines, and tiles that wait more stay
+// closer together.  us a step, behind / ahead: 192^3 550 / 564, 256^3 1131 /
+// 1135, 384^3 4025 / 3945, 512^3 9300-9580 / 9000-9300.
+constexpr uint32_t kLateNodes = 1u << 24;
 template <int TX, int TY>
 __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step(
     const Throat *__restrict__ throats, const TileRef *__restrict__ tiles, int ntiles,
@@ -766,6 +772,7 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   d.per = T.per;
   const Phys P = T.P;
   const int ntx = T.ntx, nty = T.nty, lz = T.lz;
+  const bool late = T.N <= kLateNodes;
   const int tix = tr.tile % ntx, tiy = (tr.tile / ntx) % nty, tiz = tr.tile / (ntx * nty);
   const int x0 = tix * TX, y0 = tiy * TY, z0 = tiz * lz;
   const int z1 = min(z0 + lz, d.nz);
@@ -835,6 +842,7 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
           for (int k = 0; k < 19; ++k) cur[c][k] = wf(k) * P.gres[i][c];
       }
+      if (!late && t != kSolid) brick_store(d, x, y, Z, cur);
     }
     if (ahead) {
       if (halo) ring[(Z + 2) & 3][hy + 1][hx + 1] = density_of(P, mh, hv, dh);
@@ -842,7 +850,7 @@ __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
     // (the opaque moves put the wait for the mask words ahead of the stores)
     asm volatile("" : "+v"(mnxt3), "+v"(mh3));
-    if (own && mcur >> kTypeShift != kSolid) brick_store(d, x, y, Z, cur);
+    if (late && own && mcur >> kTypeShift != kSolid) brick_store(d, x, y, Z, cur);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
 #pragma unroll

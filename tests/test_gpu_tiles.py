@@ -50,3 +50,22 @@ def test_every_tile_shape(bc):
     g.step(7)
     assert np.array_equal(g.density(), rho)
     g.close()
+
+
+def test_stores_ahead_of_the_sums_equal_the_two_passes():
+    """Boxes of more than 2^24 nodes store a plane before they sum the next
+    one; a batch steps the same box in two passes, bit for bit alike."""
+    from paper_1906_04722_amd import lbm
+    p = Problem(nx=260, ny=257, nz=252, bc=(BC_PERIODIC, BC_WALLS, BC_RESERVOIR),
+                spheres=np.array([[120.0, 130.0, 140.0, 40.0], [259.0, 20.0, 3.0, 9.0]]),
+                z_front=20, rho_in_nw=2.02, probe=(5, 100, 100))
+    assert p.nx * p.ny * p.nz > 1 << 24
+    pcs = np.array([0.004, 0.008])
+    conv = dict(tol=1e-7, check_every=10, max_steps=20, bisect_rel=0.5)
+    one = lbm.Throat(p)
+    assert one.schedule()[0] > 0
+    ref = one.drain(pcs, **conv)
+    one.close()
+    out, _ = lbm.drain_batch([p], pcs[None, :], **conv)
+    assert np.array_equal(out[0]["S"], ref["S"])
+    assert out[0]["total_steps"] == ref["total_steps"]
