@@ -1227,37 +1227,50 @@ bool get_ramp(File &F, HostRamp &R) {
   return ok && (R.phase == HostRamp::kIdle || (n >= 1 && point >= 0 && point <= n));
 }
 
-// device staging of one chunk of the file layout (compact numbering)
+// Staging of the file layout of a compact subdomain, n floats a chunk: the
+// population buffer that does not hold the state, so that saving and loading
+// ask for no device memory.  One shorter than kMinStage (a few nodes in a large
+// box, whose chunks would be launches of a few floats) gives way to kMinStage
+// floats of memory where they can be had.
+constexpr size_t kMinStage = (size_t)1 << 20;
 struct Staging {
-  float *d = nullptr;
+  float *d = nullptr, *mine = nullptr;
   size_t n = 0;
-  int make(const lbm_throat *h, size_t total) {
-    n = std::min(total, kIoChunk);
-    if (h->bricks) return LBM_OK;
-    if (hipMalloc((void **)&d, sizeof(float) * n) != hipSuccess) {
-      d = nullptr;
+  Staging(const lbm_throat *h, size_t total) : n(std::min(total, kIoChunk)) {
+    if (h->bricks || h->n_live == 0) return;
+    const size_t idle = sc::pop_elems(h->n_numbers);
+    if (idle < std::min(n, kMinStage)) {
+      n = std::min(n, kMinStage);
+      if (hipMalloc((void **)&mine, sizeof(float) * n) == hipSuccess) {
+        d = mine;
+        return;
+      }
+      mine = nullptr;
       (void)hipGetLastError();
-      set_err("hipMalloc of the %zu-byte file staging failed", sizeof(float) * n);
-      return LBM_ENOMEM;
     }
-    return LBM_OK;
+    n = std::min(n, idle);
+    d = h->g[1 - h->cur];
   }
+  Staging(const Staging &) = delete;
+  Staging &operator=(const Staging &) = delete;
   ~Staging() {
-    if (d) (void)hipFree(d);
+    if (mine) (void)hipFree(mine);
   }
 };
 
-// one population buffer to or from the file (file_elems floats), in chunks
+// one population buffer to or from the file (file_elems floats), in chunks; a
+// buffer in bricks is the file layout, one without a node is zeros
 int buffer_out(lbm_throat *h, File &F, const Staging &S, const float *dev, size_t n) {
   std::vector<float> tmp(S.n);
   const sc::Dom d = dom(h, nullptr, nullptr);
   for (size_t o = 0; o < n; o += S.n) {
     const size_t k = std::min(S.n, n - o);
-    // a buffer in bricks is the file layout
-    if (!h->bricks) HIPCHK(sc::launch_to_file(d, dev, o, k, S.d, h->stream));
-    HIPCHK(hipMemcpyAsync(tmp.data(), h->bricks ? dev + o : S.d, sizeof(float) * k,
-                          hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
+    if (S.d) HIPCHK(sc::launch_to_file(d, dev, o, k, S.d, h->stream));
+    if (S.d || h->bricks) {
+      HIPCHK(hipMemcpyAsync(tmp.data(), S.d ? S.d : dev + o, sizeof(float) * k,
+                            hipMemcpyDeviceToHost, h->stream));
+      HIPCHK(hipStreamSynchronize(h->stream));
+    }
     if (!F.put_n(tmp.data(), k)) {
       set_err("lbm_save: write failed");
       return LBM_EIO;
@@ -1275,9 +1288,10 @@ int buffer_in(lbm_throat *h, File &F, const Staging &S, float *dev, size_t n) {
       set_err("lbm_load: the file ends inside a population buffer");
       return LBM_EIO;
     }
-    HIPCHK(hipMemcpyAsync(h->bricks ? dev + o : S.d, tmp.data(), sizeof(float) * k,
+    if (!S.d && !h->bricks) continue;
+    HIPCHK(hipMemcpyAsync(S.d ? S.d : dev + o, tmp.data(), sizeof(float) * k,
                           hipMemcpyHostToDevice, h->stream));
-    if (!h->bricks) HIPCHK(sc::launch_from_file(d, S.d, o, k, dev, h->stream));
+    if (S.d) HIPCHK(sc::launch_from_file(d, S.d, o, k, dev, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
   }
   return LBM_OK;
@@ -1294,8 +1308,7 @@ int lbm_save(lbm_throat_t h, const char *path) {
   }
   HIPCHK(hipStreamSynchronize(h->stream));
   const size_t n = sc::brick_elems(h->nx, h->ny, h->nz);
-  Staging stage;
-  TRY(stage.make(h, n));
+  const Staging stage(h, n);
   File F;
   F.f = fopen(path, "wb");
   if (!F.f) {
@@ -1366,8 +1379,7 @@ int lbm_load(lbm_throat_t h, const char *path) {
   }
   if (nbuf == 3) TRY(ensure_checkpoints(h, "lbm_load"));
   const size_t n = sc::brick_elems(h->nx, h->ny, h->nz);
-  Staging stage;
-  TRY(stage.make(h, n));
+  const Staging stage(h, n);
   // from here on the handle's state is overwritten
   TRY(buffer_in(h, F, stage, h->g[h->cur], n));
   if (nbuf == 3) {
