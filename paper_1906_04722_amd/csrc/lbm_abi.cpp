@@ -1227,17 +1227,17 @@ bool get_ramp(File &F, HostRamp &R) {
   return ok && (R.phase == HostRamp::kIdle || (n >= 1 && point >= 0 && point <= n));
 }
 
-// Staging of the file layout of a compact subdomain, n floats a chunk: the
-// population buffer that does not hold the state, so that saving and loading
-// ask for no device memory.  One shorter than kMinStage (a few nodes in a large
-// box, whose chunks would be launches of a few floats) gives way to kMinStage
-// floats of memory where they can be had.
+// Staging of the file layout, n floats a chunk: the population buffer that does
+// not hold the state, so that saving and loading ask for no device memory.  One
+// shorter than kMinStage (a few nodes in a large box, whose chunks would be
+// launches of a few floats) gives way to kMinStage floats of memory where they
+// can be had.
 constexpr size_t kMinStage = (size_t)1 << 20;
 struct Staging {
   float *d = nullptr, *mine = nullptr;
   size_t n = 0;
   Staging(const lbm_throat *h, size_t total) : n(std::min(total, kIoChunk)) {
-    if (h->bricks || h->n_live == 0) return;
+    if (h->n_live == 0) return;
     const size_t idle = sc::pop_elems(h->n_numbers);
     if (idle < std::min(n, kMinStage)) {
       n = std::min(n, kMinStage);
@@ -1258,17 +1258,17 @@ struct Staging {
   }
 };
 
-// one population buffer to or from the file (file_elems floats), in chunks; a
-// buffer in bricks is the file layout, one without a node is zeros
+// One population buffer to or from the file (file_elems floats), in chunks.  The
+// file gets zeros wherever there is no node: a buffer in bricks is in the file's
+// order, but what it holds there is never written.
 int buffer_out(lbm_throat *h, File &F, const Staging &S, const float *dev, size_t n) {
   std::vector<float> tmp(S.n);
   const sc::Dom d = dom(h, nullptr, nullptr);
   for (size_t o = 0; o < n; o += S.n) {
     const size_t k = std::min(S.n, n - o);
     if (S.d) HIPCHK(sc::launch_to_file(d, dev, o, k, S.d, h->stream));
-    if (S.d || h->bricks) {
-      HIPCHK(hipMemcpyAsync(tmp.data(), S.d ? S.d : dev + o, sizeof(float) * k,
-                            hipMemcpyDeviceToHost, h->stream));
+    if (S.d) {
+      HIPCHK(hipMemcpyAsync(tmp.data(), S.d, sizeof(float) * k, hipMemcpyDeviceToHost, h->stream));
       HIPCHK(hipStreamSynchronize(h->stream));
     }
     if (!F.put_n(tmp.data(), k)) {
@@ -1288,10 +1288,10 @@ int buffer_in(lbm_throat *h, File &F, const Staging &S, float *dev, size_t n) {
       set_err("lbm_load: the file ends inside a population buffer");
       return LBM_EIO;
     }
-    if (!S.d && !h->bricks) continue;
-    HIPCHK(hipMemcpyAsync(S.d ? S.d : dev + o, tmp.data(), sizeof(float) * k,
+    if (!S.d) continue;
+    HIPCHK(hipMemcpyAsync(h->bricks ? dev + o : S.d, tmp.data(), sizeof(float) * k,
                           hipMemcpyHostToDevice, h->stream));
-    if (S.d) HIPCHK(sc::launch_from_file(d, S.d, o, k, dev, h->stream));
+    if (!h->bricks) HIPCHK(sc::launch_from_file(d, S.d, o, k, dev, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
   }
   return LBM_OK;
