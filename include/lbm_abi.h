@@ -135,14 +135,16 @@ typedef struct lbm_throat *lbm_throat_t;
 
 /* Device-memory budget of the library's allocating calls, for callers that
  * share the GPU: with bytes > 0, lbm_throat_init, lbm_drain_throat,
- * lbm_drain_batch and lbm_place compute the device memory a call needs before allocating
- * anything (an upper bound, as if every node were fluid: per subdomain two
- * population buffers of 152 bytes per padded node, plus 25 bytes per node of
- * index map, classes, densities and node list; two more population buffers
- * for the ramp checkpoints of a drain) and refuse a call that needs more than `bytes` with LBM_ENOMEM, having
- * allocated nothing.  0 (the default) sets no budget; calls are then refused
- * only when the device reports less free memory than they need.  Process
- * wide; takes effect for calls that start after it returns. */
+ * lbm_drain_batch, lbm_place and lbm_set_schedule compute the device memory a
+ * call needs before allocating anything (an upper bound, as if every node were
+ * fluid: per subdomain two population buffers of 152 bytes per padded node,
+ * plus 25 bytes per node of index map, classes, densities and node list; two
+ * more population buffers for the ramp checkpoints of a drain) and refuse a
+ * call that needs more than `bytes` with LBM_ENOMEM, having allocated nothing.
+ * lbm_set_schedule counts the storage of the shape it changes to, if that is
+ * another than the subdomain's.  0 (the default) sets no budget; calls are then
+ * refused only when the device reports less free memory than they need.
+ * Process wide; takes effect for calls that start after it returns. */
 int lbm_set_memory_budget(size_t bytes);
 
 /* Create a subdomain: voxelize the geometry on the device, allocate two FP32
@@ -306,16 +308,17 @@ int lbm_step_timer(lbm_throat_t h, int enable, double *total_ms, long long *laun
  * fused pass, a workgroup taking two such tiles on top of each other in y; 0
  * keeps the current value.  tx = LBM_SCHED_NODE_LIST selects two passes over
  * the non-solid nodes instead (ty and lz are ignored and read back as 0).  A
- * box of 2 million nodes or more, three quarters of them not solid, is stored
- * so that it is stepped in tiles, any other so that it is stepped in two
- * passes: every subdomain takes every shape and reports it, but one that is
- * not its own leaves the step as it is (two passes, or the default tiles).
- * All shapes give bit-identical results. */
+ * box of 2 million nodes or more, three quarters of them not solid, starts in
+ * tiles, any other in two passes.  The two keep their populations in different
+ * orders: a shape of the other kind moves the state and the checkpoints of a
+ * ramp over, bit for bit, for which both orders are held at once (LBM_ENOMEM,
+ * with everything as it was, if that cannot be had or exceeds the memory
+ * budget).  All shapes give bit-identical results. */
 #define LBM_SCHED_NODE_LIST (-1)
 int lbm_set_schedule(lbm_throat_t h, int tx, int ty, int lz);
 
-/* Autotune the launch shape for this subdomain.  A subdomain that has only
- * the two passes (see lbm_set_schedule) gets that shape at once.  Otherwise:
+/* Autotune the launch shape for this subdomain.  One that starts in the two
+ * passes (see lbm_set_schedule) gets that shape at once.  Otherwise:
  * time `trial_steps` steps for every tile shape in increasing z-segment length
  * (up to the first that is 1.5x slower than the shape's best) and for the
  * default shape, time the candidates within 1.25x of the best once more (each

@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "lbm_handle.h"
@@ -120,14 +121,6 @@ sc::Sched default_schedule(int nx, int ny, int nz) {
   return s;
 }
 
-// launch shape the step runs at: a compact subdomain has the two passes only,
-// one in bricks the tiles only (the two passes over bricks touch four lines
-// where tiles touch one: 4200 us a step at 256^3 against 1154)
-sc::Sched shape_of(const lbm_throat *h) {
-  if (!h->bricks) return sc::Sched{sc::kListTx, 0, 0};
-  return h->sched.tx == sc::kListTx ? default_schedule(h->nx, h->ny, h->nz) : h->sched;
-}
-
 // the descriptor: buffers, sizes, tile grid, parameters
 void fill_desc(lbm_throat *h) {
   sc::Throat &T = h->desc;
@@ -146,7 +139,7 @@ void fill_desc(lbm_throat *h) {
   T.mask = h->mask_d;
   T.N = (uint32_t)h->N;
   T.per = h->per;
-  const sc::Sched s = shape_of(h);
+  const sc::Sched s = h->sched;
   const bool tiled = s.tx != sc::kListTx;
   T.ntx = tiled ? (h->nx + s.tx - 1) / s.tx : 0;
   const int rows = sc::tile_rows(s.ty);
@@ -160,37 +153,6 @@ int sync_desc(lbm_throat *h) {
   HIPCHK(hipMemcpyAsync(h->desc_d, &h->desc, sizeof(sc::Throat), hipMemcpyHostToDevice,
                         h->stream));
   return LBM_OK;
-}
-
-// work items of the current schedule: its tiles that hold a non-solid node, or
-// the number of items of the two passes (one subdomain's need no list)
-int rebuild_tiles(lbm_throat *h) {
-  std::vector<sc::TileRef> list;
-  const sc::Sched s = shape_of(h);
-  if (s.tx == sc::kListTx) {
-    h->ntiles = (int)sc::list_count(h->n_live);
-    return sync_desc(h);
-  }
-  sc::list_tiles(h->brick_live.data(), h->nx, h->ny, h->nz, s.tx, sc::tile_rows(s.ty), s.lz, 0,
-                 list);
-  if (list.size() > h->tiles_cap) {
-    if (h->tiles_d) HIPCHK(hipStreamSynchronize(h->stream));
-    if (h->tiles_d) (void)hipFree(h->tiles_d);
-    h->tiles_d = nullptr;
-    h->tiles_cap = 0;
-    if (hipMalloc((void **)&h->tiles_d, sizeof(sc::TileRef) * std::max<size_t>(list.size(), 1)) !=
-        hipSuccess) {
-      set_err("hipMalloc of the tile list failed");
-      return LBM_ENOMEM;
-    }
-    h->tiles_cap = list.size();
-  }
-  h->ntiles = (int)list.size();
-  if (!list.empty())
-    HIPCHK(hipMemcpyAsync(h->tiles_d, list.data(), sizeof(sc::TileRef) * list.size(),
-                          hipMemcpyHostToDevice, h->stream));
-  HIPCHK(hipStreamSynchronize(h->stream));
-  return sync_desc(h);
 }
 
 int upload_rres(lbm_throat *h) {
@@ -317,9 +279,10 @@ void release(lbm_throat *h) {
 }
 
 hipError_t one_step(const lbm_throat *h, int parity) {
-  const sc::Sched s = shape_of(h);
-  return sc::launch_step(h->desc_d, h->tiles_d, h->ntiles, s.tx, s.ty, lbmh::wide(h), parity,
-                         h->stream, h->zper_d, h->n_zper);
+  // (the two passes over one subdomain take no list: its items are 0, 1, ...)
+  const sc::TileRef *tiles = h->sched.tx == sc::kListTx ? nullptr : h->tiles_d;
+  return sc::launch_step(h->desc_d, tiles, h->ntiles, h->sched.tx, h->sched.ty, lbmh::wide(h),
+                         parity, h->stream, h->zper_d, h->n_zper);
 }
 
 int run_steps(lbm_throat *h, long long n) {
@@ -421,6 +384,149 @@ namespace {
 // 1130 / 1047, 975 / 982.
 constexpr double kTileFill = 0.75;
 constexpr size_t kTileNodes = (size_t)1 << 21;
+
+bool own_bricks(const lbm_throat *h) {
+  const size_t slots = (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * h->nz;
+  return slots >= kTileNodes && (double)h->n_live >= kTileFill * (double)slots;
+}
+
+size_t brick_numbers(const lbm_throat *h) {
+  return (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * ((size_t)h->nz + 2);
+}
+
+bool alloc_device(void **q, size_t bytes) {
+  if (hipMalloc(q, std::max<size_t>(bytes, 16)) == hipSuccess) return true;
+  *q = nullptr;
+  (void)hipGetLastError();
+  set_err("hipMalloc of %zu bytes failed", bytes);
+  return false;
+}
+
+// the number of the probe node, read from `map`, on the host and the device
+bool set_probe(lbm_throat *h, const uint32_t *map) {
+  long long probe = -1;
+  if (h->probe_pos >= 0) {
+    uint32_t number = 0;
+    if (hipMemcpy(&number, map + h->probe_pos, sizeof number, hipMemcpyDeviceToHost) != hipSuccess)
+      return false;
+    probe = (long long)number;
+  }
+  const sc::RedInfo ri{probe, h->phib};
+  if (hipMemcpy(h->redinfo_d, &ri, sizeof ri, hipMemcpyHostToDevice) != hipSuccess) return false;
+  h->probe = probe;
+  return true;
+}
+
+// The other numbering for a subdomain, its state and checkpoints carried over
+// bit for bit.  Nothing of the handle is changed before all of it is there.
+int set_numbering(lbm_throat *h, bool bricks) {
+  if (h->bricks == bricks) return LBM_OK;
+  const size_t numbers = bricks ? brick_numbers(h) : h->n_live;
+  const size_t pop_bytes = sizeof(float) * sc::pop_elems(numbers);
+  const size_t map_bytes = sizeof(uint32_t) * sc::map_elems(h->nx, h->ny, h->nz);
+  const size_t side_bytes = bricks ? sizeof(uint32_t) * h->N : sizeof(float2) * numbers;
+  const bool ghosts = bricks && (h->per & 4);
+  const uint32_t n_live = (uint32_t)h->n_live;
+  struct Storage {
+    void *g[2] = {}, *save[2] = {}, *map = nullptr, *side = nullptr, *zper = nullptr;
+    ~Storage() {
+      for (void *p : {g[0], g[1], save[0], save[1], map, side, zper})
+        if (p) (void)hipFree(p);
+    }
+  } f;
+  size_t need = 2 * pop_bytes + map_bytes + side_bytes;
+  for (int i = 0; i < 2; ++i) need += h->save[i] ? pop_bytes : 0;
+  TRY(lbmh::check_budget(need, "the launch shape's storage"));
+  for (int i = 0; i < 2; ++i)
+    if (!alloc_device(&f.g[i], pop_bytes) || (h->save[i] && !alloc_device(&f.save[i], pop_bytes)))
+      return LBM_ENOMEM;
+  if (!alloc_device(&f.map, map_bytes) || !alloc_device(&f.side, side_bytes) ||
+      (ghosts && !alloc_device(&f.zper, sizeof(int))))
+    return LBM_ENOMEM;
+  const int zero = 0;
+  if (ghosts) HIPCHK(hipMemcpyAsync(f.zper, &zero, sizeof zero, hipMemcpyHostToDevice, h->stream));
+  sc::Dom d = dom(h, nullptr, nullptr);
+  d.map = (uint32_t *)f.map;
+  HIPCHK(sc::launch_renumber(d, h->types_d, h->pos_d, n_live, bricks, (uint32_t *)f.map,
+                             h->stream));
+  HIPCHK(sc::launch_move(d, h->pos_d, n_live, bricks, h->g[h->cur], (float *)f.g[h->cur],
+                         h->stream));
+  for (int i = 0; i < 2; ++i)
+    if (h->save[i])
+      HIPCHK(sc::launch_move(d, h->pos_d, n_live, bricks, h->save[i], (float *)f.save[i],
+                             h->stream));
+  if (bricks) HIPCHK(sc::launch_links(h->types_d, d, (uint32_t *)f.side, h->stream));
+  HIPCHK(hipStreamSynchronize(h->stream));
+  if (!set_probe(h, (uint32_t *)f.map)) {
+    set_err("renumbering the probe failed");
+    return LBM_EHIP;
+  }
+  // exchanged: what the handle had is released with f
+  const auto take = [](auto *&mine, void *&fresh) {
+    void *old = mine;
+    mine = static_cast<std::remove_reference_t<decltype(mine)>>(fresh);
+    fresh = old;
+  };
+  for (int i = 0; i < 2; ++i) {
+    take(h->g[i], f.g[i]);
+    take(h->save[i], f.save[i]);
+  }
+  take(h->map_d, f.map);
+  take(h->zper_d, f.zper);
+  void *none = nullptr;
+  if (bricks) {
+    take(h->mask_d, f.side);
+    take(h->rho_d, none);
+  } else {
+    take(h->rho_d, f.side);
+    take(h->mask_d, none);
+  }
+  if (none) (void)hipFree(none);
+  h->n_zper = ghosts ? 1 : 0;
+  h->bricks = bricks;
+  h->n_numbers = numbers;
+  return LBM_OK;
+}
+
+// Launch shape s: the numbering it runs over, and its work items, which are the
+// tiles that hold a non-solid node or the number of items of the two passes
+// (one subdomain's need no list).  (The two passes over bricks touch four lines
+// where tiles touch one: 4200 us a step at 256^3 against 1137, and 1523 over
+// compact nodes.)  Without the memory for it the handle stays as it was.
+int set_shape(lbm_throat *h, const sc::Sched &s) {
+  const bool tiled = s.tx != sc::kListTx;
+  std::vector<sc::TileRef> list;
+  struct Fresh {
+    void *d = nullptr;
+    ~Fresh() {
+      if (d) (void)hipFree(d);
+    }
+  } fresh;
+  if (tiled) {
+    if (h->brick_live.empty())
+      sc::brick_map(h->types.data(), h->nx, h->ny, h->nz, h->brick_live);
+    sc::list_tiles(h->brick_live.data(), h->nx, h->ny, h->nz, s.tx, sc::tile_rows(s.ty), s.lz, 0,
+                   list);
+    if (list.size() > h->tiles_cap && !alloc_device(&fresh.d, sizeof(sc::TileRef) * list.size()))
+      return LBM_ENOMEM;
+  }
+  TRY(set_numbering(h, tiled));
+  if (fresh.d) {
+    HIPCHK(hipStreamSynchronize(h->stream));
+    void *old = h->tiles_d;
+    h->tiles_d = (sc::TileRef *)fresh.d;
+    fresh.d = old;
+    h->tiles_cap = list.size();
+  }
+  h->sched = s;
+  h->ntiles = (int)(tiled ? list.size() : sc::list_count(h->n_live));
+  if (!list.empty()) {
+    HIPCHK(hipMemcpyAsync(h->tiles_d, list.data(), sizeof(sc::TileRef) * list.size(),
+                          hipMemcpyHostToDevice, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+  }
+  return sync_desc(h);
+}
 
 int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
   g_err.clear();
@@ -541,9 +647,8 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
   if (p->bc[2] == LBM_BC_RESERVOIR)
     for (size_t n = 0; n < plane; ++n)
       h->n_fluid -= (h->types[n] != sc::kSolid) + (h->types[h->N - plane + n] != sc::kSolid);
-  const size_t slots = (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * h->nz;
-  h->bricks = slots >= kTileNodes && (double)h->n_live >= kTileFill * (double)slots;
-  h->n_numbers = h->bricks ? slots / h->nz * ((size_t)h->nz + 2) : h->n_live;
+  h->bricks = own_bricks(h);
+  h->n_numbers = h->bricks ? brick_numbers(h) : h->n_live;
   const size_t pop_bytes = sizeof(float) * sc::pop_elems(h->n_numbers);
   std::vector<sc::RedChunk> chunks;
   sc::red_chunks(h->n_live, 0, chunks);
@@ -559,13 +664,7 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
     set_err("needs %zu bytes of device memory, %zu free", need, free_b);
     return fail_rows(LBM_ENOMEM);
   }
-  auto alloc = [&](auto **q, size_t bytes) {
-    if (hipMalloc((void **)q, std::max<size_t>(bytes, 16)) == hipSuccess) return true;
-    *q = nullptr;
-    (void)hipGetLastError();
-    set_err("hipMalloc of %zu bytes failed", bytes);
-    return false;
-  };
+  auto alloc = [](auto **q, size_t bytes) { return alloc_device((void **)q, bytes); };
   if (!alloc(&h->g[0], pop_bytes) || !alloc(&h->g[1], pop_bytes) ||
       !alloc(&h->pos_d, sizeof(uint32_t) * h->n_live) ||
       (!h->bricks && !alloc(&h->rho_d, sizeof(float2) * h->n_numbers)) ||
@@ -591,8 +690,6 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
     if (ok && h->bricks) {
       ok = sc::launch_links(h->types_d, dom(h, nullptr, nullptr), h->mask_d, h->stream) ==
            hipSuccess;
-      sc::brick_map(h->types.data(), h->nx, h->ny, h->nz, h->brick_live);
-      h->sched = default_schedule(h->nx, h->ny, h->nz);
       if (ok && (h->per & 4)) {
         if (!alloc(&h->zper_d, sizeof(int))) return fail_rows(LBM_ENOMEM);
         ok = hipMemcpyAsync(h->zper_d, &zero, sizeof(int), hipMemcpyHostToDevice, h->stream) ==
@@ -620,21 +717,12 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
       set_err("probe node is not a fluid node");
       return fail(LBM_EINVAL);
     }
-    uint32_t number = 0;
-    if (hipMemcpy(&number,
-                  h->map_d + sc::map_pos(h->nx, h->ny, p->probe[0], p->probe[1], p->probe[2]),
-                  sizeof number, hipMemcpyDeviceToHost) != hipSuccess) {
-      set_err("reading the probe's number failed");
-      return fail(LBM_EHIP);
-    }
-    h->probe = (long long)number;
+    h->probe_pos =
+        (long long)sc::map_pos(h->nx, h->ny, p->probe[0], p->probe[1], p->probe[2]);
   }
-  {
-    const sc::RedInfo ri{h->probe, h->phib};
-    if (hipMemcpy(h->redinfo_d, &ri, sizeof ri, hipMemcpyHostToDevice) != hipSuccess) {
-      set_err("upload of the reduction info failed");
-      return fail(LBM_EHIP);
-    }
+  if (!set_probe(h, h->map_d)) {
+    set_err("upload of the reduction info failed");
+    return fail(LBM_EHIP);
   }
   unsigned long long bad = ~0ull, *bad_d = nullptr;
   if (p->rho_init) {
@@ -666,7 +754,9 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
   }
   if (const int r = lbmh::check_rho_init(h, bad)) return fail(r);
   h->cur = 0;
-  if (rebuild_tiles(h) != LBM_OK) return fail(LBM_EHIP);
+  if (const int r = set_shape(h, h->bricks ? default_schedule(h->nx, h->ny, h->nz)
+                                          : sc::Sched{sc::kListTx, 0, 0}))
+    return fail(r);
   if (sc::launch_ghost(h->desc_d, h->zper_d, h->n_zper, 0, h->stream) != hipSuccess ||
       hipStreamSynchronize(h->stream) != hipSuccess) {
     set_err("initial ghost planes failed");
@@ -1441,8 +1531,7 @@ int lbm_set_schedule(lbm_throat_t h, int tx, int ty, int lz) {
     set_err("schedule (%d, %d, %d) not supported", s.tx, s.ty, s.lz);
     return LBM_EINVAL;
   }
-  h->sched = s;
-  return rebuild_tiles(h);
+  return set_shape(h, s);
 }
 
 int lbm_autotune(lbm_throat_t h, int trial_steps, int *tx, int *ty, int *lz) {
@@ -1450,14 +1539,14 @@ int lbm_autotune(lbm_throat_t h, int trial_steps, int *tx, int *ty, int *lz) {
     set_err("lbm_autotune: bad handle or trial_steps < 1");
     return LBM_EINVAL;
   }
-  if (!h->bricks) {  // nothing to choose from
-    h->sched = shape_of(h);
-    TRY(rebuild_tiles(h));
+  if (!own_bricks(h)) {  // nothing to choose from
+    TRY(set_shape(h, sc::Sched{sc::kListTx, 0, 0}));
     if (tx) *tx = h->sched.tx;
     if (ty) *ty = h->sched.ty;
     if (lz) *lz = h->sched.lz;
     return LBM_OK;
   }
+  if (!h->bricks) TRY(set_shape(h, default_schedule(h->nx, h->ny, h->nz)));
   // Trials advance the state with alternating buffers, as the ramp does (a
   // trial that re-reads one unchanged buffer times some shapes faster than
   // they run), from a copy of g[cur] that is put back at the end, also on an
@@ -1491,9 +1580,7 @@ int lbm_autotune(lbm_throat_t h, int trial_steps, int *tx, int *ty, int *lz) {
   cand.push_back(default_schedule(h->nx, h->ny, h->nz));
   std::vector<double> t(cand.size(), INFINITY);
   auto trial = [&](size_t c) -> int {
-    const sc::Sched &s = cand[c];
-    h->sched = s;
-    TRY(rebuild_tiles(h));
+    TRY(set_shape(h, cand[c]));
     int par = h->cur;
     auto one = [&]() {
       const hipError_t e = one_step(h, par);
@@ -1531,8 +1618,7 @@ int lbm_autotune(lbm_throat_t h, int trial_steps, int *tx, int *ty, int *lz) {
   size_t best = 0;
   for (size_t c = 1; c < cand.size(); ++c)
     if (t[c] < t[best]) best = c;
-  h->sched = cand[best];
-  TRY(rebuild_tiles(h));
+  TRY(set_shape(h, cand[best]));
   if (tx) *tx = h->sched.tx;
   if (ty) *ty = h->sched.ty;
   if (lz) *lz = h->sched.lz;

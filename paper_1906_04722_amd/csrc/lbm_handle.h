@@ -60,7 +60,8 @@ struct lbm_throat {
   hipEvent_t ev[2] = {nullptr, nullptr};
   std::vector<uint8_t> types;
   long long n_fluid = 0;
-  long long probe = -1;              // number of the probe node
+  long long probe_pos = -1;          // map position of the probe node
+  long long probe = -1;              // its number
   double tau[2], G, Gads[2], rho_major, rho_minor, rho_in, rho_out;
   double phib = 1.0;
   sc::Phys P{};

@@ -178,6 +178,13 @@ size_t number_rows(uint32_t *rows, int ny, int nz);
 hipError_t launch_number(const uint8_t *types, int nx, int ny, int nz, int per,
                          const uint32_t *rows, bool bricks, uint32_t *map, uint32_t *pos,
                          hipStream_t st);
+// The other numbering of a subdomain with positions pos: launch_renumber writes
+// the index map of bricks or of the compact numbering, launch_move takes a
+// population buffer to it from the other one (ghost planes of bricks included).
+hipError_t launch_renumber(const Dom &d, const uint8_t *types, const uint32_t *pos, uint32_t n_live,
+                           bool bricks, uint32_t *map, hipStream_t st);
+hipError_t launch_move(const Dom &d, const uint32_t *pos, uint32_t n_live, bool bricks,
+                       const float *src, float *dst, hipStream_t st);
 hipError_t launch_links(const uint8_t *types, const Dom &d, uint32_t *mask, hipStream_t st);
 // initial state; with a given one (rho_init [2][N]), *bad falls to the first
 // c N + n at which it is not finite and positive on a fluid node

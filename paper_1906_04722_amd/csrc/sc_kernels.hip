@@ -1097,15 +1097,76 @@ __global__ void k_number_rest(const uint8_t *types, int nx, int ny, int nz, int 
   }
 }
 
+static hipError_t number_rest(const uint8_t *types, int nx, int ny, int nz, int per, uint32_t *map,
+                              hipStream_t st) {
+  const size_t M = map_elems(nx, ny, nz);
+  const unsigned grid = (unsigned)std::min<size_t>((M + 255) / 256, 65536);
+  hipLaunchKernelGGL(k_number_rest, dim3(grid), dim3(256), 0, st, types, nx, ny, nz, per, map);
+  return hipGetLastError();
+}
+
 hipError_t launch_number(const uint8_t *types, int nx, int ny, int nz, int per,
                          const uint32_t *rows, bool bricks, uint32_t *map, uint32_t *pos,
                          hipStream_t st) {
   const uint32_t nrows = (uint32_t)ny * (uint32_t)nz;
   hipLaunchKernelGGL(k_number, dim3((nrows + 3) / 4), dim3(256), 0, st, types, nx, ny, nz, nrows,
                      rows, bricks ? 1 : 0, map, pos);
-  const size_t M = map_elems(nx, ny, nz);
-  const unsigned grid = (unsigned)std::min<size_t>((M + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_number_rest, dim3(grid), dim3(256), 0, st, types, nx, ny, nz, per, map);
+  return number_rest(types, nx, ny, nz, per, map, st);
+}
+
+// The compact number of the i-th listed node is i, its brick number follows
+// from its coordinates: neither numbering needs the other's map.
+__device__ __forceinline__ void coords_of(const Dom &d, uint32_t pos, int &x, int &y, int &z) {
+  const uint32_t px = (uint32_t)(d.nx + 2 * kPad), py = (uint32_t)(d.ny + 2 * kPad);
+  x = (int)(pos % px) - kPad;
+  y = (int)(pos / px % py) - kPad;
+  z = (int)(pos / px / py) - kPad;
+}
+
+__global__ __launch_bounds__(256) void k_renumber(Dom d, const uint32_t *pos, uint32_t n_live,
+                                                  int bricks, uint32_t *map) {
+  for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < n_live;
+       i += (size_t)gridDim.x * 256) {
+    int x, y, z;
+    coords_of(d, pos[i], x, y, z);
+    map[pos[i]] = bricks ? brick_number(d.nx, d.ny, x, y, z) : (uint32_t)i;
+  }
+}
+
+hipError_t launch_renumber(const Dom &d, const uint8_t *types, const uint32_t *pos, uint32_t n_live,
+                           bool bricks, uint32_t *map, hipStream_t st) {
+  if (n_live)
+    hipLaunchKernelGGL(k_renumber, dim3(std::min((n_live + 255) / 256, 65536u)), dim3(256), 0, st,
+                       d, pos, n_live, bricks ? 1 : 0, map);
+  return number_rest(types, d.nx, d.ny, d.nz, d.per, map, st);
+}
+
+__global__ __launch_bounds__(256) void k_move(Dom d, const uint32_t *pos, uint32_t n_live,
+                                              int bricks, const float *src, float *dst) {
+  for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < n_live;
+       i += (size_t)gridDim.x * 256) {
+    int x, y, z;
+    coords_of(d, pos[i], x, y, z);
+    const size_t c = node_elem((uint32_t)i), b = node_elem(brick_number(d.nx, d.ny, x, y, z));
+    const size_t from = bricks ? c : b, to = bricks ? b : c;
+    // the planes -1 and nz of z-periodic bricks repeat the planes nz - 1 and 0
+    const size_t turn = brick_plane(d.nx, d.ny) * (size_t)d.nz;
+    const bool ghosts = bricks && (d.per & 4);
+    for (int q = 0; q < kQ; ++q) {
+      const size_t o = (size_t)(q * kLine);
+      const float v = src[from + o];
+      dst[to + o] = v;
+      if (ghosts && z == 0) dst[to + turn + o] = v;
+      if (ghosts && z == d.nz - 1) dst[to - turn + o] = v;
+    }
+  }
+}
+
+hipError_t launch_move(const Dom &d, const uint32_t *pos, uint32_t n_live, bool bricks,
+                       const float *src, float *dst, hipStream_t st) {
+  if (n_live == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_move, dim3(std::min((n_live + 255) / 256, 65536u)), dim3(256), 0, st, d, pos,
+                     n_live, bricks ? 1 : 0, src, dst);
   return hipGetLastError();
 }
 

@@ -1,0 +1,151 @@
+"""The launch shape that is asked for is the one that runs: tiles over bricks,
+the two passes over the compact nodes, whichever of the two a subdomain was
+set up in.  Its state, ramp and checkpoints move between the two bit for bit,
+and a shape whose storage cannot be had leaves the subdomain as it was."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import synth
+from synth import BC_PERIODIC, BC_RESERVOIR, BC_WALLS, Problem
+
+pytestmark = pytest.mark.gpu
+
+LIST = (-1, 0, 0)
+
+
+def _sparse():
+    """A compact box of which four fifths are solid."""
+    sph = np.array([[x, y, z, 19.8] for x in (16, 48, 80) for y in (16, 48, 80)
+                    for z in (16, 48, 80)], float)
+    return Problem(nx=97, ny=98, nz=96, bc=(BC_WALLS, BC_PERIODIC, BC_RESERVOIR), spheres=sph,
+                   rho_in_nw=2.02, z_front=12)
+
+
+def _ragged(bc):
+    return Problem(nx=37, ny=34, nz=19, bc=bc, tau=(0.9, 1.1), rho_in_nw=2.02, z_front=6,
+                   spheres=np.array([[12.0, 14.0, 9.0, 7.5], [36.0, 2.0, 18.0, 3.2]]),
+                   probe=(20, 25, 10))
+
+
+def _free_bytes():
+    hip = ctypes.CDLL("/opt/rocm/lib/libamdhip64.so.7")
+    free, total = ctypes.c_size_t(), ctypes.c_size_t()
+    assert hip.hipMemGetInfo(ctypes.byref(free), ctypes.byref(total)) == 0
+    return free.value
+
+
+def test_tiles_and_two_passes_have_their_own_storage():
+    from paper_1906_04722_amd import lbm
+    p = _sparse()
+    g = lbm.Throat(p)
+    live = int((g.types() != lbm.LBM_NODE_SOLID).sum())
+    assert live < 0.35 * g.N and g.schedule() == LIST
+    g.step(7)
+    free = _free_bytes()
+    g.set_schedule(32, 8, 16)
+    more = 2 * 152 * (g.N - live)  # two buffers of every node of the box
+    assert free - _free_bytes() > 0.9 * more
+    assert g.schedule() == (32, 8, 16)
+    f = g.f()
+    g.set_schedule(*LIST)
+    assert g.schedule() == LIST and np.array_equal(g.f(), f)
+    g.close()
+
+
+@pytest.mark.parametrize("bc", [(BC_WALLS, BC_PERIODIC, BC_RESERVOIR), (BC_PERIODIC,) * 3])
+def test_the_state_moves_between_the_shapes(bc, tmp_path):
+    from paper_1906_04722_amd import lbm
+    p = _ragged(bc)
+    a, b = lbm.Throat(p), lbm.Throat(p)
+    for n, shape in ((3, (32, 4, 5)), (4, (8, 8, 2)), (1, LIST), (2, (64, 4, 40)), (5, LIST)):
+        b.set_schedule(*shape)
+        assert b.schedule() == shape
+        assert np.array_equal(a.f(), b.f())
+        a.step(n)
+        b.step(n)
+        assert np.array_equal(a.f(), b.f()) and a.probe_invaded() == b.probe_invaded()
+        (ma, Sa), (mb, Sb) = a.reduce(), b.reduce()
+        assert np.array_equal(ma, mb) and Sa == Sb
+    # a file of either numbering is the same file
+    b.set_schedule(16, 8, 3)
+    a.save(str(tmp_path / "a"))
+    b.save(str(tmp_path / "b"))
+    assert (tmp_path / "a").read_bytes() == (tmp_path / "b").read_bytes()
+    b.step(2)
+    b.load(str(tmp_path / "a"))
+    b.step(3)
+    a.step(3)
+    assert np.array_equal(a.f(), b.f())
+    a.close()
+    b.close()
+
+
+def test_a_ramp_goes_on_in_another_shape():
+    from paper_1906_04722_amd import lbm
+    p = synth.c2_problem(n=40, mean_r=32.0 * 40 / 96, seed=11)
+    r_ins, _ = synth.throat_incircle(p.spheres)
+    pcs = synth.pc_ramp(synth.GAMMA_LAPLACE, r_ins, 5, 0.1, 0.9)
+    conv = dict(tol=1e-5, check_every=100, max_steps=3000, bisect_rel=0.02)
+    one = lbm.Throat(p)
+    ref = one.drain(pcs, **conv)
+    assert ref["n_bisect"] >= 1
+    g = lbm.Throat(p)
+    g.drain_begin(pcs, **conv)
+    shapes = [(32, 8, 7), LIST, (16, 4, 40)]
+    i = 0
+    while not g.drain_advance(300):
+        g.set_schedule(*shapes[i % 3])
+        i += 1
+    got = g.drain_get()
+    assert i >= 6
+    for k in ("S", "steps", "status"):
+        assert np.array_equal(got[k], ref[k])
+    for k in ("pce_lo", "pce_hi", "invaded_at", "n_bisect", "total_steps"):
+        assert got[k] == ref[k]
+    assert np.array_equal(g.f(), one.f())
+    g.close()
+    one.close()
+
+
+def test_a_shape_beyond_the_budget_changes_nothing():
+    from paper_1906_04722_amd import lbm
+    p = _ragged((BC_PERIODIC,) * 3)
+    a, b = lbm.Throat(p), lbm.Throat(p)
+    a.step(3)
+    b.step(3)
+    lbm.set_memory_budget(1 << 20)
+    try:
+        with pytest.raises(lbm.LBMError) as e:
+            b.set_schedule(32, 8, 4)
+        assert e.value.code == lbm.LBM_ENOMEM
+    finally:
+        lbm.set_memory_budget(0)
+    assert b.schedule() == LIST
+    a.step(4)
+    b.step(4)
+    assert np.array_equal(a.f(), b.f())
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("start", [None, LIST])
+def test_autotuner_trials_leave_a_brick_box_as_it_was(start):
+    from paper_1906_04722_amd import lbm
+    p = Problem(nx=126, ny=127, nz=140, bc=(BC_PERIODIC,) * 3, z_front=60,
+                spheres=np.array([[60.0, 65.0, 70.0, 25.0], [20.0, 30.0, 1.0, 9.0]]))
+    a, b = lbm.Throat(p), lbm.Throat(p)
+    a.step(5)
+    b.step(5)
+    if start:
+        b.set_schedule(*start)
+    shape = b.autotune(3)
+    print("picked", shape)
+    assert shape[0] > 0 and b.schedule() == shape
+    assert np.array_equal(a.density(), b.density())
+    a.step(6)
+    b.step(6)
+    assert np.array_equal(a.density(), b.density())
+    a.close()
+    b.close()
