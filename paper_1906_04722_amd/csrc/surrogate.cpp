@@ -819,6 +819,15 @@ int lbm_surrogate_predict(lbm_surrogate_t s, int n, const double *feat, double *
   // is written to the caller's arrays before its flag is known
   const int chunk = std::min(n, kChunkRows);
   const bool small = n <= kPinRows;
+  // (a refused call gives its large buffer back as well)
+  struct Release {
+    lbm_surrogate_t s;
+    ~Release() {
+      if (s->stat_cap <= kKeepRows) return;
+      dfree(s->stat_d);
+      s->stat_cap = 0;
+    }
+  } release{s};
   SGTRY(s->ensure_infer(chunk, small ? 0 : n));
   double *mean_d = small ? s->pin_out : s->stat_d;
   double *std_d = mean_d + (size_t)n * sg::kOut;
@@ -849,10 +858,6 @@ int lbm_surrogate_predict(lbm_surrogate_t s, int n, const double *feat, double *
   SGCHK(hipMemcpyAsync(mean, mean_d, bytes, hipMemcpyDeviceToHost, s->stream));
   SGCHK(hipMemcpyAsync(std, std_d, bytes, hipMemcpyDeviceToHost, s->stream));
   SGCHK(hipStreamSynchronize(s->stream));
-  if (s->stat_cap > kKeepRows) {
-    dfree(s->stat_d);
-    s->stat_cap = 0;
-  }
   return LBM_OK;
 }
 
