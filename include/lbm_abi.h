@@ -308,8 +308,8 @@ int lbm_step_timer(lbm_throat_t h, int enable, double *total_ms, long long *laun
  * fused pass, a workgroup taking two such tiles on top of each other in y; 0
  * keeps the current value.  tx = LBM_SCHED_NODE_LIST selects two passes over
  * the non-solid nodes instead (ty and lz are ignored and read back as 0).  A
- * box of 2 million nodes or more, three quarters of them not solid, starts in
- * tiles, any other in two passes.  The two keep their populations in different
+ * box of 2 million nodes or more, whose non-solid nodes fill three quarters of
+ * its planes cut into 32 x 16 tiles, starts in tiles, any other in two passes.  The two keep their populations in different
  * orders: a shape of the other kind moves the state and the checkpoints of a
  * ramp over, bit for bit, for which both orders are held at once (LBM_ENOMEM,
  * with everything as it was, if that cannot be had or exceeds the memory

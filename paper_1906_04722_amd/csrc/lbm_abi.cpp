@@ -375,19 +375,25 @@ int lbm_set_memory_budget(size_t bytes) {
 
 namespace {
 
-// A subdomain is kept in bricks and stepped in tiles from this share of
-// non-solid nodes in the padded box and this many padded nodes on.  Step times
-// in us, two passes / tiles, all fluid: 96^3 71 / 88, 112^3 123 / 145, 128^3
-// 192 / 168, 160^3 377 / 307, 192^3 667 / 569, 256^3 1523 / 1154; with 10, 20,
-// 30 and 40 % solid 128^3 184 / 159, 165 / 151, 135 / 149, 128 / 144; 192^3
-// 605 / 543, 553 / 522, 486 / 498, 424 / 480; 256^3 1414 / 1133, 1268 / 1099,
-// 1130 / 1047, 975 / 982.
+// A subdomain starts in bricks, stepped in tiles, from this share of non-solid
+// nodes among the lanes of its default tiles (32 x 16 nodes a plane) and this
+// many nodes padded to bricks on; else in the two passes.  Time of the tiles
+// over that of the two passes, all fluid or with cubic arrays of spheres: by
+// size at full tiles 96^3 1.24, 112^3 1.18, 128^3 0.86, 160^3 0.80, 256^3 0.75;
+// by share, 2 to 3 M nodes 0.90 0.90, 0.80 0.95-1.00, 0.76 1.02, 0.72 1.05-1.09,
+// 0.65 1.16; 8 to 27 M 0.86 0.82-0.93, 0.78 0.96-1.02, 0.74 0.94, 0.69 0.99-1.05;
+// thin boxes 40 x 40 x 1400 (0.52) 1.24, 33 x 65 x 1000 (0.42) 1.43, 8 x 8 x
+// 33000 (0.13) 2.2.
 constexpr double kTileFill = 0.75;
 constexpr size_t kTileNodes = (size_t)1 << 21;
 
 bool own_bricks(const lbm_throat *h) {
   const size_t slots = (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * h->nz;
-  return slots >= kTileNodes && (double)h->n_live >= kTileFill * (double)slots;
+  const sc::Sched s = default_schedule(h->nx, h->ny, h->nz);
+  const int rows = sc::tile_rows(s.ty);
+  const size_t lanes = (size_t)((h->nx + s.tx - 1) / s.tx * s.tx) *
+                       (size_t)((h->ny + rows - 1) / rows * rows) * h->nz;
+  return slots >= kTileNodes && (double)h->n_live >= kTileFill * (double)lanes;
 }
 
 size_t brick_numbers(const lbm_throat *h) {

@@ -149,3 +149,14 @@ def test_autotuner_trials_leave_a_brick_box_as_it_was(start):
     assert np.array_equal(a.density(), b.density())
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("shape,tiles", [((128, 128, 128), True), ((64, 64, 520), True),
+                                         ((129, 129, 129), False), ((40, 40, 1400), False),
+                                         ((33, 65, 1000), False), ((8, 8, 33000), False)])
+def test_open_boxes_start_in_tiles_where_these_are_full(shape, tiles):
+    from paper_1906_04722_amd import lbm
+    nx, ny, nz = shape
+    g = lbm.Throat(Problem(nx=nx, ny=ny, nz=nz, bc=(BC_PERIODIC,) * 3, z_front=nz // 2))
+    assert (g.schedule()[0] > 0) == tiles
+    g.close()
