@@ -263,7 +263,8 @@ int lbm_load(lbm_throat_t h, const char *path);
 
 /* Summary of a batched drainage (optional output of lbm_drain_batch). */
 typedef struct {
-  int tx, ty, lz;           /* launch shape: LBM_SCHED_NODE_LIST, 0, 0       */
+  int tx, ty, lz;           /* launch shape: LBM_SCHED_NODE_LIST, 0, 0, or
+                               the tiles if every subdomain is stepped so    */
   int n_tiles;              /* work items of all subdomains in one launch    */
   long long replays;        /* graph replays (chunks of check_every steps)   */
   long long lattice_steps;  /* lattice steps issued                          */
@@ -277,7 +278,8 @@ typedef struct {
  * host [n][n_pc] (each row positive and strictly increasing), out[t] receives the same
  * results as lbm_drain_throat would (bit for bit: the same kernels and the
  * same reduction order).  One step covers the non-solid nodes of all running
- * subdomains in two launches; the ramp and bisection decisions are taken on
+ * subdomains in two launches, open boxes in one of tiles (see
+ * lbm_set_schedule; their sizes count together); the ramp and bisection decisions are taken on
  * the device between chunks of c->check_every steps (even), captured once as a
  * HIP graph and replayed until every subdomain is done.  Device memory:
  * 4 x 152 bytes per non-solid node (two buffers and two ramp checkpoints) plus

@@ -98,28 +98,31 @@ void fill_phys(lbm_throat *h) {
     }
 }
 
-// Tiles of 32 x 16 nodes (64 x 8 measured 1 % behind) in the number of
-// z-segments that leaves the fewest planes to march: a CU holds one workgroup,
+// Tiles of 32 x 16 nodes (64 x 8 measured 1 % behind) in the length of
+// z-segment that leaves the fewest planes to march: a CU holds one workgroup,
 // so a launch is ceil(workgroups / 256) rounds of a segment and about eight
 // planes' time to fill the pipeline.  us a step: 256^3 segments of 16, 32, 64,
 // 128 planes 1274, 1216, 1185, 1150; 192^3 of 16, 32, 64, 128 617, 589, 567,
 // 931 (144 workgroups, one of two segments short).
-sc::Sched default_schedule(int nx, int ny, int nz) {
-  sc::Sched s{32, 8, nz};
-  const int rows = sc::tile_rows(s.ty);
-  const long long columns = (long long)((nx + s.tx - 1) / s.tx) * ((ny + rows - 1) / rows);
-  long long best = LLONG_MAX;
-  for (int n = 1; n <= std::max(1, nz / 16); ++n) {
-    const int lz = (nz + n - 1) / n;
-    const long long segments = (nz + lz - 1) / lz;
-    const long long t = (columns * segments + 255) / 256 * (lz + 8);
-    if (t < best) {
-      best = t;
-      s.lz = lz;
-    }
-  }
-  return s;
+constexpr int kTileTx = 32, kTileTy = 8;
+long long tile_columns(int nx, int ny) {
+  const int rows = sc::tile_rows(kTileTy);
+  return (long long)((nx + kTileTx - 1) / kTileTx) * ((ny + rows - 1) / rows);
 }
+sc::Sched default_schedule(int nx, int ny, int nz) {
+  return sc::Sched{kTileTx, kTileTy, lbmh::tile_length({{tile_columns(nx, ny), nz}})};
+}
+
+// A subdomain starts in bricks, stepped in tiles, from this share of non-solid
+// nodes among the lanes of its default tiles (32 x 16 nodes a plane) and
+// kTileNodes nodes padded to bricks on; else in the two passes.  Time of the tiles
+// over that of the two passes, all fluid or with cubic arrays of spheres: by
+// size at full tiles 96^3 1.24, 112^3 1.18, 128^3 0.86, 160^3 0.80, 256^3 0.75;
+// by share, 2 to 3 M nodes 0.90 0.90, 0.80 0.95-1.00, 0.76 1.02, 0.72 1.05-1.09,
+// 0.65 1.16; 8 to 27 M 0.86 0.82-0.93, 0.78 0.96-1.02, 0.74 0.94, 0.69 0.99-1.05;
+// thin boxes 40 x 40 x 1400 (0.52) 1.24, 33 x 65 x 1000 (0.42) 1.43, 8 x 8 x
+// 33000 (0.13) 2.2.
+constexpr double kTileFill = 0.75;
 
 // the descriptor: buffers, sizes, tile grid, parameters
 void fill_desc(lbm_throat *h) {
@@ -357,6 +360,40 @@ int check_rho_init(const lbm_throat *h, unsigned long long bad) {
   return LBM_EINVAL;
 }
 
+bool fills_tiles(const lbm_throat *h) {
+  const size_t lanes =
+      (size_t)tile_columns(h->nx, h->ny) * (kTileTx * sc::tile_rows(kTileTy)) * (size_t)h->nz;
+  return (double)h->n_live >= kTileFill * (double)lanes;
+}
+
+int tile_length(const std::vector<std::pair<long long, int>> &boxes) {
+  int top = 1, length = 1;
+  for (const auto &b : boxes) top = std::max(top, b.second);
+  long long best = LLONG_MAX;
+  for (int n = 1; n <= std::max(1, top / 16); ++n) {
+    const int l = (top + n - 1) / n;
+    long long groups = 0;
+    for (const auto &b : boxes) {
+      const int lz = std::min(l, b.second);
+      groups += b.first * ((b.second + lz - 1) / lz);
+    }
+    const long long t = (groups + 255) / 256 * (l + 8);
+    if (t < best) {
+      best = t;
+      length = l;
+    }
+  }
+  return length;
+}
+
+sc::Sched batch_tiles(const std::vector<lbm_throat *> &boxes) {
+  std::vector<std::pair<long long, int>> b;
+  for (const lbm_throat *h : boxes) b.push_back({tile_columns(h->nx, h->ny), h->nz});
+  const sc::Sched s{kTileTx, kTileTy, tile_length(b)};
+  for (lbm_throat *h : boxes) h->sched = sc::Sched{s.tx, s.ty, std::min(s.lz, h->nz)};
+  return s;
+}
+
 void fill_desc(lbm_throat *h) { ::fill_desc(h); }
 sc::Dom dom(const lbm_throat *h) { return ::dom(h, nullptr, nullptr); }
 }  // namespace lbmh
@@ -375,29 +412,8 @@ int lbm_set_memory_budget(size_t bytes) {
 
 namespace {
 
-// A subdomain starts in bricks, stepped in tiles, from this share of non-solid
-// nodes among the lanes of its default tiles (32 x 16 nodes a plane) and this
-// many nodes padded to bricks on; else in the two passes.  Time of the tiles
-// over that of the two passes, all fluid or with cubic arrays of spheres: by
-// size at full tiles 96^3 1.24, 112^3 1.18, 128^3 0.86, 160^3 0.80, 256^3 0.75;
-// by share, 2 to 3 M nodes 0.90 0.90, 0.80 0.95-1.00, 0.76 1.02, 0.72 1.05-1.09,
-// 0.65 1.16; 8 to 27 M 0.86 0.82-0.93, 0.78 0.96-1.02, 0.74 0.94, 0.69 0.99-1.05;
-// thin boxes 40 x 40 x 1400 (0.52) 1.24, 33 x 65 x 1000 (0.42) 1.43, 8 x 8 x
-// 33000 (0.13) 2.2.
-constexpr double kTileFill = 0.75;
-constexpr size_t kTileNodes = (size_t)1 << 21;
-
 bool own_bricks(const lbm_throat *h) {
-  const size_t slots = (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * h->nz;
-  const sc::Sched s = default_schedule(h->nx, h->ny, h->nz);
-  const int rows = sc::tile_rows(s.ty);
-  const size_t lanes = (size_t)((h->nx + s.tx - 1) / s.tx * s.tx) *
-                       (size_t)((h->ny + rows - 1) / rows * rows) * h->nz;
-  return slots >= kTileNodes && (double)h->n_live >= kTileFill * (double)lanes;
-}
-
-size_t brick_numbers(const lbm_throat *h) {
-  return (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * ((size_t)h->nz + 2);
+  return lbmh::fills_tiles(h) && lbmh::brick_slots(h) >= lbmh::kTileNodes;
 }
 
 bool alloc_device(void **q, size_t bytes) {
@@ -427,7 +443,7 @@ bool set_probe(lbm_throat *h, const uint32_t *map) {
 // bit for bit.  Nothing of the handle is changed before all of it is there.
 int set_numbering(lbm_throat *h, bool bricks) {
   if (h->bricks == bricks) return LBM_OK;
-  const size_t numbers = bricks ? brick_numbers(h) : h->n_live;
+  const size_t numbers = bricks ? lbmh::brick_numbers(h) : h->n_live;
   const size_t pop_bytes = sizeof(float) * sc::pop_elems(numbers);
   const size_t map_bytes = sizeof(uint32_t) * sc::map_elems(h->nx, h->ny, h->nz);
   const size_t side_bytes = bricks ? sizeof(uint32_t) * h->N : sizeof(float2) * numbers;
@@ -654,7 +670,7 @@ int init_subdomain(const lbm_params *p, lbm_throat_t *out) {
     for (size_t n = 0; n < plane; ++n)
       h->n_fluid -= (h->types[n] != sc::kSolid) + (h->types[h->N - plane + n] != sc::kSolid);
   h->bricks = own_bricks(h);
-  h->n_numbers = h->bricks ? brick_numbers(h) : h->n_live;
+  h->n_numbers = h->bricks ? lbmh::brick_numbers(h) : h->n_live;
   const size_t pop_bytes = sizeof(float) * sc::pop_elems(h->n_numbers);
   std::vector<sc::RedChunk> chunks;
   sc::red_chunks(h->n_live, 0, chunks);

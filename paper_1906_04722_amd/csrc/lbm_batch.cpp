@@ -36,8 +36,13 @@ struct Batch {
   char *rho_d = nullptr;                       // besides given initial states
   char *geo_h = nullptr, *mem_h = nullptr;     // pinned images of their exchanged parts
   sc::Throat *th_d = nullptr;
-  sc::TileRef *items_d = nullptr;   // work items of all subdomains
+  sc::TileRef *items_d = nullptr;   // work items of the subdomains in two passes
   int nitems = 0;
+  sc::TileRef *tiles_d = nullptr;   // tiles of those in bricks, at one shape
+  int ntiles = 0;
+  sc::Sched tiles{sc::kListTx, 0, 0};
+  int *zper_d = nullptr;            // those in bricks that are periodic in z
+  int n_zper = 0;
   bool wide = false;
   sc::RedChunk *chunks_d = nullptr;  // reduction chunks of all subdomains
   int nchunks = 0;
@@ -114,8 +119,7 @@ int pinned(char **h, size_t bytes) {
 // rounds of one upload, the kernels and one wait each: the second block can be
 // laid out only when the nodes are counted.  Set up one by one, with an
 // allocation and a release per array and a wait per copy, 16 throats of 24 to
-// 36 nodes a side took 34 ms for a batch of which 17 are kernels, 8 throats of
-// 48 to 128 took 114 ms (77); now 19.8 and 78 ms.
+// 36 nodes a side took 34 ms for a batch of which 17 are kernels; now 19.8.
 int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
   const int n = B.n;
   struct At {
@@ -176,9 +180,16 @@ int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
                       hipMemcpyDeviceToHost, B.stream));
   BCHK(hipStreamSynchronize(B.stream));
 
-  // numbers and work items
-  std::vector<int> first(n), count(n);
-  std::vector<sc::TileRef> items;
+  // Numbers and work items.  Open boxes go into bricks by the rule of a single
+  // subdomain, their sizes taken together, as one launch of tiles steps them all.
+  // us a step, checks included, tiles / two passes (tuned tiles over the whole
+  // box, before the compact numbering): 256^3 1173 / 1518 (1357), three 192^3
+  // 1589 / 1929 (1727), eight 128^3 1118 / 1506 (1281), sixty-four 64^3 1139 /
+  // 1463 (1238); just at kTileNodes, eight 64^3 0.89, sixty-four 32^3 0.84 of the
+  // two passes.
+  std::vector<int> first(n), count(n), zper;
+  std::vector<sc::TileRef> items, tiles;
+  std::vector<lbm_throat *> open;
   std::vector<sc::RedChunk> chunks;
   std::vector<sc::Chunk> cchunks;
   for (int t = 0; t < n; ++t) {
@@ -188,26 +199,54 @@ int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
     if (h.bc[2] == LBM_BC_RESERVOIR)
       for (int y = 0; y < h.ny; ++y)
         baths += (long long)rows[y] + rows[(size_t)(h.nz - 1) * h.ny + y];
-    h.n_live = h.n_numbers = sc::number_rows(rows, h.ny, h.nz);
+    h.n_live = sc::number_rows(rows, h.ny, h.nz);
     h.n_fluid = (long long)h.n_live - baths;
+    if (lbmh::fills_tiles(&h)) open.push_back(&h);
+  }
+  size_t slots = 0;
+  for (const lbm_throat *h : open) slots += lbmh::brick_slots(h);
+  if (slots < lbmh::kTileNodes) open.clear();
+  for (lbm_throat *h : open) {
+    h->bricks = true;
+    h->types.resize(h->N);
+    BCHK(hipMemcpyAsync(h->types.data(), h->types_d, h->N, hipMemcpyDeviceToHost, B.stream));
+  }
+  if (!open.empty()) {
+    BCHK(hipStreamSynchronize(B.stream));
+    B.tiles = lbmh::batch_tiles(open);
+  }
+  for (int t = 0; t < n; ++t) {
+    lbm_throat &h = *B.h[t];
+    h.n_numbers = h.bricks ? lbmh::brick_numbers(&h) : h.n_live;
     first[t] = (int)chunks.size();
     sc::red_chunks(h.n_live, t, chunks);
     count[t] = (int)chunks.size() - first[t];
-    sc::list_items(h.n_live, t, items);
     sc::copy_chunks(t, sc::pop_elems(h.n_numbers), cchunks);
-    B.wide = B.wide || lbmh::wide(&h);
+    if (h.bricks) {
+      sc::brick_map(h.types.data(), h.nx, h.ny, h.nz, h.brick_live);
+      sc::list_tiles(h.brick_live.data(), h.nx, h.ny, h.nz, h.sched.tx, sc::tile_rows(h.sched.ty),
+                     h.sched.lz, t, tiles);
+      if (h.per & 4) zper.push_back(t);
+    } else {
+      sc::list_items(h.n_live, t, items);
+      B.wide = B.wide || lbmh::wide(&h);
+    }
   }
-  if (items.size() > (size_t)INT_MAX) {
-    set_err("lbm_drain_batch: %zu work items exceed one launch", items.size());
+  if (items.size() + tiles.size() > (size_t)INT_MAX) {
+    set_err("lbm_drain_batch: %zu work items exceed one launch", items.size() + tiles.size());
     return LBM_EINVAL;
   }
   B.nitems = (int)items.size();
+  B.ntiles = (int)tiles.size();
+  B.n_zper = (int)zper.size();
   B.nchunks = (int)chunks.size();
   B.ncchunks = (int)cchunks.size();
   const size_t points = (size_t)n * n_pc;
   Layout M;
   const size_t o_th = M.add(sizeof(sc::Throat) * n),
                o_items = M.add(sizeof(sc::TileRef) * items.size()),
+               o_tiles = M.add(sizeof(sc::TileRef) * tiles.size()),
+               o_zper = M.add(sizeof(int) * zper.size()),
                o_chunks = M.add(sizeof(sc::RedChunk) * chunks.size()),
                o_cchunks = M.add(sizeof(sc::Chunk) * cchunks.size()),
                o_first = M.add(sizeof(int) * n), o_count = M.add(sizeof(int) * n),
@@ -221,10 +260,11 @@ int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
                image = M.size;
   const size_t o_partials = M.add(sizeof(double) * 3 * std::max<size_t>(chunks.size(), 1)),
                o_sums = M.add(sizeof(double) * 3 * n), o_probe = M.add(sizeof(double) * 2 * n);
-  std::vector<size_t> o_pos(n), o_rho(n), o_pop[4];
+  std::vector<size_t> o_pos(n), o_side(n), o_pop[4];
   for (int t = 0; t < n; ++t) {
-    o_pos[t] = M.add(sizeof(uint32_t) * B.h[t]->n_live);
-    o_rho[t] = M.add(sizeof(float2) * B.h[t]->n_numbers);
+    const lbm_throat &h = *B.h[t];
+    o_pos[t] = M.add(sizeof(uint32_t) * h.n_live);
+    o_side[t] = M.add(h.bricks ? sizeof(uint32_t) * h.N : sizeof(float2) * h.n_numbers);
   }
   size_t lo[4];  // first buffers, second buffers, the two sets of checkpoints
   for (int i = 0; i < 4; ++i) {
@@ -245,6 +285,8 @@ int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
     if (!v.empty()) std::memcpy(B.mem_h + o, v.data(), sizeof(v[0]) * v.size());
   };
   put(o_items, items);
+  put(o_tiles, tiles);
+  put(o_zper, zper);
   put(o_chunks, chunks);
   put(o_cchunks, cchunks);
   put(o_first, first);
@@ -266,7 +308,10 @@ int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
       h.save[i] = (float *)(B.mem_d + o_pop[2 + i][t]);
     }
     h.pos_d = (uint32_t *)(B.mem_d + o_pos[t]);
-    h.rho_d = (float2 *)(B.mem_d + o_rho[t]);
+    if (h.bricks)
+      h.mask_d = (uint32_t *)(B.mem_d + o_side[t]);
+    else
+      h.rho_d = (float2 *)(B.mem_d + o_side[t]);
     h.rres_d = (double *)(B.mem_d + o_rres) + 4 * t;
     lbmh::fill_desc(&h);
     ((sc::Throat *)(B.mem_h + o_th))[t] = h.desc;
@@ -286,6 +331,8 @@ int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
   }
   B.th_d = (sc::Throat *)(B.mem_d + o_th);
   B.items_d = (sc::TileRef *)(B.mem_d + o_items);
+  B.tiles_d = (sc::TileRef *)(B.mem_d + o_tiles);
+  B.zper_d = (int *)(B.mem_d + o_zper);
   B.chunks_d = (sc::RedChunk *)(B.mem_d + o_chunks);
   B.cchunks_d = (sc::Chunk *)(B.mem_d + o_cchunks);
   B.first_d = (int *)(B.mem_d + o_first);
@@ -307,7 +354,8 @@ int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
   for (int t = 0; t < n; ++t) {
     const lbm_throat &h = *B.h[t];
     BCHK(sc::launch_number(h.types_d, h.nx, h.ny, h.nz, h.per, (uint32_t *)(B.geo_d + at[t].rows),
-                           false, h.map_d, h.pos_d, B.stream));
+                           h.bricks, h.map_d, h.pos_d, B.stream));
+    if (h.bricks) BCHK(sc::launch_links(h.types_d, lbmh::dom(&h), h.mask_d, B.stream));
   }
   BCHK(sc::launch_probe_numbers(B.th_d, n, B.info_d, B.stream));
   BCHK(hipMemcpyAsync(info, B.info_d, sizeof(sc::RedInfo) * n, hipMemcpyDeviceToHost, B.stream));
@@ -327,6 +375,7 @@ int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
                          h.rho_major, h.rho_minor, p[t].z_front, h.rres_d, h.g[0],
                          (unsigned long long *)(B.mem_d + o_bad) + t, B.stream));
   }
+  BCHK(sc::launch_ghost(B.th_d, B.zper_d, B.n_zper, 0, B.stream));
   BCHK(hipMemcpyAsync(bad, B.mem_d + o_bad, sizeof(unsigned long long) * n, hipMemcpyDeviceToHost,
                       B.stream));
   BCHK(hipStreamSynchronize(B.stream));
@@ -343,13 +392,24 @@ int setup(Batch &B, const lbm_params *p, const double *pc, int n_pc) {
   return LBM_OK;
 }
 
-// the kernels of one chunk: check_every fused steps, the reductions, the
-// ramp decisions and the checkpoint copies they request
+// one step of every running subdomain
+hipError_t enqueue_step(Batch &B, int parity) {
+  hipError_t e = hipSuccess;
+  if (B.nitems)
+    e = sc::launch_step(B.th_d, B.items_d, B.nitems, sc::kListTx, 0, B.wide, parity, B.stream,
+                        nullptr, 0);
+  if (e == hipSuccess && B.ntiles)
+    e = sc::launch_step(B.th_d, B.tiles_d, B.ntiles, B.tiles.tx, B.tiles.ty, false, parity,
+                        B.stream, B.zper_d, B.n_zper);
+  return e;
+}
+
+// the kernels of one chunk: check_every steps, the reductions, the ramp
+// decisions and the checkpoint copies they request
 hipError_t enqueue_chunk(Batch &B, const sc::RampCfg &cfg) {
   hipError_t e = hipSuccess;
   for (int i = 0; i < cfg.every && e == hipSuccess; ++i)
-    e = sc::launch_step(B.th_d, B.items_d, B.nitems, sc::kListTx, 0, B.wide, i & 1, B.stream,
-                        nullptr, 0);
+    e = enqueue_step(B, i & 1);
   if (e == hipSuccess)
     e = sc::launch_reduce_chunks(B.th_d, B.chunks_d, B.nchunks, B.info_d, 0, B.partials, B.probe,
                                  B.stream);
@@ -512,15 +572,16 @@ int lbm_drain_batch(int n, const lbm_params *p, const double *pc, int n_pc, cons
     lattice_steps = std::max(lattice_steps, R.total_steps);
   }
   if (info) {
-    info->tx = sc::kListTx;
-    info->ty = 0;
-    info->lz = 0;
+    const sc::Sched shape = B.nitems ? sc::Sched{sc::kListTx, 0, 0} : B.tiles;
+    info->tx = shape.tx;
+    info->ty = shape.ty;
+    info->lz = shape.lz;
     info->replays = replays;
     info->lattice_steps = replays * c->check_every;
     info->node_updates = node_updates;
     info->fluid_updates = fluid_updates;
     info->wall_ms = wall;
-    info->n_tiles = B.nitems;
+    info->n_tiles = B.nitems + B.ntiles;
   }
   if (failed) return LBM_WPARTIAL;
   return warn ? LBM_WNOTCONV : LBM_OK;

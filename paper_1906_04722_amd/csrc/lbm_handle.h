@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "lbm_abi.h"
@@ -109,6 +110,21 @@ inline bool wide(const lbm_throat *h) {
   return sizeof(float) * sc::pop_elems(h->n_numbers) > sc::kNarrowBytes ||
          sizeof(uint32_t) * sc::map_elems(h->nx, h->ny, h->nz) > sc::kNarrowBytes;
 }
+// bricks: the box's nodes in whole bricks, and with the ghost planes; whether
+// enough lanes of its default tiles have a node, and from how many slots on the
+// tiles pay (one box's, or all such boxes' of a batch)
+inline size_t brick_slots(const lbm_throat *h) {
+  return (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * (size_t)h->nz;
+}
+inline size_t brick_numbers(const lbm_throat *h) {
+  return (size_t)sc::pad_x(h->nx) * sc::pad_y(h->ny) * ((size_t)h->nz + 2);
+}
+bool fills_tiles(const lbm_throat *h);
+constexpr size_t kTileNodes = (size_t)1 << 21;
+// z-segments of boxes (tile columns, planes) stepped in one launch
+int tile_length(const std::vector<std::pair<long long, int>> &boxes);
+// the schedules of boxes in bricks that are stepped in one launch, and its shape
+sc::Sched batch_tiles(const std::vector<lbm_throat *> &boxes);
 // device memory of one subdomain (with or without the two ramp checkpoints)
 // and the refusal of a call whose need exceeds the memory budget
 size_t subdomain_bytes(int nx, int ny, int nz, bool checkpoints);
