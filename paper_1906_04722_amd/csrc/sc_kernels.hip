@@ -740,9 +740,13 @@ __device__ __forceinline__ void halo_slot(int h, int &hx, int &hy) {
 // Up to this many nodes of the box plane Z is stored behind the sums of plane
 // Z+2, whose wait for the pulls would wait for the stores as well; beyond, ahead
 // of them: there the step is bound by lines, and tiles that wait more stay
-// closer together.  us a step, behind / ahead: 192^3 550 / 564, 256^3 1131 /
-// 1135, 384^3 4025 / 3945, 512^3 9300-9580 / 9000-9300.
-constexpr uint32_t kLateNodes = 1u << 24;
+// closer together.  Time behind over ahead: 144^3 0.96, 192^3 0.98, 224^3 0.98,
+// 248^3 (14.5 x 2^20) 0.985, 256 x 256 x 224 0.995, 384 x 384 x 96 0.99, 128 x 128
+// x 768 0.99, 512 x 512 x 16 and x 32 0.99 and 1.01; at 2^24 by shape, 256^3
+// 0.995, 512 x 512 x 64 and 128 x 128 x 1024 1.015; 288^3 1.005, 320^3 1.01, 384^3
+// 1.02, 256 x 256 x 512 1.045.  The line lies below 2^24, where nearly every
+// shape still gains.
+constexpr uint32_t kLateNodes = 15u << 20;
 template <int TX, int TY>
 __global__ __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step(
     const Throat *__restrict__ throats, const TileRef *__restrict__ tiles, int ntiles,
@@ -920,14 +924,20 @@ static bool keep_stores(long long items) {
   return bytes >= kKeepLo && bytes <= kKeepHi;
 }
 
-// Where the two passes take a lane per component: up to 512 items (32768 nodes,
-// two wavefronts a CU), and again just above one item per SIMD (1024), where
-// whole items put two wavefronts on some SIMDs and half ones three halves.  us
-// a step, one lane a node / a lane per component: 1 k nodes 7.15 / 6.33, 8 k
-// 7.31 / 6.50, 16 k 7.39 / 6.84, 24 k 7.87 / 7.27, 32 k 8.07 / 7.75, 41 k 8.36 /
-// 8.39, 66 k 8.97 / 9.06, 67 k 10.4 / 9.6, 74 k 10.4 / 9.7, 78 k 10.4 / 10.2, 82
-// k 10.3 / 10.3, 98 k 11.0 / 11.1, 131 k 13.3 / 13.8, 440 k 39.8 / 47.5.
-static bool split_lanes(int items) { return items <= 512 || (items > 1024 && items <= 1216); }
+// Where the two passes take a lane per component, by items (whole wavefronts)
+// and SIMDs: up to half an item per SIMD, where a step is one wavefront's time,
+// and again just above one per SIMD, where whole items put two wavefronts on
+// some SIMDs and half ones three halves.  Time with a lane per component over a
+// lane per node, open boxes of 64 x 32 nodes a plane and four-sphere throats: 16
+// to 375 items 0.89-0.94, 480 0.97, 512 0.98, 544 1.02, 1024 1.03; 1056 0.96,
+// 1096 0.98, 1152 0.97, 1184 0.99, 1216 1.00, 1248 1.04, 1280 1.01, 1536 1.03.
+// Above the next multiples several wavefronts share each SIMD either way and
+// nothing is left to gain: 2080 1.02, 2176 1.00, 2304 1.01, 2560 0.99, 3104
+// 1.02, 4128 1.11.
+constexpr int kSimds = 256 * 4;
+static bool split_lanes(int items) {
+  return items <= kSimds / 2 || (items > kSimds && items <= kSimds + 3 * kSimds / 16);
+}
 
 static hipError_t step_body(const Throat *th, const TileRef *tiles, int ntiles, int tx, int ty,
                             bool wide, int parity, hipStream_t st) {
