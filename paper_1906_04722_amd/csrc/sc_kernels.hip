@@ -313,9 +313,9 @@ __device__ __forceinline__ int xcd_item(int n) {
 //
 // Bound: the rate at which the eight L2s exchange lines with the memory side
 // (6.2 TB/s for a copy).  A step fetches 152 + 152 bytes of populations per
-// node and writes 152, beside 20 of positions, index map and densities; counted
-// on the 256^3 packed sample (6.4 M of 16.8 M nodes): 2.19 GB fetched and
-// 1.02 GB written, against 1.95 and 1.02 without waste.  Before, one fused pass
+// node, 16 of positions and densities and the index map twice, and writes 160:
+// 2.19 GB and 1.02 GB on the 256^3 packed sample (6.4 M of 16.8 M nodes), where
+// 2.19 and 1.02 were counted.  Before, one fused pass
 // in tiles over all nodes of the box refetched halo lines and moved partly used
 // lines: 3.7 GB and 873-893 us a step on that sample, now 660; 40-sphere
 // sample with membrane 113 -> 64 us (57 with kept stores), 96^3 throat 18.4 ->
@@ -913,9 +913,10 @@ hipError_t launch_ghost(const Throat *th, const int *zper_ids, int n_zper, int w
 }
 
 // Both buffers of the populations, in bytes of listed nodes, for which k_node
-// stores through the caches: between what the L2s hold (8 x 4 MB) and the
-// 256 MB memory-side cache, where the lines just stored are the next step's
-// reads.  Step time, cached against non-temporal: up to 10 MB 0.97-0.98, 17-34
+// stores through the caches: where the next step reads lines just stored from
+// the 256 MB memory-side cache, and the L2s (8 x 4 MB) hold too few of them for
+// the choice to matter there.  The limits are the measured crossovers; the upper
+// one lies above that cache, which still keeps most of the lines.  Step time, cached against non-temporal: up to 10 MB 0.97-0.98, 17-34
 // MB 1.01-1.06, 69-80 MB 0.95-0.97, 102 MB 0.95, 133-156 MB 0.92, 212 MB 0.89,
 // 242 MB 0.93-0.97, 269 MB 0.91-0.95, from 335 MB on 1.01-1.13.
 constexpr long long kKeepLo = 48ll << 20, kKeepHi = 288ll << 20;
