@@ -2,25 +2,16 @@
 the two passes over the compact nodes, whichever of the two a subdomain was
 set up in.  Its state, ramp and checkpoints move between the two bit for bit,
 and a shape whose storage cannot be had leaves the subdomain as it was."""
-import ctypes
-
 import numpy as np
 import pytest
 
 import synth
 from synth import BC_PERIODIC, BC_RESERVOIR, BC_WALLS, Problem
+from tests import hip_shim
 
 pytestmark = pytest.mark.gpu
 
 LIST = (-1, 0, 0)
-
-
-def _sparse():
-    """A compact box of which four fifths are solid."""
-    sph = np.array([[x, y, z, 19.8] for x in (16, 48, 80) for y in (16, 48, 80)
-                    for z in (16, 48, 80)], float)
-    return Problem(nx=97, ny=98, nz=96, bc=(BC_WALLS, BC_PERIODIC, BC_RESERVOIR), spheres=sph,
-                   rho_in_nw=2.02, z_front=12)
 
 
 def _ragged(bc):
@@ -29,29 +20,44 @@ def _ragged(bc):
                    probe=(20, 25, 10))
 
 
-def _free_bytes():
-    hip = ctypes.CDLL("/opt/rocm/lib/libamdhip64.so.7")
-    free, total = ctypes.c_size_t(), ctypes.c_size_t()
-    assert hip.hipMemGetInfo(ctypes.byref(free), ctypes.byref(total)) == 0
-    return free.value
+# a compact box of which four fifths are solid
+STORAGE = """
+from synth import BC_PERIODIC, BC_RESERVOIR, BC_WALLS, Problem
+from paper_1906_04722_amd import lbm
+LIST = (-1, 0, 0)
+sph = np.array([[x, y, z, 19.8] for x in (16, 48, 80) for y in (16, 48, 80) for z in (16, 48, 80)],
+               float)
+g = lbm.Throat(Problem(nx=97, ny=98, nz=96, bc=(BC_WALLS, BC_PERIODIC, BC_RESERVOIR), spheres=sph,
+                       rho_in_nw=2.02, z_front=12))
+nodes = int((g.types() != lbm.LBM_NODE_SOLID).sum())
+assert nodes < 0.25 * g.N and g.schedule() == LIST
+g.step(7)
+f, compact = g.f(), live.value
+more = 2 * 152 * (g.N - nodes)  # two buffers of every node of the box
+g.set_schedule(32, 8, 16)
+print("compact", compact, "bricks", live.value, "nodes add", more)
+assert live.value - compact > 0.95 * more
+assert g.schedule() == (32, 8, 16) and np.array_equal(g.f(), f)
+g.set_schedule(*LIST)
+assert live.value - compact < 0.01 * more
+assert g.schedule() == LIST and np.array_equal(g.f(), f)
+deny.value = 1
+try:
+    g.set_schedule(16, 8, 5)
+    raise SystemExit("storage that cannot be had was not refused")
+except lbm.LBMError as e:
+    assert e.code == lbm.LBM_ENOMEM
+deny.value = 0
+assert g.schedule() == LIST and np.array_equal(g.f(), f)
+g.step(2)
+h = g.f()
+g.close()
+assert live.value == 0
+"""
 
 
-def test_tiles_and_two_passes_have_their_own_storage():
-    from paper_1906_04722_amd import lbm
-    p = _sparse()
-    g = lbm.Throat(p)
-    live = int((g.types() != lbm.LBM_NODE_SOLID).sum())
-    assert live < 0.35 * g.N and g.schedule() == LIST
-    g.step(7)
-    free = _free_bytes()
-    g.set_schedule(32, 8, 16)
-    more = 2 * 152 * (g.N - live)  # two buffers of every node of the box
-    assert free - _free_bytes() > 0.9 * more
-    assert g.schedule() == (32, 8, 16)
-    f = g.f()
-    g.set_schedule(*LIST)
-    assert g.schedule() == LIST and np.array_equal(g.f(), f)
-    g.close()
+def test_tiles_and_two_passes_have_their_own_storage(tmp_path):
+    hip_shim.run(tmp_path, STORAGE)
 
 
 @pytest.mark.parametrize("bc", [(BC_WALLS, BC_PERIODIC, BC_RESERVOIR), (BC_PERIODIC,) * 3])
