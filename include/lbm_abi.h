@@ -141,8 +141,8 @@ typedef struct lbm_throat *lbm_throat_t;
  * plus 25 bytes per node of index map, classes, densities and node list; two
  * more population buffers for the ramp checkpoints of a drain) and refuse a
  * call that needs more than `bytes` with LBM_ENOMEM, having allocated nothing.
- * lbm_set_schedule counts the storage of the shape it changes to, if that is
- * another than the subdomain's.  0 (the default) sets no budget; calls are then
+ * lbm_set_schedule counts the subdomain once more where it changes the order
+ * that its populations are kept in.  0 (the default) sets no budget; calls are then
  * refused only when the device reports less free memory than they need.
  * Process wide; takes effect for calls that start after it returns. */
 int lbm_set_memory_budget(size_t bytes);
@@ -313,9 +313,10 @@ int lbm_step_timer(lbm_throat_t h, int enable, double *total_ms, long long *laun
  * box of 2 million nodes or more, whose non-solid nodes fill three quarters of
  * its planes cut into 32 x 16 tiles, starts in tiles, any other in two passes.  The two keep their populations in different
  * orders: a shape of the other kind moves the state and the checkpoints of a
- * ramp over, bit for bit, for which both orders are held at once (LBM_ENOMEM,
- * with everything as it was, if that cannot be had or exceeds the memory
- * budget).  All shapes give bit-identical results. */
+ * ramp over, bit for bit, for which both orders are held at once.  If that
+ * memory cannot be had, two passes take the buffers that the tiles had, and
+ * tiles are refused with LBM_ENOMEM, with everything as it was, as is a change
+ * that exceeds the memory budget.  All shapes give bit-identical results. */
 #define LBM_SCHED_NODE_LIST (-1)
 int lbm_set_schedule(lbm_throat_t h, int tx, int ty, int lz);
 

@@ -441,6 +441,9 @@ bool set_probe(lbm_throat *h, const uint32_t *map) {
 
 // The other numbering for a subdomain, its state and checkpoints carried over
 // bit for bit.  Nothing of the handle is changed before all of it is there.
+// Compact populations fit the buffers that held bricks: where no others can be
+// had, they move into these, the state to the one that does not hold it and
+// each checkpoint by way of the one that then no longer does.
 int set_numbering(lbm_throat *h, bool bricks) {
   if (h->bricks == bricks) return LBM_OK;
   const size_t numbers = bricks ? lbmh::brick_numbers(h) : h->n_live;
@@ -451,17 +454,22 @@ int set_numbering(lbm_throat *h, bool bricks) {
   const uint32_t n_live = (uint32_t)h->n_live;
   struct Storage {
     void *g[2] = {}, *save[2] = {}, *map = nullptr, *side = nullptr, *zper = nullptr;
-    ~Storage() {
-      for (void *p : {g[0], g[1], save[0], save[1], map, side, zper})
-        if (p) (void)hipFree(p);
+    void drop() {
+      for (void **p : {&g[0], &g[1], &save[0], &save[1], &map, &side, &zper}) {
+        if (*p) (void)hipFree(*p);
+        *p = nullptr;
+      }
     }
+    ~Storage() { drop(); }
   } f;
-  size_t need = 2 * pop_bytes + map_bytes + side_bytes;
-  for (int i = 0; i < 2; ++i) need += h->save[i] ? pop_bytes : 0;
-  TRY(lbmh::check_budget(need, "the launch shape's storage"));
+  TRY(lbmh::check_budget(
+      lbmh::subdomain_bytes(h->nx, h->ny, h->nz, h->save[0] || h->save[1]), "lbm_set_schedule"));
+  bool room = true;
   for (int i = 0; i < 2; ++i)
-    if (!alloc_device(&f.g[i], pop_bytes) || (h->save[i] && !alloc_device(&f.save[i], pop_bytes)))
-      return LBM_ENOMEM;
+    room = room && alloc_device(&f.g[i], pop_bytes) &&
+           (!h->save[i] || alloc_device(&f.save[i], pop_bytes));
+  if (!room && bricks) return LBM_ENOMEM;
+  if (!room) f.drop();
   if (!alloc_device(&f.map, map_bytes) || !alloc_device(&f.side, side_bytes) ||
       (ghosts && !alloc_device(&f.zper, sizeof(int))))
     return LBM_ENOMEM;
@@ -471,12 +479,14 @@ int set_numbering(lbm_throat *h, bool bricks) {
   d.map = (uint32_t *)f.map;
   HIPCHK(sc::launch_renumber(d, h->types_d, h->pos_d, n_live, bricks, (uint32_t *)f.map,
                              h->stream));
-  HIPCHK(sc::launch_move(d, h->pos_d, n_live, bricks, h->g[h->cur], (float *)f.g[h->cur],
-                         h->stream));
-  for (int i = 0; i < 2; ++i)
-    if (h->save[i])
-      HIPCHK(sc::launch_move(d, h->pos_d, n_live, bricks, h->save[i], (float *)f.save[i],
-                             h->stream));
+  auto move = [&](const float *from, void *to) {
+    return sc::launch_move(d, h->pos_d, n_live, bricks, from, (float *)to, h->stream);
+  };
+  if (room) {
+    HIPCHK(move(h->g[h->cur], f.g[h->cur]));
+    for (int i = 0; i < 2; ++i)
+      if (h->save[i]) HIPCHK(move(h->save[i], f.save[i]));
+  }
   if (bricks) HIPCHK(sc::launch_links(h->types_d, d, (uint32_t *)f.side, h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));
   if (!set_probe(h, (uint32_t *)f.map)) {
@@ -489,9 +499,21 @@ int set_numbering(lbm_throat *h, bool bricks) {
     mine = static_cast<std::remove_reference_t<decltype(mine)>>(fresh);
     fresh = old;
   };
-  for (int i = 0; i < 2; ++i) {
-    take(h->g[i], f.g[i]);
-    take(h->save[i], f.save[i]);
+  if (room) {
+    for (int i = 0; i < 2; ++i) {
+      take(h->g[i], f.g[i]);
+      take(h->save[i], f.save[i]);
+    }
+  } else {
+    float *idle = h->g[h->cur];
+    h->cur = 1 - h->cur;
+    HIPCHK(move(idle, h->g[h->cur]));
+    for (float *save : h->save)
+      if (save) {
+        HIPCHK(move(save, idle));
+        HIPCHK(hipMemcpyAsync(save, idle, pop_bytes, hipMemcpyDeviceToDevice, h->stream));
+      }
+    HIPCHK(hipStreamSynchronize(h->stream));
   }
   take(h->map_d, f.map);
   take(h->zper_d, f.zper);

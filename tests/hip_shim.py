@@ -15,10 +15,10 @@ free_fn real_free;
 static void *at[4096];
 static long size[4096];
 long live;
-int deny;
+long deny;
 int hipMalloc(void **p, unsigned long n) {
   int i, r;
-  if (deny) return 2; /* out of memory */
+  if (deny && (long)n >= deny) return 2; /* out of memory */
   r = real_malloc(p, n);
   for (i = 0; r == 0 && i < 4096; ++i)
     if (!at[i]) { at[i] = *p; size[i] = (long)n; live += (long)n; break; }
@@ -32,7 +32,7 @@ int hipFree(void *p) {
 }
 """
 
-# live.value: bytes held; deny.value = 1: every hipMalloc fails
+# live.value: bytes held; deny.value: hipMallocs of that many bytes and more fail
 HEAD = """
 import ctypes, sys
 import numpy as np
@@ -42,7 +42,7 @@ shim = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)
 for ours, theirs in (("real_malloc", hip.hipMalloc), ("real_free", hip.hipFree)):
     ctypes.c_void_p.in_dll(shim, ours).value = ctypes.cast(theirs, ctypes.c_void_p).value
 live = ctypes.c_long.in_dll(shim, "live")
-deny = ctypes.c_int.in_dll(shim, "deny")
+deny = ctypes.c_long.in_dll(shim, "deny")
 """
 
 

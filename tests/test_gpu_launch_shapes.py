@@ -60,6 +60,51 @@ def test_tiles_and_two_passes_have_their_own_storage(tmp_path):
     hip_shim.run(tmp_path, STORAGE)
 
 
+# buffers of 3 MB and more are denied: populations are, the index map is not
+IN_PLACE = """
+from synth import BC_PERIODIC, BC_RESERVOIR, BC_WALLS, Problem
+from paper_1906_04722_amd import lbm
+LIST = (-1, 0, 0)
+pcs, conv = np.array([0.004, 0.02, 0.05]), dict(tol=1e-9, check_every=20, max_steps=40, bisect_rel=0.3)
+for bc in ((BC_WALLS, BC_PERIODIC, BC_RESERVOIR), (BC_PERIODIC,) * 3):
+    p = Problem(nx=37, ny=34, nz=19, bc=bc, tau=(0.9, 1.1), rho_in_nw=2.02, z_front=6,
+                spheres=np.array([[12.0, 14.0, 9.0, 7.5], [36.0, 2.0, 18.0, 3.2]]),
+                probe=(20, 25, 10))
+    one = lbm.Throat(p)
+    ref = one.drain(pcs, **conv)
+    g = lbm.Throat(p)
+    g.set_schedule(32, 8, 5)
+    g.drain_begin(pcs, **conv)
+    assert not g.drain_advance(20)
+    f, held = g.f(), live.value
+    deny.value = 3000000
+    g.set_schedule(*LIST)
+    assert abs(live.value - held) < 1000000
+    try:
+        g.set_schedule(32, 8, 5)
+        raise SystemExit("storage that cannot be had was not refused")
+    except lbm.LBMError as e:
+        assert e.code == lbm.LBM_ENOMEM
+    deny.value = 0
+    assert g.schedule() == LIST and np.array_equal(g.f(), f)
+    g.drain_advance(20)
+    g.set_schedule(16, 8, 4)
+    while not g.drain_advance(20):
+        pass
+    got = g.drain_get()
+    assert all(np.array_equal(got[k], ref[k]) for k in ("S", "steps", "status"))
+    assert got["n_bisect"] == ref["n_bisect"] and np.array_equal(g.f(), one.f())
+    print(got["S"], got["n_bisect"])
+    g.close()
+    one.close()
+assert live.value == 0
+"""
+
+
+def test_two_passes_take_the_buffers_of_the_tiles(tmp_path):
+    hip_shim.run(tmp_path, IN_PLACE)
+
+
 @pytest.mark.parametrize("bc", [(BC_WALLS, BC_PERIODIC, BC_RESERVOIR), (BC_PERIODIC,) * 3])
 def test_the_state_moves_between_the_shapes(bc, tmp_path):
     from paper_1906_04722_amd import lbm
